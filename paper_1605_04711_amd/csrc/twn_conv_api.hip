@@ -466,6 +466,8 @@ extern "C" int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_d
     if (rc == TWN_OK) rc = build_pair_problem(d1, X, weights1, alpha1, ep1, Y1, &g[1]);
     if (rc != TWN_OK) return rc;
     hipStream_t st = as_stream(stream);
+    const int small = conv_small_tile(g, 2);
+    if (small != 0) return launch_conv_small(g, 2, small, st);
     const int t0 = gather_gemm_dma_tile(g[0], true), t1 = gather_gemm_dma_tile(g[1], true);
     // One launch pays while the reduction is short: with more than 24 slabs per tile the persistent kernels with load
     // waves win back more than the saved launch (ResNet-18 b64 block heads, two launches -> one: 128 filters, K = 576:
@@ -567,7 +569,20 @@ extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, con
         // all classes in ONE launch when the dispatcher would give each of them the same tile of the
         // one-tile-per-workgroup kernel (they are too small to be worth a launch each: ResNet-18 b64, the three
         // strided 3x3 layers 33 / 34 / 48 us as four launches)
-        int batch_tile = env_int("TWN_DX_CLASS_BATCH", 1) != 0 ? gather_gemm_dma_tile(cl.g[0]) : 0;
+        const int small = env_int("TWN_DX_CLASS_BATCH", 1) != 0 ? conv_small_tile(cl.g, cl.count) : 0;
+        if (small != 0) {
+            rc = launch_conv_small(cl.g, cl.count, small, st);
+            if (rc == TWN_OK && head) {
+                for (int k = 0; k < cl.count; ++k) {
+                    cl.g[k].X = lo;
+                    cl.g[k].residual = dX;
+                }
+                rc = launch_conv_small(cl.g, cl.count, small, st);
+            }
+            if (rc != TWN_OK) return rc;
+            cl.count = 0;           // done
+        }
+        int batch_tile = env_int("TWN_DX_CLASS_BATCH", 1) != 0 && cl.count > 0 ? gather_gemm_dma_tile(cl.g[0]) : 0;
         for (int k = 1; k < cl.count && batch_tile; ++k)
             if (gather_gemm_dma_tile(cl.g[k]) != batch_tile) batch_tile = 0;
         if (batch_tile && cl.count > 1 && d->variant == TWN_VAR_BF16_POSTSCALE) {

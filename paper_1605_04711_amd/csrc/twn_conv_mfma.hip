@@ -504,6 +504,7 @@ static int gather_mode(const GatherGemm& g) {
 }
 
 int32_t gather_gemm_splits(const GatherGemm& g) {
+    if (conv_small_tile(&g, 1) != 0) return 1;
     // split K when even 64x128 tiles leave half the CUs idle and K is deep enough to share out (few workgroups
     // with two slabs in flight each are bound by memory latency when their input is not in L2)
     if (gather_mode(g) == kModeScalar || env_int("TWN_TILE", 0) != 0) return 1;
@@ -553,6 +554,8 @@ int32_t launch_gather_gemm_mfma(const GatherGemm& g, int variant, hipStream_t st
     int tile = env_int("TWN_TILE", 0);
     // 3x3 stride-1 layers over 64 channels: weights resident in registers, input patches with halo in LDS
     if (tile == 0 && env_int("TWN_C64", 1) != 0 && conv_c64_applicable(g)) return launch_conv_c64(g, st);
+    const int small = conv_small_tile(&g, 1);
+    if (small != 0) return launch_conv_small(&g, 1, small, st);
     if (mode != kModeScalar && (tile == 0 || tile > 10)) {
         // multi-stage direct-to-LDS kernel
         if (tile == 0) {

@@ -1,0 +1,460 @@
+// Implicit-GEMM ternary convolution / inner product for problems of few output tiles (gfx950).
+//
+// Same arithmetic as the other contraction kernels (bf16 activations, 2-bit codes expanded in registers to
+// 0 / +-2.0, alpha/2 and the block tail in the fp32 epilogue), for launches that the memory latency bounds: a
+// batch-1 layer, a classifier, the deep layers of a small batch.  Tiles of 32 pixels by 32 or 64 channels, and the
+// K slabs of a tile are shared out over the NW waves of ONE workgroup, whose partial tiles are summed through LDS
+// in a fixed order: no partial sums in memory and no second launch.  A wave stages its own slabs by direct-to-LDS
+// loads, DEPTH slabs ahead (rows of 128 contiguous bytes: a fragment load straight into registers touches a cache line
+// per lane and costs four times as long), and waits for its own loads only: there is no barrier before the final sum.
+#include <mutex>
+
+#include "twn_kernels.h"
+#include "twn_lds_asm.h"
+#include "twn_mfma.h"
+
+namespace twn {
+
+namespace {
+
+constexpr int kProblemsMax = 4;
+constexpr int kQuadRow = 544;               // bytes of one block of 32 pixels x 4 channels of a partial tile in LDS (padded)
+constexpr int kPartTile = 8 * kQuadRow;     // one 32x32 partial tile
+
+int64_t small_x_bytes(const GatherGemm& g) {
+    const int64_t in_rows = g.plain_gemm ? g.M : (g.M / (static_cast<int64_t>(g.OH) * g.OW)) * g.IH * g.IW;
+    return ((in_rows - 1) * g.xs + (g.plain_gemm ? g.K : g.IC)) * 2;
+}
+
+struct SmallProblem {
+    GatherGemm g;
+    FastDivU divIC, divS, divOW, divOH, divUV, divV, divTN;
+    uint32_t x_bytes, w_bytes;
+    uint32_t blocks, tiles_n;
+};
+
+template <int NP>
+struct SmallArgs {
+    SmallProblem p[NP];
+};
+
+enum SmallMode : int {
+    kSmallGemm = 0,     // rows of X are the reduction rows
+    kSmallTap = 1,      // channel count a multiple of 64: a slab lies in one tap
+    kSmallChunk = 2,    // channel count a multiple of 8: every 16-byte chunk finds its own tap
+};
+
+// Bytes of LDS one wave uses: DEPTH slabs of activations and two groups of four slabs of codes.
+constexpr int small_wave_bytes(int mt, int nt, int depth) { return depth * mt * 4096 + 2 * nt * 2048; }
+
+template <int MT, int NT, int NW, int MODE, int NP, int DEPTH>
+__global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP> args) {
+    constexpr int BM = 32 * MT, BN = 32 * NT;
+    constexpr int QUADS = BM * BN / 4;                          // groups of four channels of one pixel
+    constexpr int QPT = QUADS > 64 * NW ? QUADS / (64 * NW) : 1;
+    constexpr int STAGE = MT * 4096;                            // one slab of activations: BM rows of 128 bytes
+    constexpr int CODES = NT * 2048;                            // four slabs of codes: BN rows of 64 bytes
+    constexpr int WAVE_BYTES = small_wave_bytes(MT, NT, DEPTH);
+    constexpr int NA = 4 * MT, NB = 2 * NT;                     // loads of a slab / of a group of codes
+    static_assert(WAVE_BYTES >= MT * NT * kPartTile, "the partial tile reuses the wave's own staging memory");
+    static_assert(DEPTH >= 2 && DEPTH <= 4, "a wait spans at most one group of codes");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+
+    const SmallProblem& a = args.p[NP == 1 ? 0 : blockIdx.y];
+    if (NP > 1 && blockIdx.x >= a.blocks) return;               // whole workgroup, before any barrier
+    const GatherGemm& g = a.g;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lrow = lane & 31, lh = lane >> 5;
+
+    // workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous range of tiles
+    const uint32_t nb = a.blocks, b = blockIdx.x;
+    const uint32_t q = nb >> 3, r = nb & 7, xcd = b & 7, idx = b >> 3;
+    const uint32_t t = (xcd < r) ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
+    const uint32_t tm = fdiv_u(t, a.divTN);
+    const uint32_t m0 = tm * BM;
+    const int n0 = static_cast<int>((t - tm * a.tiles_n) * BN);
+
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(g.X, a.x_bytes), rw = make_rsrc(g.Wq, a.w_bytes);
+
+    // ---- output column parameters: requested first, used last ----
+    // output group `i` of this thread: four consecutive channels of one pixel
+    const bool vec = (g.NC % 8 == 0) && (g.ldy % 8 == 0);
+    float mul[QPT][4], add[QPT][4];
+    int ncol0[QPT];
+#pragma unroll
+    for (int i = 0; i < QPT; ++i) {
+        const int qd = i * 64 * NW + tid;                       // [pixel][BN / 4]
+        ncol0[i] = n0 + (qd % (BN / 4)) * 4;
+        if (qd >= QUADS || m0 + qd / (BN / 4) >= static_cast<uint32_t>(g.M)) ncol0[i] = g.NC;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            mul[i][e] = add[i][e] = 0.0f;
+            if (ncol0[i] + e < g.NC) {
+                const int ag = (g.rows_per_group >= g.NC) ? 0 : (ncol0[i] + e) / g.rows_per_group;
+                mul[i][e] = 0.5f * g.alpha[ag] * (g.scale ? g.scale[ncol0[i] + e] : 1.0f);      // codes were +-2
+                add[i][e] = g.shift ? g.shift[ncol0[i] + e] : 0.0f;
+            }
+        }
+    }
+
+    // ---- addresses: load i of a slab covers rows 8i .. 8i+7 (eight lanes each); LDS row r keeps logical 16-byte
+    // chunk c at position c ^ ((r >> 1) & 7), so that 16 rows of one chunk fall in 16 different bank groups ----
+    const int kc[2] = {(lane & 7) ^ ((lane >> 4) & 3), (lane & 7) ^ (4 + ((lane >> 4) & 3))};   // rows of even / odd i
+    uint32_t base[NA];              // byte offset of the row (GEMM) or first pixel of its image (convolution)
+    int ih0[NA], iw0[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const uint32_t m = m0 + i * 8 + (lane >> 3);
+        const bool ok = m < static_cast<uint32_t>(g.M);
+        if constexpr (MODE == kSmallGemm) {
+            base[i] = ok ? m * static_cast<uint32_t>(g.xs) * 2u : kBufOutside;
+            ih0[i] = iw0[i] = 0;
+        } else {
+            const uint32_t tt = fdiv_u(m, a.divOW);
+            const int ow = static_cast<int>(m - tt * static_cast<uint32_t>(g.OW));
+            const uint32_t img = fdiv_u(tt, a.divOH);
+            const int oh = static_cast<int>(tt - img * static_cast<uint32_t>(g.OH));
+            base[i] = img * static_cast<uint32_t>(g.IH) * static_cast<uint32_t>(g.IW);
+            ih0[i] = ok ? oh * g.sh - g.ph : -(1 << 28);
+            iw0[i] = ow * g.sw - g.pw;
+        }
+    }
+    // codes: load i of a group covers channels 16i .. 16i+15 (four lanes each, 64 bytes = four slabs of a channel);
+    // the slab of position c in row r is c ^ ((r >> 2) & 3)
+    uint32_t boff[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int row = i * 16 + (lane >> 2);
+        const int col = n0 + row;
+        boff[i] = (col < g.NC) ? static_cast<uint32_t>(col) * static_cast<uint32_t>(g.wpr) * 4u + ((lane & 3) ^ ((row >> 2) & 3)) * 16u
+                               : kBufOutside;
+    }
+
+    // this wave's slabs: a contiguous range
+    const int KT = (g.K + 63) / 64;
+    const int per = (KT + NW - 1) / NW;
+    const int s0 = wave * per;
+    const int ns = (s0 + per <= KT) ? per : (KT > s0 ? KT - s0 : 0);
+    unsigned char* mine = smem + wave * WAVE_BYTES;
+    const uint32_t lds_mine = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+        (__attribute__((address_space(3))) unsigned char*)mine));
+
+    auto tap_offset = [&](int i, int rr, int ss, int c, bool kok) __attribute__((always_inline)) -> uint32_t {
+        int th = ih0[i] + rr * g.dh, tw = iw0[i] + ss * g.dw;
+        bool ok = kok;
+        if (g.divh > 1) {           // wave-uniform: strided backward-data
+            const int d = th / g.divh;
+            ok = ok & (th >= 0) & (d * g.divh == th);
+            th = d;
+        }
+        if (g.divw > 1) {
+            const int d = tw / g.divw;
+            ok = ok & (tw >= 0) & (d * g.divw == tw);
+            tw = d;
+        }
+        ok = ok & (static_cast<unsigned>(th) < static_cast<unsigned>(g.IH)) & (static_cast<unsigned>(tw) < static_cast<unsigned>(g.IW));
+        const uint32_t off = ((base[i] + static_cast<uint32_t>(th * g.IW + tw)) * static_cast<uint32_t>(g.xs) + c) * 2u;
+        return ok ? off : kBufOutside;
+    };
+    // slab s of the range -> stage st (and, with the first slab of a group, the codes of the group)
+    auto fetch = [&](int s, int st) __attribute__((always_inline)) {
+        const int kt = s0 + s;
+        if ((s & 3) == 0) {
+            unsigned char* dst = mine + DEPTH * STAGE + ((s >> 2) & 1) * CODES;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) buf_dma16(rw, boff[i], static_cast<uint32_t>(kt) * 16u, dst + i * 1024);
+        }
+        unsigned char* dst = mine + st * STAGE;
+        if constexpr (MODE == kSmallGemm) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) {
+                const int k = kt * 64 + kc[i & 1] * 8;
+                buf_dma16(rx, k < g.K ? base[i] + static_cast<uint32_t>(k) * 2u : kBufOutside, 0u, dst + i * 1024);
+            }
+        } else if constexpr (MODE == kSmallTap) {
+            const uint32_t rs = fdiv_u(static_cast<uint32_t>(kt) * 64u, a.divIC);         // wave-uniform
+            const int c = kt * 64 - static_cast<int>(rs) * g.IC;
+            const int rr = static_cast<int>(fdiv_u(rs, a.divS));
+            const int ss = static_cast<int>(rs) - rr * g.S;
+#pragma unroll
+            for (int i = 0; i < NA; ++i) buf_dma16(rx, tap_offset(i, rr, ss, c + kc[i & 1] * 8, true), 0u, dst + i * 1024);
+        } else {
+            int c[2], rr[2], ss[2];
+            bool kok[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int k = kt * 64 + kc[e] * 8;
+                const uint32_t rs = fdiv_u(static_cast<uint32_t>(k), a.divIC);
+                c[e] = k - static_cast<int>(rs) * g.IC;
+                rr[e] = static_cast<int>(fdiv_u(rs, a.divS));
+                ss[e] = static_cast<int>(rs) - rr[e] * g.S;
+                kok[e] = k < g.K;
+            }
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                buf_dma16(rx, tap_offset(i, rr[i & 1], ss[i & 1], c[i & 1], kok[i & 1]), 0u, dst + i * 1024);
+        }
+    };
+
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.0f;
+
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (d < ns) fetch(d, d);
+
+    uint32_t aoff[4];               // this lane's fragment of step kk inside a stage (row lrow; the next 32 rows: + 4096)
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) aoff[kk] = lds_mine + lrow * 128 + (((lh * 4 + kk) ^ ((lrow >> 1) & 7)) * 16);
+
+    int st = 0;
+    for (int sg = 0; sg < ns; sg += 4) {
+        static_for<4>([&](auto p_tag) __attribute__((always_inline)) {
+            constexpr int p = decltype(p_tag)::value;
+            const int s = sg + p;
+            if (s >= ns) return;                                // wave-uniform
+            // slab s (and its codes) landed: younger loads may stay in flight, unless the range ends before them
+            if (s + DEPTH - 1 < ns) {
+                constexpr int younger = (DEPTH - 1) * NA + ((p + DEPTH - 1 >= 4) ? NB : 0);
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(younger) : "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            u32x2 w[NT];
+            u32x4 x[4][MT];
+            const uint32_t cbase = lds_mine + DEPTH * STAGE + ((sg >> 2) & 1) * CODES + lrow * 64 + lh * 8 + ((p ^ ((lrow >> 2) & 3)) * 16);
+            lds_read64_n<NT, 32 * 64>(w, cbase);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) lds_read128_n<MT, 4096>(x[kk], aoff[kk] + st * STAGE);
+            static_for<4>([&](auto kk_tag) __attribute__((always_inline)) {
+                constexpr int kk = decltype(kk_tag)::value;
+                lds_wait<(3 - kk) * MT>();
+                if constexpr (kk == 0) lds_ready<NT>(w);
+                lds_ready<MT>(x[kk]);
+                if constexpr (kk == 3) {
+                    if (s + DEPTH < ns) fetch(s + DEPTH, st);   // every read of this stage has returned
+                }
+                u32x4 wf[NT];
+#pragma unroll
+                for (int ni = 0; ni < NT; ++ni)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        constexpr int half = (kk & 1) * 4;
+                        const int i = half + e;                 // field i of both half-words -> bits [14,15] of two bf16
+                        wf[ni][e] = (w[ni][kk >> 1] & (0xC000C000u >> (14 - 2 * i))) << (14 - 2 * i);
+                    }
+#pragma unroll
+                for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < NT; ++ni)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[ni]),
+                                                                              __builtin_bit_cast(bf16x8, x[kk][mi]),
+                                                                              acc[mi][ni], 0, 0, 0);
+            });
+            st = (st + 1 == DEPTH) ? 0 : st + 1;
+        });
+    }
+
+    // ---- partial tiles -> LDS, each wave over its own staging memory: [mi][ni][q4*2 + lh][pixel] of four channels ----
+#pragma unroll
+    for (int mi = 0; mi < MT; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NT; ++ni)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                unsigned char* dst = mine + (mi * NT + ni) * kPartTile + (q4 * 2 + lh) * kQuadRow + lrow * 16;
+                *reinterpret_cast<f32x4*>(dst) = f32x4{acc[mi][ni][q4 * 4], acc[mi][ni][q4 * 4 + 1], acc[mi][ni][q4 * 4 + 2],
+                                                       acc[mi][ni][q4 * 4 + 3]};
+            }
+    __syncthreads();
+
+    // ---- sum in wave order, y = relu?((alpha*acc)*scale + shift + residual) ----
+#pragma unroll
+    for (int i = 0; i < QPT; ++i) {
+        if (ncol0[i] >= g.NC) continue;
+        const int qd = i * 64 * NW + tid;
+        const int pix = qd / (BN / 4), c4 = qd % (BN / 4);
+        const uint32_t m = m0 + pix;
+        int64_t orow = m;
+        if (g.orU != 0) {
+            const uint32_t n = fdiv_u(m, a.divUV);
+            const uint32_t rem = m - n * static_cast<uint32_t>(g.orU * g.orV);
+            const uint32_t u = fdiv_u(rem, a.divV);
+            const uint32_t v = rem - u * static_cast<uint32_t>(g.orV);
+            orow = (static_cast<int64_t>(n) * g.orH + g.ora + g.orsh * static_cast<int>(u)) * g.orW + g.orb + g.orsw * static_cast<int>(v);
+        }
+        const int64_t yoff = orow * g.ldy + ncol0[i];
+        const unsigned char* src = smem + ((pix >> 5) * NT + (c4 >> 3)) * kPartTile + (c4 & 7) * kQuadRow + (pix & 31) * 16;
+        f32x4 s = *reinterpret_cast<const f32x4*>(src);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += *reinterpret_cast<const f32x4*>(src + w * WAVE_BYTES);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = s[e] * mul[i][e] + add[i][e];
+        if (vec && !g.y_f32) {
+            if (g.residual) {
+                const u32x2 rr = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(g.residual) + yoff);
+                v[0] += __uint_as_float(rr[0] << 16);
+                v[1] += __uint_as_float(rr[0] & 0xFFFF0000u);
+                v[2] += __uint_as_float(rr[1] << 16);
+                v[3] += __uint_as_float(rr[1] & 0xFFFF0000u);
+            }
+            if (g.relu) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);
+            }
+            u32x2 pk;
+            pk[0] = pack_bf16x2(v[0], v[1]);
+            pk[1] = pack_bf16x2(v[2], v[3]);
+            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(g.Y) + yoff) = pk;
+        } else if (vec) {
+            if (g.residual) {
+                const f32x4 rr = *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.residual) + yoff);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += rr[e];
+            }
+            if (g.relu) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);
+            }
+            *reinterpret_cast<f32x4*>(static_cast<float*>(g.Y) + yoff) = f32x4{v[0], v[1], v[2], v[3]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (ncol0[i] + e >= g.NC) continue;
+                const int64_t off = yoff + e;
+                if (g.y_f32) {
+                    if (g.residual) v[e] += static_cast<const float*>(g.residual)[off];
+                    if (g.relu) v[e] = fmaxf(v[e], 0.0f);
+                    static_cast<float*>(g.Y)[off] = v[e];
+                } else {
+                    if (g.residual) v[e] += bf16_to_f32(static_cast<const uint16_t*>(g.residual)[off]);
+                    if (g.relu) v[e] = fmaxf(v[e], 0.0f);
+                    static_cast<uint16_t*>(g.Y)[off] = f32_to_bf16(v[e]);
+                }
+            }
+        }
+    }
+}
+
+int small_mode(const GatherGemm& g) {
+    if (g.plain_gemm) return kSmallGemm;
+    return (!g.chunk_gather && g.IC % 64 == 0) ? kSmallTap : kSmallChunk;
+}
+
+SmallProblem make_problem(const GatherGemm& g, int bm, int bn) {
+    SmallProblem p;
+    p.g = g;
+    p.divIC = make_fastdiv_u(static_cast<uint32_t>(g.IC));
+    p.divS = make_fastdiv_u(static_cast<uint32_t>(g.S));
+    p.divOW = make_fastdiv_u(static_cast<uint32_t>(g.OW));
+    p.divOH = make_fastdiv_u(static_cast<uint32_t>(g.OH));
+    p.divUV = make_fastdiv_u(g.orU ? static_cast<uint32_t>(g.orU) * static_cast<uint32_t>(g.orV) : 1u);
+    p.divV = make_fastdiv_u(g.orU ? static_cast<uint32_t>(g.orV) : 1u);
+    p.x_bytes = static_cast<uint32_t>(small_x_bytes(g));
+    p.w_bytes = static_cast<uint32_t>(static_cast<int64_t>(g.NC) * g.wpr * 4);
+    p.tiles_n = static_cast<uint32_t>((g.NC + bn - 1) / bn);
+    p.divTN = make_fastdiv_u(p.tiles_n);
+    p.blocks = static_cast<uint32_t>((g.M + bm - 1) / bm) * p.tiles_n;
+    return p;
+}
+
+template <int MT, int NT, int NW, int MODE, int NP>
+int32_t launch_small_kernel(const SmallArgs<NP>& a, uint32_t width, int count, hipStream_t st) {
+    constexpr int DEPTH = 3;
+    constexpr int SMEM = NW * small_wave_bytes(MT, NT, DEPTH);
+    static_assert(SMEM <= 160 * 1024, "LDS budget");
+    auto k = conv_small_kernel<MT, NT, NW, MODE, NP, DEPTH>;
+    // more than 64 KB of dynamic LDS has to be allowed once per kernel
+    static std::once_flag once;
+    static bool allowed = false;
+    std::call_once(once, [&] {
+        allowed = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      SMEM) == hipSuccess;
+    });
+    if (!allowed) return TWN_ERR_HIP;
+    k<<<dim3(width, static_cast<unsigned>(count)), dim3(64 * NW), SMEM, st>>>(a);
+    return launch_status();
+}
+
+template <int MT, int NT, int NW>
+int32_t launch_small_tile(const GatherGemm* gs, int count, hipStream_t st) {
+    if (count == 1) {
+        SmallArgs<1> a;
+        a.p[0] = make_problem(gs[0], 32 * MT, 32 * NT);
+        const uint32_t width = a.p[0].blocks;
+        switch (small_mode(gs[0])) {
+            case kSmallGemm: return launch_small_kernel<MT, NT, NW, kSmallGemm, 1>(a, width, 1, st);
+            case kSmallTap: return launch_small_kernel<MT, NT, NW, kSmallTap, 1>(a, width, 1, st);
+            default: return launch_small_kernel<MT, NT, NW, kSmallChunk, 1>(a, width, 1, st);
+        }
+    }
+    SmallArgs<kProblemsMax> a{};
+    uint32_t width = 0;
+    bool tap = true;
+    for (int c = 0; c < count; ++c) {
+        a.p[c] = make_problem(gs[c], 32 * MT, 32 * NT);
+        if (a.p[c].blocks > width) width = a.p[c].blocks;
+        tap = tap && gs[c].IC % 64 == 0 && !gs[c].chunk_gather;
+    }
+    return tap ? launch_small_kernel<MT, NT, NW, kSmallTap, kProblemsMax>(a, width, count, st)
+               : launch_small_kernel<MT, NT, NW, kSmallChunk, kProblemsMax>(a, width, count, st);
+}
+
+}  // namespace
+
+// Tile (32 pixels x 32 or 64 channels, number of waves: 1108, 1208, 1204) for `count` problems in one launch, 0 when the
+// other kernels are better or the shapes do not fit.  Measured per dependent launch (us, against the split-K launch pair
+// and the persistent kernels that ran such problems before):
+//   * up to 256 tiles of 32x32: eight waves per tile, one tile per CU (M, N, K = 49, 512, 4608: 10.8 -> 8.1; 784, 128, 1152:
+//     11.6 -> 5.1; 1, 1000, 512: 5.1 -> 3.6).  Two such workgroups do not fit a CU: 392 tiles take 8.7 against 6.3 with
+//   * up to 256 tiles of 32x64: eight waves (784, 512, 4608: 25.9 -> 10.7).  Above that
+//   * up to 512 tiles of 32x64: four waves, two workgroups per CU (3136, 256, 2304: 26.2 -> 11.7), where the persistent
+//     kernels cannot run (channel counts that are no multiple of 64, float32 outputs, divided taps: 13.8 -> 7.2) or K has
+//     at least 16 slabs; with shorter K they win (6272, 128, 576: 6.4 against 7.5).
+// Beyond 512 tiles the other kernels' larger tiles win (12544, 128, 1152: 8.9 against 16.4), and beyond K = 16384 one
+// workgroup per tile is too few for the loads: K ranges over several workgroups win (64, 64, 32768: 15.2 against 22.8;
+// 128, 128, 16384: 13.2 against 13.0).
+int conv_small_tile(const GatherGemm* gs, int count) {
+    if (count < 1 || count > kProblemsMax || env_int("TWN_TILE", 0) != 0 || env_int("TWN_SMALL", 1) == 0) return 0;
+    int64_t t11 = 0, t12 = 0;
+    bool persistent = true;
+    int kt = 0;
+    for (int c = 0; c < count; ++c) {
+        const GatherGemm& g = gs[c];
+        if (!g.chunk_gather && (g.IC % 8 != 0 || g.xs % 8 != 0)) return 0;
+        if (g.M <= 0 || g.M >= (1LL << 31) - 128) return 0;
+        if (!g.plain_gemm && g.M % (static_cast<int64_t>(g.OH) * g.OW) != 0) return 0;
+        const int64_t xb = small_x_bytes(g), wb = static_cast<int64_t>(g.NC) * g.wpr * 4;
+        if (xb <= 0 || xb >= (1LL << 31) || wb >= (1LL << 31)) return 0;
+        const int64_t rows = (g.M + 31) / 32;
+        t11 += rows * ((g.NC + 31) / 32);
+        t12 += rows * ((g.NC + 63) / 64);
+        const bool slabs = g.plain_gemm ? g.K % 64 == 0 : (g.IC % 64 == 0 && g.divh == 1 && g.divw == 1 && g.orU == 0);
+        persistent = persistent && slabs && !g.y_f32 && g.NC % 8 == 0 && g.ldy % 8 == 0 && !g.chunk_gather;
+        if ((g.K + 63) / 64 > kt) kt = (g.K + 63) / 64;
+    }
+    if (kt > 256) return 0;
+    if (t11 <= 256) return 1108;
+    if (t12 <= 256) return 1208;
+    if (t12 <= 512 && (kt >= 16 || !persistent)) return 1204;
+    return 0;
+}
+
+int32_t launch_conv_small(const GatherGemm* gs, int count, int tile, hipStream_t st) {
+    switch (tile) {
+        case 1108: return launch_small_tile<1, 1, 8>(gs, count, st);
+        case 1208: return launch_small_tile<1, 2, 8>(gs, count, st);
+        case 1204: return launch_small_tile<1, 2, 4>(gs, count, st);
+        default: return TWN_ERR_UNSUPPORTED;
+    }
+}
+
+}  // namespace twn

@@ -88,6 +88,11 @@ bool conv_stream_applicable(const GatherGemm& g);
 int32_t launch_conv_stream(const GatherGemm& g, int tile, hipStream_t st);
 int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int ks, int np, int stages, hipStream_t st);
 
+// Problems of few output tiles: up to four of them in one launch, the K slabs of a tile shared out over the waves of
+// one workgroup; conv_small_tile (a pure function of the problems) names the tile, 0 when other kernels are better.
+int conv_small_tile(const GatherGemm* gs, int count);
+int32_t launch_conv_small(const GatherGemm* gs, int count, int tile, hipStream_t st);
+
 // 3x3 stride-1 convolutions over 64 input channels (forward, or backward-data with mirrored taps), bf16 in and out,
 // output channels a multiple of 64: persistent kernel with the expanded weights resident in registers and the input
 // patch of an 8x8 pixel tile (with halo) in LDS; `applicable` is a pure function of the problem.
