@@ -7,7 +7,9 @@ kernels.  There is no fallback: a missing library raises.
 """
 
 import ctypes
+import math
 import os
+import struct
 from dataclasses import dataclass
 from typing import Optional
 
@@ -62,6 +64,9 @@ class ConvDesc(ctypes.Structure):
                  "x_dtype", "y_dtype", "variant", "alpha_groups")]
 
 
+_EPILOGUE = struct.Struct("PPPi4x").pack      # the bytes of an Epilogue
+
+
 class Epilogue(ctypes.Structure):
     _fields_ = [("scale", ctypes.c_void_p), ("shift", ctypes.c_void_p), ("residual", ctypes.c_void_p),
                 ("relu", ctypes.c_int32)]
@@ -79,6 +84,7 @@ def lib():
             raise FileNotFoundError(
                 "%s is missing: build it with `python -m paper_1605_04711_amd.build`" % _LIB_PATH)
         L = ctypes.CDLL(_LIB_PATH)
+        # descriptors and epilogues are passed as the bytes of the C structs (see _Plan): their parameters are plain pointers
         vp, i32, i64, sz, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t, ctypes.c_float
         L.twn_status_str.restype = ctypes.c_char_p
         L.twn_status_str.argtypes = [i32]
@@ -88,9 +94,9 @@ def lib():
         L.twn_packed_bytes.restype = sz
         L.twn_packed_bytes.argtypes = [i32, i64]
         L.twn_ternarize_workspace_bytes.restype = sz
-        L.twn_ternarize_workspace_bytes.argtypes = [ctypes.POINTER(WeightDesc), i32]
+        L.twn_ternarize_workspace_bytes.argtypes = [vp, i32]
         L.twn_ternarize.restype = i32
-        L.twn_ternarize.argtypes = [vp, ctypes.POINTER(WeightDesc), i32, f32, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.twn_ternarize.argtypes = [vp, vp, i32, f32, vp, vp, vp, vp, vp, vp, sz, vp]
         L.twn_ternarize_static_scratch_bytes.restype = sz
         L.twn_ternarize_static_scratch_bytes.argtypes = []
         L.twn_ternarize_static.restype = i32
@@ -112,22 +118,22 @@ def lib():
         L.twn_sgd_update.restype = i32
         L.twn_sgd_update.argtypes = [vp, vp, vp, i64, f32, f32, f32, vp, sz, vp]
         L.twn_ternarize_presummed.restype = i32
-        L.twn_ternarize_presummed.argtypes = [vp, ctypes.POINTER(WeightDesc), f32, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.twn_ternarize_presummed.argtypes = [vp, vp, f32, vp, vp, vp, vp, vp, vp, sz, vp]
         L.twn_gemm_fwd_workspace_bytes.restype = sz
-        L.twn_gemm_fwd_workspace_bytes.argtypes = [ctypes.POINTER(GemmDesc)]
+        L.twn_gemm_fwd_workspace_bytes.argtypes = [vp]
         L.twn_gemm_fwd.restype = i32
-        L.twn_gemm_fwd.argtypes = [ctypes.POINTER(GemmDesc), vp, vp, vp, ctypes.POINTER(Epilogue), vp, vp, sz, vp]
+        L.twn_gemm_fwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.twn_conv2d_fwd_workspace_bytes.restype = sz
-        L.twn_conv2d_fwd_workspace_bytes.argtypes = [ctypes.POINTER(ConvDesc)]
+        L.twn_conv2d_fwd_workspace_bytes.argtypes = [vp]
         L.twn_conv2d_fwd.restype = i32
-        L.twn_conv2d_fwd.argtypes = [ctypes.POINTER(ConvDesc), vp, vp, vp, ctypes.POINTER(Epilogue), vp, vp, sz, vp]
+        L.twn_conv2d_fwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.twn_conv2d_fwd_pair.restype = i32
-        L.twn_conv2d_fwd_pair.argtypes = [ctypes.POINTER(ConvDesc), ctypes.POINTER(ConvDesc), vp,
-                                          vp, vp, ctypes.POINTER(Epilogue), vp, vp, vp, ctypes.POINTER(Epilogue), vp, vp]
+        L.twn_conv2d_fwd_pair.argtypes = [vp, vp, vp,
+                                          vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.twn_conv2d_bwd_ste_workspace_bytes.restype = sz
-        L.twn_conv2d_bwd_ste_workspace_bytes.argtypes = [ctypes.POINTER(ConvDesc)]
+        L.twn_conv2d_bwd_ste_workspace_bytes.argtypes = [vp]
         L.twn_conv2d_bwd_ste.restype = i32
-        L.twn_conv2d_bwd_ste.argtypes = [ctypes.POINTER(ConvDesc), vp, vp, vp, vp, vp, vp, vp, f32, vp, sz, vp]
+        L.twn_conv2d_bwd_ste.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, f32, vp, sz, vp]
         _lib = L
     return _lib
 
@@ -142,21 +148,27 @@ def _check(status, where):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
+    """HIP stream handle.  torch.cuda.current_stream() builds a stream object (2.7 us, the kernel of a small call takes 4);
+    the handle alone takes 0.2 us."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
+
+
+def _code(dtype):
+    if dtype == torch.float32:
+        return TWN_F32
+    if dtype == torch.bfloat16:
+        return TWN_BF16
+    raise TypeError("only float32 and bfloat16 tensors are accepted")
 
 
 def _dtype_code(t):
-    if t.dtype == torch.float32:
-        return TWN_F32
-    if t.dtype == torch.bfloat16:
-        return TWN_BF16
-    raise TypeError("only float32 and bfloat16 tensors are accepted")
+    return _code(t.dtype)
 
 
 def _workspace(nbytes, device, stream=None):
@@ -222,19 +234,16 @@ def twn_ternarize(W, delta_factor=0.7, groups=1, transposed=False, out=None, wor
     if not W.is_contiguous() or W.dtype != torch.float32 or not W.is_cuda:
         raise TypeError("W must be a contiguous float32 CUDA tensor")
     L = lib()
-    wd = WeightDesc(rows, c, r, s)
     dev = W.device
     if out is None:
-        k, kt = r * s * c, r * s * rows
-        packed = torch.empty((rows, twn_packed_words_per_row(k)), dtype=torch.int32, device=dev)
-        packed_t = torch.empty((c, twn_packed_words_per_row(kt)), dtype=torch.int32, device=dev) if transposed else None
-        out = TernaryWeights(rows, c, r, s, groups, packed, packed_t,
-                             torch.empty(groups, dtype=torch.float32, device=dev),
-                             torch.empty(groups, dtype=torch.float32, device=dev),
-                             torch.empty(groups, dtype=torch.int64, device=dev))
+        out = _new_ternary_weights(rows, c, r, s, groups, transposed, dev)
+    key = ("tern", rows, c, r, s, groups)
+    plan = _Plan.kept.get(key)
+    if plan is None:
+        plan = _plan(key, lambda: _Plan(WeightDesc(rows, c, r, s), lambda d: L.twn_ternarize_workspace_bytes(d, groups)))
     if workspace is None:
-        workspace = _workspace(L.twn_ternarize_workspace_bytes(ctypes.byref(wd), groups), dev, stream)
-    rc = L.twn_ternarize(_ptr(W), ctypes.byref(wd), groups, ctypes.c_float(delta_factor),
+        workspace = _workspace(plan.need, dev, stream)
+    rc = L.twn_ternarize(_ptr(W), plan.desc, groups, delta_factor,
                          _ptr(out.packed), _ptr(out.packed_T), _ptr(out.delta), _ptr(out.alpha), _ptr(out.nnz),
                          _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "twn_ternarize")
@@ -244,6 +253,7 @@ def twn_ternarize(W, delta_factor=0.7, groups=1, transposed=False, out=None, wor
 def reload_env():
     """Have the library read its TWN_* tuning overrides again (they are read once and remembered)."""
     lib().twn_reload_env()
+    _Plan.kept.clear()      # workspace sizes may depend on the overrides
 
 
 @dataclass
@@ -297,8 +307,7 @@ def twn_sgd_update(W, V, dW, lr, momentum=0.9, weight_decay=1e-4, tern_workspace
     for name, t in (("W", W), ("V", V), ("dW", dW)):
         if not t.is_contiguous() or t.dtype != torch.float32 or not t.is_cuda or t.shape != W.shape:
             raise TypeError("%s must be a contiguous float32 CUDA tensor of the shape of W" % name)
-    rc = lib().twn_sgd_update(_ptr(W), _ptr(V), _ptr(dW), W.numel(), ctypes.c_float(lr), ctypes.c_float(momentum),
-                              ctypes.c_float(weight_decay), _ptr(tern_workspace),
+    rc = lib().twn_sgd_update(_ptr(W), _ptr(V), _ptr(dW), W.numel(), lr, momentum, weight_decay, _ptr(tern_workspace),
                               tern_workspace.numel() if tern_workspace is not None else 0, _stream(stream))
     _check(rc, "twn_sgd_update")
 
@@ -309,7 +318,7 @@ def twn_ternarize_presummed(W, out, workspace, delta_factor=0.7, stream=None):
     if not W.is_contiguous() or W.dtype != torch.float32 or not W.is_cuda:
         raise TypeError("W must be a contiguous float32 CUDA tensor")
     wd = WeightDesc(out.rows, out.C, out.R, out.S)
-    rc = lib().twn_ternarize_presummed(_ptr(W), ctypes.byref(wd), ctypes.c_float(delta_factor),
+    rc = lib().twn_ternarize_presummed(_ptr(W), ctypes.byref(wd), delta_factor,
                                        _ptr(out.packed), _ptr(out.packed_T), _ptr(out.delta), _ptr(out.alpha),
                                        _ptr(out.nnz), _ptr(workspace), workspace.numel(), _stream(stream))
     _check(rc, "twn_ternarize_presummed")
@@ -372,8 +381,33 @@ def twn_unpack_i8(packed, rows, k, stream=None):
 def _epilogue(scale, shift, residual, relu):
     if scale is None and shift is None and residual is None and not relu:
         return None
-    return Epilogue(None if scale is None else scale.data_ptr(), None if shift is None else shift.data_ptr(),
-                    None if residual is None else residual.data_ptr(), 1 if relu else 0)
+    return _EPILOGUE(0 if scale is None else scale.data_ptr(), 0 if shift is None else shift.data_ptr(),
+                     0 if residual is None else residual.data_ptr(), 1 if relu else 0)
+
+
+class _Plan:
+    """What a call derives from its shapes alone: the descriptor as the bytes of its C struct, the workspace it needs and
+    the output's shape and strides (torch.empty_strided parses its arguments in three quarters of torch.empty's time).
+    Kept per shape, so that a repeated call does not build structs and query sizes again (4 us)."""
+    __slots__ = ("desc", "need", "shape", "strides")
+    kept = {}
+    KEPT_MAX = 4096
+
+    def __init__(self, desc, query, shape=None):
+        self.desc = bytes(desc)
+        self.need = int(query(self.desc))
+        self.shape = shape
+        self.strides = None if shape is None else tuple(math.prod(shape[i + 1:]) for i in range(len(shape)))
+
+
+def _plan(key, make):
+    plan = _Plan.kept.get(key)
+    if plan is None:
+        plan = make()
+        if len(_Plan.kept) >= _Plan.KEPT_MAX:
+            _Plan.kept.clear()
+        _Plan.kept[key] = plan
+    return plan
 
 
 def twn_gemm_fwd_workspace_bytes(m, tw, x_dtype=torch.bfloat16, y_dtype=torch.bfloat16, variant=None):
@@ -381,7 +415,7 @@ def twn_gemm_fwd_workspace_bytes(m, tw, x_dtype=torch.bfloat16, y_dtype=torch.bf
         variant = TWN_VAR_FP32 if x_dtype == torch.float32 else TWN_VAR_BF16_POSTSCALE
     code = {torch.float32: TWN_F32, torch.bfloat16: TWN_BF16}
     d = GemmDesc(m, tw.rows, tw.K, code[x_dtype], code[y_dtype], variant, 0, 0, tw.groups)
-    return int(lib().twn_gemm_fwd_workspace_bytes(ctypes.byref(d)))
+    return int(lib().twn_gemm_fwd_workspace_bytes(bytes(d)))
 
 
 def twn_gemm_fwd(X, tw, y_dtype=torch.bfloat16, variant=None, scale=None, shift=None, residual=None,
@@ -392,17 +426,24 @@ def twn_gemm_fwd(X, tw, y_dtype=torch.bfloat16, variant=None, scale=None, shift=
         raise ValueError("K mismatch")
     if variant is None:
         variant = TWN_VAR_FP32 if X.dtype == torch.float32 else TWN_VAR_BF16_POSTSCALE
-    Y = out if out is not None else torch.empty((m, tw.rows), dtype=y_dtype, device=X.device)
-    d = GemmDesc(m, tw.rows, k, _dtype_code(X), _dtype_code(Y), variant, X.stride(0), Y.stride(0), tw.groups)
-    ep = _epilogue(scale, shift, residual, relu)
+    n = tw.rows
+    ldy = n
+    if out is not None:
+        y_dtype, ldy = out.dtype, out.stride(0)
     L = lib()
-    if workspace is None:
-        need = L.twn_gemm_fwd_workspace_bytes(ctypes.byref(d))
-        workspace = _workspace(need, X.device, stream) if need else None
-    rc = L.twn_gemm_fwd(ctypes.byref(d), _ptr(X), _ptr(tw.weights_for(variant)), _ptr(tw.alpha),
-                        None if ep is None else ctypes.byref(ep), _ptr(Y), _ptr(workspace),
+    key = (m, n, k, X.dtype, y_dtype, variant, X.stride(0), ldy, tw.groups)
+    plan = _Plan.kept.get(key)
+    if plan is None:
+        plan = _plan(key, lambda: _Plan(GemmDesc(m, n, k, _dtype_code(X), _code(y_dtype), variant, X.stride(0), ldy,
+                                                 tw.groups), L.twn_gemm_fwd_workspace_bytes, (m, n)))
+    Y = out if out is not None else torch.empty_strided(plan.shape, plan.strides, dtype=y_dtype, device=X.device)
+    if workspace is None and plan.need:
+        workspace = _workspace(plan.need, X.device, stream)
+    rc = L.twn_gemm_fwd(plan.desc, X.data_ptr(), tw.weights_for(variant).data_ptr(), tw.alpha.data_ptr(),
+                        _epilogue(scale, shift, residual, relu), Y.data_ptr(), _ptr(workspace),
                         0 if workspace is None else workspace.numel(), _stream(stream))
-    _check(rc, "twn_gemm_fwd")
+    if rc != 0:
+        raise TwnError(rc, "twn_gemm_fwd")
     return Y
 
 
@@ -427,33 +468,38 @@ def twn_conv2d_fwd_workspace_bytes(x_shape, tw, stride=(1, 1), pad=(0, 0), dil=(
         variant = TWN_VAR_FP32 if x_dtype == torch.float32 else TWN_VAR_BF16_POSTSCALE
     code = {torch.float32: TWN_F32, torch.bfloat16: TWN_BF16}
     d = _conv_desc(x_shape, tw, stride, pad, dil, code[x_dtype], code[y_dtype], variant)
-    return int(lib().twn_conv2d_fwd_workspace_bytes(ctypes.byref(d)))
+    return int(lib().twn_conv2d_fwd_workspace_bytes(bytes(d)))
 
 
 def twn_conv2d_fwd(X, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1), y_dtype=torch.bfloat16, variant=None,
                    scale=None, shift=None, residual=None, relu=False, out=None, workspace=None, stream=None):
     """X NHWC; returns Y NHWC [N][P][Q][O]."""
-    _need_contiguous(X=X, out=out, residual=residual)
+    if not (X.is_contiguous() and (out is None or out.is_contiguous()) and (residual is None or residual.is_contiguous())):
+        _need_contiguous(X=X, out=out, residual=residual)
     if variant is None:
         variant = TWN_VAR_FP32 if X.dtype == torch.float32 else TWN_VAR_BF16_POSTSCALE
-    Y = out if out is not None else torch.empty(conv_out_shape(X.shape, tw, stride, pad, dil), dtype=y_dtype,
-                                                device=X.device)
-    d = _conv_desc(X.shape, tw, stride, pad, dil, _dtype_code(X), _dtype_code(Y), variant)
-    ep = _epilogue(scale, shift, residual, relu)
+    if out is not None:
+        y_dtype = out.dtype
     L = lib()
-    if workspace is None:
-        need = L.twn_conv2d_fwd_workspace_bytes(ctypes.byref(d))
-        workspace = _workspace(need, X.device, stream) if need else None
-    rc = L.twn_conv2d_fwd(ctypes.byref(d), _ptr(X), _ptr(tw.weights_for(variant)), _ptr(tw.alpha),
-                          None if ep is None else ctypes.byref(ep), _ptr(Y), _ptr(workspace),
+    key = ("fwd", X.shape, tw.rows, tw.C, tw.R, tw.S, tw.groups, *stride, *pad, *dil, X.dtype, y_dtype, variant)
+    plan = _Plan.kept.get(key)
+    if plan is None:
+        plan = _plan(key, lambda: _Plan(_conv_desc(X.shape, tw, stride, pad, dil, _dtype_code(X), _code(y_dtype), variant),
+                                        L.twn_conv2d_fwd_workspace_bytes, conv_out_shape(X.shape, tw, stride, pad, dil)))
+    Y = out if out is not None else torch.empty_strided(plan.shape, plan.strides, dtype=y_dtype, device=X.device)
+    if workspace is None and plan.need:
+        workspace = _workspace(plan.need, X.device, stream)
+    rc = L.twn_conv2d_fwd(plan.desc, X.data_ptr(), tw.weights_for(variant).data_ptr(), tw.alpha.data_ptr(),
+                          _epilogue(scale, shift, residual, relu), Y.data_ptr(), _ptr(workspace),
                           0 if workspace is None else workspace.numel(), _stream(stream))
-    _check(rc, "twn_conv2d_fwd")
+    if rc != 0:
+        raise TwnError(rc, "twn_conv2d_fwd")
     return Y
 
 
 def twn_conv2d_bwd_ste_workspace_bytes(x_shape, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1)):
     d = _conv_desc(x_shape, tw, stride, pad, dil, TWN_BF16, TWN_BF16, TWN_VAR_BF16_POSTSCALE)
-    return int(lib().twn_conv2d_bwd_ste_workspace_bytes(ctypes.byref(d)))
+    return int(lib().twn_conv2d_bwd_ste_workspace_bytes(bytes(d)))
 
 
 def twn_conv2d_bwd_ste(X, dY, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1), need_dx=True, need_dw=True,
@@ -468,15 +514,20 @@ def twn_conv2d_bwd_ste(X, dY, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1), need_dx
     if need_dw and dW is None:
         dW = torch.empty((tw.rows, tw.C, tw.R, tw.S), dtype=torch.float32, device=dev)
     dbias = torch.empty(tw.rows, dtype=torch.float32, device=dev) if need_dbias else None
-    d = _conv_desc(xs, tw, stride, pad, dil, TWN_BF16, _dtype_code(dX) if need_dx else TWN_BF16, variant)
+    y_dtype = dX.dtype if need_dx else torch.bfloat16
     L = lib()
+    key = ("bwd", xs, tw.rows, tw.C, tw.R, tw.S, tw.groups, *stride, *pad, *dil, y_dtype, variant)
+    plan = _Plan.kept.get(key)
+    if plan is None:
+        plan = _plan(key, lambda: _Plan(_conv_desc(xs, tw, stride, pad, dil, TWN_BF16, _code(y_dtype), variant),
+                                        L.twn_conv2d_bwd_ste_workspace_bytes))
     if workspace is None:
-        workspace = _workspace(L.twn_conv2d_bwd_ste_workspace_bytes(ctypes.byref(d)), dev, stream)
-    rc = L.twn_conv2d_bwd_ste(ctypes.byref(d), _ptr(X), _ptr(dY), _ptr(tw.packed_T), _ptr(tw.alpha),
+        workspace = _workspace(plan.need, dev, stream)
+    rc = L.twn_conv2d_bwd_ste(plan.desc, _ptr(X), dY.data_ptr(), _ptr(tw.packed_T), tw.alpha.data_ptr(),
                               _ptr(dX) if need_dx else None, _ptr(dW) if need_dw else None, _ptr(dbias),
-                              ctypes.c_float(1.0 if accumulate else 0.0), _ptr(workspace), workspace.numel(),
-                              _stream(stream))
-    _check(rc, "twn_conv2d_bwd_ste")
+                              1.0 if accumulate else 0.0, workspace.data_ptr(), workspace.numel(), _stream(stream))
+    if rc != 0:
+        raise TwnError(rc, "twn_conv2d_bwd_ste")
     return (dX if need_dx else None), (dW if need_dw else None), dbias
 
 
@@ -499,13 +550,12 @@ def prepare_conv2d_fwd(X, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1), out=None, v
     ep = _epilogue(scale, shift, residual, relu)
     L = lib()
     if workspace is None:
-        need = L.twn_conv2d_fwd_workspace_bytes(ctypes.byref(d))
+        need = L.twn_conv2d_fwd_workspace_bytes(bytes(d))
         workspace = _workspace(need, X.device) if need else None
     fn = L.twn_conv2d_fwd
-    args = (ctypes.byref(d), _ptr(X), _ptr(tw.weights_for(variant)), _ptr(tw.alpha),
-            None if ep is None else ctypes.byref(ep), _ptr(Y), _ptr(workspace),
+    args = (bytes(d), _ptr(X), _ptr(tw.weights_for(variant)), _ptr(tw.alpha), ep, _ptr(Y), _ptr(workspace),
             0 if workspace is None else workspace.numel())
-    keep = (d, ep, X, Y, tw, scale, shift, residual, workspace)
+    keep = (X, Y, tw, scale, shift, residual, workspace)
 
     def call(stream=None, _keep=keep):
         rc = fn(*args, _stream(stream))
@@ -526,10 +576,9 @@ def prepare_conv2d_fwd_pair(X, tws, geos, outs, scales=(None, None), shifts=(Non
         ds.append(_conv_desc(X.shape, tw, st, pd, dl, _dtype_code(X), _dtype_code(Y), TWN_VAR_BF16_POSTSCALE))
         eps.append(_epilogue(sc, sf, rs, rl))
     fn = lib().twn_conv2d_fwd_pair
-    args = (ctypes.byref(ds[0]), ctypes.byref(ds[1]), _ptr(X),
-            _ptr(tws[0].packed), _ptr(tws[0].alpha), None if eps[0] is None else ctypes.byref(eps[0]), _ptr(outs[0]),
-            _ptr(tws[1].packed), _ptr(tws[1].alpha), None if eps[1] is None else ctypes.byref(eps[1]), _ptr(outs[1]))
-    keep = (ds, eps, X, tws, outs, scales, shifts, residuals)
+    args = (bytes(ds[0]), bytes(ds[1]), _ptr(X), _ptr(tws[0].packed), _ptr(tws[0].alpha), eps[0], _ptr(outs[0]),
+            _ptr(tws[1].packed), _ptr(tws[1].alpha), eps[1], _ptr(outs[1]))
+    keep = (X, tws, outs, scales, shifts, residuals)
 
     def call(stream=None, _keep=keep):
         rc = fn(*args, _stream(stream))
@@ -559,13 +608,12 @@ def prepare_gemm_fwd(X, tw, out=None, y_dtype=torch.bfloat16, variant=None, scal
     ep = _epilogue(scale, shift, residual, relu)
     L = lib()
     if workspace is None:
-        need = L.twn_gemm_fwd_workspace_bytes(ctypes.byref(d))
+        need = L.twn_gemm_fwd_workspace_bytes(bytes(d))
         workspace = _workspace(need, X.device) if need else None
     fn = L.twn_gemm_fwd
-    args = (ctypes.byref(d), _ptr(X), _ptr(tw.weights_for(variant)), _ptr(tw.alpha),
-            None if ep is None else ctypes.byref(ep), _ptr(Y), _ptr(workspace),
+    args = (bytes(d), _ptr(X), _ptr(tw.weights_for(variant)), _ptr(tw.alpha), ep, _ptr(Y), _ptr(workspace),
             0 if workspace is None else workspace.numel())
-    keep = (d, ep, X, Y, tw, scale, shift, residual, workspace)
+    keep = (X, Y, tw, scale, shift, residual, workspace)
 
     def call(stream=None, _keep=keep):
         rc = fn(*args, _stream(stream))
@@ -582,11 +630,11 @@ def prepare_conv2d_bwd_ste(X, dY, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1), dX=
     d = _conv_desc(xs, tw, stride, pad, dil, TWN_BF16, _dtype_code(dX) if dX is not None else TWN_BF16, variant)
     L = lib()
     if workspace is None:
-        workspace = _workspace(L.twn_conv2d_bwd_ste_workspace_bytes(ctypes.byref(d)), dY.device)
+        workspace = _workspace(L.twn_conv2d_bwd_ste_workspace_bytes(bytes(d)), dY.device)
     fn = L.twn_conv2d_bwd_ste
-    args = (ctypes.byref(d), _ptr(X), _ptr(dY), _ptr(tw.packed_T), _ptr(tw.alpha), _ptr(dX), _ptr(dW), _ptr(dbias),
+    args = (bytes(d), _ptr(X), _ptr(dY), _ptr(tw.packed_T), _ptr(tw.alpha), _ptr(dX), _ptr(dW), _ptr(dbias),
             ctypes.c_float(1.0 if accumulate else 0.0), _ptr(workspace), workspace.numel())
-    keep = (d, X, dY, tw, dX, dW, dbias, workspace)
+    keep = (X, dY, tw, dX, dW, dbias, workspace)
 
     def call(stream=None, _keep=keep):
         rc = fn(*args, _stream(stream))

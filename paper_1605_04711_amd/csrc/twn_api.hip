@@ -1,6 +1,5 @@
 // Host-only helpers of the C ABI: status strings, packed-format sizes, env overrides.
 #include <cstdlib>
-#include <cstring>
 #include <mutex>
 
 #include "twn_common.h"
@@ -9,34 +8,26 @@ namespace twn {
 
 // The TWN_* tuning knobs are read from the environment once each and remembered: launches do not call getenv
 // (which is neither free nor safe against a concurrent setenv).  twn_reload_env forgets what was read.
-namespace {
-struct EnvEntry {
-    const char* name;     // the caller's string literal
-    bool set;
-    int value;
-};
-constexpr int kEnvMax = 64;
-std::mutex g_env_mutex;
-EnvEntry g_env[kEnvMax];
-int g_env_count = 0;
-}  // namespace
+std::atomic<uint32_t> g_env_generation{1};
 
-int env_int(const char* name, int fallback) {
-    std::lock_guard<std::mutex> lock(g_env_mutex);
-    for (int i = 0; i < g_env_count; ++i)
-        if (g_env[i].name == name || std::strcmp(g_env[i].name, name) == 0) return g_env[i].set ? g_env[i].value : fallback;
+uint64_t env_read(EnvKnob& k, const char* name, uint32_t generation) {
+    static std::mutex mutex;
+    std::lock_guard<std::mutex> lock(mutex);
     const char* v = std::getenv(name);
     const bool set = v && *v;
-    const int value = set ? std::atoi(v) : 0;
-    if (g_env_count < kEnvMax) g_env[g_env_count++] = EnvEntry{name, set, value};
-    return set ? value : fallback;
+    const uint64_t seen = (static_cast<uint64_t>(generation) << 33) | (static_cast<uint64_t>(set) << 32) |
+                          static_cast<uint32_t>(set ? std::atoi(v) : 0);
+    k.seen.store(seen, std::memory_order_relaxed);
+    return seen;
 }
 
 }  // namespace twn
 
 extern "C" void twn_reload_env(void) {
-    std::lock_guard<std::mutex> lock(twn::g_env_mutex);
-    twn::g_env_count = 0;
+    // a generation fits 31 bits in the stamp; 0 stands for "never read"
+    uint32_t g = twn::g_env_generation.load(std::memory_order_relaxed);
+    while (!twn::g_env_generation.compare_exchange_weak(g, g == 0x7FFFFFFFu ? 1u : g + 1u, std::memory_order_relaxed)) {
+    }
 }
 
 extern "C" const char* twn_status_str(int32_t status) {

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "twn.h"
 
 namespace twn {
@@ -20,8 +22,22 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Environment override for launch-shape sweeps (0 / unset = built-in choice).
-int env_int(const char* name, int fallback);
+// Environment override for launch-shape sweeps (0 / unset = built-in choice).  Every use keeps what it read, stamped
+// with the generation that twn_reload_env advances: a dispatch asks for up to ten of them, and a locked search by
+// name cost it about a microsecond.
+struct EnvKnob {
+    std::atomic<uint64_t> seen{0};      // generation << 33 | is set << 32 | value
+};
+extern std::atomic<uint32_t> g_env_generation;      // starts at 1
+uint64_t env_read(EnvKnob& k, const char* name, uint32_t generation);
+inline int env_value(EnvKnob& k, const char* name, int fallback) {
+    const uint32_t gen = g_env_generation.load(std::memory_order_relaxed);
+    uint64_t v = k.seen.load(std::memory_order_relaxed);
+    if ((v >> 33) != gen) v = env_read(k, name, gen);
+    return ((v >> 32) & 1u) ? static_cast<int>(static_cast<uint32_t>(v)) : fallback;
+}
+#define env_int(name, fallback) \
+    ::twn::env_value([]() -> ::twn::EnvKnob& { static ::twn::EnvKnob knob; return knob; }(), name, fallback)
 
 // ---- wave / block reductions in a fixed order (bit-identical run to run) ----
 __device__ __forceinline__ double wave_sum(double v) {
