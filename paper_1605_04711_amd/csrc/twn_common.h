@@ -86,6 +86,16 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
     return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
 
+// Two bf16 values times two float32 factors, each product as two bf16 terms: hi = bf16(v), lo = bf16(v - hi).
+struct Bf16Terms {
+    uint32_t hi, lo;
+};
+__device__ __forceinline__ Bf16Terms split_scaled_bf16x2(uint32_t x, float a0, float a1) {
+    const float v0 = __uint_as_float(x << 16) * a0, v1 = __uint_as_float(x & 0xFFFF0000u) * a1;
+    const uint32_t hi = pack_bf16x2(v0, v1);
+    return Bf16Terms{hi, pack_bf16x2(v0 - __uint_as_float(hi << 16), v1 - __uint_as_float(hi & 0xFFFF0000u))};
+}
+
 // 2-bit field of the packed format: bit0 = non-zero, bit1 = negative.
 __device__ __forceinline__ uint32_t code_field(float w, float delta) {
     const uint32_t nz = fabsf(w) > delta ? 1u : 0u;

@@ -216,6 +216,14 @@ void fill_conv_fwd_small_c(GatherGemm& g, const twn_conv_desc* d, const SmallC& 
     g.chunk_gather = 1;
 }
 
+// Backward-data over dY scaled by several alphas: two bf16 terms per value, side by side as twice the channels.
+void two_terms(GatherGemm& g) {
+    g.xs *= 2;
+    g.IC *= 2;
+    g.K *= 2;
+    g.wpr = static_cast<int32_t>(twn_packed_words_per_row(g.K));
+}
+
 // Strided backward-data as stride-1 problems, one per residue class (a, b) of the output pixels
 // (h = a + sh*u, w = b + sw*v): the taps that reach the class are r = r0 + jr*sh with r0 = (a + pad_h) % sh, the
 // coordinate read is p = u + (a + pad_h - r0)/sh - jr, i.e. an undivided gather with dilation -1.  Used for
@@ -264,6 +272,7 @@ bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
             g.divh = g.divw = 1;
             g.K = nr * ns * d->O;
             g.wpr = static_cast<int32_t>(twn_packed_words_per_row(g.K));
+            if (d->alpha_groups > 1) two_terms(g);
             g.plain_gemm = 0;
             g.orU = U; g.orV = V; g.orH = d->H; g.orW = d->W;
             g.ora = a; g.orb = b; g.orsh = sh; g.orsw = sw;
@@ -273,34 +282,44 @@ bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
             out->code_words += static_cast<int64_t>(d->C) * g.wpr;
         }
     out->tb.count = out->count;
+    out->tb.sh = sh;
+    out->tb.sw = sw;
     for (int k = out->count; k <= 4; ++k) out->tb.first_word[k] = out->code_words;
     return out->count > 0;
 }
 
-size_t scaled_dy_bytes(const twn_conv_desc* d, int P, int Q);
-size_t scaled_dy_term_bytes(const twn_conv_desc* d, int P, int Q);
-
-// Workspace of the class path: gathered codes (256-byte multiple) + the two scaled copies of dY (several alphas
-// only) + the largest split-K need of a class.
-size_t strided_dx_bytes(const twn_conv_desc* d, int P, int Q) {
+// Workspace of backward-data, in this order: gathered codes (residue classes; several alphas: repeated for the second
+// term), dY scaled by several alphas as two bf16 terms, one float (the unit alpha), split-K partials of the contraction.
+struct DxPlan {
+    bool classes;           // cl describes the problem, else `g`
+    bool two;               // several alphas: two terms per value of dY
     DxClasses cl;
-    if (!strided_dx_classes(d, P, Q, &cl)) return 0;
-    size_t split = 0;
-    for (int k = 0; k < cl.count; ++k) {
-        const size_t b = splitk_bytes(cl.g[k], d->variant);
-        if (b > split) split = b;
-    }
-    return round_up(static_cast<size_t>(cl.code_words) * sizeof(uint32_t), 256) + scaled_dy_bytes(d, P, Q) + split;
-}
+    GatherGemm g;           // all taps in one problem (also when classes is set: the fallback without a workspace)
+    DxClassTable tb;        // its codes, all taps as one class
+    size_t code_bytes, scaled_bytes, one_bytes, split_bytes;
+    size_t bytes() const { return code_bytes + scaled_bytes + one_bytes + split_bytes; }
+};
 
-// Backward-data with one alpha per group of filters: two scaled copies of dY (high and low bf16 term) + one float
-// (the unit alpha).
-size_t scaled_dy_term_bytes(const twn_conv_desc* d, int P, int Q) {
-    return round_up(static_cast<size_t>(d->N) * P * Q * d->O * sizeof(uint16_t), 256);
-}
-size_t scaled_dy_bytes(const twn_conv_desc* d, int P, int Q) {
-    if (d->alpha_groups == 1) return 0;
-    return 2 * scaled_dy_term_bytes(d, P, Q) + 256;
+void plan_dx(const twn_conv_desc* d, int P, int Q, DxPlan* p, bool allow_classes) {
+    p->two = d->alpha_groups > 1;
+    p->classes = allow_classes && strided_dx_classes(d, P, Q, &p->cl);
+    p->g = GatherGemm{};
+    fill_conv_bwd_data(p->g, d, P, Q);
+    p->code_bytes = p->scaled_bytes = p->one_bytes = p->split_bytes = 0;
+    if (p->two) {
+        two_terms(p->g);
+        p->tb = DxClassTable{};
+        p->tb.count = p->tb.sh = p->tb.sw = 1;
+        p->tb.nr[0] = d->R;
+        p->tb.ns[0] = d->S;
+        p->tb.wpr[0] = p->g.wpr;
+        for (int k = 1; k <= 4; ++k) p->tb.first_word[k] = static_cast<int64_t>(d->C) * p->g.wpr;
+        p->scaled_bytes = round_up(static_cast<size_t>(d->N) * P * Q * d->O * 2 * sizeof(uint16_t), 256);
+        p->one_bytes = 256;
+    }
+    const int64_t words = p->classes ? p->cl.code_words : (p->two ? p->tb.first_word[1] : 0);
+    p->code_bytes = round_up(static_cast<size_t>(words) * sizeof(uint32_t), 256);
+    if (!p->classes) p->split_bytes = splitk_bytes(p->g, d->variant);      // classes are never split
 }
 
 // Weight-gradient workspace: [padded copy of X in first-layer mode] + split partials + bias partials.
@@ -488,13 +507,97 @@ extern "C" size_t twn_conv2d_bwd_ste_workspace_bytes(const twn_conv_desc* d) {
     int P, Q;
     if (check_conv_desc(d, &P, &Q) != TWN_OK) return 0;
     // the data-gradient split-K partials and the weight-gradient partials use the workspace one after the other
-    GatherGemm g{};
-    fill_conv_bwd_data(g, d, P, Q);
-    size_t a = scaled_dy_bytes(d, P, Q) + splitk_bytes(g, d->variant);
-    const size_t a2 = strided_dx_bytes(d, P, Q);
-    if (a2 > a) a = a2;
+    DxPlan p;
+    plan_dx(d, P, Q, &p, false);
+    size_t a = p.bytes();
+    plan_dx(d, P, Q, &p, true);
+    if (p.bytes() > a) a = p.bytes();
     const size_t b = weight_grad_bytes(d, P, Q);
     return a > b ? a : b;
+}
+
+// dX of the straight-through backward: one contraction over dY (one per residue class of a strided layer).
+static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* dY, const uint32_t* packed_T, const float* alpha,
+                             void* dX, void* workspace, size_t workspace_bytes, hipStream_t st) {
+    int32_t rc = TWN_OK;
+    DxPlan p;
+    plan_dx(d, P, Q, &p, env_int("TWN_DX_CLASSES", 1) != 0);
+    if (p.classes && !(workspace && workspace_bytes >= p.bytes() && aligned(workspace, 256) && aligned(dX, 16)))
+        plan_dx(d, P, Q, &p, false);            // no room for the gathered codes: the generic gather
+    if (p.two && (!workspace || workspace_bytes < p.bytes() || !aligned(workspace, 256))) return TWN_ERR_WORKSPACE;
+    unsigned char* ws = static_cast<unsigned char*>(workspace);
+    uint32_t* codes = static_cast<uint32_t*>(workspace);
+    uint16_t* scaled = reinterpret_cast<uint16_t*>(ws + p.code_bytes);
+    float* one = reinterpret_cast<float*>(ws + p.code_bytes + p.scaled_bytes);
+    const size_t head = p.code_bytes + p.scaled_bytes + p.one_bytes;
+    const int count = p.classes ? p.cl.count : 1;
+    GatherGemm* gs = p.classes ? p.cl.g : &p.g;
+    for (int k = 0; k < count; ++k) {
+        GatherGemm& g = gs[k];
+        g.X = p.two ? static_cast<const void*>(scaled) : dY;
+        g.Wq = p.classes ? codes + p.cl.tb.first_word[k] : (p.two ? codes : packed_T);
+        g.alpha = p.two ? one : alpha;
+        g.Y = dX;
+        g.splits = 1;
+        g.partial = nullptr;
+    }
+    if (p.two && !p.classes && d->variant == TWN_VAR_BF16_POSTSCALE) {
+        // 3x3 stride-1 layers with 64 filters scale dY inside the contraction: nothing to prepare
+        GatherGemm g{};
+        fill_conv_bwd_data(g, d, P, Q);
+        g.X = dY;
+        g.Wq = packed_T;
+        g.alpha = alpha;
+        g.Y = dX;
+        g.splits = 1;
+        if (env_int("TWN_TILE", 0) == 0 && env_int("TWN_C64", 1) != 0 && conv_c64_applicable(g))
+            return launch_conv_c64_scaled(g, alpha, d->O / d->alpha_groups, st);
+    }
+    if (p.two || p.classes) {
+        DxPrep q{};
+        q.O = d->O;
+        if (p.two) {
+            q.dY = static_cast<const uint16_t*>(dY);
+            q.alpha = alpha;
+            q.rows_per_group = d->O / d->alpha_groups;
+            q.pixels = static_cast<int64_t>(d->N) * P * Q;
+            q.scaled = scaled;
+            q.one = one;
+        }
+        q.packed_T = packed_T;
+        q.C = d->C;
+        q.wprT = static_cast<int32_t>(twn_packed_words_per_row(static_cast<int64_t>(d->R) * d->S * d->O));
+        q.S = d->S;
+        q.terms = p.two ? 2 : 1;
+        q.tb = p.classes ? p.cl.tb : p.tb;
+        q.codes = codes;
+        if (p.classes && p.cl.any_empty) {
+            q.zero = dX;
+            q.zero16 = static_cast<int64_t>(d->N) * d->H * d->W * d->C * (d->y_dtype == TWN_F32 ? 4 : 2) / 16;
+        }
+        rc = launch_dx_prep(q, st);
+        if (rc != TWN_OK) return rc;
+    }
+    if (!p.classes) return dispatch(p.g, d->variant, ws + head, workspace_bytes > head ? workspace_bytes - head : 0, st);
+    // all classes in ONE launch when the dispatcher would give each of them the same tile (they are too small to be worth
+    // a launch each: ResNet-18 b64, the three strided 3x3 layers 33 / 34 / 48 us as four launches, 26 / 20 / 24 us as one)
+    const bool batch = env_int("TWN_DX_CLASS_BATCH", 1) != 0 && count > 1;
+    const int small = batch ? conv_small_tile(gs, count) : 0;
+    if (small != 0) return launch_conv_small(gs, count, small, st);
+    int batch_tile = batch ? gather_gemm_dma_tile(gs[0]) : 0;
+    for (int k = 1; k < count && batch_tile; ++k)
+        if (gather_gemm_dma_tile(gs[k]) != batch_tile) batch_tile = 0;
+    if (batch_tile != 0) {
+        rc = launch_gather_gemm_dma_batch(gs, count, batch_tile, st);
+        if (rc != TWN_ERR_UNSUPPORTED) return rc;
+    }
+    // no split-K here: a class is one of several launches of a layer whose own launch would not be split either,
+    // and partial tiles plus a finishing launch per class cost more than the idle CUs (ResNet-18 stage 4: 70 -> 48 us)
+    for (int k = 0; k < count; ++k) {
+        rc = dispatch(gs[k], d->variant, nullptr, 0, st, false);
+        if (rc != TWN_OK) return rc;
+    }
+    return TWN_OK;
 }
 
 extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, const void* dY,
@@ -527,129 +630,8 @@ extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, con
     }
     hipStream_t st = as_stream(stream);
 
-    DxClasses cl;
-    if (dX && env_int("TWN_DX_CLASSES", 1) != 0 && strided_dx_classes(d, P, Q, &cl) && workspace &&
-        workspace_bytes >= strided_dx_bytes(d, P, Q) && aligned(workspace, 256) && aligned(dX, 16)) {
-        // strided layer: one stride-1 contraction per residue class of the output pixels
-        const size_t code_bytes = round_up(static_cast<size_t>(cl.code_words) * sizeof(uint32_t), 256);
-        uint32_t* codes = static_cast<uint32_t*>(workspace);
-        rc = launch_gather_class_codes(packed_T, d->C, static_cast<int>(twn_packed_words_per_row(
-                                           static_cast<int64_t>(d->R) * d->S * d->O)),
-                                       d->S, d->O, d->stride_h, d->stride_w, cl.tb, cl.code_words, codes, st);
-        if (rc != TWN_OK) return rc;
-        if (cl.any_empty) {
-            const int64_t bytes = static_cast<int64_t>(d->N) * d->H * d->W * d->C * (d->y_dtype == TWN_F32 ? 4 : 2);
-            rc = launch_zero_fill(dX, bytes, st);
-            if (rc != TWN_OK) return rc;
-        }
-        // several alphas: the two bf16 terms of alpha_o * dY, as in the undivided path below
-        const size_t head = scaled_dy_bytes(d, P, Q);
-        unsigned char* wsb = static_cast<unsigned char*>(workspace) + code_bytes;
-        const uint16_t* hi = nullptr;
-        const uint16_t* lo = nullptr;
-        const float* one = nullptr;
-        if (head) {
-            uint16_t* h = reinterpret_cast<uint16_t*>(wsb);
-            uint16_t* l = reinterpret_cast<uint16_t*>(wsb + scaled_dy_term_bytes(d, P, Q));
-            float* o1 = reinterpret_cast<float*>(wsb + head - 256);
-            rc = launch_scale_channels(static_cast<const uint16_t*>(dY), alpha, d->O / d->alpha_groups, d->O,
-                                       static_cast<int64_t>(d->N) * P * Q, h, l, o1, st);
-            if (rc != TWN_OK) return rc;
-            hi = h; lo = l; one = o1;
-        }
-        for (int k = 0; k < cl.count; ++k) {
-            GatherGemm& g = cl.g[k];
-            g.X = head ? static_cast<const void*>(hi) : dY;
-            g.Wq = codes + cl.tb.first_word[k];
-            g.alpha = head ? one : alpha;
-            g.Y = dX;
-            g.splits = 1;
-            g.partial = nullptr;
-        }
-        // all classes in ONE launch when the dispatcher would give each of them the same tile of the
-        // one-tile-per-workgroup kernel (they are too small to be worth a launch each: ResNet-18 b64, the three
-        // strided 3x3 layers 33 / 34 / 48 us as four launches)
-        const int small = env_int("TWN_DX_CLASS_BATCH", 1) != 0 ? conv_small_tile(cl.g, cl.count) : 0;
-        if (small != 0) {
-            rc = launch_conv_small(cl.g, cl.count, small, st);
-            if (rc == TWN_OK && head) {
-                for (int k = 0; k < cl.count; ++k) {
-                    cl.g[k].X = lo;
-                    cl.g[k].residual = dX;
-                }
-                rc = launch_conv_small(cl.g, cl.count, small, st);
-            }
-            if (rc != TWN_OK) return rc;
-            cl.count = 0;           // done
-        }
-        int batch_tile = env_int("TWN_DX_CLASS_BATCH", 1) != 0 && cl.count > 0 ? gather_gemm_dma_tile(cl.g[0]) : 0;
-        for (int k = 1; k < cl.count && batch_tile; ++k)
-            if (gather_gemm_dma_tile(cl.g[k]) != batch_tile) batch_tile = 0;
-        if (batch_tile && cl.count > 1 && d->variant == TWN_VAR_BF16_POSTSCALE) {
-            rc = launch_gather_gemm_dma_batch(cl.g, cl.count, batch_tile, st);
-            if (rc == TWN_OK && head) {
-                for (int k = 0; k < cl.count; ++k) {
-                    cl.g[k].X = lo;
-                    cl.g[k].residual = dX;
-                }
-                rc = launch_gather_gemm_dma_batch(cl.g, cl.count, batch_tile, st);
-            }
-            if (rc != TWN_ERR_UNSUPPORTED) {
-                if (rc != TWN_OK) return rc;
-                cl.count = 0;       // done
-            } else {
-                for (int k = 0; k < cl.count; ++k) {
-                    cl.g[k].X = head ? static_cast<const void*>(hi) : dY;
-                    cl.g[k].residual = nullptr;
-                }
-            }
-        }
-        for (int k = 0; k < cl.count; ++k) {
-            GatherGemm& g = cl.g[k];
-            // no split-K here: a class is one of several launches of a layer whose own launch would not be split either,
-            // and partial tiles plus a finishing launch per class cost more than the idle CUs (ResNet-18 stage 4: 70 -> 48 us)
-            rc = dispatch(g, d->variant, wsb + head, workspace_bytes - code_bytes - head, st, false);
-            if (rc != TWN_OK) return rc;
-            if (head) {
-                g.X = lo;
-                g.residual = dX;
-                rc = dispatch(g, d->variant, wsb + head, workspace_bytes - code_bytes - head, st, false);
-                if (rc != TWN_OK) return rc;
-            }
-        }
-    } else if (dX) {
-        GatherGemm g{};
-        g.X = dY;
-        g.Wq = packed_T;
-        g.alpha = alpha;
-        g.Y = dX;
-        fill_conv_bwd_data(g, d, P, Q);
-        unsigned char* ws = static_cast<unsigned char*>(workspace);
-        size_t ws_bytes = workspace_bytes;
-        const size_t head = scaled_dy_bytes(d, P, Q);
-        if (head) {
-            // alpha multiplies per forward output channel o, which is a K index here: with several alphas dY is
-            // scaled first (into the workspace) and the contraction runs with alpha = 1
-            if (!workspace || workspace_bytes < head + splitk_bytes(g, d->variant) || !aligned(workspace, 256))
-                return TWN_ERR_WORKSPACE;
-            uint16_t* hi = static_cast<uint16_t*>(workspace);
-            uint16_t* lo = reinterpret_cast<uint16_t*>(ws + scaled_dy_term_bytes(d, P, Q));
-            float* one = reinterpret_cast<float*>(ws + head - 256);
-            rc = launch_scale_channels(static_cast<const uint16_t*>(dY), alpha, d->O / d->alpha_groups, d->O,
-                                       static_cast<int64_t>(d->N) * P * Q, hi, lo, one, st);
-            if (rc != TWN_OK) return rc;
-            g.X = hi;
-            g.alpha = one;
-            ws += head;
-            ws_bytes -= head;
-            rc = dispatch(g, d->variant, ws, ws_bytes, st);
-            if (rc != TWN_OK) return rc;
-            // second term, added onto the first: every output element is read (as the residual) and written by the
-            // same thread of the second pass
-            g.X = lo;
-            g.residual = dX;
-        }
-        rc = dispatch(g, d->variant, ws, ws_bytes, st);
+    if (dX) {
+        rc = data_gradient(d, P, Q, dY, packed_T, alpha, dX, workspace, workspace_bytes, st);
         if (rc != TWN_OK) return rc;
     }
     if (dW || dbias) {

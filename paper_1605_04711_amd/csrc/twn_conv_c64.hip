@@ -34,7 +34,7 @@ constexpr int kC64Stg = 4 * 32 * 80;            // epilogue staging: 32 pixel ro
 constexpr int kC64Chunks = kC64PSide * kC64PSide * 8;   // 16-byte chunks of a patch (800)
 constexpr int kC64Nit = (kC64Chunks + 255) / 256;       // chunks per lane (4)
 constexpr int kC64Steps = 36;                   // MFMA steps: 9 taps x 4 groups of 16 channels
-constexpr int kC64Smem = 2 * kC64Patch + kC64Stg + 2 * 64 * 4;
+constexpr int c64_smem(bool scaled) { return (scaled ? 4 : 2) * kC64Patch + kC64Stg + 2 * 64 * 4; }
 
 struct C64Args {
     const uint16_t* X;
@@ -51,14 +51,20 @@ struct C64Args {
     uint32_t tiles, tiles_x, tiles_y;
     FastDivU divTX, divTY;
     uint32_t x_bytes, y_bytes;      // sizes of X and of the output / residual tensor
+    const float* alpha_in;          // SCALED: factor of input channel c is alpha_in[c / in_rows_per_group]
+    int32_t in_rows_per_group;
 };
 
 // FLIP: the taps run against the pixel order (backward-data: input row = output row + pad - r)
 // RES: a residual tensor is added (its values for a tile are requested before the tile's MFMA loop)
-template <bool FLIP, bool RES>
+// SCALED: the input is alpha_in * X (backward-data with several alphas): every product is formed in float32 on the way from
+// the registers to LDS and kept as two bf16 terms in two patches; both are multiplied with the same resident weights into
+// the same accumulators (12.8 M values, 64 channels: a scaling pass and two contractions 80 us, this 30 us)
+template <bool FLIP, bool RES, bool SCALED>
 __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    unsigned char* stg_base = smem + 2 * kC64Patch;
+    constexpr int BUF = (SCALED ? 2 : 1) * kC64Patch;       // one of two patch buffers (SCALED: high terms, then low terms)
+    unsigned char* stg_base = smem + 2 * BUF;
     float* colmul = reinterpret_cast<float*>(stg_base + kC64Stg);     // [64] 0.5*alpha*scale
     float* coladd = colmul + 64;                                       // [64] shift
 
@@ -72,7 +78,7 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args a) {
     if (tid < 64) {
         const int ncol = n0 + tid;
         const int ag = (a.rows_per_group >= a.NC) ? 0 : ncol / a.rows_per_group;
-        colmul[tid] = 0.5f * a.alpha[ag] * (a.scale ? a.scale[ncol] : 1.0f);     // codes become +-2
+        colmul[tid] = 0.5f * (SCALED ? 1.0f : a.alpha[ag]) * (a.scale ? a.scale[ncol] : 1.0f);     // codes become +-2
         coladd[tid] = a.shift ? a.shift[ncol] : 0.0f;
     }
 
@@ -120,6 +126,11 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args a) {
         loff[it] = static_cast<uint32_t>(y * kC64RowB + x * kC64PixB + c * 16);
     }
     u32x4 pr[kC64Nit];
+    float al[SCALED ? 8 : 1];                   // a lane's chunks all hold the same eight channels
+    if constexpr (SCALED) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) al[e] = a.alpha_in[((tid & 7) * 8 + e) / a.in_rows_per_group];
+    }
     auto load_patch = [&](const Tile& t, bool live) __attribute__((always_inline)) {
         const int y0 = t.p0 + a.y0off, x0 = t.q0 + a.x0off;
         // 32-bit wrapping arithmetic: the offset of every chunk that lies inside the image is in [0, x_bytes);
@@ -135,7 +146,21 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args a) {
     auto store_patch = [&](unsigned char* buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int it = 0; it < kC64Nit; ++it)
-            if (has[it]) *reinterpret_cast<u32x4*>(buf + loff[it]) = pr[it];
+            if (has[it]) {
+                if constexpr (SCALED) {
+                    u32x4 hi, lo;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const Bf16Terms t = split_scaled_bf16x2(pr[it][e], al[2 * e], al[2 * e + 1]);
+                        hi[e] = t.hi;
+                        lo[e] = t.lo;
+                    }
+                    *reinterpret_cast<u32x4*>(buf + loff[it]) = hi;
+                    *reinterpret_cast<u32x4*>(buf + kC64Patch + loff[it]) = lo;
+                } else {
+                    *reinterpret_cast<u32x4*>(buf + loff[it]) = pr[it];
+                }
+            }
     };
 
     // per-lane fragment base inside a patch: pixel (tile row wm*4 + (lrow >> 3), tile column lrow & 7), k half lh
@@ -209,32 +234,33 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args a) {
     int buf = 0;
     for (uint32_t i = 0; i < n_my; ++i) {
         const bool more = (i + 1 < n_my), more2 = (i + 2 < n_my);
-        const uint32_t pb = lds_base + static_cast<uint32_t>(buf * kC64Patch + pbase);
+        const uint32_t pb = lds_base + static_cast<uint32_t>(buf * BUF + pbase);
         {
             // Step ks = tap * 4 + cq reads the 16 channels 16 cq .. 16 cq + 15 of the pixel one tap away: the whole
             // offset is an immediate.  The reads run AHEAD steps in front of the MFMAs through a ring of RING
             // registers (inline assembly with exact lgkmcnt waits: LDS operations complete in issue order); the
             // read of step ks + AHEAD lands in the registers of step ks - 1.
             constexpr int AHEAD = 8, RING = 9;
+            constexpr int TERMS = SCALED ? 2 : 1, READS = kC64Steps * TERMS;    // read i: term i % TERMS of step i / TERMS
             u32x4 af[RING];
-            auto read_step = [&](auto ks_tag) __attribute__((always_inline)) {
-                constexpr int ks = decltype(ks_tag)::value;
+            auto read_step = [&](auto i_tag) __attribute__((always_inline)) {
+                constexpr int i = decltype(i_tag)::value, ks = i / TERMS;
                 constexpr int t = ks >> 2, cq = ks & 3;
                 constexpr int r = t / 3, s = t - 3 * r;
                 constexpr int ro = FLIP ? 2 - r : r, co = FLIP ? 2 - s : s;
-                lds_read128<ro * kC64RowB + co * kC64PixB + cq * 32>(af[ks % RING], pb);
+                lds_read128<ro * kC64RowB + co * kC64PixB + cq * 32 + (i % TERMS) * kC64Patch>(af[i % RING], pb);
             };
             static_for<AHEAD>(read_step);
-            static_for<kC64Steps>([&](auto ks_tag) __attribute__((always_inline)) {
-                constexpr int ks = decltype(ks_tag)::value;
-                if constexpr (ks + AHEAD < kC64Steps) read_step(std::integral_constant<int, ks + AHEAD>{});
-                constexpr int last = (ks + AHEAD < kC64Steps) ? ks + AHEAD : kC64Steps - 1;      // youngest read issued
-                lds_wait<last - ks>();
-                lds_ready<1>(&af[ks % RING]);
+            static_for<READS>([&](auto i_tag) __attribute__((always_inline)) {
+                constexpr int i = decltype(i_tag)::value;
+                if constexpr (i + AHEAD < READS) read_step(std::integral_constant<int, i + AHEAD>{});
+                constexpr int last = (i + AHEAD < READS) ? i + AHEAD : READS - 1;      // youngest read issued
+                lds_wait<last - i>();
+                lds_ready<1>(&af[i % RING]);
                 // the first step starts from a zero C operand (an inline constant): no clearing pass
-                const f32x16 c_in = (ks == 0) ? f32x16{} : acc;
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bfrag[ks]),
-                                                              __builtin_bit_cast(bf16x8, af[ks % RING]), c_in, 0, 0, 0);
+                const f32x16 c_in = (i == 0) ? f32x16{} : acc;
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bfrag[i / TERMS]),
+                                                              __builtin_bit_cast(bf16x8, af[i % RING]), c_in, 0, 0, 0);
             });
         }
         // Everything this wave has requested so far (patch i+1, the residual values of tile i, the stores of tile
@@ -243,7 +269,7 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args a) {
         // tensor and no memory is touched; the full wait needs no such assumption and sits behind a whole MFMA
         // loop, so it costs nothing measurable with two workgroups per CU.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        store_patch(smem + (buf ^ 1) * kC64Patch);
+        store_patch(smem + (buf ^ 1) * BUF);
         const Tile nn = tile_of(i + 2);
         load_patch(nn, more2);
         // ---- epilogue: accumulator element e in this lane: tile pixel (wm*4 + (lrow>>3), lrow & 7),
@@ -327,6 +353,8 @@ static bool c64_plan(const GatherGemm& g, C64Args* a) {
     a->x0off = -g.pw + (g.dw < 0 ? -2 : 0);
     a->wpr = g.wpr; a->rows_per_group = g.rows_per_group; a->relu = g.relu;
     a->ldy = static_cast<int32_t>(g.ldy);
+    a->alpha_in = nullptr;
+    a->in_rows_per_group = 1;
     a->tiles_x = static_cast<uint32_t>((g.OW + kC64Tile - 1) / kC64Tile);
     a->tiles_y = static_cast<uint32_t>((g.OH + kC64Tile - 1) / kC64Tile);
     const int64_t tiles = n_img * a->tiles_x * a->tiles_y;
@@ -346,13 +374,12 @@ bool conv_c64_applicable(const GatherGemm& g) {
     return c64_plan(g, &a);
 }
 
-int32_t launch_conv_c64(const GatherGemm& g, hipStream_t st) {
-    C64Args a;
-    if (!c64_plan(g, &a)) return TWN_ERR_UNSUPPORTED;
+static int32_t launch_c64(const C64Args& a, bool flip, bool scaled, hipStream_t st) {
     using Kern = void (*)(const C64Args);
-    static const Kern kerns[4] = {conv_c64_kernel<false, false>, conv_c64_kernel<false, true>,
-                                  conv_c64_kernel<true, false>, conv_c64_kernel<true, true>};
-    const Kern k = kerns[(g.dh < 0 ? 2 : 0) + (g.residual ? 1 : 0)];
+    static const Kern kerns[5] = {conv_c64_kernel<false, false, false>, conv_c64_kernel<false, true, false>,
+                                  conv_c64_kernel<true, false, false>, conv_c64_kernel<true, true, false>,
+                                  conv_c64_kernel<true, false, true>};
+    const Kern k = kerns[scaled ? 4 : (flip ? 2 : 0) + (a.residual ? 1 : 0)];
     static std::once_flag once;
     static int cus = 256;
     static bool allowed = false;
@@ -362,20 +389,34 @@ int32_t launch_conv_c64(const GatherGemm& g, hipStream_t st) {
         if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess && p.multiProcessorCount > 0)
             cus = p.multiProcessorCount;
         allowed = true;
-        for (Kern kk : kerns)
-            allowed = allowed && hipFuncSetAttribute(reinterpret_cast<const void*>(kk),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kC64Smem) == hipSuccess;
+        for (int i = 0; i < 5; ++i)
+            allowed = allowed && hipFuncSetAttribute(reinterpret_cast<const void*>(kerns[i]),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, c64_smem(i == 4)) == hipSuccess;
     });
     if (!allowed) return TWN_ERR_HIP;
-    const unsigned tiles_n = static_cast<unsigned>(g.NC / 64);
+    const unsigned tiles_n = static_cast<unsigned>(a.NC / 64);
     int per_cu = 2;
     const int cap = env_int("TWN_C64_OCC", 0);
     if (cap > 0 && cap < per_cu) per_cu = cap;
     int64_t gx = static_cast<int64_t>(cus) * per_cu / tiles_n;
     if (gx < 8) gx = 8;
     if (gx > a.tiles) gx = a.tiles;
-    k<<<dim3(static_cast<unsigned>(gx), tiles_n), dim3(256), kC64Smem, st>>>(a);
+    k<<<dim3(static_cast<unsigned>(gx), tiles_n), dim3(256), c64_smem(scaled), st>>>(a);
     return launch_status();
+}
+
+int32_t launch_conv_c64(const GatherGemm& g, hipStream_t st) {
+    C64Args a;
+    if (!c64_plan(g, &a)) return TWN_ERR_UNSUPPORTED;
+    return launch_c64(a, g.dh < 0, false, st);
+}
+
+int32_t launch_conv_c64_scaled(const GatherGemm& g, const float* alpha_in, int32_t in_rows_per_group, hipStream_t st) {
+    C64Args a;
+    if (!c64_plan(g, &a) || g.dh >= 0 || g.residual) return TWN_ERR_UNSUPPORTED;
+    a.alpha_in = alpha_in;
+    a.in_rows_per_group = in_rows_per_group;
+    return launch_c64(a, true, true, st);
 }
 
 }  // namespace twn

@@ -23,6 +23,7 @@ namespace twn {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
@@ -401,75 +402,107 @@ int32_t launch_pad_repack_c4(const uint16_t* X, int N, int H, int W, int C, int 
     return launch_status();
 }
 
-// Backward-data with one alpha per group of filters (Alg. 1 steps 3-7 feeding step 9): alpha multiplies per forward
-// output channel o, which is a reduction index of dX, so it cannot be applied after the sum.  dY is scaled instead.
-// The product v = dY[p][o] * alpha[o / rows_per_group] (float32) is carried as two bf16 terms, hi = bf16(v) and
-// lo = bf16(v - hi), which together hold v to about 2^-17: the contraction runs once over each (alpha = 1, which
-// thread 0 writes to `one`), the second pass adding onto the first, and no rounding of the inputs is added.
-__global__ __launch_bounds__(256) void scale_channels_kernel(const uint16_t* __restrict__ dY, const float* __restrict__ alpha,
-                                                             int rows_per_group, int O, int64_t total,
-                                                             uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
-                                                             float* __restrict__ one) {
-    const int64_t id = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (id == 0) *one = 1.0f;
-    if (id >= total) return;
-    const int o = static_cast<int>(id % O);
-    const float v = bf16_to_f32(dY[id]) * alpha[o / rows_per_group];
-    const uint16_t h = f32_to_bf16(v);
-    hi[id] = h;
-    lo[id] = f32_to_bf16(v - bf16_to_f32(h));
+// ---- preparation of a backward-data pass ----
+// One alpha per group of filters (Alg. 1 steps 3-7 feeding step 9): alpha multiplies per forward output channel o, which
+// is a reduction index of dX, so it cannot be applied after the sum.  dY is scaled instead.  The product
+// v = dY[p][o] * alpha[o / rows_per_group] (float32) is carried as two bf16 terms, hi = bf16(v) and lo = bf16(v - hi),
+// which together hold v to about 2^-17; they lie next to each other as 2*O channels of one pixel and the codes of
+// every tap are repeated for the second term, so that ONE contraction with alpha = 1 adds both in its float32
+// accumulators.  (Two contractions, the second adding onto the stored result of the first, took two more passes over dX
+// and rounded it twice.)
+// Eight channels per thread where the rows allow it: HBM-bound, 6 bytes per value (12.8 M values: 42 us one value per
+// thread, 14 us).
+template <bool VEC>
+__device__ __forceinline__ void scale_body(const DxPrep& p, int64_t block) {
+    const int64_t id = block * 256 + threadIdx.x;
+    if (id == 0) *p.one = 1.0f;
+    if constexpr (VEC) {
+        const int chunks = p.O >> 3;
+        if (id >= p.pixels * chunks) return;
+        const int64_t pix = id / chunks;
+        const int o = static_cast<int>(id - pix * chunks) * 8;
+        const u32x4 x = *reinterpret_cast<const u32x4*>(p.dY + pix * p.O + o);
+        float al[8];
+        if (p.rows_per_group == 1) {
+            const f32x4 a0 = *reinterpret_cast<const f32x4*>(p.alpha + o), a1 = *reinterpret_cast<const f32x4*>(p.alpha + o + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { al[e] = a0[e]; al[4 + e] = a1[e]; }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) al[e] = p.alpha[(o + e) / p.rows_per_group];
+        }
+        u32x4 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const Bf16Terms t = split_scaled_bf16x2(x[e], al[2 * e], al[2 * e + 1]);
+            hi[e] = t.hi;
+            lo[e] = t.lo;
+        }
+        *reinterpret_cast<u32x4*>(p.scaled + pix * 2 * p.O + o) = hi;
+        *reinterpret_cast<u32x4*>(p.scaled + pix * 2 * p.O + p.O + o) = lo;
+    } else {
+        if (id >= p.pixels * p.O) return;
+        const int64_t pix = id / p.O;
+        const int o = static_cast<int>(id - pix * p.O);
+        const float v = bf16_to_f32(p.dY[id]) * p.alpha[o / p.rows_per_group];
+        const uint16_t h = f32_to_bf16(v);
+        p.scaled[pix * 2 * p.O + o] = h;
+        p.scaled[pix * 2 * p.O + p.O + o] = f32_to_bf16(v - bf16_to_f32(h));
+    }
 }
 
-int32_t launch_scale_channels(const uint16_t* dY, const float* alpha, int rows_per_group, int O, int64_t pixels,
-                              uint16_t* hi, uint16_t* lo, float* one, hipStream_t st) {
-    const int64_t total = pixels * O;
-    if (total <= 0 || (total + 255) / 256 >= (1LL << 31)) return TWN_ERR_SHAPE;
-    scale_channels_kernel<<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(dY, alpha, rows_per_group, O, total,
-                                                                                   hi, lo, one);
-    return launch_status();
-}
-
-// Strided backward-data as one stride-1 problem per residue class of the output pixels: the taps that reach
-// class (a, b) are r = r0 + jr*sh, s = s0 + js*sw.  Their codes are gathered from the transposed copy into a
-// contiguous K range per class: out[class][c][(jr*ns + js)*O/16 + t] = packed_T[c][((r0+jr*sh)*S + s0+js*sw)*O/16 + t].
-__global__ __launch_bounds__(256) void gather_class_codes_kernel(const uint32_t* __restrict__ packed_T, int C, int wprT, int S,
-                                                                 int O16, int sh, int sw, DxClassTable tb,
-                                                                 uint32_t* __restrict__ out) {
-    const int64_t id = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+// Codes of the taps r = r0 + jr*sh, s = s0 + js*sw of class k, gathered from the transposed copy into a contiguous K range:
+// K order (jr, js, term, o).  Whole words where a tap's codes are whole words, field by field otherwise.
+__device__ __forceinline__ void class_codes_body(const DxPrep& p, int64_t block) {
+    const int64_t id = block * 256 + threadIdx.x;
+    const DxClassTable& tb = p.tb;
     int k = 0;
     while (k + 1 < tb.count && id >= tb.first_word[k + 1]) ++k;
     const int64_t local = id - tb.first_word[k];
     const int wpr = tb.wpr[k];
-    if (k >= tb.count || local >= static_cast<int64_t>(C) * wpr) return;
+    if (k >= tb.count || local >= static_cast<int64_t>(p.C) * wpr) return;
     const int c = static_cast<int>(local / wpr), j = static_cast<int>(local % wpr);
+    const uint32_t* row = p.packed_T + static_cast<int64_t>(c) * p.wprT;
+    const int taps = tb.nr[k] * tb.ns[k], per_tap = p.terms * p.O;
     uint32_t word = 0u;
-    if (j < tb.nr[k] * tb.ns[k] * O16) {
-        const int tap = j / O16, t = j % O16;
-        const int jr = tap / tb.ns[k], js = tap % tb.ns[k];
-        const int src_tap = (tb.r0[k] + jr * sh) * S + tb.s0[k] + js * sw;
-        word = packed_T[static_cast<int64_t>(c) * wprT + static_cast<int64_t>(src_tap) * O16 + t];
+    auto source_tap = [&](int tap) { return (tb.r0[k] + (tap / tb.ns[k]) * tb.sh) * p.S + tb.s0[k] + (tap % tb.ns[k]) * tb.sw; };
+    if (p.O % 16 == 0) {
+        const int tap = j * 16 / per_tap;
+        if (tap < taps) word = row[(source_tap(tap) * p.O + (j * 16 - tap * per_tap) % p.O) >> 4];
+    } else {
+        for (int t = 0; t < 16; ++t) {
+            const int k2 = j * 16 + t, tap = k2 / per_tap;
+            if (tap >= taps) break;
+            const int src = source_tap(tap) * p.O + (k2 - tap * per_tap) % p.O;
+            const int ts = src & 15;
+            word |= ((row[src >> 4] >> ((ts & 1) * 16 + (ts >> 1) * 2)) & 3u) << ((t & 1) * 16 + (t >> 1) * 2);
+        }
     }
-    out[id] = word;
+    p.codes[id] = word;
 }
 
-int32_t launch_gather_class_codes(const uint32_t* packed_T, int C, int wprT, int S, int O, int sh, int sw,
-                                  const DxClassTable& tb, int64_t total_words, uint32_t* out, hipStream_t st) {
-    if (total_words <= 0 || (total_words + 255) / 256 >= (1LL << 31)) return TWN_ERR_SHAPE;
-    gather_class_codes_kernel<<<static_cast<unsigned>((total_words + 255) / 256), 256, 0, st>>>(packed_T, C, wprT, S, O / 16,
-                                                                                             sh, sw, tb, out);
-    return launch_status();
+// The first scale_blocks workgroups scale dY, the next code_blocks gather codes, the rest clear dX: the parts are
+// independent, and a launch costs more than any of the small ones.
+template <bool VEC>
+__global__ __launch_bounds__(256) void dx_prep_kernel(const DxPrep p, unsigned scale_blocks, unsigned code_blocks) {
+    if (blockIdx.x < scale_blocks) {
+        scale_body<VEC>(p, blockIdx.x);
+    } else if (blockIdx.x < scale_blocks + code_blocks) {
+        class_codes_body(p, blockIdx.x - scale_blocks);
+    } else {
+        const int64_t id = static_cast<int64_t>(blockIdx.x - scale_blocks - code_blocks) * 256 + threadIdx.x;
+        if (id < p.zero16) static_cast<u32x4*>(p.zero)[id] = u32x4{0u, 0u, 0u, 0u};
+    }
 }
 
-// Zero fill in 16-byte units (a kernel rather than a memset, so that callers may capture it into a graph).
-__global__ __launch_bounds__(256) void zero_fill_kernel(u32x4* __restrict__ p, int64_t n16) {
-    const int64_t id = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (id < n16) p[id] = u32x4{0u, 0u, 0u, 0u};
-}
-
-int32_t launch_zero_fill(void* p, int64_t bytes, hipStream_t st) {
-    const int64_t n16 = bytes / 16;
-    if (bytes % 16 != 0 || n16 <= 0 || (n16 + 255) / 256 >= (1LL << 31)) return TWN_ERR_SHAPE;
-    zero_fill_kernel<<<static_cast<unsigned>((n16 + 255) / 256), 256, 0, st>>>(static_cast<u32x4*>(p), n16);
+int32_t launch_dx_prep(const DxPrep& p, hipStream_t st) {
+    const bool vec = p.O % 8 == 0 && aligned(p.dY, 16) && (p.rows_per_group != 1 || aligned(p.alpha, 16));
+    const int64_t scale_n = p.scaled ? (vec ? p.pixels * (p.O / 8) : p.pixels * p.O) : 0;
+    const int64_t code_n = p.codes ? p.tb.first_word[p.tb.count] : 0;
+    const int64_t sb = (scale_n + 255) / 256, cb = (code_n + 255) / 256, zb = p.zero ? (p.zero16 + 255) / 256 : 0;
+    if (sb + cb + zb <= 0 || sb + cb + zb >= (1LL << 31)) return TWN_ERR_SHAPE;
+    auto k = vec ? dx_prep_kernel<true> : dx_prep_kernel<false>;
+    k<<<static_cast<unsigned>(sb + cb + zb), 256, 0, st>>>(p, static_cast<unsigned>(sb), static_cast<unsigned>(cb));
     return launch_status();
 }
 

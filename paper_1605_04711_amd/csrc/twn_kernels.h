@@ -56,17 +56,32 @@ int32_t launch_gather_gemm_mfma(const GatherGemm& g, int variant, hipStream_t st
 // with Sp = S rounded up to even (codes of the phantom tap / channels are zero).
 int32_t launch_pad_c4(const uint16_t* X, int N, int H, int W, int C, int ph, int pw, int Hp, int Wp,
                       uint16_t* Xp, hipStream_t st);
-// Residue classes of a strided backward-data pass (at most 4: stride products up to 4), by value to the kernel.
+// Tap subsets of a backward-data pass whose codes are gathered into contiguous K ranges: the residue classes of a strided
+// layer (at most 4: stride products up to 4), or all taps as one class.  By value to the kernel.
 struct DxClassTable {
-    int32_t count;
+    int32_t count, sh, sw;
     int32_t r0[4], nr[4], s0[4], ns[4], wpr[4];
     int64_t first_word[5];      // offset of each class's codes in the gathered buffer, in 32-bit words
 };
-int32_t launch_gather_class_codes(const uint32_t* packed_T, int C, int wprT, int S, int O, int sh, int sw,
-                                  const DxClassTable& tb, int64_t total_words, uint32_t* out, hipStream_t st);
-int32_t launch_zero_fill(void* p, int64_t bytes, hipStream_t st);
-int32_t launch_scale_channels(const uint16_t* dY, const float* alpha, int rows_per_group, int O, int64_t pixels,
-                              uint16_t* hi, uint16_t* lo, float* one, hipStream_t st);
+// Everything a backward-data pass needs prepared, in one launch; every part is optional (null pointer).
+struct DxPrep {
+    // dY times alpha, carried as two bf16 terms next to each other: scaled[p][0..O) high, scaled[p][O..2O) low; *one = 1
+    const uint16_t* dY;
+    const float* alpha;
+    int32_t rows_per_group, O;
+    int64_t pixels;
+    uint16_t* scaled;
+    float* one;
+    // codes of the classes, K order (tap, term, o) with `terms` copies of every tap's O codes
+    const uint32_t* packed_T;
+    int32_t C, wprT, S, terms;
+    DxClassTable tb;
+    uint32_t* codes;
+    // 16-byte units of dX to clear (classes without taps)
+    void* zero;
+    int64_t zero16;
+};
+int32_t launch_dx_prep(const DxPrep& p, hipStream_t st);
 int32_t launch_pad_repack_c4(const uint16_t* X, int N, int H, int W, int C, int ph, int pw, int Hp, int Wp, uint16_t* Xp,
                              const uint32_t* packed, int rows, int R, int S, int Sp, uint32_t* out, hipStream_t st);
 int32_t launch_gather_gemm_dma(const GatherGemm& g, int tile, hipStream_t st);
@@ -98,6 +113,9 @@ int32_t launch_conv_small(const GatherGemm* gs, int count, int tile, hipStream_t
 // patch of an 8x8 pixel tile (with halo) in LDS; `applicable` is a pure function of the problem.
 bool conv_c64_applicable(const GatherGemm& g);
 int32_t launch_conv_c64(const GatherGemm& g, hipStream_t st);
+// The same kernel over alpha_in[c / in_rows_per_group] * X instead of X (backward-data with several alphas): the product
+// is carried as two bf16 terms that are formed on the way into LDS.
+int32_t launch_conv_c64_scaled(const GatherGemm& g, const float* alpha_in, int32_t in_rows_per_group, hipStream_t st);
 
 // First layers with three input channels, bf16 in and out, dilation 1 (forward): one persistent kernel, no
 // workspace and no preparation launch; `applicable` is a pure function of the problem (shapes and alignment).
