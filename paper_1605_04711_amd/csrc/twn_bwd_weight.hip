@@ -888,12 +888,19 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
     a.plan = plan_weight_grad(w.N, w.P, w.Q, w.C, w.O, w.R, w.S);
     a.divSX = make_fastdiv(a.plan.patch ? a.plan.sx : 1);
     a.divSY = make_fastdiv(a.plan.patch ? a.plan.sy : 1);
-    const int32_t splits = a.plan.splits;
+    // filters with several taps: patches with halo, unless this is a first layer's 4-channel copy
+    WgTapsPlan taps{};
+    if (w.dW && !w.pad_sp)
+        taps = plan_weight_grad_taps(WgShape{w.N, w.H, w.W, w.C, w.O, w.R, w.S, w.P, w.Q, w.sh, w.sw, w.dh, w.dw});
+    const int32_t splits = taps.use ? taps.splits : a.plan.splits;
     a.slabs_per_split = static_cast<int32_t>((a.plan.slabs + splits - 1) / splits);
     a.xcd_map = env_int("TWN_WG_XCD", 1);
     a.dy_bytes = a.x_bytes = 0;
     a.exact = 0;
-    if (w.dW) {
+    if (taps.use) {
+        const int32_t rc = launch_weight_grad_taps(w, taps, st);
+        if (rc != TWN_OK) return rc;
+    } else if (w.dW) {
         const dim3 grid(a.plan.tiles, splits);
         if (a.plan.patch) {
             const int64_t dyb = a.pixels * w.O * 2;
@@ -936,7 +943,7 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
         }
     }
     if (w.dbias) {
-        float* bp = w.partial + static_cast<int64_t>(splits) * w.O * a.J;
+        float* bp = w.dW ? w.partial + static_cast<int64_t>(splits) * w.O * a.J : w.partial;
         bias_grad_partial_kernel<<<dim3((w.O + 63) / 64, kBiasSplits), 256, 0, st>>>(w.dY, a.pixels, w.O, bp);
         bias_grad_final_kernel<<<(w.O + 255) / 256, 256, 0, st>>>(bp, w.O, w.dbias);
     }

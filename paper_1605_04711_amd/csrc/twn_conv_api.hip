@@ -322,6 +322,10 @@ void plan_dx(const twn_conv_desc* d, int P, int Q, DxPlan* p, bool allow_classes
     if (!p->classes) p->split_bytes = splitk_bytes(p->g, d->variant);      // classes are never split
 }
 
+WgShape taps_shape(const twn_conv_desc* d, int P, int Q) {
+    return WgShape{d->N, d->H, d->W, d->C, d->O, d->R, d->S, P, Q, d->stride_h, d->stride_w, d->dil_h, d->dil_w};
+}
+
 // Weight-gradient workspace: [padded copy of X in first-layer mode] + split partials + bias partials.
 size_t weight_grad_bytes(const twn_conv_desc* d, int P, int Q) {
     SmallC sc;
@@ -331,7 +335,8 @@ size_t weight_grad_bytes(const twn_conv_desc* d, int P, int Q) {
         return sc.x_bytes + static_cast<size_t>((splits * d->O * Jp + 64LL * d->O) * sizeof(float));
     }
     const int64_t J = static_cast<int64_t>(d->R) * d->S * d->C;
-    const int64_t splits = plan_weight_grad(d->N, P, Q, d->C, d->O, d->R, d->S).splits;
+    const WgTapsPlan taps = plan_weight_grad_taps(taps_shape(d, P, Q));
+    const int64_t splits = taps.use ? taps.splits : plan_weight_grad(d->N, P, Q, d->C, d->O, d->R, d->S).splits;
     return static_cast<size_t>((splits * d->O * J + 64LL * d->O) * sizeof(float));
 }
 

@@ -166,4 +166,22 @@ struct WgPlan {
 WgPlan plan_weight_grad(int32_t N, int32_t P, int32_t Q, int32_t C, int32_t O, int32_t R, int32_t S);
 int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st);
 
+// Weight gradient of filters with several taps over patches with halo (twn_bwd_weight_taps.hip).
+struct WgShape {
+    int32_t N, H, W, C, O, R, S, P, Q, sh, sw, dh, dw;
+};
+struct WgTapsPlan {
+    int32_t use;                        // 0: the general kernel takes the layer
+    int32_t pn, ph, pw;                 // patch of 32 output pixels: images x rows x columns, powers of two
+    int32_t sn, sy, sx, slabs;          // patches along batch, rows, columns; in total
+    int32_t hh, ww;                     // input rows and columns of one image of a patch
+    int32_t row_slots, img_slots;       // pitch of a patch row and of an image in LDS, in pixels of 32 channels
+    int32_t slots, nb;                  // pixels of a patch in LDS (with padding), loads of half of them
+    int32_t stage_bytes, depth;
+    int32_t tiles_o, tiles_c, groups, tiles;
+    int32_t per, splits;                // patches per pixel range, ranges
+};
+WgTapsPlan plan_weight_grad_taps(const WgShape& w);
+int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipStream_t st);
+
 }  // namespace twn
