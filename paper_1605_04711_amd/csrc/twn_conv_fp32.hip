@@ -1,166 +1,285 @@
-// float32 path of the ternary convolution / inner product (Eq. 2, Alg. 1 step 8)
-// for float32 activations: LDS-tiled implicit GEMM on the vector ALUs.  Inputs
-// and outputs are float32; the running sums are kept in float64 (products with
-// a code are exact, so only the additions round) because float32 accumulation
-// of cancelling sums cannot hold a 1e-5 relative bound on small outputs.
-// Weights are the same packed twn2 codes, expanded to {-1, 0, +1} floats while
-// staging the tile; alpha is applied afterwards.
-// The layers that use it (LeNet-sized) are small, so the kernel is kept simple, but two things matter even
-// there: the gathers of the next K slab are in flight (in registers) while the current slab is multiplied, and
-// problems with few 64x64 tiles (the fully-connected layers at batch 64) run 32x32 tiles, four times as many
-// workgroups.  A thread owns (TS/16)^2 outputs.  Problems that still have few tiles and a long reduction (the
-// fully-connected layers of LeNet at batch 64: 32 tiles, 13 slabs each) are split along K over blockIdx.y: every
-// range writes its float64 sums to the workspace and a second launch adds them in a fixed order and applies the tail.
+// float32 path of the ternary convolution / inner product (Eq. 2, Alg. 1 step 8) for float32 activations: implicit
+// GEMM on the float64 matrix cores.  Inputs and outputs are float32; products with a code are exact and the running
+// sums are float64, because float32 accumulation of cancelling sums cannot hold a 1e-5 relative bound on small
+// outputs.  The codes are expanded in registers to 0 / +-2.0 (one shift and one mask give the high half of the double,
+// the low half is zero; the factor is taken back exactly before the rounding to float32), alpha is applied afterwards.
+//
+// v_mfma_f64_16x16x4_f64 occupies the matrix core for 64 cycles and takes one double per lane and operand, so a wave
+// needs 1 KB of activations and one word of codes per lane and 16-channel column for 256 cycles and more of matrix
+// work: both come straight from global memory (L1, L2) and nothing is staged in LDS.  What bounds the path is the
+// float64 rate (79 TFLOP/s) for large problems and latency for LeNet-sized ones, so a tile is small (16 pixels by 16,
+// 32 or 64 channels) and the K blocks of a tile are shared out over the NW waves of a workgroup, whose float64 sums
+// are added through LDS in a fixed order.  LeNet b64 against float64 FMAs on tiles staged in LDS, split along K over
+// workgroups with a finishing launch: 4096 pixels x 64 x 800 34 -> 13.3 us, 36864 x 32 x 25 13.9 -> 9.8,
+// 64 x 512 x 1024 16.3 -> 6.7, 64 x 10 x 512 12.3 -> 4.9; 1024 x 1024 x 1024 136 -> 44 (float64 floor 27).
 #include "twn_kernels.h"
+#include "twn_mfma.h"
 
 namespace twn {
 
-// SPLIT: blockIdx.y owns `kps` slabs of K and writes raw float64 sums to g.partial ([split][M][NC] doubles)
-template <int TS, bool SPLIT>
-__global__ __launch_bounds__(256) void gather_gemm_fp32_kernel(const GatherGemm g, int kps) {
-    // K slab: 32 for 64x64 tiles, 64 for 32x32 tiles.  Both operands are widened to float64 once, when they are
-    // staged (every staged value is read by 16 threads), so the inner loop is LDS reads and float64 FMAs only.
-    constexpr int kF32K = (TS == 32) ? 64 : 32;
-    constexpr int EA = TS * kF32K / 256;        // consecutive k one thread stages per row / column (8)
-    constexpr int TPR = kF32K / EA;             // threads per staged row
-    constexpr int TT = TS / 16;                 // outputs per thread along each side
-    static_assert(16 % EA == 0, "the codes a thread expands sit in one packed word");
-    __shared__ double As[kF32K][TS + 2];
-    __shared__ double Bs[kF32K][TS + 2];
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+// four floats at float alignment: global_load_dwordx4 needs dword alignment only
+struct __attribute__((packed, aligned(4))) Float4 {
+    float v[4];
+};
 
-    const int tid = threadIdx.x;
-    const int tiles_n = (g.NC + TS - 1) / TS;
-    const int64_t m0 = static_cast<int64_t>(blockIdx.x / tiles_n) * TS;
-    const int n0 = static_cast<int>(blockIdx.x % tiles_n) * TS;
+enum F32Mode : int {
+    kF32Gemm = 0,       // rows of X are the reduction rows
+    kF32Quad = 1,       // channel count a multiple of 4: four consecutive k lie in one tap
+    kF32Element = 2,    // every element finds its own tap
+};
+
+struct F32Args {
+    GatherGemm g;
+    FastDivU divIC, divS;
+    int64_t tiles;
+    int32_t tiles_n;
+};
+
+// Parameters of one output column; requested before the sums they are applied to.
+struct F32Column {
+    float al, sc, sf;
+};
+__device__ __forceinline__ F32Column f32_column(const GatherGemm& g, int ncol) {
+    if (ncol >= g.NC) return F32Column{0.0f, 0.0f, 0.0f};
+    return F32Column{g.alpha[g.rows_per_group >= g.NC ? 0 : ncol / g.rows_per_group], g.scale ? g.scale[ncol] : 1.0f,
+                     g.shift ? g.shift[ncol] : 0.0f};
+}
+
+__device__ __forceinline__ void f32_tail_store(const GatherGemm& g, int64_t m, int ncol, double sum, const F32Column& c) {
+    float v = (static_cast<float>(sum) * c.al) * c.sc + c.sf;
+    const int64_t off = m * g.ldy + ncol;
+    if (g.y_f32) {
+        if (g.residual) v += static_cast<const float*>(g.residual)[off];
+        if (g.relu) v = fmaxf(v, 0.0f);
+        static_cast<float*>(g.Y)[off] = v;
+    } else {
+        if (g.residual) v += bf16_to_f32(static_cast<const uint16_t*>(g.residual)[off]);
+        if (g.relu) v = fmaxf(v, 0.0f);
+        static_cast<uint16_t*>(g.Y)[off] = f32_to_bf16(v);
+    }
+}
+
+// blockIdx.x walks the tiles, blockIdx.y is the K range when g.splits > 1 (float64 sums to g.partial [split][M][NC]).
+template <int NT, int NW, int MODE>
+__global__ __launch_bounds__(64 * NW) void gather_gemm_f64_kernel(const F32Args args) {
+    constexpr int BN = 16 * NT;
+    constexpr int DEPTH = 4;                            // K blocks of 16 in flight
+    __shared__ double part[NW > 1 ? NW * 16 * BN : 1];
+    const GatherGemm& g = args.g;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, quad = lane >> 4;        // pixel / channel of the tile; which four k of a block
     const float* __restrict__ X = static_cast<const float*>(g.X);
     const uint32_t* __restrict__ Wq = static_cast<const uint32_t*>(g.Wq);
 
-    // A staging: EA consecutive k of one row; B staging: EA consecutive codes of one output channel
-    const int arow = tid / TPR;
-    const int akq = (tid % TPR) * EA;
-    const int64_t am = m0 + arow;
-    int64_t pixbase = 0;
-    int ih0 = -(1 << 28), iw0 = -(1 << 28);
-    if (am < g.M) {
-        const int ow = static_cast<int>(am % g.OW);
-        const int64_t t = am / g.OW;
-        const int oh = static_cast<int>(t % g.OH);
-        pixbase = (t / g.OH) * g.IH * g.IW;
-        ih0 = oh * g.sh - g.ph;
-        iw0 = ow * g.sw - g.pw;
-    }
-    const int bn = n0 + arow;
+    // the wave's range of K blocks; a ragged last block is done element by element after the others
+    const int nkb = (g.K + 15) >> 4;
+    const int64_t parts = static_cast<int64_t>(g.splits) * NW;
+    const int64_t p = static_cast<int64_t>(blockIdx.y) * NW + wave;
+    const int kb0 = static_cast<int>(nkb * p / parts), kb1 = static_cast<int>(nkb * (p + 1) / parts);
+    const int kfull = (MODE == kF32Element) ? kb1 : min(kb1, g.K >> 4);
 
-    float pa[EA];
-    uint32_t pw = 0;
-    // Branch-free: every lane loads (element 0 when its tap is outside the image or beyond K) and the value is
-    // selected afterwards, so the EA loads of a slab are issued back to back instead of one exposed latency each.
-    bool okv[EA];       // which of the prefetched values are real (applied when they are staged, so that nothing
-    bool wok = false;   // waits for the loads before the slab in between has been multiplied)
-    auto fetch = [&](int k0) {
-        int64_t idx[EA];
-        // (tap, channel) of the first element by division (there is no integer divide in hardware: one pair per
-        // slab and thread, not one per element), of the following ones by stepping
-        const int kf = k0 + akq;
-        int rs = g.plain_gemm ? 0 : kf / g.IC;
-        int c = kf - rs * g.IC;
-        int r = g.plain_gemm ? 0 : rs / g.S;
-        int s_ = rs - r * g.S;
+    for (int64_t t = blockIdx.x; t < args.tiles; t += gridDim.x) {
+        const int64_t tm = t / args.tiles_n;
+        const int64_t m0 = tm * 16;
+        const int n0 = static_cast<int>(t - tm * args.tiles_n) * BN;
+
+        // columns this thread writes: one per 16-channel group (one wave), or those of its share of the summed tile
+        constexpr int NE = (NW == 1) ? NT : (BN > 4 * NW ? BN / (4 * NW) : 1);
+        F32Column col[NE];
 #pragma unroll
-        for (int e = 0; e < EA; ++e) {
-            int th = ih0 + r * g.dh, tw = iw0 + s_ * g.dw;
-            bool ok = kf + e < g.K;
-            if (g.divh > 1) { ok = ok && th >= 0 && (th % g.divh) == 0; th /= g.divh; }
-            if (g.divw > 1) { ok = ok && tw >= 0 && (tw % g.divw) == 0; tw /= g.divw; }
-            ok = ok && static_cast<unsigned>(th) < static_cast<unsigned>(g.IH) &&
-                 static_cast<unsigned>(tw) < static_cast<unsigned>(g.IW);
-            okv[e] = ok;
-            idx[e] = ok ? (pixbase + static_cast<int64_t>(th) * g.IW + tw) * g.xs + c : 0;
-            if (++c == g.IC) {
-                c = 0;
-                if (++s_ == g.S) {
-                    s_ = 0;
-                    ++r;
+        for (int i = 0; i < NE; ++i) col[i] = f32_column(g, n0 + (NW == 1 ? 16 * i + l16 : (threadIdx.x + i * 64 * NW) % BN));
+
+        // rows and columns beyond the problem repeat the last one; they are not stored
+        const int64_t m = min(m0 + l16, g.M - 1);
+        const float* xrow;
+        int ih0 = 0, iw0 = 0;
+        if (MODE == kF32Gemm) {
+            xrow = X + m * g.xs;
+        } else {
+            int64_t img;
+            int oh, ow;
+            if (g.M <= 0x7FFFFFFF) {                    // 64-bit division costs about a microsecond
+                const uint32_t mm = static_cast<uint32_t>(m);
+                const uint32_t row = mm / static_cast<uint32_t>(g.OW);
+                ow = static_cast<int>(mm - row * static_cast<uint32_t>(g.OW));
+                const uint32_t im = row / static_cast<uint32_t>(g.OH);
+                oh = static_cast<int>(row - im * static_cast<uint32_t>(g.OH));
+                img = im;
+            } else {
+                const int64_t row = m / g.OW;
+                ow = static_cast<int>(m - row * g.OW);
+                img = row / g.OH;
+                oh = static_cast<int>(row - img * g.OH);
+            }
+            xrow = X + img * g.IH * g.IW * g.xs;
+            ih0 = oh * g.sh - g.ph;
+            iw0 = ow * g.sw - g.pw;
+        }
+        const uint32_t* wrow[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) wrow[j] = Wq + static_cast<int64_t>(min(n0 + 16 * j + l16, g.NC - 1)) * g.wpr;
+
+        // Four consecutive elements of the lane's row from k on; an element is real if k < K and its tap lies in the
+        // image.  No short cuts in the conditions: the loads of a block are issued back to back.
+        struct Place {
+            int c, s, th, tw;
+            int64_t off;
+        };
+        auto place = [&](int k) {
+            const uint32_t rs = fdiv_u(static_cast<uint32_t>(k), args.divIC);
+            const uint32_t r = fdiv_u(rs, args.divS);
+            Place q;
+            q.c = k - static_cast<int>(rs) * g.IC;
+            q.s = static_cast<int>(rs - r * static_cast<uint32_t>(g.S));
+            q.th = ih0 + static_cast<int>(r) * g.dh;
+            q.tw = iw0 + q.s * g.dw;
+            q.off = static_cast<int64_t>(q.th * g.IW + q.tw) * g.xs + q.c;
+            return q;
+        };
+        auto inside = [&](const Place& q) {
+            return static_cast<uint32_t>(static_cast<unsigned>(q.th) < static_cast<unsigned>(g.IH)) &
+                   static_cast<uint32_t>(static_cast<unsigned>(q.tw) < static_cast<unsigned>(g.IW));
+        };
+        auto load_elements = [&](int k, float (&v)[4]) {
+            uint32_t real = 0;
+            if (MODE == kF32Gemm) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool ok = k + i < g.K;
+                    real |= static_cast<uint32_t>(ok) << i;
+                    v[i] = xrow[ok ? k + i : 0];
+                }
+                return real;
+            }
+            Place q = place(k);
+            const int64_t next_tap = static_cast<int64_t>(g.dw) * g.xs - g.IC;
+            const int64_t next_row = static_cast<int64_t>(g.dh) * g.IW * g.xs - static_cast<int64_t>(g.S) * g.dw * g.xs;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t ok = inside(q) & static_cast<uint32_t>(k + i < g.K);
+                real |= ok << i;
+                v[i] = xrow[ok ? q.off : 0];
+                const bool wc = q.c + 1 == g.IC;
+                q.c = wc ? 0 : q.c + 1;
+                q.s += wc ? 1 : 0;
+                q.tw += wc ? g.dw : 0;
+                q.off += 1 + (wc ? next_tap : 0);
+                const bool ws = q.s == g.S;
+                q.s = ws ? 0 : q.s;
+                q.th += ws ? g.dh : 0;
+                q.tw = ws ? iw0 : q.tw;
+                q.off += ws ? next_row : 0;
+            }
+            return real;
+        };
+
+        float xa[DEPTH][4];
+        uint32_t wa[DEPTH][NT];
+        uint32_t okv[DEPTH];            // bit i: element i is real
+        auto load = [&](int d, int kb) {
+            const int k = kb * 16 + quad * 4;
+            if (MODE == kF32Element) {
+                okv[d] = load_elements(k, xa[d]);
+            } else {
+                const Float4* src = reinterpret_cast<const Float4*>(xrow + k);
+                okv[d] = 15u;
+                if (MODE == kF32Quad) {
+                    const Place q = place(k);
+                    const uint32_t ok = inside(q);
+                    okv[d] = ok ? 15u : 0u;
+                    src = reinterpret_cast<const Float4*>(xrow + (ok ? q.off : 0));
+                }
+                const Float4 v = *src;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) xa[d][i] = v.v[i];
+            }
+#pragma unroll
+            for (int j = 0; j < NT; ++j) wa[d][j] = wrow[j][kb];
+        };
+        f64x4 acc[NT] = {};
+        auto multiply = [&](int d) {
+            double a[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] = static_cast<double>(((okv[d] >> i) & 1u) ? xa[d][i] : 0.0f);
+            // codes 4*quad + i of the word sit, after this shift, at bits 0, 16, 2, 18
+            uint32_t w[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) w[j] = wa[d][j] >> (4 * quad);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int sh = 30 - ((i & 1) * 16 + (i >> 1) * 2);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const double b = __hiloint2double(static_cast<int>((w[j] << sh) & 0xC0000000u), 0);
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b, acc[j], 0, 0, 0);
                 }
             }
-        }
-#pragma unroll
-        for (int e = 0; e < EA; ++e) pa[e] = X[idx[e]];
-        const int k = k0 + akq;
-        wok = bn < g.NC && k < g.K;
-        pw = Wq[wok ? static_cast<int64_t>(bn) * g.wpr + (k >> 4) : 0];
-    };
-    auto stage = [&](int k0) {
-        const int kb = k0 + akq;
-#pragma unroll
-        for (int e = 0; e < EA; ++e) {
-            As[akq + e][arow] = okv[e] ? static_cast<double>(pa[e]) : 0.0;
-            const int t = (kb + e) & 15;
-            const uint32_t fld = wok ? (pw >> ((t & 1) * 16 + (t >> 1) * 2)) & 3u : 0u;
-            Bs[akq + e][arow] = (fld & 1u) ? ((fld & 2u) ? -1.0 : 1.0) : 0.0;
-        }
-    };
+        };
 
-    const int ty = tid >> 4, tx = tid & 15;
-    double acc[TT][TT] = {};
-
-    const int kbeg = SPLIT ? static_cast<int>(blockIdx.y) * kps * kF32K : 0;
-    const int kend = SPLIT ? min(g.K, kbeg + kps * kF32K) : g.K;
-    fetch(kbeg);
-    for (int k0 = kbeg; k0 < kend; k0 += kF32K) {
-        stage(k0);
-        __syncthreads();
-        if (k0 + kF32K < kend) fetch(k0 + kF32K);        // in flight while this slab is multiplied
-#pragma unroll 8
-        for (int k = 0; k < kF32K; ++k) {
-            double a[TT], b[TT];
+        const int n = kfull - kb0;
+        int i = 0;
+        if (n >= DEPTH) {
 #pragma unroll
-            for (int i = 0; i < TT; ++i) a[i] = As[k][ty * TT + i];
+            for (int d = 0; d < DEPTH; ++d) load(d, kb0 + d);
+            for (; i + 2 * DEPTH <= n; i += DEPTH) {
 #pragma unroll
-            for (int j = 0; j < TT; ++j) b[j] = Bs[k][tx * TT + j];
-#pragma unroll
-            for (int i = 0; i < TT; ++i)
-#pragma unroll
-                for (int j = 0; j < TT; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-
-    if constexpr (SPLIT) {
-        double* __restrict__ part = reinterpret_cast<double*>(g.partial) + static_cast<int64_t>(blockIdx.y) * g.M * g.NC;
-#pragma unroll
-        for (int i = 0; i < TT; ++i) {
-            const int64_t m = m0 + ty * TT + i;
-#pragma unroll
-            for (int j = 0; j < TT; ++j) {
-                const int ncol = n0 + tx * TT + j;
-                if (m < g.M && ncol < g.NC) part[m * g.NC + ncol] = acc[i][j];
+                for (int d = 0; d < DEPTH; ++d) {
+                    multiply(d);
+                    load(d, kb0 + i + d + DEPTH);
+                }
             }
-        }
-        return;
-    }
 #pragma unroll
-    for (int j = 0; j < TT; ++j) {
-        const int ncol = n0 + tx * TT + j;
-        if (ncol >= g.NC) continue;
-        const float al = g.alpha[ncol / g.rows_per_group];
-        const float sc = g.scale ? g.scale[ncol] : 1.0f;
-        const float sf = g.shift ? g.shift[ncol] : 0.0f;
-#pragma unroll
-        for (int i = 0; i < TT; ++i) {
-            const int64_t m = m0 + ty * TT + i;
-            if (m >= g.M) continue;
-            float v = (static_cast<float>(acc[i][j]) * al) * sc + sf;
-            const int64_t off = m * g.ldy + ncol;
-            if (g.y_f32) {
-                if (g.residual) v += static_cast<const float*>(g.residual)[off];
-                if (g.relu) v = fmaxf(v, 0.0f);
-                static_cast<float*>(g.Y)[off] = v;
-            } else {
-                if (g.residual) v += bf16_to_f32(static_cast<const uint16_t*>(g.residual)[off]);
-                if (g.relu) v = fmaxf(v, 0.0f);
-                static_cast<uint16_t*>(g.Y)[off] = f32_to_bf16(v);
+            for (int d = 0; d < DEPTH; ++d) {
+                multiply(d);
+                if (i + d + DEPTH < n) load(d, kb0 + i + d + DEPTH);
             }
+            i += DEPTH;
+        } else {
+#pragma unroll
+            for (int d = 0; d < DEPTH - 1; ++d)
+                if (d < n) load(d, kb0 + d);
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d)
+            if (i + d < n) multiply(d);
+        if (MODE != kF32Element && kb1 > kfull && kb1 > kb0) {      // the ragged block is the last one of K
+            okv[0] = load_elements(kfull * 16 + quad * 4, xa[0]);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) wa[0][j] = wrow[j][kfull];
+            multiply(0);
+        }
+
+        // register r of a lane is pixel quad + 4r, channel l16
+        auto finish = [&](int64_t mo, int ncol, double sum, const F32Column& c) {
+            if (mo >= g.M || ncol >= g.NC) return;
+            if (g.splits > 1)
+                reinterpret_cast<double*>(g.partial)[(static_cast<int64_t>(blockIdx.y) * g.M + mo) * g.NC + ncol] = sum;
+            else
+                f32_tail_store(g, mo, ncol, sum, c);
+        };
+        if (NW == 1) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) finish(m0 + quad + 4 * r, n0 + 16 * j + l16, 0.5 * acc[j][r], col[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) part[(wave * 16 + quad + 4 * r) * BN + 16 * j + l16] = acc[j][r];
+            __syncthreads();
+#pragma unroll
+            for (int o = 0; o < NE; ++o) {
+                const int e = threadIdx.x + o * 64 * NW;
+                if (e >= 16 * BN) break;
+                double sum = part[e];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) sum += part[w * 16 * BN + e];
+                finish(m0 + e / BN, n0 + e % BN, 0.5 * sum, col[o]);
+            }
+            __syncthreads();            // the next tile reuses `part`
         }
     }
 }
@@ -175,81 +294,88 @@ __global__ __launch_bounds__(256) void fp32_splitk_finish_kernel(const GatherGem
     for (int s = 0; s < g.splits; ++s) sum += part[static_cast<int64_t>(s) * total + i];
     const int64_t m = i / g.NC;
     const int ncol = static_cast<int>(i - m * g.NC);
-    const float al = g.alpha[ncol / g.rows_per_group];
-    const float sc = g.scale ? g.scale[ncol] : 1.0f;
-    const float sf = g.shift ? g.shift[ncol] : 0.0f;
-    float v = (static_cast<float>(sum) * al) * sc + sf;
-    const int64_t off = m * g.ldy + ncol;
-    if (g.y_f32) {
-        if (g.residual) v += static_cast<const float*>(g.residual)[off];
-        if (g.relu) v = fmaxf(v, 0.0f);
-        static_cast<float*>(g.Y)[off] = v;
-    } else {
-        if (g.residual) v += bf16_to_f32(static_cast<const uint16_t*>(g.residual)[off]);
-        if (g.relu) v = fmaxf(v, 0.0f);
-        static_cast<uint16_t*>(g.Y)[off] = f32_to_bf16(v);
-    }
+    f32_tail_store(g, m, ncol, sum, f32_column(g, ncol));
 }
 
-// Tile side and K ranges of the float32 path: a pure function of the shapes (the workspace query and the launch
-// agree).  Problems with at least 128 tiles of 64x64 run those, unsplit.  Smaller ones are split along K towards
-// about 1024 workgroups, every range at least two slabs long, at most 16 ranges; they keep 64x64 tiles (half the
-// LDS reads per multiply-add of 32x32 tiles) if that still gives 256 workgroups, else 32x32 tiles.
+// Tile width, waves per tile and K ranges of the float32 path: a pure function of the shapes (the workspace query and
+// the launch agree).  Wide tiles share the activations and their conversion between columns; they are taken while 512
+// tiles (64 channels: 1024) remain and they pad the channels by no more than an eighth above 16-channel tiles.
+// Waves are added to a tile up to about 1.5 per SIMD in all (4096 x 64 x 800, 512 tiles: 2 waves 22.6 us, 4 waves 13.3,
+// 8 waves 14.3; 128 tiles of 64 x 512 x 1024: 4 waves 7.0, 8 waves 6.7, 16 waves 7.4), each with at least two K blocks (36864 x 32 x 25 on two
+// blocks: 1 wave 9.8 us, 2 waves 13.9).  Only problems whose waves would walk more than 32 blocks on an idle chip (few
+// outputs, K beyond 8192) are cut over workgroups too.
 struct Fp32Plan {
-    int ts, kslab, splits, kps;
+    int nt, nw, splits;
+    int64_t tiles;
+    int32_t tiles_n;
 };
 static Fp32Plan fp32_plan(const GatherGemm& g) {
-    auto blocks = [&](int ts) { return ((g.M + ts - 1) / ts) * ((g.NC + ts - 1) / ts); };
-    auto slabs = [&](int kslab) { return (static_cast<int64_t>(g.K) + kslab - 1) / kslab; };
-    Fp32Plan p{64, 32, 1, 0};
-    if (blocks(64) >= 128) return p;
-    const bool split = env_int("TWN_F32_SPLITK", 1) != 0;
-    auto ranges = [&](int64_t tiles, int64_t kt, int* kps) {
-        int64_t want = 1024 / tiles;
-        if (want > kt / 2) want = kt / 2;
-        if (want > 16) want = 16;
-        if (want < 2 || !split) {
-            *kps = 0;
-            return 1;
-        }
-        *kps = static_cast<int>((kt + want - 1) / want);
-        return static_cast<int>((kt + *kps - 1) / *kps);
-    };
-    int kps64 = 0;
-    const int s64 = ranges(blocks(64), slabs(32), &kps64);
-    if (split && g.M >= 48 && g.NC >= 48 && blocks(64) * s64 >= 256) {
-        p.splits = s64;
-        p.kps = kps64;
-        return p;
+    const int64_t tm = (g.M + 15) / 16, nkb = (static_cast<int64_t>(g.K) + 15) / 16;
+    const int64_t tn1 = (static_cast<int64_t>(g.NC) + 15) / 16;
+    Fp32Plan p{1, 1, 1, 0, 0};
+    for (int nt = 4; nt >= 2; nt >>= 1) {
+        const int64_t tn = (tn1 + nt - 1) / nt;
+        if (tn * nt * 8 > tn1 * 9 || tm * tn < (nt == 4 ? 1024 : 512)) continue;
+        p.nt = nt;
+        break;
     }
-    p.ts = 32;
-    p.kslab = 64;
-    p.splits = ranges(blocks(32), slabs(64), &p.kps);
+    const int64_t tn = (tn1 + p.nt - 1) / p.nt;
+    p.tiles = tm * tn;
+    p.tiles_n = static_cast<int32_t>(tn);
+    const int nw_max = 16 / p.nt;
+    while (p.nw < nw_max && p.tiles * p.nw < 1536 && nkb >= 4 * p.nw && (p.nw < 8 || p.tiles <= 64)) p.nw *= 2;
+    if (p.nw == nw_max && nkb > 32 * p.nw && env_int("TWN_F32_SPLITK", 1) != 0) {
+        int64_t want = 2048 / (p.tiles * p.nw);
+        if (want > nkb / (8 * p.nw)) want = nkb / (8 * p.nw);
+        if (want > 16) want = 16;
+        if (want > 1) p.splits = static_cast<int>(want);
+    }
     return p;
 }
 
 int32_t gather_gemm_fp32_splits(const GatherGemm& g) { return fp32_plan(g).splits; }
 
+template <int NT, int NW>
+static void launch_f64(const F32Args& a, int mode, hipStream_t st) {
+    // tiles beyond the grid are walked in a loop
+    const dim3 grid(static_cast<unsigned>(a.tiles < (1 << 22) ? a.tiles : (1 << 22)), static_cast<unsigned>(a.g.splits));
+    if (mode == kF32Gemm)
+        gather_gemm_f64_kernel<NT, NW, kF32Gemm><<<grid, 64 * NW, 0, st>>>(a);
+    else if (mode == kF32Quad)
+        gather_gemm_f64_kernel<NT, NW, kF32Quad><<<grid, 64 * NW, 0, st>>>(a);
+    else
+        gather_gemm_f64_kernel<NT, NW, kF32Element><<<grid, 64 * NW, 0, st>>>(a);
+}
+
 int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st) {
     const Fp32Plan p = fp32_plan(g);
-    const int64_t nb = ((g.M + p.ts - 1) / p.ts) * ((g.NC + p.ts - 1) / p.ts);
-    if (nb <= 0 || nb >= (1LL << 31)) return TWN_ERR_SHAPE;
-    if (g.splits > 1) {
-        if (g.splits != p.splits || !g.partial) return TWN_ERR_WORKSPACE;
-        const int64_t total = g.M * g.NC;
-        if (total >= (1LL << 31) * 256) return TWN_ERR_SHAPE;
-        const dim3 grid(static_cast<unsigned>(nb), static_cast<unsigned>(g.splits));
-        if (p.ts == 64)
-            gather_gemm_fp32_kernel<64, true><<<grid, 256, 0, st>>>(g, p.kps);
-        else
-            gather_gemm_fp32_kernel<32, true><<<grid, 256, 0, st>>>(g, p.kps);
-        fp32_splitk_finish_kernel<<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(g);
-        return launch_status();
+    if (p.tiles <= 0) return TWN_ERR_SHAPE;
+    if (g.splits > 1 && (g.splits != p.splits || !g.partial)) return TWN_ERR_WORKSPACE;
+    F32Args a;
+    a.g = g;
+    a.divIC = make_fastdiv_u(static_cast<uint32_t>(g.IC));
+    a.divS = make_fastdiv_u(static_cast<uint32_t>(g.S));
+    a.tiles = p.tiles;
+    a.tiles_n = p.tiles_n;
+    const int mode = g.plain_gemm ? kF32Gemm : (g.IC % 4 == 0) ? kF32Quad : kF32Element;
+    switch (p.nt * 32 + p.nw) {
+        case 32 + 1: launch_f64<1, 1>(a, mode, st); break;
+        case 32 + 2: launch_f64<1, 2>(a, mode, st); break;
+        case 32 + 4: launch_f64<1, 4>(a, mode, st); break;
+        case 32 + 8: launch_f64<1, 8>(a, mode, st); break;
+        case 32 + 16: launch_f64<1, 16>(a, mode, st); break;
+        case 64 + 1: launch_f64<2, 1>(a, mode, st); break;
+        case 64 + 2: launch_f64<2, 2>(a, mode, st); break;
+        case 64 + 4: launch_f64<2, 4>(a, mode, st); break;
+        case 64 + 8: launch_f64<2, 8>(a, mode, st); break;
+        case 128 + 1: launch_f64<4, 1>(a, mode, st); break;
+        case 128 + 2: launch_f64<4, 2>(a, mode, st); break;
+        default: launch_f64<4, 4>(a, mode, st); break;
     }
-    if (p.ts == 64)
-        gather_gemm_fp32_kernel<64, false><<<static_cast<unsigned>(nb), 256, 0, st>>>(g, 0);
-    else
-        gather_gemm_fp32_kernel<32, false><<<static_cast<unsigned>(nb), 256, 0, st>>>(g, 0);
+    if (g.splits > 1) {
+        const int64_t total = g.M * g.NC;
+        fp32_splitk_finish_kernel<<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(g);
+    }
     return launch_status();
 }
 
