@@ -319,7 +319,7 @@ def main():
                 "graph_replay_us": None if t_graph is None else round(t_graph * 1e3, 1),
                 "img_per_s": round(64 / (best * 1e-3), 1), "gflops": round(flops / best / 1e6, 1),
                 "per_layer_us": {n: round(t * 1e3, 1) for n, t in rows},
-                "bound": "latency: 0.55 GFLOP in four dependent launches of 2 to 576 workgroups"}
+                "bound": "latency: 0.55 GFLOP in four dependent launches"}
 
     def side_vgg16():
         layers = wl.vgg16_ssd(32)
