@@ -227,9 +227,10 @@ int32_t twn_conv2d_fwd(const twn_conv_desc* d, const void* X, const void* weight
 /* Two convolutions over the SAME input X in one call: the first convolution of a
  * residual block and its projection shortcut (the ResNet-18 of Sec. 3.1 has three
  * such block heads).  Results are those of two twn_conv2d_fwd calls (each problem
- * has its own filters, alpha, geometry, epilogue and output); when both problems
- * get the same tile shape and short reductions (K <= 1536) they run in ONE
- * launch, else one after the other.
+ * has its own filters, alpha, geometry, epilogue and output), also when one of
+ * them reads or writes what the other writes: such problems run one after the
+ * other.  Independent ones run in ONE launch when they are small (up to 512 tiles
+ * of 32x64 together) or get the same tile shape and short reductions (K <= 1536).
  * Product variant, bf16 in and out, C % 8 == 0 (else TWN_ERR_UNSUPPORTED); d0 and
  * d1 must agree in N, H, W, C (else TWN_ERR_SHAPE); no workspace is used. */
 int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_desc* d1, const void* X,

@@ -479,6 +479,24 @@ static int32_t build_pair_problem(const twn_conv_desc* d, const void* X, const v
     return TWN_OK;
 }
 
+// Whether two problems over one input give the results of two calls when they run at the same time: neither writes what
+// the other reads or writes (a second problem whose residual is the first one's output has to wait for it).
+static bool pair_independent(const GatherGemm* g) {
+    struct Range {
+        uintptr_t at;
+        uint64_t bytes;
+        bool meets(const Range& o) const { return at != 0 && o.at != 0 && at < o.at + o.bytes && o.at < at + bytes; }
+    };
+    auto range = [](const void* p, int64_t values) { return Range{reinterpret_cast<uintptr_t>(p), static_cast<uint64_t>(values) * 2}; };
+    const Range x = range(g[0].X, g[0].M / (static_cast<int64_t>(g[0].OH) * g[0].OW) * g[0].IH * g[0].IW * g[0].xs);
+    Range y[2], res[2];
+    for (int i = 0; i < 2; ++i) {
+        y[i] = range(g[i].Y, g[i].M * g[i].ldy);
+        res[i] = range(g[i].residual, g[i].M * g[i].ldy);
+    }
+    return !y[0].meets(y[1]) && !y[0].meets(res[1]) && !y[1].meets(res[0]) && !y[0].meets(x) && !y[1].meets(x);
+}
+
 extern "C" int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_desc* d1, const void* X,
                                        const void* weights0, const float* alpha0, const twn_epilogue* ep0, void* Y0,
                                        const void* weights1, const float* alpha1, const twn_epilogue* ep1, void* Y1,
@@ -490,7 +508,8 @@ extern "C" int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_d
     if (rc == TWN_OK) rc = build_pair_problem(d1, X, weights1, alpha1, ep1, Y1, &g[1]);
     if (rc != TWN_OK) return rc;
     hipStream_t st = as_stream(stream);
-    const int small = conv_small_tile(g, 2);
+    const bool together = pair_independent(g);
+    const int small = together ? conv_small_tile(g, 2) : 0;
     if (small != 0) return launch_conv_small(g, 2, small, st);
     const int t0 = gather_gemm_dma_tile(g[0], true), t1 = gather_gemm_dma_tile(g[1], true);
     // One launch pays while the reduction is short: with more than 24 slabs per tile the persistent kernels with load
@@ -498,11 +517,11 @@ extern "C" int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_d
     // 23.4 -> 19.1 us; 256 filters, K = 1152: 17.9 -> 15.9 us; 512 filters, K = 2304: 18.2 -> 19.3 us).
     const int64_t kmax = g[0].K > g[1].K ? g[0].K : g[1].K;
     const int pair_knob = env_int("TWN_FWD_PAIR", 1);          // 0: never one launch, 2: whenever the tiles agree
-    if (t0 != 0 && t0 == t1 && (pair_knob == 2 || (pair_knob == 1 && kmax <= 1536))) {
+    if (together && t0 != 0 && t0 == t1 && (pair_knob == 2 || (pair_knob == 1 && kmax <= 1536))) {
         rc = launch_gather_gemm_dma_batch(g, 2, t0, st);
         if (rc != TWN_ERR_UNSUPPORTED) return rc;
     }
-    // different tile shapes (or no build for the pair): one after the other, as two twn_conv2d_fwd calls without a workspace
+    // dependent problems, different tile shapes (or no build for the pair): one after the other, as two twn_conv2d_fwd calls without a workspace
     rc = dispatch(g[0], d0->variant, nullptr, 0, st, false);
     if (rc != TWN_OK) return rc;
     return dispatch(g[1], d1->variant, nullptr, 0, st, false);
