@@ -22,6 +22,10 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// 64-wide slabs of a reduction of length k.  The sum is unsigned: two terms of alpha*dY double a K that may be just below
+// 2^30, and k + 63 would pass the largest int.
+__host__ __device__ inline int k_slabs(int32_t k) { return static_cast<int>((static_cast<uint32_t>(k) + 63u) >> 6); }
+
 // Environment override for launch-shape sweeps (0 / unset = built-in choice).  Every use keeps what it read, stamped
 // with the generation that twn_reload_env advances: a dispatch asks for up to ten of them, and a locked search by
 // name cost it about a microsecond.

@@ -171,7 +171,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     const uint32_t voffB = (bcol < g.NC) ? static_cast<uint32_t>(bcol) * static_cast<uint32_t>(g.wpr) * 4u : kBufOutside;
 
     // K slabs handled by this workgroup: all of them, or one range of a split-K launch (blockIdx.y)
-    const int KT_all = (g.K + 63) / 64;
+    const int KT_all = k_slabs(g.K);
     const int kps = SPLITK ? (KT_all + g.splits - 1) / g.splits : KT_all;
     const int kt_begin = SPLITK ? static_cast<int>(by) * kps : 0;
     const int KT = (kt_begin + kps < KT_all) ? kt_begin + kps : KT_all;      // end of this range

@@ -133,7 +133,7 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
     }
 
     // this wave's slabs: a contiguous range
-    const int KT = (g.K + 63) / 64;
+    const int KT = k_slabs(g.K);
     const int per = (KT + NW - 1) / NW;
     const int s0 = wave * per;
     const int ns = (s0 + per <= KT) ? per : (KT > s0 ? KT - s0 : 0);
@@ -439,7 +439,7 @@ int conv_small_tile(const GatherGemm* gs, int count) {
         t12 += rows * ((g.NC + 63) / 64);
         const bool slabs = g.plain_gemm ? g.K % 64 == 0 : (g.IC % 64 == 0 && g.divh == 1 && g.divw == 1 && g.orU == 0);
         persistent = persistent && slabs && !g.y_f32 && g.NC % 8 == 0 && g.ldy % 8 == 0 && !g.chunk_gather;
-        if ((g.K + 63) / 64 > kt) kt = (g.K + 63) / 64;
+        if (k_slabs(g.K) > kt) kt = k_slabs(g.K);
     }
     if (kt > 256) return 0;
     if (t11 <= 256) return 1108;

@@ -39,3 +39,17 @@ def test_dx(n, h, w, c, o, r, stride, pad, groups):
         dx = torch.full((n, h, w, c), 7.0, dtype=dtype, device="cuda")
         api.twn_conv2d_bwd_ste(None, to_dev_bf16(dy), tw, *geo, need_dw=False, x_shape=(n, h, w, c), dX=dx)
         assert rel_err(to_host_f64(dx), ref) <= bar
+
+
+def test_dx_of_the_longest_reduction():
+    """2^30 - 8 filters in two groups: the two terms make a reduction within 63 of the largest int.  All codes +1 and
+    dY = 1: the sum of the alphas, whose partial sums of whole steps are exact in float32."""
+    o, c = (1 << 30) - 8, 8
+    words = api.twn_packed_words_per_row(o)
+    codes = torch.full((c, words), 0x55555555, dtype=torch.int32, device="cuda")
+    tw = api.TernaryWeights(o, c, 1, 1, 2, None, codes, None, torch.tensor([1.0, 0.5], device="cuda"), None)
+    dy = torch.ones((1, 1, 1, o), dtype=torch.bfloat16, device="cuda")
+    dx = torch.zeros((1, 1, 1, c), dtype=torch.float32, device="cuda")
+    ws = torch.empty(9 << 30, dtype=torch.uint8, device="cuda")      # what dX needs (the query covers dW too: 288 GB)
+    api.twn_conv2d_bwd_ste(None, dy, tw, need_dw=False, x_shape=(1, 1, 1, c), dX=dx, workspace=ws)
+    assert rel_err(to_host_f64(dx), np.full(c, (o // 2) * 1.5)) <= 1e-4
