@@ -6,18 +6,25 @@
 
 namespace twn {
 
-// The TWN_* tuning knobs are read from the environment once each and remembered: launches do not call getenv
+// The TWN_* overrides are read from the environment once each and remembered: launches do not call getenv
 // (which is neither free nor safe against a concurrent setenv).  twn_reload_env forgets what was read.
+std::atomic<uint64_t> g_env[static_cast<int>(Env::kCount)] = {};
 std::atomic<uint32_t> g_env_generation{1};
 
-uint64_t env_read(EnvKnob& k, const char* name, uint32_t generation) {
+uint64_t env_read(Env name, uint32_t generation) {
+#define TWN_ENV_STRING(n) "TWN_" #n,
+    static const char* const names[] = {TWN_ENV_NAMES(TWN_ENV_STRING)};
+#undef TWN_ENV_STRING
     static std::mutex mutex;
     std::lock_guard<std::mutex> lock(mutex);
-    const char* v = std::getenv(name);
+    std::atomic<uint64_t>& kept = g_env[static_cast<int>(name)];
+    uint64_t seen = kept.load(std::memory_order_relaxed);
+    if ((seen >> 33) == generation) return seen;        // another thread has read it meanwhile
+    const char* v = std::getenv(names[static_cast<int>(name)]);
     const bool set = v && *v;
-    const uint64_t seen = (static_cast<uint64_t>(generation) << 33) | (static_cast<uint64_t>(set) << 32) |
-                          static_cast<uint32_t>(set ? std::atoi(v) : 0);
-    k.seen.store(seen, std::memory_order_relaxed);
+    seen = (static_cast<uint64_t>(generation) << 33) | (static_cast<uint64_t>(set) << 32) |
+           static_cast<uint32_t>(set ? std::atoi(v) : 0);
+    kept.store(seen, std::memory_order_relaxed);
     return seen;
 }
 

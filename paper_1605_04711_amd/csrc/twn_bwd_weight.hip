@@ -810,7 +810,7 @@ __global__ __launch_bounds__(256) void bias_grad_final_kernel(const float* __res
 }
 
 static int32_t choose_splits(int64_t tiles, int64_t slabs, int ks = 1) {
-    int64_t want = env_int("TWN_WG_BLOCKS", 512) / ks;
+    int64_t want = env_int(Env::WG_BLOCKS, 512) / ks;
     // tiles x splits must not exceed the workgroups that are resident at once (two of four waves or one of eight
     // per CU), or the launch grows a second, nearly empty round
     int64_t splits = (tiles >= 256) ? 1 : want / tiles;
@@ -852,7 +852,7 @@ WgPlan plan_weight_grad(int32_t N, int32_t P, int32_t Q, int32_t C, int32_t O, i
     // Layers with fewer tiles than CUs split the pixels over workgroups, and every workgroup dumps a partial tile
     // (128 KB) that the reduction pass reads back: two groups of waves per workgroup halve that traffic at the
     // same number of waves per CU.  TWN_WG_KS=1 keeps four-wave workgroups.
-    pl.ks = (pl.tiles < 256 && env_int("TWN_WG_KS", 2) == 2 && pl.slabs >= 4) ? 2 : 1;
+    pl.ks = (pl.tiles < 256 && env_int(Env::WG_KS, 2) == 2 && pl.slabs >= 4) ? 2 : 1;
     pl.splits = choose_splits(pl.tiles, pl.slabs, pl.ks);
     return pl;
 }
@@ -894,7 +894,7 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
         taps = plan_weight_grad_taps(WgShape{w.N, w.H, w.W, w.C, w.O, w.R, w.S, w.P, w.Q, w.sh, w.sw, w.dh, w.dw});
     const int32_t splits = taps.use ? taps.splits : a.plan.splits;
     a.slabs_per_split = static_cast<int32_t>((a.plan.slabs + splits - 1) / splits);
-    a.xcd_map = env_int("TWN_WG_XCD", 1);
+    a.xcd_map = env_int(Env::WG_XCD, 1);
     a.dy_bytes = a.x_bytes = 0;
     a.exact = 0;
     if (taps.use) {
@@ -905,7 +905,7 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
         if (a.plan.patch) {
             const int64_t dyb = a.pixels * w.O * 2;
             const int64_t xb = ((static_cast<int64_t>(w.N) * w.H * w.W - 1) * w.xc + w.C) * 2;
-            const bool buf = env_int("TWN_BUFLOAD", 1) != 0 && dyb < (1LL << 31) && xb < (1LL << 31);
+            const bool buf = env_int(Env::BUFLOAD, 1) != 0 && dyb < (1LL << 31) && xb < (1LL << 31);
             a.dy_bytes = static_cast<uint32_t>(buf ? dyb : 0);
             a.x_bytes = static_cast<uint32_t>(buf ? xb : 0);
             a.exact = (w.N % a.plan.pn == 0 && w.P % a.plan.ph == 0 && w.Q % a.plan.pw == 0) ? 1 : 0;
@@ -931,7 +931,7 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
             const int64_t total = static_cast<int64_t>(w.O) * a.J;
             const int C = w.pad_sp ? w.c_real : w.C, S = w.pad_sp ? w.s_real : w.S;
             const int RS = w.R * w.S;
-            if (!w.pad_sp && w.C % 64 == 0 && RS <= kReduceRowsMaxTaps && splits <= env_int("TWN_WG_ROWS_SPLITS", 32))
+            if (!w.pad_sp && w.C % 64 == 0 && RS <= kReduceRowsMaxTaps && splits <= env_int(Env::WG_ROWS_SPLITS, 32))
                 weight_grad_reduce_rows_kernel<<<static_cast<unsigned>(w.O * (w.C / 64)), 256, 0, st>>>(
                     w.partial, splits, w.O, w.C, RS, w.beta, w.dW);
             else if (total % 4 == 0)

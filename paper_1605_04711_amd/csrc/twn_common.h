@@ -26,22 +26,29 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // 2^30, and k + 63 would pass the largest int.
 __host__ __device__ inline int k_slabs(int32_t k) { return static_cast<int>((static_cast<uint32_t>(k) + 63u) >> 6); }
 
-// Environment override for launch-shape sweeps (0 / unset = built-in choice).  Every use keeps what it read, stamped
-// with the generation that twn_reload_env advances: a dispatch asks for up to ten of them, and a locked search by
-// name cost it about a microsecond.
-struct EnvKnob {
-    std::atomic<uint64_t> seen{0};      // generation << 33 | is set << 32 | value
+// Environment overrides for launch-shape sweeps, TWN_<name> (unset = built-in choice).  One value per name: a workspace
+// query and the launch after it ask at different places and have to agree.  It is stamped with the generation that
+// twn_reload_env advances: a dispatch asks for up to ten of them, and a locked search by name cost it about a microsecond.
+#define TWN_ENV_NAMES(X) \
+    X(BUFLOAD) X(C64) X(C64_OCC) X(DX_CLASSES) X(DX_CLASS_BATCH) X(DX_CLASS_MIN_PIXELS) X(F32_SPLITK) X(FIRST) \
+    X(FIRST_OCC) X(FIRST_STAGGER) X(FIRST_THROUGH) X(FWD_PAIR) X(SMALL) X(STREAM) X(STREAM_KS) X(STREAM_OCC) \
+    X(STREAM_PC) X(STREAM_PC_STAGES) X(TERN_BLOCKS) X(TERN_REVERSE) X(TILE) X(WG_BLOCKS) X(WG_KS) \
+    X(WG_ROWS_SPLITS) X(WG_TAPS) X(WG_XCD)
+enum class Env : int {
+#define TWN_ENV_ENUM(n) n,
+    TWN_ENV_NAMES(TWN_ENV_ENUM)
+#undef TWN_ENV_ENUM
+    kCount
 };
+extern std::atomic<uint64_t> g_env[static_cast<int>(Env::kCount)];      // generation << 33 | is set << 32 | value
 extern std::atomic<uint32_t> g_env_generation;      // starts at 1
-uint64_t env_read(EnvKnob& k, const char* name, uint32_t generation);
-inline int env_value(EnvKnob& k, const char* name, int fallback) {
+uint64_t env_read(Env name, uint32_t generation);
+inline int env_int(Env name, int fallback) {
     const uint32_t gen = g_env_generation.load(std::memory_order_relaxed);
-    uint64_t v = k.seen.load(std::memory_order_relaxed);
-    if ((v >> 33) != gen) v = env_read(k, name, gen);
+    uint64_t v = g_env[static_cast<int>(name)].load(std::memory_order_relaxed);
+    if ((v >> 33) != gen) v = env_read(name, gen);
     return ((v >> 32) & 1u) ? static_cast<int>(static_cast<uint32_t>(v)) : fallback;
 }
-#define env_int(name, fallback) \
-    ::twn::env_value([]() -> ::twn::EnvKnob& { static ::twn::EnvKnob knob; return knob; }(), name, fallback)
 
 // ---- wave / block reductions in a fixed order (bit-identical run to run) ----
 __device__ __forceinline__ double wave_sum(double v) {

@@ -242,7 +242,7 @@ bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
         d->variant != TWN_VAR_BF16_POSTSCALE || d->x_dtype != TWN_BF16)
         return false;
     // several small launches only pay when each class still has enough pixels to fill the chip
-    if (static_cast<int64_t>(d->N) * ((d->H + sh - 1) / sh) * ((d->W + sw - 1) / sw) < env_int("TWN_DX_CLASS_MIN_PIXELS", 2048))
+    if (static_cast<int64_t>(d->N) * ((d->H + sh - 1) / sh) * ((d->W + sw - 1) / sw) < env_int(Env::DX_CLASS_MIN_PIXELS, 2048))
         return false;
     out->count = 0;
     out->any_empty = false;
@@ -416,7 +416,7 @@ extern "C" int32_t twn_conv2d_fwd(const twn_conv_desc* d, const void* X, const v
     set_epilogue(g, ep);
     g.Y = Y;
     if (d->variant == TWN_VAR_BF16_POSTSCALE && d->x_dtype == TWN_BF16 && d->y_dtype == TWN_BF16 && d->C == 3 &&
-        d->dil_h == 1 && d->dil_w == 1 && env_int("TWN_FIRST", 1) != 0) {
+        d->dil_h == 1 && d->dil_w == 1 && env_int(Env::FIRST, 1) != 0) {
         // three-channel first layer: persistent kernel with the input patch widened to four channels in LDS and
         // the expanded weights resident in registers (no workspace, no preparation launch)
         FirstLayer f{};
@@ -516,7 +516,7 @@ extern "C" int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_d
     // waves win back more than the saved launch (ResNet-18 b64 block heads, two launches -> one: 128 filters, K = 576:
     // 23.4 -> 19.1 us; 256 filters, K = 1152: 17.9 -> 15.9 us; 512 filters, K = 2304: 18.2 -> 19.3 us).
     const int64_t kmax = g[0].K > g[1].K ? g[0].K : g[1].K;
-    const int pair_knob = env_int("TWN_FWD_PAIR", 1);          // 0: never one launch, 2: whenever the tiles agree
+    const int pair_knob = env_int(Env::FWD_PAIR, 1);          // 0: never one launch, 2: whenever the tiles agree
     if (together && t0 != 0 && t0 == t1 && (pair_knob == 2 || (pair_knob == 1 && kmax <= 1536))) {
         rc = launch_gather_gemm_dma_batch(g, 2, t0, st);
         if (rc != TWN_ERR_UNSUPPORTED) return rc;
@@ -545,7 +545,7 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
                              void* dX, void* workspace, size_t workspace_bytes, hipStream_t st) {
     int32_t rc = TWN_OK;
     DxPlan p;
-    plan_dx(d, P, Q, &p, env_int("TWN_DX_CLASSES", 1) != 0);
+    plan_dx(d, P, Q, &p, env_int(Env::DX_CLASSES, 1) != 0);
     if (p.classes && !(workspace && workspace_bytes >= p.bytes() && aligned(workspace, 256) && aligned(dX, 16)))
         plan_dx(d, P, Q, &p, false);            // no room for the gathered codes: the generic gather
     if (p.two && (!workspace || workspace_bytes < p.bytes() || !aligned(workspace, 256))) return TWN_ERR_WORKSPACE;
@@ -574,7 +574,7 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
         g.alpha = alpha;
         g.Y = dX;
         g.splits = 1;
-        if (env_int("TWN_TILE", 0) == 0 && env_int("TWN_C64", 1) != 0 && conv_c64_applicable(g))
+        if (env_int(Env::TILE, 0) == 0 && env_int(Env::C64, 1) != 0 && conv_c64_applicable(g))
             return launch_conv_c64_scaled(g, alpha, d->O / d->alpha_groups, st);
     }
     if (p.two || p.classes) {
@@ -605,7 +605,7 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
     if (!p.classes) return dispatch(p.g, d->variant, ws + head, workspace_bytes > head ? workspace_bytes - head : 0, st);
     // all classes in ONE launch when the dispatcher would give each of them the same tile (they are too small to be worth
     // a launch each: ResNet-18 b64, the three strided 3x3 layers 33 / 34 / 48 us as four launches, 26 / 20 / 24 us as one)
-    const bool batch = env_int("TWN_DX_CLASS_BATCH", 1) != 0 && count > 1;
+    const bool batch = env_int(Env::DX_CLASS_BATCH, 1) != 0 && count > 1;
     const int small = batch ? conv_small_tile(gs, count) : 0;
     if (small != 0) return launch_conv_small(gs, count, small, st);
     int batch_tile = batch ? gather_gemm_dma_tile(gs[0]) : 0;

@@ -396,7 +396,7 @@ static int32_t launch_c64(const C64Args& a, bool flip, bool scaled, hipStream_t 
     if (!allowed) return TWN_ERR_HIP;
     const unsigned tiles_n = static_cast<unsigned>(a.NC / 64);
     int per_cu = 2;
-    const int cap = env_int("TWN_C64_OCC", 0);
+    const int cap = env_int(Env::C64_OCC, 0);
     if (cap > 0 && cap < per_cu) per_cu = cap;
     int64_t gx = static_cast<int64_t>(cus) * per_cu / tiles_n;
     if (gx < 8) gx = 8;

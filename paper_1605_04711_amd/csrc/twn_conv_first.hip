@@ -452,10 +452,10 @@ static bool first_plan(const FirstLayer& f, FirstArgs* a) {
     const int64_t yb = static_cast<int64_t>(f.N) * f.P * f.Q * f.O * 2;
     if (yb >= (1LL << 31)) return false;
     a->y_bytes = static_cast<uint32_t>(yb);
-    a->stagger = env_int("TWN_FIRST_STAGGER", 0);
+    a->stagger = env_int(Env::FIRST_STAGGER, 0);
     // Ordinary stores by default: written through, this kernel alone is faster (ResNet-18 stem 35.6 -> 33.7 us) but the
     // step it is part of slower (0.442 -> 0.450 ms, A/B on one box): its 103 MB of output then drain into the next launch.
-    a->through = env_int("TWN_FIRST_THROUGH", 0) != 0 ? 1 : 0;
+    a->through = env_int(Env::FIRST_THROUGH, 0) != 0 ? 1 : 0;
     return true;
 }
 
@@ -486,7 +486,7 @@ static int32_t launch_first(const FirstArgs& a, hipStream_t st) {
     const unsigned tiles_n = static_cast<unsigned>((a.O + 63) / 64);
     int per_cu = (160 * 1024) / smem;
     if (per_cu > 3) per_cu = 3;
-    const int cap = env_int("TWN_FIRST_OCC", 0);
+    const int cap = env_int(Env::FIRST_OCC, 0);
     if (cap > 0 && cap < per_cu) per_cu = cap;
     int64_t gx = static_cast<int64_t>(cus) * per_cu / tiles_n;
     if (gx < 8) gx = 8;

@@ -324,7 +324,7 @@ static Fp32Plan fp32_plan(const GatherGemm& g) {
     p.tiles_n = static_cast<int32_t>(tn);
     const int nw_max = 16 / p.nt;
     while (p.nw < nw_max && p.tiles * p.nw < 1536 && nkb >= 4 * p.nw && (p.nw < 8 || p.tiles <= 64)) p.nw *= 2;
-    if (p.nw == nw_max && nkb > 32 * p.nw && env_int("TWN_F32_SPLITK", 1) != 0) {
+    if (p.nw == nw_max && nkb > 32 * p.nw && env_int(Env::F32_SPLITK, 1) != 0) {
         int64_t want = 2048 / (p.tiles * p.nw);
         if (want > nkb / (8 * p.nw)) want = nkb / (8 * p.nw);
         if (want > 16) want = 16;

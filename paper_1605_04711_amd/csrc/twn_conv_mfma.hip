@@ -540,7 +540,7 @@ int32_t gather_gemm_splits(const GatherGemm& g) {
     if (conv_small_tile(&g, 1) != 0) return 1;
     // split K when even 64x128 tiles leave half the CUs idle and K is deep enough to share out (few workgroups
     // with two slabs in flight each are bound by memory latency when their input is not in L2)
-    if (gather_mode(g) == kModeScalar || env_int("TWN_TILE", 0) != 0) return 1;
+    if (gather_mode(g) == kModeScalar || env_int(Env::TILE, 0) != 0) return 1;
     const int64_t blocks = ((g.M + 127) / 128) * ((g.NC + 127) / 128);
     const int64_t blocks64 = ((g.M + 63) / 64) * ((g.NC + 127) / 128);
     const int KT = k_slabs(g.K);
@@ -560,8 +560,8 @@ int32_t gather_gemm_splits(const GatherGemm& g) {
 // or 0 when the problem would not run there (scalar gathers, forced tiles; persistent kernels unless
 // `instead_of_persistent` asks for the tile the problem would get if they did not exist).
 int32_t gather_gemm_dma_tile(const GatherGemm& g, bool instead_of_persistent) {
-    if (gather_mode(g) == kModeScalar || env_int("TWN_TILE", 0) != 0 || g.splits > 1) return 0;
-    if (!instead_of_persistent && env_int("TWN_STREAM", 1) != 0 && conv_stream_applicable(g)) return 0;
+    if (gather_mode(g) == kModeScalar || env_int(Env::TILE, 0) != 0 || g.splits > 1) return 0;
+    if (!instead_of_persistent && env_int(Env::STREAM, 1) != 0 && conv_stream_applicable(g)) return 0;
     auto blocks = [&](int bm, int bn) { return ((g.M + bm - 1) / bm) * ((g.NC + bn - 1) / bn); };
     int tile;
     if (g.NC <= 64) tile = 16;
@@ -584,9 +584,9 @@ int32_t launch_gather_gemm_mfma(const GatherGemm& g, int variant, hipStream_t st
     if (variant != TWN_VAR_BF16_POSTSCALE) return TWN_ERR_UNSUPPORTED;
 
     // Tile choice: the largest tile that still gives every CU work; narrow N tiles for narrow layers.
-    int tile = env_int("TWN_TILE", 0);
+    int tile = env_int(Env::TILE, 0);
     // 3x3 stride-1 layers over 64 channels: weights resident in registers, input patches with halo in LDS
-    if (tile == 0 && env_int("TWN_C64", 1) != 0 && conv_c64_applicable(g)) return launch_conv_c64(g, st);
+    if (tile == 0 && env_int(Env::C64, 1) != 0 && conv_c64_applicable(g)) return launch_conv_c64(g, st);
     const int small = conv_small_tile(&g, 1);
     if (small != 0) return launch_conv_small(&g, 1, small, st);
     if (mode != kModeScalar && (tile == 0 || tile > 10)) {
@@ -603,7 +603,7 @@ int32_t launch_gather_gemm_mfma(const GatherGemm& g, int variant, hipStream_t st
             // instead of twice; a few percent faster than the 2x2 arrangement, which keeps the split-K builds
             if (tile == 12 && g.splits == 1) tile = 15;
         }
-        if ((tile == 12 || (tile >= 14 && tile <= 17)) && env_int("TWN_STREAM", 1) != 0 && conv_stream_applicable(g))
+        if ((tile == 12 || (tile >= 14 && tile <= 17)) && env_int(Env::STREAM, 1) != 0 && conv_stream_applicable(g))
             return launch_conv_stream(g, tile, st);
         return launch_gather_gemm_dma(g, tile, st);
     }

@@ -697,7 +697,7 @@ static DmaArgs make_dma_args(const GatherGemm& g) {
         const bool shape_ok = g.plain_gemm ? (g.K % 64 == 0)
                                            : (g.divh == 1 && g.divw == 1 && g.IC % 64 == 0 && !g.chunk_gather &&
                                               g.M % (static_cast<int64_t>(g.OH) * g.OW) == 0);
-        a.use_buf = (env_int("TWN_BUFLOAD", 1) != 0 && shape_ok && xb > 0 && xb < (1LL << 31) && wb < (1LL << 31)) ? 1 : 0;
+        a.use_buf = (env_int(Env::BUFLOAD, 1) != 0 && shape_ok && xb > 0 && xb < (1LL << 31) && wb < (1LL << 31)) ? 1 : 0;
         a.x_bytes = static_cast<uint32_t>(xb < (1LL << 31) ? xb : 0);
         a.w_bytes = static_cast<uint32_t>(wb < (1LL << 31) ? wb : 0);
     }

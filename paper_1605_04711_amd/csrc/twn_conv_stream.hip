@@ -565,7 +565,7 @@ int32_t launch_stream_kernel(const StreamArgs& a, hipStream_t st) {
     });
     if (per_cu <= 0) return TWN_ERR_HIP;
     int occ = per_cu;
-    const int cap = env_int("TWN_STREAM_OCC", 0);
+    const int cap = env_int(Env::STREAM_OCC, 0);
     if (cap > 0 && cap < occ) occ = cap;
     int64_t grid = static_cast<int64_t>(num_cus(st)) * occ;
     if (grid > a.tiles) grid = a.tiles;
@@ -601,16 +601,16 @@ int32_t launch_stream_tile(const GatherGemm& g, hipStream_t st) {
 int32_t launch_conv_stream(const GatherGemm& g, int tile, hipStream_t st) {
     // K groups: layers whose 64x128 tiles do not even give every CU one workgroup (few pixels, deep K) run two
     // groups of four waves per tile (ResNet-18 stage 4: 31 -> 24 us); TWN_STREAM_KS overrides for experiments
-    int ks = env_int("TWN_STREAM_KS", 0);
+    int ks = env_int(Env::STREAM_KS, 0);
     // Load waves (conv_stream_pc_kernel): four of them next to the four compute waves.  They pay off where a
     // workgroup has few tiles and a deep K (ResNet-18 stages 3 and 4: 22 -> 19.5 us and 24 -> 20.7 us per 3x3
     // layer), and replace the K groups there; with 128x256 tiles one workgroup of 4 + 4 waves per CU does what two
     // workgroups of four waves did (VGG-16 conv5-7: 5-8 % faster); 128x64 tiles (64 output channels) gain nothing.
     // TWN_STREAM_PC: 0 = never, 2 / 4 = that many load waves wherever a build exists, unset = this rule.
-    int np = env_int("TWN_STREAM_PC", -1);
+    int np = env_int(Env::STREAM_PC, -1);
     if (np < 0) np = (tile == 14 || tile == 15 || tile == 17) ? 4 : 0;
     if (np > 0) {
-        const int32_t rc = launch_conv_stream_pc(g, tile, ks == 0 ? 1 : ks, np, env_int("TWN_STREAM_PC_STAGES", 4), st);
+        const int32_t rc = launch_conv_stream_pc(g, tile, ks == 0 ? 1 : ks, np, env_int(Env::STREAM_PC_STAGES, 4), st);
         if (rc != TWN_ERR_UNSUPPORTED) return rc;
     }
     if (ks == 0) {

@@ -532,7 +532,7 @@ int32_t launch_pc_kernel(const StreamPcArgs& a, hipStream_t st) {
     });
     if (per_cu <= 0) return TWN_ERR_HIP;
     int occ = per_cu;
-    const int cap = env_int("TWN_STREAM_OCC", 0);
+    const int cap = env_int(Env::STREAM_OCC, 0);
     if (cap > 0 && cap < occ) occ = cap;
     int64_t grid = static_cast<int64_t>(pc_num_cus()) * occ;
     if (grid > a.tiles) grid = a.tiles;

@@ -690,7 +690,7 @@ static int32_t ternarize_check(const float* W, const twn_weight_desc* wd, int32_
 // the parameter update that leaves pass-1 sums behind uses the same partition.
 static int pass1_blocks(int64_t n) {
     const int64_t nchunks = (n + kChunk - 1) / kChunk;
-    int want = env_int("TWN_TERN_BLOCKS", 512);
+    int want = env_int(Env::TERN_BLOCKS, 512);
     if (want < 1) want = 1;
     if (want > kMaxBlocks) want = kMaxBlocks;
     return static_cast<int>(nchunks < want ? nchunks : want);
@@ -724,7 +724,7 @@ static int32_t ternarize_impl(const float* W, const twn_weight_desc* wd, int32_t
         // writes both from one read of W instead of a second, gathering pass
         const bool flat = (RS == 1) && (K % 128 == 0) && !(packed_T && tile_ok(wd->rows, wd->C, 1));
         if (flat) {
-            const int reverse = env_int("TWN_TERN_REVERSE", 1);
+            const int reverse = env_int(Env::TERN_REVERSE, 1);
             mask_pack_flat_kernel<<<nb, kTernThreads, 0, st>>>(W, n, ws, nb, delta_factor, packed, reverse);
             finalize_kernel<<<1, kTernThreads, 0, st>>>(ws, nb, nb, delta_factor, n, delta, alpha, nnz);
             if (packed_T) {

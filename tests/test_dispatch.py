@@ -3,7 +3,7 @@ ends of the ranges that the dispatch rules accept."""
 
 import pytest
 
-from launches import conv, launches
+from launches import conv, gemm, launches
 
 
 def kernels(answer):
@@ -26,3 +26,11 @@ def test_pair_shares_a_launch_only_if_independent(first, second):
                  dict(base, ptr={"Y": x + 4096}), dict(base, ptr={"Y1": x})]
     answers = launches(independent + dependent)
     assert [len(kernels(a)) for a in answers] == [1] * len(independent) + [2] * len(dependent)
+
+
+def test_an_override_has_one_value_until_it_is_reloaded():
+    # set after the workspace query has asked for it: the launch, which asks at another place, still has it unset
+    late = dict(fn="gemm", d=gemm(8192, 4096, 4096), env_late={"TWN_TILE": 4})
+    set_, unset, late = launches([dict(late, env=late["env_late"], env_late={}), dict(late, env_late={}), late])
+    assert kernels(set_) == ["gather_gemm_mfma_kernel"]
+    assert kernels(late) == kernels(unset) == ["conv_stream_pc_kernel"]
