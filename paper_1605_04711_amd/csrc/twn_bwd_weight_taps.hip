@@ -435,7 +435,11 @@ int b_read_passes(const WgTapsPlan& p, const PixelBits& m) {
 static WgTapsPlan make_taps_plan(const WgShape& w) {
     WgTapsPlan best{};
     best.use = 0;
-    if (w.sh != 1 || w.sw != 1 || w.R * w.S < 4 || w.R * w.S > kTapsMax || w.C % 8 != 0 || w.O % 8 != 0 || env_int(Env::WG_TAPS, 1) == 0) return best;
+    if (w.sh != 1 || w.sw != 1 || w.R * w.S < 4 || w.R * w.S > kTapsMax || w.C % 8 != 0 || w.O % 8 != 0) return best;
+    // an override that shapes the general kernel means multi-tap filters too
+    if (env_int(Env::WG_TAPS, 1) == 0 || env_int(Env::BUFLOAD, 1) == 0 || env_set(Env::WG_BLOCKS) || env_set(Env::WG_KS) ||
+        env_set(Env::WG_ROWS_SPLITS) || env_set(Env::WG_XCD))
+        return best;
     // small filter banks over few pixels: the fixed part (first loads, the sum over slices, the final pass: 12 us) is more than
     // the general kernel's whole time (25088 pixels, 64 x 64 channels: 18.2 against 16.1 us; 6272 pixels, 128 x 128: 17.4
     // against 25.6; 200704 pixels, 64 x 64: 33.5 against 39.4)

@@ -43,10 +43,14 @@ enum class Env : int {
 extern std::atomic<uint64_t> g_env[static_cast<int>(Env::kCount)];      // generation << 33 | is set << 32 | value
 extern std::atomic<uint32_t> g_env_generation;      // starts at 1
 uint64_t env_read(Env name, uint32_t generation);
-inline int env_int(Env name, int fallback) {
+inline uint64_t env_value(Env name) {
     const uint32_t gen = g_env_generation.load(std::memory_order_relaxed);
-    uint64_t v = g_env[static_cast<int>(name)].load(std::memory_order_relaxed);
-    if ((v >> 33) != gen) v = env_read(name, gen);
+    const uint64_t v = g_env[static_cast<int>(name)].load(std::memory_order_relaxed);
+    return (v >> 33) == gen ? v : env_read(name, gen);
+}
+inline bool env_set(Env name) { return (env_value(name) >> 32) & 1u; }
+inline int env_int(Env name, int fallback) {
+    const uint64_t v = env_value(name);
     return ((v >> 32) & 1u) ? static_cast<int>(static_cast<uint32_t>(v)) : fallback;
 }
 

@@ -508,7 +508,8 @@ extern "C" int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_d
     if (rc == TWN_OK) rc = build_pair_problem(d1, X, weights1, alpha1, ep1, Y1, &g[1]);
     if (rc != TWN_OK) return rc;
     hipStream_t st = as_stream(stream);
-    const bool together = pair_independent(g);
+    const int pair_knob = env_int(Env::FWD_PAIR, 1);          // 0: never one launch, 2: whenever the tiles agree
+    const bool together = pair_knob != 0 && pair_independent(g);
     const int small = together ? conv_small_tile(g, 2) : 0;
     if (small != 0) return launch_conv_small(g, 2, small, st);
     const int t0 = gather_gemm_dma_tile(g[0], true), t1 = gather_gemm_dma_tile(g[1], true);
@@ -516,12 +517,12 @@ extern "C" int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_d
     // waves win back more than the saved launch (ResNet-18 b64 block heads, two launches -> one: 128 filters, K = 576:
     // 23.4 -> 19.1 us; 256 filters, K = 1152: 17.9 -> 15.9 us; 512 filters, K = 2304: 18.2 -> 19.3 us).
     const int64_t kmax = g[0].K > g[1].K ? g[0].K : g[1].K;
-    const int pair_knob = env_int(Env::FWD_PAIR, 1);          // 0: never one launch, 2: whenever the tiles agree
-    if (together && t0 != 0 && t0 == t1 && (pair_knob == 2 || (pair_knob == 1 && kmax <= 1536))) {
+    if (together && t0 != 0 && t0 == t1 && (pair_knob == 2 || kmax <= 1536)) {
         rc = launch_gather_gemm_dma_batch(g, 2, t0, st);
         if (rc != TWN_ERR_UNSUPPORTED) return rc;
     }
-    // dependent problems, different tile shapes (or no build for the pair): one after the other, as two twn_conv2d_fwd calls without a workspace
+    // dependent problems, different tile shapes or no build for the pair: one after the other, as two twn_conv2d_fwd calls
+    // without a workspace
     rc = dispatch(g[0], d0->variant, nullptr, 0, st, false);
     if (rc != TWN_OK) return rc;
     return dispatch(g[1], d1->variant, nullptr, 0, st, false);

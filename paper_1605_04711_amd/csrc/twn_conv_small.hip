@@ -423,7 +423,11 @@ int32_t launch_small_tile(const GatherGemm* gs, int count, hipStream_t st) {
 // workgroup per tile is too few for the loads: K ranges over several workgroups win (64, 64, 32768: 15.2 against 22.8;
 // 128, 128, 16384: 13.2 against 13.0).
 int conv_small_tile(const GatherGemm* gs, int count) {
-    if (count < 1 || count > kProblemsMax || env_int(Env::TILE, 0) != 0 || env_int(Env::SMALL, 1) == 0) return 0;
+    if (count < 1 || count > kProblemsMax || env_int(Env::SMALL, 1) == 0) return 0;
+    // an override that names or shapes another kernel means problems of every size
+    if (env_int(Env::TILE, 0) != 0 || env_int(Env::STREAM, 1) == 0 || env_int(Env::BUFLOAD, 1) == 0 || env_set(Env::STREAM_KS) ||
+        env_set(Env::STREAM_PC) || env_set(Env::STREAM_PC_STAGES) || env_set(Env::STREAM_OCC))
+        return 0;
     int64_t t11 = 0, t12 = 0;
     bool persistent = true;
     int kt = 0;

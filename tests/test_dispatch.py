@@ -34,3 +34,33 @@ def test_an_override_has_one_value_until_it_is_reloaded():
     set_, unset, late = launches([dict(late, env=late["env_late"], env_late={}), dict(late, env_late={}), late])
     assert kernels(set_) == ["gather_gemm_mfma_kernel"]
     assert kernels(late) == kernels(unset) == ["conv_stream_pc_kernel"]
+
+
+SMALL = [dict(fn="gemm", d=gemm(64, 1000, 512)), dict(fn="conv", d=conv(1, 14, 14, 256, 512, 3, 2)),
+         dict(fn="bwd", d=conv(6, 38, 36, 32, 64, 3, 2), parts="dx"), dict(fn="bwd", d=conv(8, 12, 12, 128, 64, 3), parts="dw")]
+
+
+@pytest.mark.parametrize("name,value,wanted", [
+    ("TWN_STREAM", 0, ["gather_gemm_dma_kernel", "gather_gemm_dma_kernel", "gather_gemm_dma_batch_kernel", None]),
+    ("TWN_BUFLOAD", 0, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", "gather_gemm_dma_batch_kernel", "weight_grad_patch_kernel"]),
+    ("TWN_STREAM_PC", 0, ["conv_stream_kernel", "gather_gemm_dma_kernel", None, None]),
+    ("TWN_STREAM_PC_STAGES", 4, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", None, None]),
+    ("TWN_STREAM_KS", 2, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", None, None]),
+    ("TWN_STREAM_OCC", 1, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", None, None]),
+    ("TWN_WG_KS", 1, [None, None, None, "weight_grad_patch_kernel"]),
+    ("TWN_WG_BLOCKS", 256, [None, None, None, "weight_grad_patch_kernel"]),
+    ("TWN_WG_XCD", 0, [None, None, None, "weight_grad_patch_kernel"]),
+    ("TWN_WG_ROWS_SPLITS", 4, [None, None, None, "weight_grad_patch_kernel"])])
+def test_overrides_of_other_kernels_reach_small_problems(name, value, wanted):
+    for kernel, a in zip(wanted, launches([dict(c, env={name: value}) for c in SMALL])):
+        if kernel is not None:
+            assert kernel in kernels(a)
+            assert "conv_small_kernel" not in kernels(a) and "weight_grad_taps_kernel" not in kernels(a)
+        if name == "TWN_BUFLOAD":           # the template argument BUF
+            at = {"gather_gemm_dma_kernel": 7, "gather_gemm_dma_batch_kernel": 5, "weight_grad_patch_kernel": 1}
+            assert all(l["args"][at[l["kernel"]]] == "false" for l in a["launches"] if l["kernel"] in at)
+
+
+def test_pair_override_never_one_launch():
+    for a in launches([dict(fn="pair", d=first, d1=second, env={"TWN_FWD_PAIR": 0}) for first, second in HEADS]):
+        assert len(kernels(a)) == 2
