@@ -482,15 +482,16 @@ __device__ __forceinline__ void class_codes_body(const DxPrep& p, int64_t block)
 }
 
 // The first scale_blocks workgroups scale dY, the next code_blocks gather codes, the rest clear dX: the parts are
-// independent, and a launch costs more than any of the small ones.
+// independent, and a launch costs more than any of the small ones.  `first` is the number of the launch's first workgroup.
 template <bool VEC>
-__global__ __launch_bounds__(256) void dx_prep_kernel(const DxPrep p, unsigned scale_blocks, unsigned code_blocks) {
-    if (blockIdx.x < scale_blocks) {
-        scale_body<VEC>(p, blockIdx.x);
-    } else if (blockIdx.x < scale_blocks + code_blocks) {
-        class_codes_body(p, blockIdx.x - scale_blocks);
+__global__ __launch_bounds__(256) void dx_prep_kernel(const DxPrep p, int64_t first, int64_t scale_blocks, int64_t code_blocks) {
+    const int64_t block = first + blockIdx.x;
+    if (block < scale_blocks) {
+        scale_body<VEC>(p, block);
+    } else if (block < scale_blocks + code_blocks) {
+        class_codes_body(p, block - scale_blocks);
     } else {
-        const int64_t id = static_cast<int64_t>(blockIdx.x - scale_blocks - code_blocks) * 256 + threadIdx.x;
+        const int64_t id = (block - scale_blocks - code_blocks) * 256 + threadIdx.x;
         if (id < p.zero16) static_cast<u32x4*>(p.zero)[id] = u32x4{0u, 0u, 0u, 0u};
     }
 }
@@ -500,10 +501,18 @@ int32_t launch_dx_prep(const DxPrep& p, hipStream_t st) {
     const int64_t scale_n = p.scaled ? (vec ? p.pixels * (p.O / 8) : p.pixels * p.O) : 0;
     const int64_t code_n = p.codes ? p.tb.first_word[p.tb.count] : 0;
     const int64_t sb = (scale_n + 255) / 256, cb = (code_n + 255) / 256, zb = p.zero ? (p.zero16 + 255) / 256 : 0;
-    if (sb + cb + zb <= 0 || sb + cb + zb >= (1LL << 31)) return TWN_ERR_SHAPE;
+    const int64_t blocks = sb + cb + zb;
+    if (blocks <= 0) return TWN_ERR_SHAPE;
     auto k = vec ? dx_prep_kernel<true> : dx_prep_kernel<false>;
-    k<<<static_cast<unsigned>(sb + cb + zb), 256, 0, st>>>(p, static_cast<unsigned>(sb), static_cast<unsigned>(cb));
-    return launch_status();
+    // a grid has fewer than 2^32 threads
+    constexpr int64_t kBlocksMax = 1 << 23;
+    for (int64_t first = 0; first < blocks; first += kBlocksMax) {
+        const int64_t n = blocks - first < kBlocksMax ? blocks - first : kBlocksMax;
+        k<<<static_cast<unsigned>(n), 256, 0, st>>>(p, first, sb, cb);
+        const int32_t rc = launch_status();
+        if (rc != TWN_OK) return rc;
+    }
+    return TWN_OK;
 }
 
 int32_t launch_pad_c4(const uint16_t* X, int N, int H, int W, int C, int ph, int pw, int Hp, int Wp,

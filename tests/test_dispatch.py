@@ -64,3 +64,13 @@ def test_overrides_of_other_kernels_reach_small_problems(name, value, wanted):
 def test_pair_override_never_one_launch():
     for a in launches([dict(fn="pair", d=first, d1=second, env={"TWN_FWD_PAIR": 0}) for first, second in HEADS]):
         assert len(kernels(a)) == 2
+
+
+@pytest.mark.parametrize("d", [conv(1, 1, 1, 1 << 15, 1 << 20, 1, groups=2),            # 2^32 words of repeated codes
+                               conv(32, 512, 512, 4096, 64, 1, 2)])                    # 2^32 chunks of dX to clear
+def test_preparation_of_dx_stays_below_the_largest_grid(d):
+    (a,) = launches([dict(fn="bwd", d=d, parts="dx")])
+    prep = [l for l in a["launches"] if l["kernel"] == "dx_prep_kernel"]
+    assert a["rc"] == 0 and len(prep) > 1
+    assert all(l["grid"][0] * l["block"][0] < 1 << 32 for l in prep)
+    assert sum(l["grid"][0] for l in prep) >= 1 << 24
