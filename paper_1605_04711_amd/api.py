@@ -109,6 +109,12 @@ def lib():
         L.twn_unpack_i8.argtypes = [vp, i32, i64, vp, vp]
         L.twn_reload_env.restype = None
         L.twn_reload_env.argtypes = []
+        reload_overrides = L.twn_reload_env
+
+        def reload_overrides_and_plans():
+            reload_overrides()
+            _Plan.kept.clear()      # workspace sizes may depend on the overrides
+        L.twn_reload_env = reload_overrides_and_plans
         L.twn_packed1_words_per_row.restype = i64
         L.twn_packed1_words_per_row.argtypes = [i64]
         L.twn_binarize_workspace_bytes.restype = sz
@@ -253,7 +259,6 @@ def twn_ternarize(W, delta_factor=0.7, groups=1, transposed=False, out=None, wor
 def reload_env():
     """Have the library read its TWN_* tuning overrides again (they are read once and remembered)."""
     lib().twn_reload_env()
-    _Plan.kept.clear()      # workspace sizes may depend on the overrides
 
 
 @dataclass

@@ -157,3 +157,11 @@ def test_output_and_residual_alignment_is_validated():
     c2 = api.ConvDesc(1, 8, 8, 16, 30, 3, 3, 1, 1, 1, 1, 1, 1, api.TWN_BF16, api.TWN_BF16, api.TWN_VAR_BF16_POSTSCALE, 1)
     assert L.twn_conv2d_bwd_ste(ctypes.byref(c2), None, FAKE, FAKE, FAKE, None, None, None, ctypes.c_float(0.0),
                                 None, 0, None) != -3
+
+
+def test_reading_the_overrides_again_drops_the_kept_plans():
+    # a plan holds a workspace size that an override may change, whichever way the library is told to read them again
+    for reload_env in (api.reload_env, lambda: api.lib().twn_reload_env()):
+        api._plan(("kept",), lambda: api._Plan(b"", lambda desc: 0))
+        reload_env()
+        assert not api._Plan.kept
