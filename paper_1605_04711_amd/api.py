@@ -444,7 +444,7 @@ def twn_gemm_fwd(X, tw, y_dtype=torch.bfloat16, variant=None, scale=None, shift=
     Y = out if out is not None else torch.empty_strided(plan.shape, plan.strides, dtype=y_dtype, device=X.device)
     if workspace is None and plan.need:
         workspace = _workspace(plan.need, X.device, stream)
-    rc = L.twn_gemm_fwd(plan.desc, X.data_ptr(), tw.weights_for(variant).data_ptr(), tw.alpha.data_ptr(),
+    rc = L.twn_gemm_fwd(plan.desc, X.data_ptr(), _ptr(tw.weights_for(variant)), _ptr(tw.alpha),
                         _epilogue(scale, shift, residual, relu), Y.data_ptr(), _ptr(workspace),
                         0 if workspace is None else workspace.numel(), _stream(stream))
     if rc != 0:
@@ -494,7 +494,7 @@ def twn_conv2d_fwd(X, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1), y_dtype=torch.b
     Y = out if out is not None else torch.empty_strided(plan.shape, plan.strides, dtype=y_dtype, device=X.device)
     if workspace is None and plan.need:
         workspace = _workspace(plan.need, X.device, stream)
-    rc = L.twn_conv2d_fwd(plan.desc, X.data_ptr(), tw.weights_for(variant).data_ptr(), tw.alpha.data_ptr(),
+    rc = L.twn_conv2d_fwd(plan.desc, X.data_ptr(), _ptr(tw.weights_for(variant)), _ptr(tw.alpha),
                           _epilogue(scale, shift, residual, relu), Y.data_ptr(), _ptr(workspace),
                           0 if workspace is None else workspace.numel(), _stream(stream))
     if rc != 0:
@@ -528,7 +528,7 @@ def twn_conv2d_bwd_ste(X, dY, tw, stride=(1, 1), pad=(0, 0), dil=(1, 1), need_dx
                                         L.twn_conv2d_bwd_ste_workspace_bytes))
     if workspace is None:
         workspace = _workspace(plan.need, dev, stream)
-    rc = L.twn_conv2d_bwd_ste(plan.desc, _ptr(X), dY.data_ptr(), _ptr(tw.packed_T), tw.alpha.data_ptr(),
+    rc = L.twn_conv2d_bwd_ste(plan.desc, _ptr(X), dY.data_ptr(), _ptr(tw.packed_T), _ptr(tw.alpha),
                               _ptr(dX) if need_dx else None, _ptr(dW) if need_dw else None, _ptr(dbias),
                               1.0 if accumulate else 0.0, workspace.data_ptr(), workspace.numel(), _stream(stream))
     if rc != 0:

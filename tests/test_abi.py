@@ -165,3 +165,25 @@ def test_reading_the_overrides_again_drops_the_kept_plans():
         api._plan(("kept",), lambda: api._Plan(b"", lambda desc: 0))
         reload_env()
         assert not api._Plan.kept
+
+
+def test_missing_tensors_reach_the_library_as_null():
+    # a weight gradient needs neither codes nor alpha; a forward call without them is refused by the library
+    import torch
+
+    class Stream:
+        cuda_stream = 0
+
+    tw = api.TernaryWeights(8, 16, 3, 3, 1, None, None, None, None, None)
+    x, dy = torch.zeros((2, 6, 6, 16), dtype=torch.bfloat16), torch.zeros((2, 6, 6, 8), dtype=torch.bfloat16)
+    small = torch.empty(16, dtype=torch.uint8)
+    with pytest.raises(api.TwnError) as e:
+        api.twn_conv2d_bwd_ste(x, dy, tw, pad=(1, 1), need_dx=False, workspace=small, stream=Stream)
+    assert e.value.status == -5
+    with pytest.raises(api.TwnError) as e:
+        api.twn_conv2d_fwd(x, tw, pad=(1, 1), workspace=small, stream=Stream)
+    assert e.value.status == -1
+    with pytest.raises(api.TwnError) as e:
+        api.twn_gemm_fwd(x.reshape(8, 144), api.TernaryWeights(8, 144, 1, 1, 1, None, None, None, None, None), workspace=small,
+                         stream=Stream)
+    assert e.value.status == -1
