@@ -489,7 +489,8 @@ static WgTapsPlan make_taps_plan(const WgShape& w) {
         }
     if (!best.use) return best;
     best.stage_bytes = 4096 + best.nb * 2048;
-    best.depth = kSlices * 4 * best.stage_bytes <= kSmemMax ? 4 : 3;
+    best.depth = best.nb == 3 ? 4 : 3;          // what 160 KB of LDS hold
+    static_assert(kSlices * 4 * (4096 + 3 * 2048) <= kSmemMax && kSlices * 3 * (4096 + 4 * 2048) <= kSmemMax, "stages fit");
     best.tiles_o = (w.O + 63) / 64;
     best.tiles_c = (w.C + 16 * kWC - 1) / (16 * kWC);
     best.groups = (w.R * w.S + kTapsPer - 1) / kTapsPer;
@@ -577,7 +578,7 @@ int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipSt
     }
     a.aligned_out = aligned(w.dW, 16) && aligned(w.partial, 16);
     int32_t rc;
-    if (pl.nb == 3) rc = pl.depth == 4 ? launch_taps<3, 4>(a, st) : launch_taps<3, 3>(a, st);
+    if (pl.nb == 3) rc = launch_taps<3, 4>(a, st);
     else if (pl.nb == 4) rc = launch_taps<4, 3>(a, st);
     else return TWN_ERR_UNSUPPORTED;
     if (rc != TWN_OK || pl.splits == 1) return rc;

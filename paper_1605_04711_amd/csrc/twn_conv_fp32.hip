@@ -322,9 +322,8 @@ static Fp32Plan fp32_plan(const GatherGemm& g) {
     const int64_t tn = (tn1 + p.nt - 1) / p.nt;
     p.tiles = tm * tn;
     p.tiles_n = static_cast<int32_t>(tn);
-    const int nw_max = 16 / p.nt;
-    while (p.nw < nw_max && p.tiles * p.nw < 1536 && nkb >= 4 * p.nw && (p.nw < 8 || p.tiles <= 64)) p.nw *= 2;
-    if (p.nw == nw_max && nkb > 32 * p.nw && env_int(Env::F32_SPLITK, 1) != 0) {
+    while (p.nw < 16 && p.tiles * p.nw < 1536 && nkb >= 4 * p.nw && (p.nw < 8 || p.tiles <= 64)) p.nw *= 2;
+    if (p.nw == 16 && nkb > 32 * p.nw && env_int(Env::F32_SPLITK, 1) != 0) {
         int64_t want = 2048 / (p.tiles * p.nw);
         if (want > nkb / (8 * p.nw)) want = nkb / (8 * p.nw);
         if (want > 16) want = 16;
@@ -367,10 +366,9 @@ int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st) {
         case 64 + 1: launch_f64<2, 1>(a, mode, st); break;
         case 64 + 2: launch_f64<2, 2>(a, mode, st); break;
         case 64 + 4: launch_f64<2, 4>(a, mode, st); break;
-        case 64 + 8: launch_f64<2, 8>(a, mode, st); break;
         case 128 + 1: launch_f64<4, 1>(a, mode, st); break;
         case 128 + 2: launch_f64<4, 2>(a, mode, st); break;
-        default: launch_f64<4, 4>(a, mode, st); break;
+        default: return TWN_ERR_UNSUPPORTED;
     }
     if (g.splits > 1) {
         const int64_t total = g.M * g.NC;

@@ -1,9 +1,11 @@
 """Which kernels the calls of the C ABI launch, on the CPU (see `launches`): dependent problems, the overrides, and the
 ends of the ranges that the dispatch rules accept."""
 
+import random
+
 import pytest
 
-from launches import conv, gemm, launches
+from launches import F32, conv, gemm, launches
 
 
 def kernels(answer):
@@ -74,3 +76,22 @@ def test_preparation_of_dx_stays_below_the_largest_grid(d):
     assert a["rc"] == 0 and len(prep) > 1
     assert all(l["grid"][0] * l["block"][0] < 1 << 32 for l in prep)
     assert sum(l["grid"][0] for l in prep) >= 1 << 24
+
+
+def _log(rng, lo, hi):
+    return int(round(lo * (hi / lo) ** rng.random()))
+
+
+def test_every_plan_has_a_build():
+    rng = random.Random(3)
+    f32 = [dict(fn="gemm", d=gemm(_log(rng, 1, 1 << 20), _log(rng, 1, 4096), _log(rng, 1, 20000), x=F32, y=F32)) for _ in range(400)]
+    f32.append(dict(fn="gemm", d=gemm(1024, 1024, 1024, x=F32, y=F32)))
+    dw = [dict(fn="bwd", d=conv(_log(rng, 1, 200), _log(rng, 7, 120), _log(rng, 7, 120), 8 * _log(rng, 1, 64), 8 * _log(rng, 8, 64),
+                                rng.choice([2, 3, 5, 7]), dil=rng.choice([1, 1, 2])), parts="dw") for _ in range(400)]
+    dw = [c for c in dw if c["d"]["H"] * c["d"]["W"] * c["d"]["N"] < 1 << 20]
+    builds = set()
+    for a in launches(f32 + dw):
+        builds.update((k, tuple(l["args"][:2])) for k, l in zip(kernels(a), a["launches"]))
+    assert {b[1] for b in builds if b[0] == "gather_gemm_f64_kernel"} == {
+        ("1", "1"), ("1", "2"), ("1", "4"), ("1", "8"), ("1", "16"), ("2", "1"), ("2", "2"), ("2", "4"), ("4", "1"), ("4", "2")}
+    assert {b[1] for b in builds if b[0] == "weight_grad_taps_kernel"} == {("3", "4"), ("4", "3")}
