@@ -32,3 +32,12 @@ def knob(monkeypatch):
     yield set_knob
     monkeypatch.undo()
     api.reload_env()
+
+
+@pytest.fixture(params=["dispatch", "large-problem kernels"])
+def both_dispatches(request, knob):
+    """The test once as the library dispatches it, and once without the kernels for problems of few tiles and for multi-tap
+    weight gradients, which take nearly every shape of test size: then the kernels that large problems run are tested."""
+    if request.param != "dispatch":
+        knob("TWN_SMALL", 0)
+        knob("TWN_WG_TAPS", 0)

@@ -1,11 +1,12 @@
-"""Which kernels the calls of the C ABI launch, on the CPU (see `launches`): dependent problems, the overrides, and the
-ends of the ranges that the dispatch rules accept."""
+"""Which kernels the calls of the C ABI launch, on the CPU (see `launches`): dependent problems, the overrides, the
+ends of the ranges that the dispatch rules accept, and whether the GPU tests of a path have shapes that take it."""
 
 import random
 
 import pytest
 
-from launches import F32, conv, gemm, launches
+import test_gpu_conv as shapes
+from launches import BF16, F32, conv, gemm, launches
 
 
 def kernels(answer):
@@ -95,3 +96,69 @@ def test_every_plan_has_a_build():
     assert {b[1] for b in builds if b[0] == "gather_gemm_f64_kernel"} == {
         ("1", "1"), ("1", "2"), ("1", "4"), ("1", "8"), ("1", "16"), ("2", "1"), ("2", "2"), ("2", "4"), ("4", "1"), ("4", "2")}
     assert {b[1] for b in builds if b[0] == "weight_grad_taps_kernel"} == {("3", "4"), ("4", "3")}
+
+
+def _conv_case(case, **kw):
+    n, h, w, c, o, r, s, st, pd, dl = case
+    return dict(conv(n, h, w, c, o, r, groups=kw.pop("groups", 1), **kw), S=s, stride_h=st[0], stride_w=st[1], pad_h=pd[0],
+                pad_w=pd[1], dil_h=dl[0], dil_w=dl[1])
+
+
+@pytest.mark.parametrize("y", [F32, BF16])
+def test_split_k_tests_split(y):
+    calls = [dict(fn="gemm", d=gemm(m, n, k, y=y), env={"TWN_SMALL": small}) for m, n, k, small in shapes.SPLITK_GEMM_CASES]
+    assert all("splitk_finish_kernel" in kernels(a) for a in launches(calls))
+    ds = [(conv(n, h, w, c, o, 3, groups=g, y=y), small) for n, h, w, c, o, g, small in shapes.SPLITK_CONV_CASES]
+    fwd = launches([dict(fn="conv", d=d, env={"TWN_SMALL": small}) for d, small in ds])
+    dx = launches([dict(fn="bwd", d=d, parts="dx", env={"TWN_SMALL": small}) for d, small in ds])
+    assert ["splitk_finish_kernel" in kernels(a) for a in fwd] == [True, False, False, True, False]
+    assert ["splitk_finish_kernel" in kernels(a) for a in dx] == [False, True, True, False, True]
+
+
+def test_float32_split_k_tests_split():
+    for split in (1, 0):
+        env = {"TWN_F32_SPLITK": split}
+        got = launches([dict(fn="gemm", d=gemm(m, n, k, x=F32, y=F32), env=env) for m, n, k in shapes.F32_SPLIT_CASES])
+        got += launches([dict(fn="conv", d=conv(*xs, ws[0], ws[2], pad=pad, x=F32, y=F32), env=env) for xs, ws, pad in shapes.F32_CONV_CASES])
+        cut = [m * n < 1 << 13 and k > 8192 for m, n, k in shapes.F32_SPLIT_CASES] + [False, True]
+        assert ["fp32_splitk_finish_kernel" in kernels(a) for a in got] == [c and split == 1 for c in cut]
+
+
+def test_pair_tests_run_one_launch_of_each_kernel():
+    heads = [(conv(*xs, o0, 3, 2), conv(*xs, o1, 1, 2)) for xs, o0, o1 in shapes.PAIR_CASES]
+    for small, one, wanted in ((1, 2, [["conv_small_kernel"]] * 4), (0, 2, [["gather_gemm_dma_batch_kernel"]] * 3 + [None]),
+                               (1, 0, [["conv_small_kernel"] * 2] * 4), (0, 0, [None] * 4)):
+        env = {"TWN_SMALL": small, "TWN_FWD_PAIR": one}
+        for a, w in zip(launches([dict(fn="pair", d=d, d1=d1, env=env) for d, d1 in heads]), wanted):
+            assert kernels(a) == w if w else len(kernels(a)) == 2 and "conv_small_kernel" not in kernels(a)
+
+
+def test_residue_class_tests_run_one_launch_and_one_each():
+    calls = [dict(fn="bwd", parts="dx", d=_conv_case(case + ((1, 1),), y=F32, groups=case[4] if per_filter else 1))
+             for case in shapes.STRIDED_DX_CASES for per_filter in (0, 1)]
+    for small, kernel in ((1, "conv_small_kernel"), (0, "gather_gemm_dma_batch_kernel")):
+        env = {"TWN_DX_CLASS_MIN_PIXELS": 0, "TWN_SMALL": small}
+        one = [kernels(a) for a in launches([dict(c, env=env) for c in calls])]
+        each = [kernels(a) for a in launches([dict(c, env=dict(env, TWN_DX_CLASS_BATCH=0)) for c in calls])]
+        assert all(k[0] == "dx_prep_kernel" and len(k) == 2 for k in one)
+        several = [i for i, k in enumerate(each) if len(k) > 2]
+        assert len(several) == 16 and all(one[i][1] == kernel for i in several)         # the 1x1 layer has one class
+
+
+def test_weight_gradient_and_pointer_load_tests_take_the_general_kernels():
+    for ks in (1, 2):
+        calls = [dict(fn="bwd", parts="dw", d=_conv_case((4 * shapes.CONV_CASES[ci][0],) + shapes.CONV_CASES[ci][1:]),
+                      env={"TWN_WG_KS": ks}) for ci in (1, 2, 4, 7)]
+        for a in launches(calls):
+            (patch,) = [l for l in a["launches"] if l["kernel"] == "weight_grad_patch_kernel"]
+            assert patch["args"][3] == str(ks)
+    env = {"TWN_BUFLOAD": 0}
+    calls = [dict(fn="gemm", d=gemm(520, 300, 448, y=F32), env=env)]
+    for ci in (1, 2):
+        calls += [dict(fn="conv", d=_conv_case(shapes.CONV_CASES[ci], y=F32), env=env),
+                  dict(fn="bwd", d=_conv_case(shapes.CONV_CASES[ci], y=F32), parts="dx dw", env=env)]
+    buf = {"gather_gemm_dma_kernel": 7, "gather_gemm_dma_batch_kernel": 5, "weight_grad_patch_kernel": 1}
+    for a in launches(calls):
+        loads = [l["args"][buf[l["kernel"]]] for l in a["launches"] if l["kernel"] in buf]
+        assert loads and set(loads) == {"false"}
+        assert not {"conv_small_kernel", "weight_grad_taps_kernel"} & set(kernels(a))

@@ -37,6 +37,7 @@ def make_layer(seed, x_shape, w_shape, bf16=True, groups=1, transposed=False):
 GEMM_CASES = [(300, 200, 320), (257, 130, 64), (1, 10, 1024), (128, 1000, 512), (64, 40, 100), (513, 257, 136)]
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("m,n,k", GEMM_CASES)
 def test_gemm_fwd_bf16(m, n, k):
     x, w, tw, codes, alpha = make_layer(m + n + k, (m, k), (n, k))
@@ -122,6 +123,7 @@ STRIDE1_CASES = [
 ]
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("ci", range(len(STRIDE1_CASES)))
 def test_stride1_multi_tap_layers_forward_and_backward_data(ci):
     n, h, w_, c, o, r, s, pd, dl = STRIDE1_CASES[ci]
@@ -144,6 +146,7 @@ def test_stride1_multi_tap_layers_forward_and_backward_data(ci):
         assert rel_err(to_host_f64(dx), oc.conv2d_bwd_data(dy, codes, alpha, (n, h, w_, c), st, pd, dl)) <= 1e-4
 
 
+@pytest.mark.usefixtures("both_dispatches")
 def test_gemm_epilogue_groups_and_strides():
     m, n, k = 200, 96, 256
     x, w, tw, codes, alpha = make_layer(11, (m, k), (n, k), groups=n)
@@ -228,6 +231,7 @@ def test_conv2d_bwd_data_alpha_at_expansion_variant():
     assert rel_err(to_host_f64(dx), ref) <= BF16_TOL
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("ci", range(len(CONV_CASES)))
 def test_conv2d_fwd_bf16(ci):
     n, h, w_, c, o, r, s, st, pd, dl = CONV_CASES[ci]
@@ -240,6 +244,7 @@ def test_conv2d_fwd_bf16(ci):
     assert rel_err(to_host_f64(yb), ref) <= BF16_TOL
 
 
+@pytest.mark.usefixtures("both_dispatches")
 def test_conv2d_fwd_fused_block_tail():
     n, h, w_, c, o, r, s, st, pd, dl = CONV_CASES[1]
     x, w, tw, codes, alpha = make_layer(7, (n, h, w_, c), (o, c, r, s), groups=o)
@@ -253,14 +258,15 @@ def test_conv2d_fwd_fused_block_tail():
     assert rel_err(to_host_f64(y), oc.epilogue(ref0, scale, shift, res, relu=True)) <= BF16_TOL
 
 
-PAIR_CASES = [   # x shape, O of the 3x3 / stride-2 convolution, O of the 1x1 / stride-2 shortcut
-    ((4, 28, 28, 64), 128, 128),       # same tile shape: one launch; 784 pixels leave a ragged last tile
+PAIR_CASES = [   # x shape, O of the 3x3 / stride-2 convolution, O of the 1x1 / stride-2 shortcut (few tiles: one launch for all)
+    ((4, 28, 28, 64), 128, 128),       # same tile of the large-problem kernels: one launch; 784 pixels leave a ragged last tile
     ((3, 14, 14, 128), 256, 256),
     ((2, 13, 9, 72), 136, 136),        # odd image, C % 64 != 0 (per-lane pointer loads), ragged channel tile
     ((2, 16, 16, 64), 64, 128),        # different tile shapes: one launch after the other
 ]
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("one_launch", [2, 0])
 @pytest.mark.parametrize("ci", range(len(PAIR_CASES)))
 def test_conv2d_fwd_pair(ci, one_launch, knob):
@@ -311,8 +317,9 @@ def test_lenet_layers_fp32(batch):
     assert rel_err(to_host_f64(y), oc.gemm_fwd(x, codes.reshape(layer.O, layer.C), alpha)) <= FP32_TOL
 
 
-F32_SPLIT_CASES = [   # M, N, K: float32 problems with few tiles, so that K is cut into ranges (ragged last range and slab)
+F32_SPLIT_CASES = [   # M, N, K: float32 problems with few tiles: K shared out over the waves of a tile's workgroup, and beyond
     (64, 500, 800), (64, 10, 500), (200, 100, 1000), (33, 48, 130), (96, 130, 2000), (5, 7, 4000),
+    (64, 10, 16400), (5, 7, 40003), (100, 64, 9001), (33, 40, 33007),       # 8192 over workgroups too (ragged last block)
 ]
 
 
@@ -331,15 +338,57 @@ def test_gemm_fwd_fp32_split_k(m, n, k, split, knob):
     assert rel_err(to_host_f64(y), ref) <= FP32_TOL
 
 
-def test_conv2d_fwd_fp32_split_k_on_large_tiles():
-    # 4096 pixels x 64 filters x K = 800: few 64x64 tiles, the reduction is cut into ranges of 32-wide slabs
-    x = wl.uniform01(0, 91, (16, 20, 20, 32))
+F32_CONV_CASES = [((16, 20, 20, 32), (64, 32, 5, 5), 0),       # 4096 pixels x K = 800: four waves share K
+                  ((1, 5, 5, 404), (20, 404, 5, 5), 2)]        # 25 pixels x K = 10100: K over the waves of several workgroups
+
+
+@pytest.mark.parametrize("xs,ws,pad", F32_CONV_CASES)
+def test_conv2d_fwd_fp32_shared_k(xs, ws, pad):
+    x = wl.uniform01(0, 91, xs)
     g = np.random.default_rng(17)
-    w = (g.standard_normal((64, 32, 5, 5)) * 0.05).astype(np.float32)
+    w = (g.standard_normal(ws) * 0.05).astype(np.float32)
     tw = api.twn_ternarize(to_dev_f32(w), F)
     codes, delta, alpha, nnz = ot.ternarize(w, F)
-    y = api.twn_conv2d_fwd(to_dev_f32(x), tw, (1, 1), (0, 0), (1, 1), y_dtype=torch.float32)
-    assert rel_err(to_host_f64(y), oc.conv2d_fwd(x, codes, alpha, (1, 1), (0, 0), (1, 1))) <= FP32_TOL
+    y = api.twn_conv2d_fwd(to_dev_f32(x), tw, (1, 1), (pad, pad), (1, 1), y_dtype=torch.float32)
+    assert rel_err(to_host_f64(y), oc.conv2d_fwd(x, codes, alpha, (1, 1), (pad, pad), (1, 1))) <= FP32_TOL
+
+
+SPLITK_GEMM_CASES = [   # M, N, K, TWN_SMALL: bf16 products whose K is cut into ranges with a finishing launch
+    (64, 64, 32768, 1), (33, 72, 16648, 1), (130, 40, 17000, 1),                     # by the rule: K above 16384
+    (64, 1000, 1024, 0), (40, 72, 1160, 0), (200, 130, 2056, 0), (1, 10, 4096, 0)]   # with the few-tile kernel off
+SPLITK_CONV_CASES = [   # N, H, W, C, O, alpha groups, TWN_SMALL (3x3): forward over 9 C, data gradient over 9 O (twice with groups)
+    (1, 7, 7, 2048, 40, 1, 1), (2, 5, 6, 24, 1864, 1, 1), (1, 6, 6, 16, 1024, 1024, 1), (1, 9, 8, 136, 72, 1, 0), (2, 7, 7, 24, 136, 4, 0)]
+# n additions of float32 round a sum that stays within 4 RMS by 2^-24 * 4 RMS each, with random signs: sqrt(n) * 2^-24 * 4 RMS,
+# n = K / 16 (an MFMA step adds 16 products), against the metric's floor of 1 % of the RMS: 1.1e-3 for K = 32768
+SPLITK_BAR = 1.1e-3
+
+
+@pytest.mark.parametrize("m,n,k,small", SPLITK_GEMM_CASES)
+def test_gemm_fwd_split_k(m, n, k, small, knob):
+    knob("TWN_SMALL", small)
+    x, w, tw, codes, alpha = make_layer(m + n + k, (m, k), (n, k), groups=n if m % 2 == 0 else 1)
+    ref = oc.gemm_fwd(x, codes.reshape(n, k), alpha)
+    assert api.twn_gemm_fwd_workspace_bytes(m, tw) > 0                  # K is cut
+    assert rel_err(to_host_f64(api.twn_gemm_fwd(to_dev_bf16(x), tw, y_dtype=torch.float32)), ref) <= SPLITK_BAR
+    g = np.random.default_rng(k)
+    scale, shift = g.uniform(0.5, 1.5, n).astype(np.float32), g.standard_normal(n).astype(np.float32)
+    res = wl.bf16_round(g.standard_normal((m, n)).astype(np.float32))
+    y = api.twn_gemm_fwd(to_dev_bf16(x), tw, scale=to_dev_f32(scale), shift=to_dev_f32(shift), residual=to_dev_bf16(res), relu=True)
+    assert rel_err(to_host_f64(y), oc.epilogue(ref, scale, shift, res, relu=True)) <= BF16_TOL
+
+
+@pytest.mark.parametrize("n,h,w_,c,o,groups,small", SPLITK_CONV_CASES)
+def test_convolution_split_k(n, h, w_, c, o, groups, small, knob):
+    knob("TWN_SMALL", small)
+    geo = (1, 1), (1, 1), (1, 1)
+    x, w, tw, codes, alpha = make_layer(n + c + o, (n, h, w_, c), (o, c, 3, 3), groups=groups, transposed=True)
+    y = api.twn_conv2d_fwd(to_dev_bf16(x), tw, *geo, y_dtype=torch.float32)
+    ref = oc.conv2d_fwd(x, codes, alpha, *geo)
+    assert rel_err(to_host_f64(y), ref) <= SPLITK_BAR
+    dy = wl.bf16_round(np.random.default_rng(o).standard_normal(ref.shape).astype(np.float32))
+    dx, _, _ = api.twn_conv2d_bwd_ste(None, to_dev_bf16(dy), tw, *geo, need_dw=False, x_shape=x.shape, dx_dtype=torch.float32)
+    # two bf16 terms per value with several alphas: 2^-17 of each, bar of the per-filter tests
+    assert rel_err(to_host_f64(dx), oc.conv2d_bwd_data(dy, codes, alpha, x.shape, *geo)) <= (2e-3 if groups > 1 else SPLITK_BAR)
 
 
 BWD_CASES = list(range(len(CONV_CASES)))      # includes the 7x7 / stride-2 / C = 3 stem shape (index 5)
@@ -361,6 +410,7 @@ def test_weight_grad_wave_groups(ci, ks, knob):
     assert rel_err(to_host_f64(dw), oc.conv2d_bwd_weight(x, dy, codes.shape, st, pd, dl)) <= 1e-4
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("ci", BWD_CASES)
 def test_conv2d_bwd_ste(ci):
     n, h, w_, c, o, r, s, st, pd, dl = CONV_CASES[ci]
@@ -382,6 +432,7 @@ def test_conv2d_bwd_ste(ci):
     assert rel_err(to_host_f64(dw2), 2 * ref_dw) <= 1e-4
 
 
+@pytest.mark.usefixtures("both_dispatches")
 def test_fc_backward_is_the_1x1_case():
     m, k, n = 128, 512, 1000
     x, w, tw, codes, alpha = make_layer(9, (m, 1, 1, k), (n, k, 1, 1), transposed=True)
@@ -590,6 +641,7 @@ def test_per_lane_pointer_load_path(knob):
         assert rel_err(to_host_f64(dw), oc.conv2d_bwd_weight(x, dy, codes.shape, st, pd, dl)) <= 1e-4
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("groups", ["filters", 4])
 def test_conv2d_bwd_data_per_filter_alpha(groups):
     # Alg. 1 with one alpha per filter (or per group of filters): alpha_o sits inside the sum over o, so the
@@ -625,6 +677,7 @@ STRIDED_DX_CASES = [
 ]
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("ci", range(len(STRIDED_DX_CASES)))
 def test_strided_backward_data_by_residue_classes(ci, knob):
     # strided layers run one stride-1 contraction per residue class of the output pixels (forced here for
@@ -652,10 +705,11 @@ def test_strided_backward_data_by_residue_classes(ci, knob):
     assert rel_err(to_host_f64(dxg), ref) <= 1e-4
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("ci", range(len(STRIDED_DX_CASES)))
 def test_strided_backward_data_by_residue_classes_per_filter_alpha(ci, knob):
-    # the residue-class path with one alpha per filter: alpha_o * dY as two bf16 terms, two contraction passes per
-    # class, the second adding onto the first through the output-row remap (bars as in the per-filter test above)
+    # the residue-class path with one alpha per filter: alpha_o * dY as two bf16 terms side by side, one contraction
+    # per class over both through the output-row remap (bars as in the per-filter test above)
     n, h, w_, c, o, r, s, st, pd = STRIDED_DX_CASES[ci]
     dl = (1, 1)
     x, w, tw, codes, alpha = make_layer(720 + ci, (n, h, w_, c), (o, c, r, s), groups=o, transposed=True)
@@ -807,7 +861,7 @@ def test_resident_weight_3x3_kernel_backward_data(ci):
 
 @pytest.mark.parametrize("ci", [0, 3])
 def test_resident_weight_3x3_kernel_backward_data_per_filter_alpha(ci):
-    # one alpha per filter: alpha * dY goes through the kernel as two bf16 terms, the second adding onto the first in place
+    # one alpha per filter: the kernel forms alpha * dY as two bf16 terms on the way into LDS and multiplies both
     n, h, w_, c, pd = C64_CASES[ci]
     st = dl = (1, 1)
     x, w, tw, codes, alpha = make_layer(940 + ci, (n, h, w_, c), (64, c, 3, 3), groups=64, transposed=True)

@@ -38,7 +38,11 @@ def test_dx(n, h, w, c, o, r, stride, pad, groups):
     for dtype, bar in ((torch.float32, 2e-3), (torch.bfloat16, BF16_TOL)):
         dx = torch.full((n, h, w, c), 7.0, dtype=dtype, device="cuda")
         api.twn_conv2d_bwd_ste(None, to_dev_bf16(dy), tw, *geo, need_dw=False, x_shape=(n, h, w, c), dX=dx)
-        assert rel_err(to_host_f64(dx), ref) <= bar
+        got = to_host_f64(dx)
+        assert rel_err(got, ref) <= bar
+    # rounded to bf16 once: 2^-7 / sqrt(12) of the low end of a value's binade, 1.5e-3 of values spread over binades and
+    # 1.66e-3 on these layers; rounding the sum of the high terms first makes it 2.00e-3
+    assert np.linalg.norm(got - ref) <= 1.8e-3 * np.linalg.norm(ref)
 
 
 def test_dx_of_the_longest_reduction():

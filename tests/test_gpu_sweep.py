@@ -1,5 +1,5 @@
 """Seeded random shapes through the specialised forward kernels (first layers with three channels, 3x3 layers
-over 64 channels, two convolutions over one input, the float32 path with K ranges) and random geometries through
+over 64 channels, two convolutions over one input, the float32 path) and random geometries through
 forward, data gradient and weight gradient, against the direct-loop oracle (Eq. 2; Alg. 1 steps 8-10): the fixed
 cases elsewhere pick shapes by hand, these do not."""
 
@@ -71,6 +71,7 @@ def test_random_first_layers(seed):
     assert rel_err(to_host_f64(y), oc.epilogue(ref0, sc, sf, res, relu=relu)) <= BF16_TOL
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("seed", range(10))
 def test_random_block_heads(seed):
     rng = np.random.default_rng(3000 + seed)
@@ -102,6 +103,7 @@ def test_random_float32_products(seed):
     assert rel_err(to_host_f64(y), oc.gemm_fwd(x, codes.reshape(n, k), alpha)) <= FP32_TOL
 
 
+@pytest.mark.usefixtures("both_dispatches")
 @pytest.mark.parametrize("seed", range(20))
 def test_random_geometries_forward_and_backward(seed):
     rng = np.random.default_rng(5000 + seed)
