@@ -17,10 +17,12 @@
 //     over workgroups is a plain element-wise pass.
 // More than nine taps: groups of nine per workgroup (the patch covers the whole filter).
 // Measured against the general kernel (us, with the final pass; stride 1, 3x3): 131072 pixels, 128 -> 128 channels 55 -> 48.6
-// (793 TFLOP/s); 8192, 512 -> 512: 51 -> 43; 6272, 128 -> 128: 25.6 -> 17.4; 392, 512 -> 512: 26 -> 12.  A slab of eight waves
-// takes 2000 clocks of a CU against 1152 of MFMAs: the loads hold their waves for about 100 clocks each, and the two waves
-// of a SIMD run in step.  Starting half of the waves half a slab later, reading fragments four or five taps ahead, and
-// stages private to each wave (no barrier) were all slower or equal.
+// (793 TFLOP/s); 8192, 512 -> 512: 51 -> 43; 6272, 128 -> 128: 25.6 -> 17.4; 392, 512 -> 512: 26 -> 12.  A round of four
+// slabs takes 0.83 us, 2000 clocks, against 1152 of MFMAs on a SIMD (512 -> 512, kernel alone: 8192 pixels, 32 rounds, 41.4 us;
+// 4096 pixels, 16 rounds, 28.0), and about 15 us of a launch do not depend on the rounds; 8.5 where one range writes dW itself
+// (2048 and 512 pixels: 16 and 4 rounds, 22.1 and 11.9 us).  Over the VGG-7 layers the matrix pipe works 0.30 of a launch's
+// nominal clocks and LDS 0.17, 1 % of it lost to bank conflicts.  Starting half of the waves half a slab later, reading
+// fragments four or five taps ahead, and stages private to each wave (no barrier) were all slower or equal.
 #include <mutex>
 
 #include "twn_kernels.h"

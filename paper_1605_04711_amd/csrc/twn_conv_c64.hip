@@ -266,8 +266,8 @@ __global__ __launch_bounds__(256, 2) void conv_c64_kernel(const C64Args a) {
         // Everything this wave has requested so far (patch i+1, the residual values of tile i, the stores of tile
         // i-1) is complete before the registers are used: one full wait instead of counted ones.  Counted waits
         // would rest on requests being answered in issue order also when all lanes of a request fall outside the
-        // tensor and no memory is touched; the full wait needs no such assumption and sits behind a whole MFMA
-        // loop, so it costs nothing measurable with two workgroups per CU.
+        // tensor and no memory is touched (as the counted waits of the other kernels do: see buf_dma16), with stores in
+        // between; the full wait needs no such assumption and sits behind a whole MFMA loop, so it costs nothing measurable with two workgroups per CU.
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         store_patch(smem + (buf ^ 1) * BUF);
         const Tile nn = tile_of(i + 2);

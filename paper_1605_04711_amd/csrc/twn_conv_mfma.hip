@@ -547,14 +547,16 @@ static int gather_mode(const GatherGemm& g) {
 
 int32_t gather_gemm_splits(const GatherGemm& g) {
     if (conv_small_tile(&g, 1) != 0) return 1;
-    // split K when even 64x128 tiles leave half the CUs idle and K is deep enough to share out (few workgroups
-    // with two slabs in flight each are bound by memory latency when their input is not in L2)
+    // What the few-tile kernel leaves: K above 16384 (64 x 64 x 32768: 15.2 us in ranges against 22.8 there), tensors of 2 GiB
+    // and more, and everything small when an override keeps it off that kernel.  K is cut when even 64x128 tiles leave half the
+    // CUs idle and it is deep enough to share out (few workgroups with two slabs in flight each are bound by memory latency
+    // when their input is not in L2).
     if (gather_mode(g) == kModeScalar || env_int(Env::TILE, 0) != 0) return 1;
     const int64_t blocks = ((g.M + 127) / 128) * ((g.NC + 127) / 128);
     const int64_t blocks64 = ((g.M + 63) / 64) * ((g.NC + 127) / 128);
     const int KT = k_slabs(g.K);
-    // below 16 slabs the persistent kernel with K groups inside the workgroup does it in one launch
-    // (ResNet-18 classifier, 64 x 1000 x 512: 11 us in two launches -> 5 us)
+    // below 16 slabs the persistent kernel does it in one launch (64 x 1000 x 512 with the few-tile kernel off: 11 us in two
+    // launches -> 5 us)
     if (blocks64 >= 128 || KT < 16) return 1;
     int64_t splits = (448 + blocks - 1) / blocks;
     if (splits > KT / 4) splits = KT / 4;

@@ -414,7 +414,8 @@ int32_t launch_small_tile(const GatherGemm* gs, int count, hipStream_t st) {
 // other kernels are better or the shapes do not fit.  Measured per dependent launch (us, against the split-K launch pair
 // and the persistent kernels that ran such problems before):
 //   * up to 256 tiles of 32x32: eight waves per tile, one tile per CU (M, N, K = 49, 512, 4608: 10.8 -> 8.1; 784, 128, 1152:
-//     11.6 -> 5.1; 1, 1000, 512: 5.1 -> 3.6).  Two such workgroups do not fit a CU: 392 tiles take 8.7 against 6.3 with
+//     11.6 -> 5.1; 1, 1000, 512: 5.1 -> 3.6).  Two such workgroups do not fit a CU: 1568, 256, 2304, 392 tiles of 32x32 or
+//     196 of 32x64, takes 8.1 with the former and 6.4 with the latter
 //   * up to 256 tiles of 32x64: eight waves (784, 512, 4608: 25.9 -> 10.7).  Above that
 //   * up to 512 tiles of 32x64: four waves, two workgroups per CU (3136, 256, 2304: 26.2 -> 11.7), where the persistent
 //     kernels cannot run (channel counts that are no multiple of 64, float32 outputs, divided taps: 13.8 -> 7.2) or K has

@@ -48,6 +48,9 @@ __device__ __forceinline__ void dma16(const void* gsrc, void* lds_dst) {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, static_cast<int>(bytes), 0x00020000);
 }
+// vmcnt counts such a load whether or not a lane lies inside, and a wave's loads are counted off in the order they were
+// issued: every kernel here that waits for "all but the n youngest" rests on both (padding rows, taps outside the image and
+// slabs past the end are requested like any other), with no other vector memory operation between the loads it counts.
 __device__ __forceinline__ void buf_dma16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voffset, uint32_t soffset, void* lds_dst) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)lds_dst, 16,
                                              static_cast<int>(voffset), static_cast<int>(soffset), 0, 0);
