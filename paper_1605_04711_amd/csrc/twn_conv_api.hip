@@ -669,6 +669,7 @@ extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, con
         w.dW = dW;
         w.dbias = dbias;
         w.partial = static_cast<float*>(workspace);
+        w.partial_floats = static_cast<int64_t>(weight_grad_bytes(d, P, Q) / sizeof(float));
         w.beta = dW_beta;
         w.N = d->N; w.H = d->H; w.W = d->W; w.C = d->C; w.O = d->O; w.R = d->R; w.S = d->S;
         w.P = P; w.Q = Q;
@@ -684,6 +685,7 @@ extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, con
             if (rc != TWN_OK) return rc;
             w.X = Xp;
             w.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + sc.x_bytes);
+            w.partial_floats -= static_cast<int64_t>(sc.x_bytes / sizeof(float));
             w.H = sc.Hp; w.W = sc.Wp; w.C = 8; w.S = sc.Sp / 2;
             w.ph = w.pw = 0; w.dw = 2;
             w.xc = 4;
