@@ -9,7 +9,8 @@
 //                     word of the normal and of the transposed copy; the normal
 //                     words also carry the masked sum and count
 //   pack_gather       codes only (transposed copy of flat layouts, per-filter groups)
-//   group_stats       one block per group when there are several groups (per filter)
+//   filter_pack       one Delta and alpha per filter: statistics and codes of 16 filters per workgroup
+//   group_stats       one block per group for other groups and for filters that filter_pack does not take
 //
 //   finalize          fixed-order sum of the pass-2 partials -> Delta, alpha, nnz
 //
@@ -309,14 +310,30 @@ __global__ __launch_bounds__(kTernThreads) void mask_pack_gather_kernel(
     mask_pack_gather_body(W, rows, C, RS, ws, nb1, f, packed, wpr, packed_T, wprT, blockIdx.x, gridDim.x);
 }
 
-// Pass 2 for tensors with rows % 16 == 0 and C % 16 == 0 (filter banks, and matrices that also need the
-// transposed copy), staged through LDS: block `bid` owns 16 consecutive filters x CT consecutive channels
-// x all taps.  Its weights are 16 contiguous runs
-// of CT*R*S floats, read once with coalesced float4 loads; the 2-bit fields go to LDS as bytes in memory
-// order, and the words of both copies are assembled from LDS (16 byte reads per word), so no thread
-// gathers from global memory.  Words written: per filter and tap CT/16 normal words; per channel and tap
-// one transposed word (its 16 codes are the block's 16 filters).  Row padding words are written by the
-// blocks with channel tile 0 (normal) and filter tile 0 (transposed).
+// Codes of tensors with rows % 16 == 0 and C % 16 == 0 (filter banks, and matrices that also need the transposed copy),
+// staged through LDS: block `bid` owns 16 consecutive filters x CT consecutive channels x all taps.  Its weights are 16
+// contiguous runs of CT*R*S floats, read once with float4 loads, the first nine per thread before Delta is known; the 2-bit
+// fields go to LDS as bytes in memory order, and the words of both copies are assembled from there, so no thread gathers
+// from global memory.  Words written: per filter and tap CT/16 normal words; per channel and tap one transposed word (its
+// 16 codes are the block's 16 filters).  Row padding words are written by the blocks with channel tile 0 (normal) and
+// filter tile 0 (transposed).
+// 16 code bytes of consecutive k -> one word of the packed format (even k in the low half-word).
+__device__ __forceinline__ uint32_t word_of_bytes(const uint32_t* d) {
+    uint32_t word = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t low = (d[i] & 3u) | ((d[i] >> 14) & 0xCu);
+        const uint32_t high = ((d[i] >> 8) & 3u) | ((d[i] >> 22) & 0xCu);
+        word |= (low | (high << 16)) << (4 * i);
+    }
+    return word;
+}
+
+// Four consecutive weights, four-byte aligned (a filter of odd length starts anywhere).
+struct __attribute__((packed, aligned(4))) Weights4 {
+    float w[4];
+};
+
 constexpr int kTileRows = 16;
 constexpr int kTileLdsBytes = 16 * 64 * 25;   // CT <= 64 with R*S <= 25 taps; CT <= 1024 for matrices
 __host__ __device__ inline int tile_ct(int C, int RS) {
@@ -333,48 +350,79 @@ __host__ __device__ inline bool tile_ok(int rows, int C, int RS) {
            static_cast<int64_t>(rows / 16) * (C / tile_ct(C, RS)) <= kMaxBlocks;
 }
 
-__device__ __forceinline__ void mask_pack_tile_body(
-    const float* __restrict__ W, int rows, int C, int RS, TernWorkspace* __restrict__ ws, int nb1, float f,
-    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT, int bid) {
+__device__ __forceinline__ void mask_pack_tile_body(const float* __restrict__ W, int rows, int C, int RS,
+                                                    TernWorkspace* __restrict__ ws, int nb1, float f,
+                                                    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T,
+                                                    int wprT, int bid) {
+    constexpr int U = 9;                           // 64 channels x 9 taps x 16 filters: nine float4 per thread
     __shared__ double scratch[16];
     __shared__ unsigned long long scratch_u[16];
     __shared__ __attribute__((aligned(16))) unsigned char codes[kTileLdsBytes];
-    const int64_t n = static_cast<int64_t>(rows) * C * RS;
-    const float delta = delta_from_partials(ws->p1, nb1, f, n, scratch);
-    const int CT = tile_ct(C, RS), ctiles = C / CT;
-    const int o0 = (bid / ctiles) * kTileRows, c0 = (bid % ctiles) * CT;
-    const int seg = CT * RS;                       // floats (and code bytes) per filter in this block
-    const int tid = threadIdx.x;
+    // A transposed word is four bytes of a row that 16-filter neighbours share: the blocks of one XCD (every eighth) take
+    // consecutive filter tiles, so that its L2 collects whole lines (2048 x 320 x 3 x 3 with the pass before: 23.8 -> 22.1 us).
+    const int CT = tile_ct(C, RS), otiles = rows / kTileRows, tiles = otiles * (C / CT);
+    const int xcd = bid & 7, extra = tiles & 7;
+    const int tile = xcd * (tiles >> 3) + (xcd < extra ? xcd : extra) + (bid >> 3);
+    const int o0 = (tile % otiles) * kTileRows, c0 = (tile / otiles) * CT;
+    const int seg = CT * RS, seg4 = seg / 4;       // floats (and code bytes) per filter in this block
+    const int tid = threadIdx.x, items = kTileRows * seg4;
+    const float* base = W + (static_cast<int64_t>(o0) * C + c0) * RS;
+    const int64_t pitch = static_cast<int64_t>(C) * RS;
+    const float inv = 1.0f / static_cast<float>(seg4);
+    auto row_of = [&](int p) { return static_cast<int>((static_cast<float>(p) + 0.5f) * inv); };      // exact: p < 6400
+    float4 v[U];
+    auto load = [&](int p0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = p0 + u * kTernThreads;
+            if (p < items) {
+                const int ol = row_of(p);
+                v[u] = reinterpret_cast<const float4*>(base + ol * pitch)[p - ol * seg4];
+            }
+        }
+    };
+    load(tid);
+    const float delta = delta_from_partials(ws->p1, nb1, f, static_cast<int64_t>(rows) * C * RS, scratch);
     double acc = 0.0;
     uint32_t count = 0;
-    for (int ol = 0; ol < kTileRows; ++ol) {
-        const float4* src = reinterpret_cast<const float4*>(W + (static_cast<int64_t>(o0 + ol) * C + c0) * RS);
-        for (int p = tid; p < seg / 4; p += kTernThreads) {
-            const float4 v = src[p];
-            const float w4[4] = {v.x, v.y, v.z, v.w};
-            uint32_t four = 0;
+    for (int p0 = tid;;) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t fld = code_field(w4[e], delta);
-                if (fld) {
-                    acc += static_cast<double>(fabsf(w4[e]));
-                    ++count;
+        for (int u = 0; u < U; ++u) {
+            const int p = p0 + u * kTernThreads;
+            if (p < items) {
+                const float w4[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                uint32_t four = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool on = fabsf(w4[e]) > delta;
+                    acc += static_cast<double>(on ? fabsf(w4[e]) : 0.0f);
+                    count += on ? 1u : 0u;
+                    four |= (on ? (__float_as_uint(w4[e]) >> 31) << 1 | 1u : 0u) << (8 * e);
                 }
-                four |= fld << (8 * e);
+                reinterpret_cast<uint32_t*>(codes)[p] = four;
             }
-            *reinterpret_cast<uint32_t*>(codes + ol * seg + 4 * p) = four;
         }
+        p0 += U * kTernThreads;
+        if (p0 - tid >= items) break;
+        load(p0);
     }
     __syncthreads();
     // normal copy: word (ol, rs, g) holds channels c0 + 16g .. +15 of tap rs
-    const int groups = CT / 16;
-    for (int wi = tid; wi < kTileRows * RS * groups; wi += kTernThreads) {
-        const int g = wi % groups, t1 = wi / groups;
-        const int rs = t1 % RS, ol = t1 / RS;
+    const int groups = CT / 16, normal = kTileRows * RS * groups;
+    const float invg = 1.0f / static_cast<float>(groups), invrs = 1.0f / static_cast<float>(RS);
+    for (int wi = tid; wi < normal; wi += kTernThreads) {
+        const int t1 = static_cast<int>((static_cast<float>(wi) + 0.5f) * invg), g = wi - t1 * groups;
+        const int ol = static_cast<int>((static_cast<float>(t1) + 0.5f) * invrs), rs = t1 - ol * RS;
         const unsigned char* src = codes + ol * seg + (16 * g) * RS + rs;
         uint32_t word = 0;
+        if (RS == 1) {
+            const uint4 q = *reinterpret_cast<const uint4*>(src);
+            const uint32_t d[4] = {q.x, q.y, q.z, q.w};
+            word = word_of_bytes(d);
+        } else {
 #pragma unroll
-        for (int t = 0; t < 16; ++t) word |= static_cast<uint32_t>(src[t * RS]) << ((t & 1) * 16 + (t >> 1) * 2);
+            for (int t = 0; t < 16; ++t) word |= static_cast<uint32_t>(src[t * RS]) << ((t & 1) * 16 + (t >> 1) * 2);
+        }
         packed[static_cast<int64_t>(o0 + ol) * wpr + (rs * C + c0) / 16 + g] = word;
     }
     if (c0 == 0) {
@@ -383,17 +431,26 @@ __device__ __forceinline__ void mask_pack_tile_body(
             packed[static_cast<int64_t>(o0 + wi / pad) * wpr + kw + wi % pad] = 0u;
     }
     if (packed_T) {
-        // transposed copy: word (cl, rs) holds filters o0 .. o0+15
-        for (int wi = tid; wi < CT * RS; wi += kTernThreads) {
-            const int rs = wi % RS, cl = wi / RS;
-            const unsigned char* src = codes + cl * RS + rs;
-            uint32_t word = 0;
+        // transposed copy: word (cl, rs) holds filters o0 .. o0+15; four consecutive (cl, rs) per thread
+        for (int it = tid; it < seg4; it += kTernThreads) {
+            uint32_t word[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int t = 0; t < 16; ++t) word |= static_cast<uint32_t>(src[t * seg]) << ((t & 1) * 16 + (t >> 1) * 2);
-            packed_T[static_cast<int64_t>(c0 + cl) * wprT + (rs * rows + o0) / 16] = word;
+            for (int t = 0; t < kTileRows; ++t) {
+                const uint32_t b = reinterpret_cast<const uint32_t*>(codes)[t * seg4 + it];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) word[e] |= ((b >> (8 * e)) & 3u) << ((t & 1) * 16 + (t >> 1) * 2);
+            }
+            int cl = static_cast<int>((static_cast<float>(4 * it) + 0.5f) * invrs), rs = 4 * it - cl * RS;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                packed_T[static_cast<int64_t>(c0 + cl) * wprT + (static_cast<int64_t>(rs) * rows + o0) / 16] = word[e];
+                const bool next = ++rs == RS;
+                rs = next ? 0 : rs;
+                cl += next ? 1 : 0;
+            }
         }
         if (o0 == 0) {
-            const int kw = RS * rows / 16, pad = wprT - kw;
+            const int kw = static_cast<int>(static_cast<int64_t>(RS) * rows / 16), pad = wprT - kw;
             for (int wi = tid; wi < CT * pad; wi += kTernThreads)
                 packed_T[static_cast<int64_t>(c0 + wi / pad) * wprT + kw + wi % pad] = 0u;
         }
@@ -432,8 +489,9 @@ struct BatchItem {
     // several groups (one Delta, alpha per `rows / groups` filters): the tensor takes no part in the three per-layer
     // launches (nb1 = nb2 = 0) but in the two per-group ones
     int32_t groups;
-    int32_t firstg, firstp;     // index of its first block in the group-statistics / the code-packing launch
-    int32_t npb;                // its blocks in the code-packing launch
+    int32_t firstg, ngb;        // first block and blocks in the group-statistics launch,
+    int32_t firstp, npb;        // in the code-packing launch after it,
+    int32_t firstf, nfb;        // in the launch that does both for tensors with one group per filter
 };
 struct BatchTable {
     BatchItem item[kBatchMax];
@@ -441,27 +499,26 @@ struct BatchTable {
     float f;
 };
 
-__device__ __forceinline__ int batch_find(const BatchTable& tb, int block, bool pass2) {
-    int i = 0;
-    while (i + 1 < tb.count && block >= (pass2 ? tb.item[i + 1].first2 : tb.item[i + 1].first1)) ++i;
-    return i;
-}
-// the same for the two per-group launches (a tensor without blocks in a launch shares its first index with its
-// successor and is passed over)
-__device__ __forceinline__ int batch_find_group(const BatchTable& tb, int block, bool pack) {
-    int i = 0;
-    while (i + 1 < tb.count && block >= (pack ? tb.item[i + 1].firstp : tb.item[i + 1].firstg)) ++i;
-    return i;
+// The tensor whose range of blocks in a launch holds `block`: every lane tests one entry (a walk through the table costs a
+// scalar-load latency per tensor).  `first` and `blocks` name the launch's members of BatchItem.
+__device__ __forceinline__ int batch_find(const BatchTable& tb, int block, int32_t BatchItem::*first, int32_t BatchItem::*blocks) {
+    const int lane = threadIdx.x & (kWave - 1);
+    bool hit = false;
+    if (lane < tb.count) {
+        const int local = block - tb.item[lane].*first;
+        hit = local >= 0 && local < tb.item[lane].*blocks;
+    }
+    return __builtin_amdgcn_readfirstlane(static_cast<int>(__ffsll(__ballot(hit))) - 1);
 }
 
 __global__ __launch_bounds__(kTernThreads) void batch_abs_sum_kernel(const BatchTable tb, TernWorkspace* __restrict__ ws) {
-    const int i = batch_find(tb, blockIdx.x, false);
+    const int i = batch_find(tb, blockIdx.x, &BatchItem::first1, &BatchItem::nb1);
     const BatchItem& it = tb.item[i];
     abs_sum_body(it.W, static_cast<int64_t>(it.rows) * it.C * it.RS, ws[i].p1, blockIdx.x - it.first1, it.nb1);
 }
 
 __global__ __launch_bounds__(kTernThreads) void batch_mask_pack_kernel(const BatchTable tb, TernWorkspace* __restrict__ ws) {
-    const int i = batch_find(tb, blockIdx.x, true);
+    const int i = batch_find(tb, blockIdx.x, &BatchItem::first2, &BatchItem::nb2);
     const BatchItem& it = tb.item[i];
     if (it.flat_blocks > 0) {
         const int local = blockIdx.x - it.first2;
@@ -481,7 +538,7 @@ __global__ __launch_bounds__(kTernThreads) void batch_mask_pack_kernel(const Bat
 
 __global__ __launch_bounds__(kTernThreads) void batch_finalize_kernel(const BatchTable tb, const TernWorkspace* __restrict__ ws) {
     const BatchItem& it = tb.item[blockIdx.x];
-    if (it.groups > 1) return;      // per-group tensors were finished by batch_group_stats_kernel
+    if (it.groups > 1) return;      // per-group tensors have launches of their own
     finalize_body(ws + blockIdx.x, it.nb1, it.nb2, tb.f, static_cast<int64_t>(it.rows) * it.C * it.RS, it.delta, it.alpha,
                   it.nnz);
 }
@@ -522,10 +579,166 @@ __global__ __launch_bounds__(kTernThreads) void group_stats_kernel(
 }
 
 __global__ __launch_bounds__(kTernThreads) void batch_group_stats_kernel(const BatchTable tb) {
-    const int i = batch_find_group(tb, blockIdx.x, false);
+    const int i = batch_find(tb, blockIdx.x, &BatchItem::firstg, &BatchItem::ngb);
     const BatchItem& it = tb.item[i];
     group_stats_body(it.W, static_cast<int64_t>(it.rows) * it.C * it.RS / it.groups, tb.f, it.delta, it.alpha, it.nnz,
                      blockIdx.x - it.firstg);
+}
+
+// One Delta and alpha per filter, statistics and codes in one launch: a workgroup owns 16 filters, one per wave.  A wave sums
+// its filter, which gives Delta, reads it again (from L2: at most 36 KB per wave) for the masked sum, the count and the
+// codes, which go to LDS as bytes in the order of W; the words of both copies are then assembled from LDS: a word of the
+// normal copy is 16 bytes of one filter, one of the transposed copy the same byte of 16 filters.  Bound by vector
+// instructions (about 15 per weight) and by the latency of the reads.  Against one workgroup per filter
+// for the statistics and a gathering pass per word (us): ResNet-18, 4800 filters, both copies 91 -> 30; VGG-7 89 -> 35;
+// one tensor 8192 x 8192 375 -> 138.
+constexpr int kFilterRows = 16;
+constexpr int kFilterThreads = kFilterRows * kWave;
+constexpr int kFilterMaxK = 9216;                      // 16 x 9216 bytes of LDS
+__host__ __device__ inline int filter_pitch(int K) { return (K + 15) / 16 * 16; }
+// Rows of taps that no multiple of 16 filters divides make the transposed words straddle workgroups.  A few long filters
+// are better shared out over a workgroup each (33 x 7001: 16.2 us as three launches, 18.0 as one).
+__host__ inline bool filter_ok(int rows, int64_t K, int RS, bool transposed) {
+    return K <= (rows >= 512 ? kFilterMaxK : 4608) && (!transposed || RS == 1 || rows % kFilterRows == 0);
+}
+
+__device__ __forceinline__ void filter_pack_body(const float* __restrict__ W, int rows, int C, int RS, float f,
+                                                 uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T,
+                                                 int wprT, float* __restrict__ delta, float* __restrict__ alpha,
+                                                 uint64_t* __restrict__ nnz, int bid, unsigned char* codes) {
+    constexpr int U = 6;                            // loads in flight per wave and pass
+    const int K = C * RS, pitch = filter_pitch(K);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int o0 = bid * kFilterRows, o = o0 + wave;
+    unsigned char* mine = codes + wave * pitch;     // [channel][tap], the order of W
+    if (o < rows) {
+        const float* seg = W + static_cast<int64_t>(o) * K;
+        const Weights4* seg4 = reinterpret_cast<const Weights4*>(seg);
+        const int n4 = K / 4;
+        double acc = 0.0;
+        for (int i = lane; i < n4; i += U * kWave) {
+            Weights4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + u * kWave < n4) v[u] = seg4[i + u * kWave];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + u * kWave < n4)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc += static_cast<double>(fabsf(v[u].w[e]));
+        }
+        if (4 * n4 + lane < K) acc += static_cast<double>(fabsf(seg[4 * n4 + lane]));
+        const float d = static_cast<float>((static_cast<double>(f) * wave_sum(acc)) / static_cast<double>(K));
+        acc = 0.0;
+        uint32_t count = 0;
+        auto code = [&](float w) -> uint32_t {
+            const bool on = fabsf(w) > d;
+            acc += static_cast<double>(on ? fabsf(w) : 0.0f);
+            count += on ? 1u : 0u;
+            return on ? ((__float_as_uint(w) >> 31) << 1 | 1u) : 0u;
+        };
+        for (int i = lane; i < n4; i += U * kWave) {
+            Weights4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + u * kWave < n4) v[u] = seg4[i + u * kWave];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i + u * kWave < n4)
+                    reinterpret_cast<uint32_t*>(mine)[i + u * kWave] =
+                        code(v[u].w[0]) | (code(v[u].w[1]) << 8) | (code(v[u].w[2]) << 16) | (code(v[u].w[3]) << 24);
+        }
+        if (4 * n4 + lane < K) mine[4 * n4 + lane] = static_cast<unsigned char>(code(seg[4 * n4 + lane]));
+        if (K + lane < pitch) mine[K + lane] = 0;
+        const double s = wave_sum(acc);
+        const unsigned long long total = wave_sum(static_cast<unsigned long long>(count));
+        if (lane == 0) {
+            delta[o] = d;
+            nnz[o] = total;
+            alpha[o] = total ? static_cast<float>(s / static_cast<double>(total)) : 0.0f;
+        }
+        // the normal copy needs nothing of the other waves
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        uint32_t* out = packed + static_cast<int64_t>(o) * wpr;
+        if (RS == 1) {
+            for (int j = lane; j < wpr; j += kWave) {
+                uint32_t word = 0;
+                if (16 * j < pitch) {
+                    const uint4 b = reinterpret_cast<const uint4*>(mine)[j];
+                    const uint32_t q[4] = {b.x, b.y, b.z, b.w};
+                    word = word_of_bytes(q);
+                }
+                out[j] = word;
+            }
+        } else {
+            const float inv = 1.0f / static_cast<float>(C);
+            for (int j = lane; j < wpr; j += kWave) {
+                uint32_t word = 0;
+                if (16 * j < K) {
+                    int rs = static_cast<int>((static_cast<float>(16 * j) + 0.5f) * inv);      // exact: below 2^14
+                    int c = 16 * j - rs * C;
+                    if ((C & 15) == 0) {
+                        const unsigned char* src = mine + c * RS + rs;
+#pragma unroll
+                        for (int t = 0; t < 16; ++t) word |= static_cast<uint32_t>(src[t * RS]) << ((t & 1) * 16 + (t >> 1) * 2);
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < 16; ++t) {
+                            if (rs < RS) word |= static_cast<uint32_t>(mine[c * RS + rs]) << ((t & 1) * 16 + (t >> 1) * 2);
+                            const bool next = ++c == C;
+                            c = next ? 0 : c;
+                            rs += next ? 1 : 0;
+                        }
+                    }
+                }
+                out[j] = word;
+            }
+        }
+    } else if (packed_T) {
+        for (int m = lane; m < pitch / 4; m += kWave) reinterpret_cast<uint32_t*>(mine)[m] = 0u;      // no filter: zero codes
+    }
+    if (!packed_T) return;
+    __syncthreads();
+    // transposed copy: word (c, rs) holds filters o0 .. o0+15; four consecutive (c, rs) per thread
+    const float inv = 1.0f / static_cast<float>(RS);
+    for (int it = tid; 4 * it < K; it += kFilterThreads) {
+        uint32_t word[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int t = 0; t < kFilterRows; ++t) {
+            const uint32_t b = *reinterpret_cast<const uint32_t*>(codes + t * pitch + 4 * it);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) word[e] |= ((b >> (8 * e)) & 3u) << ((t & 1) * 16 + (t >> 1) * 2);
+        }
+        int c = static_cast<int>((static_cast<float>(4 * it) + 0.5f) * inv);
+        int rs = 4 * it - c * RS;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (c < C) packed_T[static_cast<int64_t>(c) * wprT + (static_cast<int64_t>(rs) * rows + o0) / 16] = word[e];
+            const bool next = ++rs == RS;
+            rs = next ? 0 : rs;
+            c += next ? 1 : 0;
+        }
+    }
+    if (bid == 0) {
+        const int kw = static_cast<int>((static_cast<int64_t>(RS) * rows + 15) / 16), pad = wprT - kw;
+        for (int wi = tid; wi < C * pad; wi += kFilterThreads)
+            packed_T[static_cast<int64_t>(wi / pad) * wprT + kw + wi % pad] = 0u;
+    }
+}
+
+__global__ __launch_bounds__(kFilterThreads) void filter_pack_kernel(
+    const float* __restrict__ W, int rows, int C, int RS, float f, uint32_t* __restrict__ packed, int wpr,
+    uint32_t* __restrict__ packed_T, int wprT, float* __restrict__ delta, float* __restrict__ alpha, uint64_t* __restrict__ nnz) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char filter_codes[];
+    filter_pack_body(W, rows, C, RS, f, packed, wpr, packed_T, wprT, delta, alpha, nnz, blockIdx.x, filter_codes);
+}
+
+__global__ __launch_bounds__(kFilterThreads) void batch_filter_pack_kernel(const BatchTable tb) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char filter_codes[];
+    const int i = batch_find(tb, blockIdx.x, &BatchItem::firstf, &BatchItem::nfb);
+    const BatchItem& it = tb.item[i];
+    filter_pack_body(it.W, it.rows, it.C, it.RS, tb.f, it.packed, it.wpr, it.packed_T, it.wprT, it.delta, it.alpha, it.nnz,
+                     blockIdx.x - it.firstf, filter_codes);
 }
 
 // ---- sign binarization of the binary-weight comparison (Sec. 3) ------------------------------------------
@@ -638,7 +851,7 @@ __global__ __launch_bounds__(256) void pack_gather_kernel(
 
 // Per-group tensors of a multi-tensor call: the words of the normal copy, then those of the transposed copy.
 __global__ __launch_bounds__(256) void batch_pack_gather_kernel(const BatchTable tb) {
-    const int i = batch_find_group(tb, blockIdx.x, true);
+    const int i = batch_find(tb, blockIdx.x, &BatchItem::firstp, &BatchItem::npb);
     const BatchItem& it = tb.item[i];
     const int64_t id = static_cast<int64_t>(blockIdx.x - it.firstp) * blockDim.x + threadIdx.x;
     const int64_t words_n = static_cast<int64_t>(it.rows) * it.wpr;
@@ -696,6 +909,27 @@ static int pass1_blocks(int64_t n) {
     return static_cast<int>(nchunks < want ? nchunks : want);
 }
 
+// LDS of a workgroup.  Long filters in more workgroups than CUs run one workgroup per CU (more than half of the 160 KB):
+// two at once would share a CU from the start while others finish early (ResNet-18's 21 tensors 34 -> 30 us).
+static int filter_lds(int K, int64_t blocks) {
+    const int need = kFilterRows * filter_pitch(K);
+    return K > 2048 && blocks > 256 && need < 84 * 1024 ? 84 * 1024 : need;
+}
+
+// The dynamic-LDS limit of the per-filter kernels is raised once.
+static bool filter_lds_allowed() {
+    static std::once_flag once;
+    static bool allowed = false;
+    std::call_once(once, [] {
+        const int bytes = kFilterRows * kFilterMaxK;
+        allowed = hipFuncSetAttribute(reinterpret_cast<const void*>(filter_pack_kernel),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess &&
+                  hipFuncSetAttribute(reinterpret_cast<const void*>(batch_filter_pack_kernel),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+    });
+    return allowed;
+}
+
 // Launches of one ternarization; `workspace` is device memory of at least sizeof(TernWorkspace) bytes, either
 // the caller's (twn_ternarize) or the library's own per-device array (twn_ternarize_static).
 static int32_t ternarize_impl(const float* W, const twn_weight_desc* wd, int32_t groups,
@@ -747,6 +981,11 @@ static int32_t ternarize_impl(const float* W, const twn_weight_desc* wd, int32_t
             finalize_kernel<<<1, kTernThreads, 0, st>>>(ws, nb, static_cast<int>(nb2), delta_factor, n, delta, alpha,
                                                         nnz);
         }
+    } else if (groups == wd->rows && filter_ok(wd->rows, K, static_cast<int>(RS), packed_T != nullptr)) {
+        if (!filter_lds_allowed()) return TWN_ERR_HIP;
+        filter_pack_kernel<<<static_cast<unsigned>((wd->rows + kFilterRows - 1) / kFilterRows), kFilterThreads,
+                             filter_lds(static_cast<int>(K), (wd->rows + kFilterRows - 1) / kFilterRows), st>>>(
+            W, wd->rows, wd->C, static_cast<int>(RS), delta_factor, packed, wpr, packed_T, wprT, delta, alpha, nnz);
     } else {
         group_stats_kernel<<<groups, kTernThreads, 0, st>>>(W, n / groups, delta_factor, delta, alpha, nnz);
         const int64_t words = static_cast<int64_t>(wd->rows) * wpr;
@@ -980,6 +1219,7 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
     // blocks are shared out in proportion to the tensor sizes: about 1024 per pass in total
     int first1 = 0, first2 = 0;
     int64_t firstg = 0, firstp = 0;
+    int filter_k = 0;
     for (int i = 0; i < count; ++i) {
         const twn_ternarize_item& in = items[i];
         const twn_weight_desc& wd = in.wd;
@@ -992,20 +1232,25 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
         it.wpr = static_cast<int32_t>(twn_packed_words_per_row(K));
         it.wprT = static_cast<int32_t>(twn_packed_words_per_row(KT));
         it.groups = in.groups;
-        it.firstg = static_cast<int32_t>(firstg);
-        it.firstp = static_cast<int32_t>(firstp);
-        it.npb = 0;
+        it.firstg = it.firstp = it.firstf = 0;
+        it.ngb = it.npb = it.nfb = 0;
         if (in.groups > 1) {
+            it.nb1 = it.nb2 = it.first1 = it.first2 = 0;
+            it.tiled = it.flat_blocks = 0;
+            if (in.groups == wd.rows && filter_ok(wd.rows, K, static_cast<int>(RS), in.packed_T != nullptr)) {
+                it.nfb = (wd.rows + kFilterRows - 1) / kFilterRows;      // placed below
+                if (K > filter_k) filter_k = static_cast<int>(K);
+                continue;
+            }
             // one block per group for the statistics, one thread per output word for the codes
             const int64_t words = static_cast<int64_t>(wd.rows) * it.wpr + (in.packed_T ? static_cast<int64_t>(wd.C) * it.wprT : 0);
+            it.firstg = static_cast<int32_t>(firstg);
+            it.firstp = static_cast<int32_t>(firstp);
+            it.ngb = in.groups;
             it.npb = static_cast<int32_t>((words + 255) / 256);
-            firstg += in.groups;
+            firstg += it.ngb;
             firstp += it.npb;
             if (firstg >= (1LL << 30) || firstp >= (1LL << 30)) return TWN_ERR_SHAPE;
-            it.nb1 = it.nb2 = 0;
-            it.tiled = it.flat_blocks = 0;
-            it.first1 = first1;
-            it.first2 = first2;
             continue;
         }
         int64_t share = (1024 * n + total_n - 1) / total_n;
@@ -1035,12 +1280,32 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
         first1 += it.nb1;
         first2 += it.nb2;
     }
+    // longest filters first: a long one that starts late ends the launch late
+    int64_t firstf = 0;
+    for (int64_t below = kFilterMaxK + 1; filter_k > 0 && below > 0;) {
+        int64_t longest = 0;
+        for (int i = 0; i < count; ++i) {
+            const int64_t K = static_cast<int64_t>(tb.item[i].C) * tb.item[i].RS;
+            if (tb.item[i].nfb > 0 && K < below && K > longest) longest = K;
+        }
+        for (int i = 0; i < count && longest > 0; ++i)
+            if (tb.item[i].nfb > 0 && static_cast<int64_t>(tb.item[i].C) * tb.item[i].RS == longest) {
+                tb.item[i].firstf = static_cast<int32_t>(firstf);
+                firstf += tb.item[i].nfb;
+            }
+        if (firstf >= (1LL << 22)) return TWN_ERR_SHAPE;        // grid below 2^32 threads
+        below = longest;
+    }
     hipStream_t st = as_stream(stream);
     TernWorkspace* ws = static_cast<TernWorkspace*>(workspace);
     if (first1 > 0) {
         batch_abs_sum_kernel<<<first1, kTernThreads, 0, st>>>(tb, ws);
         batch_mask_pack_kernel<<<first2, kTernThreads, 0, st>>>(tb, ws);
         batch_finalize_kernel<<<count, kTernThreads, 0, st>>>(tb, ws);
+    }
+    if (firstf > 0) {
+        if (!filter_lds_allowed()) return TWN_ERR_HIP;
+        batch_filter_pack_kernel<<<static_cast<unsigned>(firstf), kFilterThreads, filter_lds(filter_k, firstf), st>>>(tb);
     }
     if (firstg > 0) {
         batch_group_stats_kernel<<<static_cast<unsigned>(firstg), kTernThreads, 0, st>>>(tb);
