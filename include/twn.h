@@ -173,9 +173,9 @@ int32_t twn_ternarize_static(const float* W, const twn_weight_desc* wd, int32_t 
                              float* delta, float* alpha, uint64_t* nnz, void* stream);
 
 /* ---- 1b. several tensors per call (same passages as above) ------------------
- * twn_ternarize for `count` <= 32 weight tensors at once, in three launches in
- * total for the tensors with one group and two more for those with several
- * (per-filter) groups: meant for the weight tensors of a network, which are too
+ * twn_ternarize for `count` <= 32 weight tensors at once, in two launches in
+ * total for the tensors with one group, one for those with one group per filter
+ * and two for other groups: meant for the weight tensors of a network, which are too
  * small to fill the chip one at a time.  `items` is a
  * host array (read during the call, not retained); the pointers inside are
  * device pointers with the meaning and alignment of twn_ternarize's arguments

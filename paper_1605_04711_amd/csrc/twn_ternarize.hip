@@ -12,12 +12,8 @@
 //   filter_pack       one Delta and alpha per filter: statistics and codes of 16 filters per workgroup
 //   group_stats       one block per group for other groups and for filters that filter_pack does not take
 //
-//   finalize          fixed-order sum of the pass-2 partials -> Delta, alpha, nnz
-//
-// (A "last block finishes" variant with a ticket counter was measured and dropped:
-// the device-scope release it needs writes back the L2 of every XCD once per block
-// and cost 75 us on the 2^28 tensor.)  All floating-point sums run in a fixed
-// order: results are bit-identical from run to run; no floating-point atomics.
+// The block of pass 2 that delivers its partials last sums them in a fixed order -> Delta, alpha, nnz (see deliver()).
+// All floating-point sums run in a fixed order: results are bit-identical from run to run; no floating-point atomics.
 #include <mutex>
 
 #include "twn_common.h"
@@ -29,10 +25,14 @@ constexpr int kChunk = kTernThreads * 16;   // weights per block iteration
 constexpr int kMaxBlocks = 4096;
 
 struct TernWorkspace {
-    double p1[kMaxBlocks];     // pass-1 partial sums of |W|
+    double p1[kMaxBlocks];     // pass-1 partial sums of |W|; from slot kMaxPass1 on the tickets of pass 2
     double p2[kMaxBlocks];     // pass-2 partial masked sums
     uint64_t cnt[kMaxBlocks];  // pass-2 partial counts
 };
+// Tickets of pass 2, in lines of their own at the end of p1: sixteen that the blocks share out, and one that the last block
+// of each of them takes.  Pass 1 zeroes them.
+constexpr int kTickets = 17, kTicketStep = 16;
+constexpr int kMaxPass1 = kMaxBlocks - kTickets * kTicketStep;
 
 // Pass 1 of block `bid` out of `nblk` cooperating blocks: float64 partial sum of |W| -> partial[bid].
 __device__ __forceinline__ void abs_sum_body(const float* __restrict__ W, int64_t n, double* __restrict__ partial,
@@ -78,6 +78,7 @@ __device__ __forceinline__ void abs_sum_body(const float* __restrict__ W, int64_
     }
     const double total = block_sum(acc, scratch);
     if (tid == 0) partial[bid] = total;
+    if (bid == 0 && tid < kTickets) partial[kMaxPass1 + tid * kTicketStep] = 0.0;
 }
 
 __global__ __launch_bounds__(kTernThreads) void abs_sum_kernel(const float* __restrict__ W, int64_t n,
@@ -94,37 +95,46 @@ __device__ __forceinline__ float delta_from_partials(const double* __restrict__ 
     return static_cast<float>((static_cast<double>(f) * s1) / static_cast<double>(n));
 }
 
-// Fixed-order sum of the pass-2 partials of `nb2` blocks -> Delta, alpha, nnz (one block).
-__device__ __forceinline__ void finalize_body(const TernWorkspace* __restrict__ ws, int nb1, int nb2,
-                                              float f, int64_t n, float* __restrict__ delta,
-                                              float* __restrict__ alpha, uint64_t* __restrict__ nnz) {
-    __shared__ double scratch[16];
-    __shared__ unsigned long long scratch_u[16];
-    // all loads of the three partial arrays are issued before any sum is formed
-    double a1 = 0.0, acc = 0.0;
+// End of pass 2 of block `slot` out of `slots`: its masked sum and count go to the workspace, and the block that delivers last
+// sums all of them in slot order and writes Delta, alpha and nnz, which saves the launch that used to do it (4-5 us).
+// The partials are agent-scope atomic stores: they reach memory past the XCD's L2 by themselves, so waiting for them before
+// taking the ticket orders them, and the last block reads them by atomic loads that no stale L2 line can serve.  (A release
+// fence would write back the whole L2 of the XCD, once per block: 75 us on 2^28 weights.)  One counter for a
+// thousand blocks costs 7 us, two levels of them 2.  The tickets are left at zero, for another pass 2 on the same sums.
+__device__ __forceinline__ void deliver(TernWorkspace* __restrict__ ws, int slot, int slots, double sum, unsigned long long n,
+                                        float delta, float* __restrict__ delta_out, float* __restrict__ alpha_out,
+                                        uint64_t* __restrict__ nnz_out, double* scratch, unsigned long long* scratch_u) {
+    __shared__ int last;
+    unsigned long long* tickets = reinterpret_cast<unsigned long long*>(&ws->p1[kMaxPass1]);
+    constexpr int kShared = kTickets - 1;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&ws->p2[slot], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(reinterpret_cast<unsigned long long*>(&ws->cnt[slot]), n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const int mine = slot % kShared, of = (slots - mine + kShared - 1) / kShared;
+        auto take = [&](int t) {
+            return __hip_atomic_fetch_add(tickets + t * kTicketStep, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        last = take(mine) == static_cast<unsigned long long>(of - 1) &&
+               take(kShared) == static_cast<unsigned long long>((slots < kShared ? slots : kShared) - 1);
+    }
+    __syncthreads();
+    if (!last) return;
+    double acc = 0.0;
     unsigned long long c = 0;
 #pragma unroll 4
-    for (int i = threadIdx.x; i < nb1; i += blockDim.x) a1 += ws->p1[i];
-#pragma unroll 4
-    for (int i = threadIdx.x; i < nb2; i += blockDim.x) {
-        acc += ws->p2[i];
-        c += ws->cnt[i];
+    for (int i = threadIdx.x; i < slots; i += blockDim.x) {
+        acc += __hip_atomic_load(&ws->p2[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        c += __hip_atomic_load(reinterpret_cast<unsigned long long*>(&ws->cnt[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    const double s1 = block_sum(a1, scratch);
-    const float d = static_cast<float>((static_cast<double>(f) * s1) / static_cast<double>(n));
     const double s = block_sum(acc, scratch);
     const unsigned long long total = block_sum(c, scratch_u);
     if (threadIdx.x == 0) {
-        delta[0] = d;
-        nnz[0] = total;
-        alpha[0] = total ? static_cast<float>(s / static_cast<double>(total)) : 0.0f;
+        delta_out[0] = delta;
+        nnz_out[0] = total;
+        alpha_out[0] = total ? static_cast<float>(s / static_cast<double>(total)) : 0.0f;
     }
-}
-
-__global__ __launch_bounds__(kTernThreads) void finalize_kernel(const TernWorkspace* __restrict__ ws, int nb1, int nb2,
-                                                                float f, int64_t n, float* __restrict__ delta,
-                                                                float* __restrict__ alpha, uint64_t* __restrict__ nnz) {
-    finalize_body(ws, nb1, nb2, f, n, delta, alpha, nnz);
+    if (threadIdx.x < kTickets) tickets[threadIdx.x * kTicketStep] = 0ULL;
 }
 
 __device__ __forceinline__ uint32_t quad_or(uint32_t v) {
@@ -142,7 +152,8 @@ __device__ __forceinline__ uint32_t quad_or(uint32_t v) {
 // contiguous bytes.
 __device__ __forceinline__ void mask_pack_flat_body(
     const float* __restrict__ W, int64_t n, TernWorkspace* __restrict__ ws, int nb1, float f,
-    uint32_t* __restrict__ packed, int reverse, int bid, int nblk) {
+    uint32_t* __restrict__ packed, int reverse, int bid, int nblk, int slots, float* __restrict__ delta_out,
+    float* __restrict__ alpha_out, uint64_t* __restrict__ nnz_out) {
     const double* __restrict__ p1 = ws->p1;
     __shared__ double scratch[16];
     __shared__ unsigned long long scratch_u[16];
@@ -230,16 +241,14 @@ __device__ __forceinline__ void mask_pack_flat_body(
     }
     const double total = block_sum(acc, scratch);
     const unsigned long long ctotal = block_sum(static_cast<unsigned long long>(count), scratch_u);
-    if (threadIdx.x == 0) {
-        ws->p2[bid] = total;
-        ws->cnt[bid] = ctotal;
-    }
+    deliver(ws, bid, slots, total, ctotal, delta, delta_out, alpha_out, nnz_out, scratch, scratch_u);
 }
 
 __global__ __launch_bounds__(kTernThreads) void mask_pack_flat_kernel(
     const float* __restrict__ W, int64_t n, TernWorkspace* __restrict__ ws, int nb1, float f,
-    uint32_t* __restrict__ packed, int reverse) {
-    mask_pack_flat_body(W, n, ws, nb1, f, packed, reverse, blockIdx.x, gridDim.x);
+    uint32_t* __restrict__ packed, int reverse, float* __restrict__ delta_out, float* __restrict__ alpha_out,
+    uint64_t* __restrict__ nnz_out) {
+    mask_pack_flat_body(W, n, ws, nb1, f, packed, reverse, blockIdx.x, gridDim.x, gridDim.x, delta_out, alpha_out, nnz_out);
 }
 
 // Pass 2 for any layout: grid-stride over the output words of the normal copy (which also carry the
@@ -248,7 +257,8 @@ __global__ __launch_bounds__(kTernThreads) void mask_pack_flat_kernel(
 //   transposed: row = input channel c, k_T = (r*S+s)*rows + o   (threads ordered with c fastest)
 __device__ __forceinline__ void mask_pack_gather_body(
     const float* __restrict__ W, int rows, int C, int RS, TernWorkspace* __restrict__ ws, int nb1, float f,
-    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT, int bid, int nblk,
+    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT, int bid, int nblk, int slots,
+    float* __restrict__ delta_out, float* __restrict__ alpha_out, uint64_t* __restrict__ nnz_out,
     bool only_transposed = false, int slot0 = 0) {
     __shared__ double scratch[16];
     __shared__ unsigned long long scratch_u[16];
@@ -298,16 +308,15 @@ __device__ __forceinline__ void mask_pack_gather_body(
     }
     const double total = block_sum(acc, scratch);
     const unsigned long long ctotal = block_sum(static_cast<unsigned long long>(count), scratch_u);
-    if (threadIdx.x == 0) {
-        ws->p2[slot0 + bid] = total;
-        ws->cnt[slot0 + bid] = ctotal;
-    }
+    deliver(ws, slot0 + bid, slots, total, ctotal, delta, delta_out, alpha_out, nnz_out, scratch, scratch_u);
 }
 
 __global__ __launch_bounds__(kTernThreads) void mask_pack_gather_kernel(
     const float* __restrict__ W, int rows, int C, int RS, TernWorkspace* __restrict__ ws, int nb1, float f,
-    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT) {
-    mask_pack_gather_body(W, rows, C, RS, ws, nb1, f, packed, wpr, packed_T, wprT, blockIdx.x, gridDim.x);
+    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT, float* __restrict__ delta_out,
+    float* __restrict__ alpha_out, uint64_t* __restrict__ nnz_out) {
+    mask_pack_gather_body(W, rows, C, RS, ws, nb1, f, packed, wpr, packed_T, wprT, blockIdx.x, gridDim.x, gridDim.x, delta_out,
+                          alpha_out, nnz_out);
 }
 
 // Codes of tensors with rows % 16 == 0 and C % 16 == 0 (filter banks, and matrices that also need the transposed copy),
@@ -353,7 +362,8 @@ __host__ __device__ inline bool tile_ok(int rows, int C, int RS) {
 __device__ __forceinline__ void mask_pack_tile_body(const float* __restrict__ W, int rows, int C, int RS,
                                                     TernWorkspace* __restrict__ ws, int nb1, float f,
                                                     uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T,
-                                                    int wprT, int bid) {
+                                                    int wprT, int bid, float* __restrict__ delta_out,
+                                                    float* __restrict__ alpha_out, uint64_t* __restrict__ nnz_out) {
     constexpr int U = 9;                           // 64 channels x 9 taps x 16 filters: nine float4 per thread
     __shared__ double scratch[16];
     __shared__ unsigned long long scratch_u[16];
@@ -457,22 +467,20 @@ __device__ __forceinline__ void mask_pack_tile_body(const float* __restrict__ W,
     }
     const double total = block_sum(acc, scratch);
     const unsigned long long ctotal = block_sum(static_cast<unsigned long long>(count), scratch_u);
-    if (tid == 0) {
-        ws->p2[bid] = total;
-        ws->cnt[bid] = ctotal;
-    }
+    deliver(ws, bid, tiles, total, ctotal, delta, delta_out, alpha_out, nnz_out, scratch, scratch_u);
 }
 
 __global__ __launch_bounds__(kTernThreads) void mask_pack_tile_kernel(
     const float* __restrict__ W, int rows, int C, int RS, TernWorkspace* __restrict__ ws, int nb1, float f,
-    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT) {
-    mask_pack_tile_body(W, rows, C, RS, ws, nb1, f, packed, wpr, packed_T, wprT, blockIdx.x);
+    uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT, float* __restrict__ delta_out,
+    float* __restrict__ alpha_out, uint64_t* __restrict__ nnz_out) {
+    mask_pack_tile_body(W, rows, C, RS, ws, nb1, f, packed, wpr, packed_T, wprT, blockIdx.x, delta_out, alpha_out, nnz_out);
 }
 
 // ---- several tensors per launch --------------------------------------------------------------
 // The weight tensors of a network are small (at most a few MB): ternarizing them one call at a time is
 // bound by launch latency and by kernels too small to fill the chip.  The batch entry point runs the same
-// three passes once for up to kBatchMax tensors; a block finds its tensor in a table passed by value.
+// passes once for up to kBatchMax tensors; a block finds its tensor in a table passed by value.
 constexpr int kBatchMax = 32;
 struct BatchItem {
     const float* W;
@@ -486,7 +494,7 @@ struct BatchItem {
     int32_t tiled;              // pass 2 through the LDS-staged tile body
     int32_t flat_blocks;        // > 0: flat layout, the first flat_blocks pass-2 blocks stream W, the rest gather the transposed copy
     int32_t first1, first2;     // index of its first block in the pass-1 / pass-2 launch
-    // several groups (one Delta, alpha per `rows / groups` filters): the tensor takes no part in the three per-layer
+    // several groups (one Delta, alpha per `rows / groups` filters): the tensor takes no part in the two per-layer
     // launches (nb1 = nb2 = 0) but in the two per-group ones
     int32_t groups;
     int32_t firstg, ngb;        // first block and blocks in the group-statistics launch,
@@ -524,23 +532,18 @@ __global__ __launch_bounds__(kTernThreads) void batch_mask_pack_kernel(const Bat
         const int local = blockIdx.x - it.first2;
         const int64_t n = static_cast<int64_t>(it.rows) * it.C;
         if (local < it.flat_blocks)
-            mask_pack_flat_body(it.W, n, ws + i, it.nb1, tb.f, it.packed, 1, local, it.flat_blocks);
+            mask_pack_flat_body(it.W, n, ws + i, it.nb1, tb.f, it.packed, 1, local, it.flat_blocks, it.nb2, it.delta, it.alpha,
+                                it.nnz);
         else
             mask_pack_gather_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
-                                  local - it.flat_blocks, it.nb2 - it.flat_blocks, true, it.flat_blocks);
+                                  local - it.flat_blocks, it.nb2 - it.flat_blocks, it.nb2, it.delta, it.alpha, it.nnz, true,
+                                  it.flat_blocks);
     } else if (it.tiled)
         mask_pack_tile_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
-                            blockIdx.x - it.first2);
+                            blockIdx.x - it.first2, it.delta, it.alpha, it.nnz);
     else
         mask_pack_gather_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
-                              blockIdx.x - it.first2, it.nb2);
-}
-
-__global__ __launch_bounds__(kTernThreads) void batch_finalize_kernel(const BatchTable tb, const TernWorkspace* __restrict__ ws) {
-    const BatchItem& it = tb.item[blockIdx.x];
-    if (it.groups > 1) return;      // per-group tensors have launches of their own
-    finalize_body(ws + blockIdx.x, it.nb1, it.nb2, tb.f, static_cast<int64_t>(it.rows) * it.C * it.RS, it.delta, it.alpha,
-                  it.nnz);
+                              blockIdx.x - it.first2, it.nb2, it.nb2, it.delta, it.alpha, it.nnz);
 }
 
 // One block per group: both passes over the group's contiguous weights.
@@ -905,7 +908,7 @@ static int pass1_blocks(int64_t n) {
     const int64_t nchunks = (n + kChunk - 1) / kChunk;
     int want = env_int(Env::TERN_BLOCKS, 512);
     if (want < 1) want = 1;
-    if (want > kMaxBlocks) want = kMaxBlocks;
+    if (want > kMaxPass1) want = kMaxPass1;
     return static_cast<int>(nchunks < want ? nchunks : want);
 }
 
@@ -959,8 +962,7 @@ static int32_t ternarize_impl(const float* W, const twn_weight_desc* wd, int32_t
         const bool flat = (RS == 1) && (K % 128 == 0) && !(packed_T && tile_ok(wd->rows, wd->C, 1));
         if (flat) {
             const int reverse = env_int(Env::TERN_REVERSE, 1);
-            mask_pack_flat_kernel<<<nb, kTernThreads, 0, st>>>(W, n, ws, nb, delta_factor, packed, reverse);
-            finalize_kernel<<<1, kTernThreads, 0, st>>>(ws, nb, nb, delta_factor, n, delta, alpha, nnz);
+            mask_pack_flat_kernel<<<nb, kTernThreads, 0, st>>>(W, n, ws, nb, delta_factor, packed, reverse, delta, alpha, nnz);
             if (packed_T) {
                 const int64_t words = static_cast<int64_t>(wd->C) * wprT;
                 pack_gather_kernel<<<static_cast<unsigned>((words + 255) / 256), 256, 0, st>>>(
@@ -974,12 +976,10 @@ static int32_t ternarize_impl(const float* W, const twn_weight_desc* wd, int32_t
             if (tile_ok(wd->rows, wd->C, static_cast<int>(RS))) {
                 nb2 = static_cast<int64_t>(wd->rows / kTileRows) * (wd->C / tile_ct(wd->C, static_cast<int>(RS)));
                 mask_pack_tile_kernel<<<static_cast<unsigned>(nb2), kTernThreads, 0, st>>>(
-                    W, wd->rows, wd->C, static_cast<int>(RS), ws, nb, delta_factor, packed, wpr, packed_T, wprT);
+                    W, wd->rows, wd->C, static_cast<int>(RS), ws, nb, delta_factor, packed, wpr, packed_T, wprT, delta, alpha, nnz);
             } else
-            mask_pack_gather_kernel<<<static_cast<unsigned>(nb2), kTernThreads, 0, st>>>(
-                W, wd->rows, wd->C, static_cast<int>(RS), ws, nb, delta_factor, packed, wpr, packed_T, wprT);
-            finalize_kernel<<<1, kTernThreads, 0, st>>>(ws, nb, static_cast<int>(nb2), delta_factor, n, delta, alpha,
-                                                        nnz);
+                mask_pack_gather_kernel<<<static_cast<unsigned>(nb2), kTernThreads, 0, st>>>(
+                    W, wd->rows, wd->C, static_cast<int>(RS), ws, nb, delta_factor, packed, wpr, packed_T, wprT, delta, alpha, nnz);
         }
     } else if (groups == wd->rows && filter_ok(wd->rows, K, static_cast<int>(RS), packed_T != nullptr)) {
         if (!filter_lds_allowed()) return TWN_ERR_HIP;
@@ -1087,6 +1087,7 @@ __global__ __launch_bounds__(kTernThreads) void sgd_update_kernel(float* __restr
     }
     const double total = block_sum(acc, scratch);
     if (partial && tid == 0) partial[bid] = total;
+    if (partial && bid == 0 && tid < kTickets) partial[kMaxPass1 + tid * kTicketStep] = 0.0;       // as pass 1 leaves them
 }
 
 extern "C" int32_t twn_sgd_update(float* W, float* V, const float* dW, int64_t n, float lr, float momentum,
@@ -1261,7 +1262,7 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
         int64_t nb2 = (words + kTernThreads - 1) / kTernThreads;
         if (nb2 > 4 * share) nb2 = 4 * share;
         if (nb2 > kMaxBlocks) nb2 = kMaxBlocks;
-        if (it.nb1 > kMaxBlocks) it.nb1 = kMaxBlocks;
+        if (it.nb1 > kMaxPass1) it.nb1 = kMaxPass1;
         const bool flat = (RS == 1) && (K % 128 == 0) && !(in.packed_T && tile_ok(wd.rows, wd.C, 1));
         it.tiled = (!flat && tile_ok(wd.rows, wd.C, static_cast<int>(RS))) ? 1 : 0;
         if (it.tiled) nb2 = static_cast<int64_t>(wd.rows / kTileRows) * (wd.C / tile_ct(wd.C, static_cast<int>(RS)));
@@ -1301,7 +1302,6 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
     if (first1 > 0) {
         batch_abs_sum_kernel<<<first1, kTernThreads, 0, st>>>(tb, ws);
         batch_mask_pack_kernel<<<first2, kTernThreads, 0, st>>>(tb, ws);
-        batch_finalize_kernel<<<count, kTernThreads, 0, st>>>(tb, ws);
     }
     if (firstf > 0) {
         if (!filter_lds_allowed()) return TWN_ERR_HIP;
