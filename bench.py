@@ -273,6 +273,10 @@ def main():
         t_fwd = time_call(lambda: api.twn_ternarize(big, F, out=btw, workspace=ws), reps=50, warm=10)
         del os.environ["TWN_TERN_REVERSE"]
         api.reload_env()
+        # with the workspace that the query asks for: codes from one stream of W, 4.25 B/weight and what is read again
+        t_one = time_call(lambda: api.twn_ternarize(big, F, out=btw), reps=100, warm=20)
+        res["one_stream_us"] = round(t_one * 1e3, 1)
+        res["one_stream_GBps"] = round((1 << 28) * 4.25 / t_one / 1e6, 1)
         res["forward_walk_us"] = round(t_fwd * 1e3, 1)
         res["forward_walk_GBps"] = round(nbytes / t_fwd / 1e6, 1)
         res["forward_walk_frac"] = round(nbytes / t_fwd / 1e6 / PEAK_HBM_GBPS, 4)

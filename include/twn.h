@@ -146,7 +146,10 @@ size_t  twn_packed_bytes(int32_t rows, int64_t K);     /* rows * words_per_row *
  * run to run); comparisons are float32.
  * Outputs: packed [rows][words_per_row(R*S*C)] (twn2 format above);
  * packed_T [C][words_per_row(R*S*rows)] or NULL; delta, alpha: float32[groups];
- * nnz: uint64[groups].  delta_factor must be in (0, 1]. */
+ * nnz: uint64[groups].  delta_factor must be in (0, 1].
+ * Workspace: 98304 bytes are enough for every tensor; for large matrices the
+ * query asks for 1/128 byte per weight more, with which W is read once instead
+ * of twice. */
 size_t  twn_ternarize_workspace_bytes(const twn_weight_desc* wd, int32_t groups);
 int32_t twn_ternarize(const float* W, const twn_weight_desc* wd, int32_t groups,
                       float delta_factor,
