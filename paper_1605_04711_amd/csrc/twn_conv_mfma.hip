@@ -613,8 +613,19 @@ int32_t launch_gather_gemm_mfma(const GatherGemm& g, int variant, hipStream_t st
             // unsplit 128x128 tiles: waves side by side (128x32 each) expand every code once per workgroup
             // instead of twice; a few percent faster than the 2x2 arrangement, which keeps the split-K builds
             if (tile == 12 && g.splits == 1) tile = 15;
+            // A wave tile of 128x64 reads half the fragments per MFMA that one of 128x32 does.  128x256 and 256x128 tiles have
+            // it, at one workgroup per CU: they win where they leave the busiest CU no more 128x128 blocks than the smaller
+            // tiles do (3x3, us, 128x128 -> larger: 32768 pixels, 256 -> 256 channels 33.9 -> 29.4; 50176, 128 -> 128
+            // 19.0 -> 17.2; 720000, 128 -> 128 219 -> 211; 131072, 128 -> 128 36.9 both; 8192, 512 -> 512, 128 CUs with two
+            // blocks against 256 with one, 36.5 -> 43) and K is long enough to hide an epilogue that nothing overlaps.
+            if (tile == 15 && g.K >= 1024 && !env_set(Env::STREAM_PC) && !env_set(Env::STREAM_KS)) {
+                auto busiest = [&](int bm, int bn) { return (blocks(bm, bn) + 255) / 256 * (bm / 128) * (bn / 128); };
+                const int64_t have = busiest(128, 128);
+                if (g.NC > 128 && busiest(128, 256) <= have) tile = 17;
+                else if (busiest(256, 128) <= have && conv_stream_applicable(g) && env_int(Env::STREAM, 1) != 0) tile = 18;
+            }
         }
-        if ((tile == 12 || (tile >= 14 && tile <= 17)) && env_int(Env::STREAM, 1) != 0 && conv_stream_applicable(g))
+        if ((tile == 12 || (tile >= 14 && tile <= 18)) && env_int(Env::STREAM, 1) != 0 && conv_stream_applicable(g))
             return launch_conv_stream(g, tile, st);
         return launch_gather_gemm_dma(g, tile, st);
     }

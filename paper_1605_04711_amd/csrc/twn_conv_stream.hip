@@ -608,7 +608,7 @@ int32_t launch_conv_stream(const GatherGemm& g, int tile, hipStream_t st) {
     // workgroups of four waves did (VGG-16 conv5-7: 5-8 % faster); 128x64 tiles (64 output channels) gain nothing.
     // TWN_STREAM_PC: 0 = never, 2 / 4 = that many load waves wherever a build exists, unset = this rule.
     int np = env_int(Env::STREAM_PC, -1);
-    if (np < 0) np = (tile == 14 || tile == 15 || tile == 17) ? 4 : 0;
+    if (np < 0) np = (tile == 14 || tile == 15 || tile == 17 || tile == 18) ? 4 : 0;
     if (np > 0) {
         const int32_t rc = launch_conv_stream_pc(g, tile, ks == 0 ? 1 : ks, np, env_int(Env::STREAM_PC_STAGES, 4), st);
         if (rc != TWN_ERR_UNSUPPORTED) return rc;

@@ -577,6 +577,7 @@ int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int ks, int np, int
         case 15144: return launch_pc_tile<128, 128, 1, 4, 4, 2, 1, 4>(g, st);
         case 16144: return launch_pc_tile<128, 64, 2, 2, 4, 2, 1, 4>(g, st);
         case 17144: return launch_pc_tile<128, 256, 1, 4, 4, 1, 1, 4>(g, st);
+        case 18144: return launch_pc_tile<256, 128, 2, 2, 4, 1, 1, 4>(g, st);
         default: return TWN_ERR_UNSUPPORTED;
     }
 }
