@@ -944,6 +944,26 @@ WgPlan plan_weight_grad(int32_t N, int32_t P, int32_t Q, int32_t C, int32_t O, i
     // same number of waves per CU.  TWN_WG_KS=1 keeps four-wave workgroups.
     pl.ks = (pl.tiles < 256 && env_int(Env::WG_KS, 2) == 2 && pl.slabs >= 4) ? 2 : 1;
     pl.splits = choose_splits(pl.tiles, pl.slabs, pl.ks);
+    // Fewer ranges where the slabs are few: a range more saves slabs of 0.83 us a round and costs its partial tiles (written and
+    // read: 0.34 us per MB), the first one the final pass besides (3 us); one range over several taps writes dW in single
+    // floats instead (6 us).  (us, all the ranges that fill the chip -> this: 588 pixels, 128 -> 256 channels 3x3/2
+    // 25.3 -> 15.3; 1470, 256 -> 512 27.5 -> 22.8; 64, 512 -> 1000 1x1 15.7 -> 11.0; 12544, 128 -> 256 27.5 -> 25.3 with the final pass
+    // below)
+    if (!env_set(Env::WG_BLOCKS)) {
+        const double mb = static_cast<double>(O) * J * 4e-6;
+        auto cost = [&](int64_t s) {
+            const int64_t rounds = ((pl.slabs + s - 1) / s + pl.ks - 1) / pl.ks;
+            return 0.83 * static_cast<double>(rounds) + (s > 1 ? 3.0 + 0.34 * mb * static_cast<double>(s) : (R * S > 1 ? 6.0 : 0.0));
+        };
+        double best_us = cost(pl.splits);
+        for (int64_t s = pl.splits / 2; s >= 1; s /= 2) {
+            const int64_t per = (pl.slabs + s - 1) / s, used = (pl.slabs + per - 1) / per;
+            if (cost(used) < best_us) {
+                best_us = cost(used);
+                pl.splits = static_cast<int32_t>(used);
+            }
+        }
+    }
     return pl;
 }
 
@@ -1021,7 +1041,9 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
             const int64_t total = static_cast<int64_t>(w.O) * a.J;
             const int C = w.pad_sp ? w.c_real : w.C, S = w.pad_sp ? w.s_real : w.S;
             const int RS = w.R * w.S;
-            if (!w.pad_sp && w.C % 64 == 0 && RS <= kReduceRowsMaxTaps && splits <= env_int(Env::WG_ROWS_SPLITS, 32))
+            // whole rows up to 16 ranges (us of both launches, rows / scattered floats: 588 pixels, 256 -> 512 channels 3x3/2, 3
+            // ranges 19.6 / 25.3; 3136, the same, 6 ranges 27.6 / 32.2; 12544, 128 -> 256, 24 ranges 27.6 / 25.3)
+            if (!w.pad_sp && w.C % 64 == 0 && RS > 1 && RS <= kReduceRowsMaxTaps && splits <= env_int(Env::WG_ROWS_SPLITS, 16))
                 weight_grad_reduce_rows_kernel<<<static_cast<unsigned>(w.O * (w.C / 64)), 256, 0, st>>>(
                     w.partial, splits, w.O, w.C, RS, w.beta, w.dW);
             else if (total % 4 == 0)
