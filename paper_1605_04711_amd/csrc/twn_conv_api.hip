@@ -329,13 +329,24 @@ WgShape taps_shape(const twn_conv_desc* d, int P, int Q) {
     return WgShape{d->N, d->H, d->W, d->C, d->O, d->R, d->S, P, Q, d->stride_h, d->stride_w, d->dil_h, d->dil_w};
 }
 
+// Three-channel first layers have a kernel of their own, unless an override shapes the general one.
+FirstGradPlan first_grad_plan(const twn_conv_desc* d, int P, int Q) {
+    if (env_int(Env::FIRST, 1) == 0 || env_int(Env::BUFLOAD, 1) == 0 || env_set(Env::WG_BLOCKS) || env_set(Env::WG_KS) ||
+        env_set(Env::WG_ROWS_SPLITS) || env_set(Env::WG_XCD))
+        return FirstGradPlan{};
+    return plan_first_weight_grad(taps_shape(d, P, Q));
+}
+
 // Weight-gradient workspace: [padded copy of X in first-layer mode] + split partials + bias partials.
 size_t weight_grad_bytes(const twn_conv_desc* d, int P, int Q) {
     SmallC sc;
     if (small_c(d, &sc) && d->O % 8 == 0) {
         const int64_t Jp = static_cast<int64_t>(d->R) * sc.Sp * 4;
         const int64_t splits = plan_weight_grad(d->N, P, Q, 8, d->O, d->R, sc.Sp / 2).splits;
-        return sc.x_bytes + static_cast<size_t>((splits * d->O * Jp + 64LL * d->O) * sizeof(float));
+        const size_t general = sc.x_bytes + static_cast<size_t>((splits * d->O * Jp + 64LL * d->O) * sizeof(float));
+        const FirstGradPlan f = first_grad_plan(d, P, Q);
+        const size_t own = f.use ? static_cast<size_t>(f.splits) * d->O * f.J * sizeof(float) : 0;
+        return general > own ? general : own;       // X may turn out not to be aligned for the three-channel kernel
     }
     const int64_t J = static_cast<int64_t>(d->R) * d->S * d->C;
     const WgTapsPlan taps = plan_weight_grad_taps(taps_shape(d, P, Q));
@@ -677,7 +688,15 @@ extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, con
         w.dh = d->dil_h; w.dw = d->dil_w;
         w.xc = d->C;
         SmallC sc;
-        if (dW && small_c(d, &sc) && d->O % 8 == 0) {
+        const bool small = dW && small_c(d, &sc) && d->O % 8 == 0;
+        const FirstGradPlan f = small && aligned(X, 4) && aligned(dY, 16) ? first_grad_plan(d, P, Q) : FirstGradPlan{};
+        if (f.use) {
+            rc = launch_first_weight_grad(taps_shape(d, P, Q), d->pad_h, d->pad_w, f, w.X, w.dY, w.partial, st);
+            if (rc == TWN_OK)
+                rc = launch_first_weight_grad_sum(w.partial, f.splits, d->O, d->C, d->R, d->S, 4 * f.G, dW_beta, dW, st);
+            if (rc != TWN_OK || !dbias) return rc;
+            w.dW = nullptr;                 // the bias gradient is left
+        } else if (small) {
             // first-layer mode: gather from the zero-bordered 4-channel copy (rebuilt here: the call is stateless)
             uint16_t* Xp = static_cast<uint16_t*>(workspace);
             rc = launch_pad_c4(static_cast<const uint16_t*>(X), d->N, d->H, d->W, d->C, d->pad_h, d->pad_w, sc.Hp,

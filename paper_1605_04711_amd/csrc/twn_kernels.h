@@ -185,4 +185,18 @@ struct WgTapsPlan {
 WgTapsPlan plan_weight_grad_taps(const WgShape& w);
 int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipStream_t st);
 
+// Weight gradient of a three-channel first layer (twn_bwd_first.hip): partial tiles [splits][O][(r*G + s/4)*16 + (s%4)*4 + c],
+// i.e. those of the first-layer mode above with pad_sp = 4 G.
+struct FirstGradPlan {
+    int32_t use;                // 0: the general kernel takes the layer
+    int32_t G, J;               // blocks of four taps per filter row, columns of a partial tile
+    int32_t tiles, per, splits; // tiles of 16x16 output pixels, per workgroup, ranges
+};
+FirstGradPlan plan_first_weight_grad(const WgShape& w);
+int32_t launch_first_weight_grad(const WgShape& w, int32_t ph, int32_t pw, const FirstGradPlan& p, const uint16_t* X,
+                                 const uint16_t* dY, float* partial, hipStream_t st);
+// dW = beta*dW + sum of partial tiles in first-layer mode.
+int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
+                                     float beta, float* dW, hipStream_t st);
+
 }  // namespace twn
