@@ -230,7 +230,7 @@ void two_terms(GatherGemm& g) {
 // Strided backward-data as stride-1 problems, one per residue class (a, b) of the output pixels
 // (h = a + sh*u, w = b + sw*v): the taps that reach the class are r = r0 + jr*sh with r0 = (a + pad_h) % sh, the
 // coordinate read is p = u + (a + pad_h - r0)/sh - jr, i.e. an undivided gather with dilation -1.  Used for
-// dilation 1, O % 64 == 0 (every tap is whole K slabs), C % 8 == 0, stride products up to 4.
+// dilation 1, O % 8 == 0, C % 8 == 0, stride products up to 4.
 struct DxClasses {
     int count;                  // classes that have taps
     bool any_empty;             // some class has none: those pixels of dX are zero
@@ -241,12 +241,14 @@ struct DxClasses {
 
 bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
     const int sh = d->stride_h, sw = d->stride_w;
-    if (sh * sw <= 1 || sh * sw > 4 || d->dil_h != 1 || d->dil_w != 1 || d->O % 64 != 0 || d->C % 8 != 0 ||
+    if (sh * sw <= 1 || sh * sw > 4 || d->dil_h != 1 || d->dil_w != 1 || d->O % 8 != 0 || d->C % 8 != 0 ||
         d->variant != TWN_VAR_BF16_POSTSCALE || d->x_dtype != TWN_BF16)
         return false;
-    // several small launches only pay when each class still has enough pixels to fill the chip
-    if (static_cast<int64_t>(d->N) * ((d->H + sh - 1) / sh) * ((d->W + sw - 1) / sw) < env_int(Env::DX_CLASS_MIN_PIXELS, 2048))
-        return false;
+    // Launches of the large kernels (whole slabs per tap) only pay when each class still has enough pixels to fill the chip;
+    // below that, and for taps of no whole slabs, the classes have to fit one launch of the few-tile kernel.
+    const bool enough = static_cast<int64_t>(d->N) * ((d->H + sh - 1) / sh) * ((d->W + sw - 1) / sw) >=
+                        env_int(Env::DX_CLASS_MIN_PIXELS, 2048);
+    if (!enough && env_set(Env::DX_CLASS_MIN_PIXELS)) return false;
     out->count = 0;
     out->any_empty = false;
     out->code_words = 0;
@@ -288,7 +290,26 @@ bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
     out->tb.sh = sh;
     out->tb.sw = sw;
     for (int k = out->count; k <= 4; ++k) out->tb.first_word[k] = out->code_words;
-    return out->count > 0;
+    if (out->count == 0 || (enough && d->O % 64 == 0)) return out->count > 0;
+    if (conv_small_tile(out->g, out->count) == 0) return false;
+    // Against all taps in one problem, most of whose products are zeros: a slab of a tile costs 0.3 us of a CU and 0.16 us of the
+    // chain of its workgroup, the launch that gathers the codes 3.5 (several alphas have it anyway).  (us, dX alone, all taps ->
+    // classes: 5x45x61 pixels, 72 filters 5x5/2 over 40 channels 16.8 -> 15.1; 5x27x25, 200, 5x5/2 over 40, several alphas
+    // 37.6 -> 17.3; 3x14x14, 512, 3x3/2 over 256, several alphas 28.6 -> 12.5, one alpha 14.6 -> 9.5)
+    auto cost = [](const GatherGemm* g, int count) {
+        double slabs = 0.0, chain = 0.0;
+        for (int k = 0; k < count; ++k) {
+            const int kt = k_slabs(g[k].K);
+            slabs += static_cast<double>((g[k].M + 31) / 32) * ((g[k].NC + 31) / 32) * kt;
+            if (0.16 * kt > chain) chain = 0.16 * kt;
+        }
+        const double chip = 0.3 * slabs / 256.0;
+        return chip > chain ? chip : chain;
+    };
+    GatherGemm all{};
+    fill_conv_bwd_data(all, d, P, Q);
+    if (d->alpha_groups > 1) two_terms(all);
+    return conv_small_tile(&all, 1) == 0 || cost(&all, 1) > cost(out->g, out->count) + (d->alpha_groups > 1 ? 0.0 : 3.5);
 }
 
 // Workspace of backward-data, in this order: gathered codes (residue classes; several alphas: repeated for the second
