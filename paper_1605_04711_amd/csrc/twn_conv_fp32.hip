@@ -31,9 +31,11 @@ enum F32Mode : int {
 
 struct F32Args {
     GatherGemm g;
-    FastDivU divIC, divS;
+    FastDivU divIC, divS, divOW, divOH, divTN;
     int64_t tiles;
     int32_t tiles_n;
+    int32_t narrow;         // rows and tiles below 2^31: divisions by multiplication (a 64-bit one costs about a microsecond)
+    int32_t walk;           // short kernel: row blocks per wave
 };
 
 // Parameters of one output column; requested before the sums they are applied to.
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(64 * NW) void gather_gemm_f64_kernel(const F32Args 
     const int kfull = (MODE == kF32Element) ? kb1 : min(kb1, g.K >> 4);
 
     for (int64_t t = blockIdx.x; t < args.tiles; t += gridDim.x) {
-        const int64_t tm = t / args.tiles_n;
+        const int64_t tm = args.narrow ? static_cast<int64_t>(fdiv_u(static_cast<uint32_t>(t), args.divTN)) : t / args.tiles_n;
         const int64_t m0 = tm * 16;
         const int n0 = static_cast<int>(t - tm * args.tiles_n) * BN;
 
@@ -100,11 +102,11 @@ __global__ __launch_bounds__(64 * NW) void gather_gemm_f64_kernel(const F32Args 
         } else {
             int64_t img;
             int oh, ow;
-            if (g.M <= 0x7FFFFFFF) {                    // 64-bit division costs about a microsecond
+            if (args.narrow) {
                 const uint32_t mm = static_cast<uint32_t>(m);
-                const uint32_t row = mm / static_cast<uint32_t>(g.OW);
+                const uint32_t row = fdiv_u(mm, args.divOW);
                 ow = static_cast<int>(mm - row * static_cast<uint32_t>(g.OW));
-                const uint32_t im = row / static_cast<uint32_t>(g.OH);
+                const uint32_t im = fdiv_u(row, args.divOH);
                 oh = static_cast<int>(row - im * static_cast<uint32_t>(g.OH));
                 img = im;
             } else {
@@ -284,6 +286,98 @@ __global__ __launch_bounds__(64 * NW) void gather_gemm_f64_kernel(const F32Args 
     }
 }
 
+// Convolutions whose channel count is no multiple of 4 and whose K is at most 16 KB (KB blocks of 16): a wave walks over row
+// blocks of one column block, independently of the others of its workgroup.  Where an element lies relative to its pixel and the doubles of the codes do not change
+// from row block to row block: both are kept in registers, and a row block costs its loads, its bounds tests and its matrix
+// work; the next block's elements are in flight while this one is multiplied.  36864 pixels x 32 channels, 5x5 over one channel
+// (K = 25): 11.6 -> 8.5 us.
+constexpr int kShortWaves = 4;              // independent waves per workgroup
+template <int NT, int KB>
+__global__ __launch_bounds__(64 * kShortWaves) void gather_gemm_f64_short_kernel(const F32Args args) {
+    const GatherGemm& g = args.g;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, quad = lane >> 4;
+    const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(
+        static_cast<int>(blockIdx.x) * kShortWaves + static_cast<int>(threadIdx.x >> 6)));
+    const float* __restrict__ X = static_cast<const float*>(g.X);
+    const uint32_t* __restrict__ Wq = static_cast<const uint32_t*>(g.Wq);
+    const uint32_t span = fdiv_u(wave, args.divTN);
+    const int n0 = static_cast<int>(wave - span * static_cast<uint32_t>(args.tiles_n)) * 16 * NT;
+    const int64_t rows = (g.M + 15) / 16;
+    const int64_t first = static_cast<int64_t>(span) * args.walk;
+    const int64_t last = first + args.walk < rows ? first + args.walk : rows;
+    if (first >= last) return;
+
+    F32Column col[NT];
+    uint32_t b[KB][4][NT];                  // high halves of the codes' doubles
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        col[j] = f32_column(g, n0 + 16 * j + l16);
+        const uint32_t* wrow = Wq + static_cast<int64_t>(min(n0 + 16 * j + l16, g.NC - 1)) * g.wpr;
+#pragma unroll
+        for (int d = 0; d < KB; ++d) {
+            const uint32_t w = wrow[d] >> (4 * quad);       // rows are padded to 128 codes
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[d][i][j] = (w << (30 - ((i & 1) * 16 + (i >> 1) * 2))) & 0xC0000000u;
+        }
+    }
+    int off[KB][4], th[KB][4], tw[KB][4];   // element k against (ih0, iw0) of the pixel
+#pragma unroll
+    for (int d = 0; d < KB; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = d * 16 + quad * 4 + i;
+            const uint32_t rs = fdiv_u(static_cast<uint32_t>(k), args.divIC), r = fdiv_u(rs, args.divS);
+            th[d][i] = k < g.K ? static_cast<int>(r) * g.dh : -(1 << 28);       // beyond K: outside every image
+            tw[d][i] = static_cast<int>(rs - r * static_cast<uint32_t>(g.S)) * g.dw;
+            off[d][i] = (static_cast<int>(r) * g.dh * g.IW + tw[d][i]) * static_cast<int>(g.xs) + (k - static_cast<int>(rs) * g.IC);
+        }
+    float x[2][KB][4];
+    auto load = [&](int64_t tm, float (&v)[KB][4]) __attribute__((always_inline)) {
+        const int64_t at = tm * 16 + l16;
+        const uint32_t m = static_cast<uint32_t>(at < g.M ? at : g.M - 1);
+        const uint32_t row = fdiv_u(m, args.divOW), img = fdiv_u(row, args.divOH);
+        const int ih0 = static_cast<int>(row - img * static_cast<uint32_t>(g.OH)) * g.sh - g.ph;
+        const int iw0 = static_cast<int>(m - row * static_cast<uint32_t>(g.OW)) * g.sw - g.pw;
+        const int base = ((static_cast<int>(img) * g.IH + ih0) * g.IW + iw0) * static_cast<int>(g.xs);
+#pragma unroll
+        for (int d = 0; d < KB; ++d)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool ok = (static_cast<unsigned>(ih0 + th[d][i]) < static_cast<unsigned>(g.IH)) &
+                                (static_cast<unsigned>(iw0 + tw[d][i]) < static_cast<unsigned>(g.IW));
+                const float t = X[ok ? base + off[d][i] : 0];
+                v[d][i] = ok ? t : 0.0f;
+            }
+    };
+    auto finish = [&](int64_t tm, const float (&v)[KB][4]) __attribute__((always_inline)) {
+        f64x4 acc[NT] = {};
+#pragma unroll
+        for (int d = 0; d < KB; ++d)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(v[d][i]),
+                                                                  __hiloint2double(static_cast<int>(b[d][i][j]), 0), acc[j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t m = tm * 16 + quad + 4 * r;
+                const int n = n0 + 16 * j + l16;
+                if (m < g.M && n < g.NC) f32_tail_store(g, m, n, 0.5 * acc[j][r], col[j]);
+            }
+    };
+    load(first, x[0]);
+    for (int64_t t = first; t < last; t += 2) {
+        if (t + 1 < last) load(t + 1, x[1]);
+        finish(t, x[0]);
+        if (t + 1 >= last) break;
+        if (t + 2 < last) load(t + 2, x[0]);
+        finish(t + 1, x[1]);
+    }
+}
+
 // Sum of the K ranges in a fixed order (float64), then the same tail as the unsplit kernel.
 __global__ __launch_bounds__(256) void fp32_splitk_finish_kernel(const GatherGemm g) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -346,6 +440,19 @@ static void launch_f64(const F32Args& a, int mode, hipStream_t st) {
         gather_gemm_f64_kernel<NT, NW, kF32Element><<<grid, 64 * NW, 0, st>>>(a);
 }
 
+template <int NT>
+static void launch_short(F32Args& a, hipStream_t st) {
+    // about two waves per SIMD, each with a walk of whole row blocks
+    const int64_t rows = (a.g.M + 15) / 16;
+    a.walk = static_cast<int32_t>((rows * a.tiles_n + 2047) / 2048);
+    const int64_t waves = (rows + a.walk - 1) / a.walk * a.tiles_n;
+    const unsigned grid = static_cast<unsigned>((waves + kShortWaves - 1) / kShortWaves);
+    if (a.g.K <= 32)
+        gather_gemm_f64_short_kernel<NT, 2><<<grid, 64 * kShortWaves, 0, st>>>(a);
+    else
+        gather_gemm_f64_short_kernel<NT, 4><<<grid, 64 * kShortWaves, 0, st>>>(a);
+}
+
 int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st) {
     const Fp32Plan p = fp32_plan(g);
     if (p.tiles <= 0) return TWN_ERR_SHAPE;
@@ -356,7 +463,22 @@ int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st) {
     a.divS = make_fastdiv_u(static_cast<uint32_t>(g.S));
     a.tiles = p.tiles;
     a.tiles_n = p.tiles_n;
+    a.narrow = g.M < (1LL << 31) - 16 && p.tiles < (1LL << 31);
+    a.divOW = make_fastdiv_u(static_cast<uint32_t>(g.OW));
+    a.divOH = make_fastdiv_u(static_cast<uint32_t>(g.OH));
+    a.divTN = make_fastdiv_u(static_cast<uint32_t>(p.tiles_n));
+    a.walk = 0;
     const int mode = g.plain_gemm ? kF32Gemm : (g.IC % 4 == 0) ? kF32Quad : kF32Element;
+    // short K, no taps to divide: offsets in 32 bits, one wave per tile in the plan
+    if (mode == kF32Element && g.K <= 64 && p.nw == 1 && g.splits <= 1 && a.narrow && g.divh == 1 && g.divw == 1 &&
+        g.M / (static_cast<int64_t>(g.OH) * g.OW) * g.IH * g.IW * g.xs < (1LL << 30) &&
+        static_cast<int64_t>(g.R) * abs(g.dh) < (1 << 24) && static_cast<int64_t>(g.S) * abs(g.dw) < (1 << 24) &&
+        (static_cast<int64_t>(g.R) * abs(g.dh) * g.IW + static_cast<int64_t>(g.S) * abs(g.dw)) * g.xs < (1LL << 30)) {
+        if (p.nt == 4) launch_short<4>(a, st);
+        else if (p.nt == 2) launch_short<2>(a, st);
+        else launch_short<1>(a, st);
+        return launch_status();
+    }
     switch (p.nt * 32 + p.nw) {
         case 32 + 1: launch_f64<1, 1>(a, mode, st); break;
         case 32 + 2: launch_f64<1, 2>(a, mode, st); break;
