@@ -239,7 +239,7 @@ struct DxClasses {
     int64_t code_words;
 };
 
-bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
+bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, bool two, DxClasses* out) {
     const int sh = d->stride_h, sw = d->stride_w;
     if (sh * sw <= 1 || sh * sw > 4 || d->dil_h != 1 || d->dil_w != 1 || d->O % 8 != 0 || d->C % 8 != 0 ||
         d->variant != TWN_VAR_BF16_POSTSCALE || d->x_dtype != TWN_BF16)
@@ -277,7 +277,7 @@ bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
             g.divh = g.divw = 1;
             g.K = nr * ns * d->O;
             g.wpr = static_cast<int32_t>(twn_packed_words_per_row(g.K));
-            if (d->alpha_groups > 1) two_terms(g);
+            if (two) two_terms(g);
             g.plain_gemm = 0;
             g.orU = U; g.orV = V; g.orH = d->H; g.orW = d->W;
             g.ora = a; g.orb = b; g.orsh = sh; g.orsw = sw;
@@ -308,8 +308,8 @@ bool strided_dx_classes(const twn_conv_desc* d, int P, int Q, DxClasses* out) {
     };
     GatherGemm all{};
     fill_conv_bwd_data(all, d, P, Q);
-    if (d->alpha_groups > 1) two_terms(all);
-    return conv_small_tile(&all, 1) == 0 || cost(&all, 1) > cost(out->g, out->count) + (d->alpha_groups > 1 ? 0.0 : 3.5);
+    if (two) two_terms(all);
+    return conv_small_tile(&all, 1) == 0 || cost(&all, 1) > cost(out->g, out->count) + (two ? 0.0 : 3.5);
 }
 
 // Workspace of backward-data, in this order: gathered codes (residue classes; several alphas: repeated for the second
@@ -324,9 +324,10 @@ struct DxPlan {
     size_t bytes() const { return code_bytes + scaled_bytes + one_bytes + split_bytes; }
 };
 
-void plan_dx(const twn_conv_desc* d, int P, int Q, DxPlan* p, bool allow_classes) {
-    p->two = d->alpha_groups > 1;
-    p->classes = allow_classes && strided_dx_classes(d, P, Q, &p->cl);
+// `inside`: several alphas stay with the codes (alpha_in of the problems) instead of making two terms of dY.
+void plan_dx(const twn_conv_desc* d, int P, int Q, DxPlan* p, bool allow_classes, bool inside = false) {
+    p->two = d->alpha_groups > 1 && !inside;
+    p->classes = allow_classes && strided_dx_classes(d, P, Q, p->two, &p->cl);
     p->g = GatherGemm{};
     fill_conv_bwd_data(p->g, d, P, Q);
     p->code_bytes = p->scaled_bytes = p->one_bytes = p->split_bytes = 0;
@@ -576,6 +577,24 @@ extern "C" size_t twn_conv2d_bwd_ste_workspace_bytes(const twn_conv_desc* d) {
     return a > b ? a : b;
 }
 
+// Preparation of residue classes: their codes, one copy, and the clearing of dX where a class has no taps.
+static DxPrep class_prep(const twn_conv_desc* d, const DxClasses& cl, const uint32_t* packed_T, uint32_t* codes, void* dX) {
+    DxPrep q{};
+    q.O = d->O;
+    q.packed_T = packed_T;
+    q.C = d->C;
+    q.wprT = static_cast<int32_t>(twn_packed_words_per_row(static_cast<int64_t>(d->R) * d->S * d->O));
+    q.S = d->S;
+    q.terms = 1;
+    q.tb = cl.tb;
+    q.codes = codes;
+    if (cl.any_empty) {
+        q.zero = dX;
+        q.zero16 = static_cast<int64_t>(d->N) * d->H * d->W * d->C * (d->y_dtype == TWN_F32 ? 4 : 2) / 16;
+    }
+    return q;
+}
+
 // dX of the straight-through backward: one contraction over dY (one per residue class of a strided layer).
 static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* dY, const uint32_t* packed_T, const float* alpha,
                              void* dX, void* workspace, size_t workspace_bytes, hipStream_t st) {
@@ -613,8 +632,36 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
         if (env_int(Env::TILE, 0) == 0 && env_int(Env::C64, 1) != 0 && conv_c64_applicable(g))
             return launch_conv_c64_scaled(g, alpha, d->O / d->alpha_groups, st);
     }
+    if (p.two && d->variant == TWN_VAR_BF16_POSTSCALE && d->y_dtype == TWN_BF16 && d->O <= kSmallAlphaMax &&
+        conv_small_tile(gs, count) != 0) {
+        // Problems that would run in the few-tile kernel take the alphas with their codes: nothing is scaled (a longer K is cut over
+        // workgroups, with two terms of alpha * dY).  bf16 outputs only: two terms of alpha are as
+        // good as two of alpha * dY on average (2-norm error 2.0e-6 .. 3.1e-6 by how the alphas lie to powers of two, against 2.45e-6),
+        // which one rounding of dX to bf16 hides (1.655e-3 either way) and a float32 dX would show.
+        DxPlan in;
+        plan_dx(d, P, Q, &in, p.classes, true);
+        const int n = in.classes ? in.cl.count : 1;
+        GatherGemm* g = in.classes ? in.cl.g : &in.g;
+        const int tile = conv_small_tile(g, n);
+        if (tile != 0) {
+            for (int k = 0; k < n; ++k) {
+                g[k].X = dY;
+                g[k].Wq = in.classes ? codes + in.cl.tb.first_word[k] : packed_T;
+                g[k].alpha = alpha;
+                g[k].alpha_in = alpha;
+                g[k].alpha_in_rows = d->O / d->alpha_groups;
+                g[k].Y = dX;
+                g[k].splits = 1;
+            }
+            if (in.classes) {
+                rc = launch_dx_prep(class_prep(d, in.cl, packed_T, codes, dX), st);
+                if (rc != TWN_OK) return rc;
+            }
+            return launch_conv_small(g, n, tile, st);
+        }
+    }
     if (p.two || p.classes) {
-        DxPrep q{};
+        DxPrep q = p.classes ? class_prep(d, p.cl, packed_T, codes, dX) : DxPrep{};
         q.O = d->O;
         if (p.two) {
             q.dY = static_cast<const uint16_t*>(dY);
@@ -631,10 +678,6 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
         q.terms = p.two ? 2 : 1;
         q.tb = p.classes ? p.cl.tb : p.tb;
         q.codes = codes;
-        if (p.classes && p.cl.any_empty) {
-            q.zero = dX;
-            q.zero16 = static_cast<int64_t>(d->N) * d->H * d->W * d->C * (d->y_dtype == TWN_F32 ? 4 : 2) / 16;
-        }
         rc = launch_dx_prep(q, st);
         if (rc != TWN_OK) return rc;
     }

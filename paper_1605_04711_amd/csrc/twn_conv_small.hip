@@ -47,7 +47,7 @@ enum SmallMode : int {
 // Bytes of LDS one wave uses: DEPTH slabs of activations and two groups of four slabs of codes.
 constexpr int small_wave_bytes(int mt, int nt, int depth) { return depth * mt * 4096 + 2 * nt * 2048; }
 
-template <int MT, int NT, int NW, int MODE, int NP, int DEPTH>
+template <int MT, int NT, int NW, int MODE, int NP, int DEPTH, bool ALPHA>
 __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP> args) {
     constexpr int BM = 32 * MT, BN = 32 * NT;
     constexpr int QUADS = BM * BN / 4;                          // groups of four channels of one pixel
@@ -93,7 +93,8 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
             mul[i][e] = add[i][e] = 0.0f;
             if (ncol0[i] + e < g.NC) {
                 const int ag = (g.rows_per_group >= g.NC) ? 0 : (ncol0[i] + e) / g.rows_per_group;
-                mul[i][e] = 0.5f * g.alpha[ag] * (g.scale ? g.scale[ncol0[i] + e] : 1.0f);      // codes were +-2
+                // codes were +-2
+                mul[i][e] = (ALPHA ? 1.0f : 0.5f * g.alpha[ag]) * (g.scale ? g.scale[ncol0[i] + e] : 1.0f);
                 add[i][e] = g.shift ? g.shift[ncol0[i] + e] : 0.0f;
             }
         }
@@ -206,9 +207,29 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.0f;
 
+    // the terms of alpha_in: [hi | lo], whole slabs; requested before the first slabs, written after
+    const int span = (g.IC + 63) & ~63;
+    uint16_t* const terms = reinterpret_cast<uint16_t*>(smem + NW * WAVE_BYTES);
+    const uint32_t lds_terms = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+        (__attribute__((address_space(3))) unsigned char*)(smem + NW * WAVE_BYTES)));
+    float my_alpha = 0.0f;
+    if constexpr (ALPHA) {
+        if (tid < g.IC) my_alpha = g.alpha_in[tid / g.alpha_in_rows];
+    }
+
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d)
         if (d < ns) fetch(d, d);
+
+    if constexpr (ALPHA) {
+        for (int c = tid; c < span; c += 64 * NW) {
+            const float v = c == tid ? my_alpha : (c < g.IC ? g.alpha_in[c / g.alpha_in_rows] : 0.0f);
+            const uint16_t hi = f32_to_bf16(v);
+            terms[c] = hi;
+            terms[span + c] = f32_to_bf16(v - bf16_to_f32(hi));
+        }
+        __syncthreads();
+    }
 
     uint32_t aoff[4];               // this lane's fragment of step kk inside a stage (row lrow; the next 32 rows: + 4096)
 #pragma unroll
@@ -229,34 +250,64 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
             }
             u32x2 w[NT];
             u32x4 x[4][MT];
+            u32x4 al[4][2];
+            constexpr int READS = MT + (ALPHA ? 2 : 0);         // of a step
             const uint32_t cbase = lds_mine + DEPTH * STAGE + ((sg >> 2) & 1) * CODES + lrow * 64 + lh * 8 + ((p ^ ((lrow >> 2) & 3)) * 16);
             lds_read64_n<NT, 32 * 64>(w, cbase);
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) lds_read128_n<MT, 4096>(x[kk], aoff[kk] + st * STAGE);
+            for (int kk = 0; kk < 4; ++kk) {
+                lds_read128_n<MT, 4096>(x[kk], aoff[kk] + st * STAGE);
+                if constexpr (ALPHA) {
+                    // reduction channel of this half's chunk
+                    uint32_t c = static_cast<uint32_t>((s0 + s) * 64 + (lh * 4 + kk) * 8);
+                    if constexpr (MODE == kSmallTap) {
+                        const uint32_t first = static_cast<uint32_t>(s0 + s) * 64u;          // wave-uniform
+                        c -= fdiv_u(first, a.divIC) * static_cast<uint32_t>(g.IC);
+                    } else if constexpr (MODE == kSmallChunk) {
+                        c -= fdiv_u(c, a.divIC) * static_cast<uint32_t>(g.IC);
+                    }
+                    lds_read128<0>(al[kk][0], lds_terms + c * 2u);
+                    lds_read128<0>(al[kk][1], lds_terms + static_cast<uint32_t>(span + static_cast<int>(c)) * 2u);
+                }
+            }
             static_for<4>([&](auto kk_tag) __attribute__((always_inline)) {
                 constexpr int kk = decltype(kk_tag)::value;
-                lds_wait<(3 - kk) * MT>();
+                lds_wait<(3 - kk) * READS>();
                 if constexpr (kk == 0) lds_ready<NT>(w);
                 lds_ready<MT>(x[kk]);
+                if constexpr (ALPHA) lds_ready<2>(al[kk]);
                 if constexpr (kk == 3) {
                     if (s + DEPTH < ns) fetch(s + DEPTH, st);   // every read of this stage has returned
                 }
-                u32x4 wf[NT];
+                u32x4 wf[NT], wl[NT];
 #pragma unroll
                 for (int ni = 0; ni < NT; ++ni)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         constexpr int half = (kk & 1) * 4;
                         const int i = half + e;                 // field i of both half-words -> bits [14,15] of two bf16
-                        wf[ni][e] = (w[ni][kk >> 1] & (0xC000C000u >> (14 - 2 * i))) << (14 - 2 * i);
+                        if constexpr (ALPHA) {
+                            typedef short s16x2 __attribute__((ext_vector_type(2)));
+                            const uint32_t f = w[ni][kk >> 1] << (14 - 2 * i), sign = f & 0x80008000u;
+                            const uint32_t on = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, f << 1) >> 15);
+                            wf[ni][e] = (al[kk][0][e] & on) ^ sign;
+                            wl[ni][e] = (al[kk][1][e] & on) ^ sign;
+                        } else {
+                            wf[ni][e] = (w[ni][kk >> 1] & (0xC000C000u >> (14 - 2 * i))) << (14 - 2 * i);
+                        }
                     }
 #pragma unroll
                 for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
-                    for (int ni = 0; ni < NT; ++ni)
+                    for (int ni = 0; ni < NT; ++ni) {
                         acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[ni]),
                                                                               __builtin_bit_cast(bf16x8, x[kk][mi]),
                                                                               acc[mi][ni], 0, 0, 0);
+                        if constexpr (ALPHA)
+                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wl[ni]),
+                                                                                  __builtin_bit_cast(bf16x8, x[kk][mi]),
+                                                                                  acc[mi][ni], 0, 0, 0);
+                    }
             });
             st = (st + 1 == DEPTH) ? 0 : st + 1;
         });
@@ -366,22 +417,32 @@ SmallProblem make_problem(const GatherGemm& g, int bm, int bn) {
     return p;
 }
 
-template <int MT, int NT, int NW, int MODE, int NP>
-int32_t launch_small_kernel(const SmallArgs<NP>& a, uint32_t width, int count, hipStream_t st) {
-    constexpr int DEPTH = 3;
-    constexpr int SMEM = NW * small_wave_bytes(MT, NT, DEPTH);
-    static_assert(SMEM <= 160 * 1024, "LDS budget");
-    auto k = conv_small_kernel<MT, NT, NW, MODE, NP, DEPTH>;
+template <int MT, int NT, int NW, int MODE, int NP, bool ALPHA>
+int32_t launch_small_build(const SmallArgs<NP>& a, uint32_t width, int count, hipStream_t st) {
+    // the table of terms takes the third slab's place where both do not fit
+    constexpr int DEPTH = ALPHA && NT == 2 ? 2 : 3;
+    constexpr int STAGES = NW * small_wave_bytes(MT, NT, DEPTH);
+    constexpr int MOST = STAGES + (ALPHA ? kSmallAlphaMax * 4 : 0);
+    static_assert(MOST <= 160 * 1024, "LDS budget");
+    const int SMEM = STAGES + (ALPHA ? ((a.p[0].g.IC + 63) & ~63) * 4 : 0);
+    auto k = conv_small_kernel<MT, NT, NW, MODE, NP, DEPTH, ALPHA>;
     // more than 64 KB of dynamic LDS has to be allowed once per kernel
     static std::once_flag once;
     static bool allowed = false;
     std::call_once(once, [&] {
         allowed = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      SMEM) == hipSuccess;
+                                      MOST) == hipSuccess;
     });
     if (!allowed) return TWN_ERR_HIP;
     k<<<dim3(width, static_cast<unsigned>(count)), dim3(64 * NW), SMEM, st>>>(a);
     return launch_status();
+}
+
+template <int MT, int NT, int NW, int MODE, int NP>
+int32_t launch_small_kernel(const SmallArgs<NP>& a, uint32_t width, int count, hipStream_t st) {
+    if (!a.p[0].g.alpha_in) return launch_small_build<MT, NT, NW, MODE, NP, false>(a, width, count, st);
+    if (a.p[0].g.IC > kSmallAlphaMax) return TWN_ERR_UNSUPPORTED;
+    return launch_small_build<MT, NT, NW, MODE, NP, true>(a, width, count, st);
 }
 
 template <int MT, int NT, int NW>

@@ -42,6 +42,10 @@ struct GatherGemm {
     int32_t orU, orV, orH, orW, ora, orb, orsh, orsw;
     float* partial;         // split-K workspace [splits][M][NC] float32 (float64 on the float32 path; null when splits == 1)
     int32_t splits;         // K is cut into this many ranges of whole 64-wide slabs
+    // Backward-data with several alphas, inside the contraction: the code of reduction channel c counts alpha_in[c / alpha_in_rows]
+    // times, as two bf16 terms (null: 1).  Only the few-tile kernel takes it.
+    const float* alpha_in;
+    int32_t alpha_in_rows;
 };
 
 // Number of K ranges the MFMA path uses for this problem (1 = no split); a pure function of the
@@ -106,6 +110,7 @@ int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int ks, int np, int
 // Problems of few output tiles: up to four of them in one launch, the K slabs of a tile shared out over the waves of
 // one workgroup; conv_small_tile (a pure function of the problems) names the tile, 0 when other kernels are better.
 int conv_small_tile(const GatherGemm* gs, int count);
+constexpr int kSmallAlphaMax = 4096;        // reduction channels with an alpha of their own that its table in LDS holds
 int32_t launch_conv_small(const GatherGemm* gs, int count, int tile, hipStream_t st);
 
 // 3x3 stride-1 convolutions over 64 input channels (forward, or backward-data with mirrored taps), bf16 in and out,

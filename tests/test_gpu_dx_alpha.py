@@ -1,0 +1,46 @@
+"""Backward-data with several alphas taken with their codes: every tile of the few-tile kernel, taps of whole slabs, of single
+chunks and plain products, one problem and residue classes, filters per alpha, the largest table and the first beyond it.  One
+rounding to bf16 is at most 2^-9 = 1.95e-3 of a value, so the 2-norm error stays below 2.0e-3 with the terms' own 3e-6; with one
+term of alpha dropped it would be 2.3e-3 (two roundings of 1.66e-3 each).  float32 outputs keep the terms of alpha * dY (2^-18 of a product)."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import conv as oc
+from oracle import ternarize as ot
+from paper_1605_04711_amd import api
+from paper_1605_04711_amd import workloads as wl
+from parity import BF16_TOL, rel_err, to_dev_bf16, to_dev_f32, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,h,w,c,o,r,stride,pad,dil,per", [
+    (1, 7, 7, 64, 128, 3, 1, 1, 1, 1),        # 32x32 tiles, whole slabs
+    (3, 14, 14, 128, 192, 3, 1, 1, 1, 1),     # 32x64 tiles, eight waves
+    (5, 28, 27, 200, 128, 3, 1, 1, 1, 4),     # four waves, several filters per alpha
+    (2, 9, 11, 40, 72, 3, 1, 1, 2, 1),        # chunks that find their taps, dilation
+    (2, 13, 11, 40, 200, 5, 2, 2, 1, 1),      # residue classes, chunks
+    (2, 12, 12, 64, 512, 3, 2, 1, 1, 2),      # residue classes, whole slabs
+    (33, 1, 1, 72, 1000, 1, 1, 0, 1, 1),      # plain product, K = 1000
+    (9, 1, 1, 16, 4096, 1, 1, 0, 1, 1),       # the largest table
+    (9, 1, 1, 16, 4104, 1, 1, 0, 1, 1)])      # beyond it: terms of alpha * dY
+def test_dx_alpha(n, h, w, c, o, r, stride, pad, dil, per):
+    rng = np.random.default_rng(n * h + o)
+    geo = (stride,) * 2, (pad,) * 2, (dil,) * 2
+    groups = o // per
+    wt = (rng.standard_normal((o, c, r, r)) * 0.05 * np.exp(rng.standard_normal((o, 1, 1, 1)))).astype(np.float32)
+    if per == 1:
+        wt[o // 2] = 0.0                      # an alpha of zero
+    tw = api.twn_ternarize(to_dev_f32(wt), 0.7, groups=groups, transposed=True)
+    codes, _, alpha, _ = ot.ternarize(wt, 0.7, groups=groups)
+    p, q = (h + 2 * pad - dil * (r - 1) - 1) // stride + 1, (w + 2 * pad - dil * (r - 1) - 1) // stride + 1
+    x = to_dev_bf16(np.zeros((n, h, w, c), np.float32))
+    dy = wl.bf16_round((rng.standard_normal((n, p, q, o)) * 1e-5).astype(np.float32))
+    ref = oc.conv2d_bwd_data(dy, codes, alpha, (n, h, w, c), *geo)
+    for dtype, norm, worst in ((torch.bfloat16, 2.0e-3, BF16_TOL), (torch.float32, 4e-6, 2e-3)):
+        dx, _, _ = api.twn_conv2d_bwd_ste(x, to_dev_bf16(dy), tw, *geo, need_dw=False, dx_dtype=dtype)
+        got = to_host_f64(dx)
+        assert np.linalg.norm(got - ref) <= norm * np.linalg.norm(ref)
+        assert rel_err(got, ref) <= worst
