@@ -660,6 +660,18 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
             return launch_conv_small(g, n, tile, st);
         }
     }
+    if (p.two && !p.classes && d->variant == TWN_VAR_BF16_POSTSCALE && d->y_dtype == TWN_BF16) {
+        // the same in the persistent kernel
+        GatherGemm g{};
+        fill_conv_bwd_data(g, d, P, Q);
+        g.X = dY;
+        g.Wq = packed_T;
+        g.alpha = g.alpha_in = alpha;
+        g.alpha_in_rows = d->O / d->alpha_groups;
+        g.Y = dX;
+        g.splits = 1;
+        if (gather_gemm_splits(p.g) <= 1 && conv_stream_alpha_applicable(g)) return launch_conv_stream_alpha(g, st);
+    }
     if (p.two || p.classes) {
         DxPrep q = p.classes ? class_prep(d, p.cl, packed_T, codes, dX) : DxPrep{};
         q.O = d->O;

@@ -12,6 +12,13 @@
 // for its own loads of the next slab (s_waitcnt vmcnt) before it arrives, a compute wave arrives when it has
 // finished the first half of the current slab; after the barrier the load waves refill the stage of the
 // previous slab.  Four stages, so that a load has two slab times to land.
+//
+// ALPHA: backward-data with several alphas (alpha_in of the problem).  alpha of a reduction channel, as two bf16 terms hi = bf16(alpha)
+// and lo = bf16(alpha - hi), replaces the 2 of its codes, and a fragment of dY is multiplied by both: against two terms of alpha * dY
+// side by side, half the slabs, half the fragment reads per MFMA and no launch that scales dY.  The terms lie in LDS; a step
+// reads the sixteen of the step after the next (the same for all lanes of a half).  dX with the scaling launch before (us): 64x28x28,
+// 128 -> 128 channels 3x3 54.3 -> 39.5; 64x14x14, 256 47.2 -> 35.3; 64x7x7, 512 49.5 -> 40.4; 128x16x16, 256 84.8 -> 73.7;
+// 64x40x40, 256 233 -> 216; 20x56x56, 1x1, 512 filters over 128 53.6 -> 20.4.
 #include <mutex>
 
 #include "twn_kernels.h"
@@ -51,7 +58,7 @@ struct StreamPcArgs {
     int32_t spt;                // 64-channel slabs per tap (IC / 64)
 };
 
-template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, int OCC, int KS, int NP>
+template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, int OCC, int KS, int NP, bool ALPHA = false>
 // (the second launch bound is in waves per SIMD)
 __global__ __launch_bounds__(64 * (WM * WN * KS + NP), (OCC * (WM * WN * KS + NP) + 3) / 4)
 void conv_stream_pc_kernel(const StreamPcArgs a) {
@@ -86,6 +93,8 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     float* colbuf = reinterpret_cast<float*>(smem + STAGES * STAGE_BYTES);          // [2][2][BN]: mul, add of even / odd tiles
     unsigned char* dummy = smem + STAGES * STAGE_BYTES + 4 * BN * 4;                // 1 KB sink of the padding loads
+    uint16_t* const terms = reinterpret_cast<uint16_t*>(dummy + 1024);              // ALPHA: [hi | lo] of alpha_in
+    static_assert(!ALPHA || KS == 1, "the slabs of a wave are consecutive");
 
     const GatherGemm& g = a.g;
     const int tid = threadIdx.x;
@@ -260,7 +269,7 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         cp_shift = 0.0f;
         if (tid < BN && ncol < g.NC) {
             const int ag = (g.rows_per_group >= g.NC) ? 0 : ncol / g.rows_per_group;
-            cp_alpha = g.alpha[ag];
+            cp_alpha = ALPHA ? 2.0f : g.alpha[ag];
             if (g.scale) cp_scale = g.scale[ncol];
             if (g.shift) cp_shift = g.shift[ncol];
         }
@@ -287,6 +296,13 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     u32x2 breg[2][NI];      // packed codes of the slab being multiplied / of the next slab
     u32x4 afrag[2][MI];     // activation fragments of step kk in set kk & 1
     u32x4 bfrag[2][NI];     // expanded codes of step kk in set kk & 1
+    u32x4 blow[2][NI];      // ALPHA: the same with the low terms
+    u32x4 al[2][2];         // ALPHA: high and low terms of step kk in set kk & 1
+    int c_cur = 0, c_next = 0;      // ALPHA: first reduction channel of the slab being multiplied / of the next
+    const uint32_t term_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+        (__attribute__((address_space(3))) unsigned char*)(dummy + 1024))) + static_cast<uint32_t>(lh) * 64u;
+    const uint32_t term_low = static_cast<uint32_t>(a.spt) * 128u;      // 64 * spt channels of two bytes
+    auto after = [&](int c) __attribute__((always_inline)) { return c + 64 == a.spt * 64 ? 0 : c + 64; };
 
     uint32_t kmask[8];
     kmask[0] = sgpr_const<static_cast<int>(0xC000C000u >> 14)>();
@@ -300,7 +316,15 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     auto expand = [&](auto kk_tag, auto ni_tag, auto e_tag, const u32x2* br, u32x4* out) __attribute__((always_inline)) {
         constexpr int kk = decltype(kk_tag)::value, ni = decltype(ni_tag)::value, e = decltype(e_tag)::value;
         constexpr int i = (kk & 1) * 4 + e;
-        out[ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
+        if constexpr (ALPHA) {
+            typedef short s16x2 __attribute__((ext_vector_type(2)));
+            const uint32_t f = br[ni][kk >> 1] << (14 - 2 * i), sign = f & 0x80008000u;
+            const uint32_t on = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, f << 1) >> 15);
+            out[ni][e] = (al[kk & 1][0][e] & on) ^ sign;
+            blow[kk & 1][ni][e] = (al[kk & 1][1][e] & on) ^ sign;
+        } else {
+            out[ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
+        }
     };
 
     // One MFMA step (see gather_gemm_dma_kernel): fragment reads and code expansion of the next step are placed
@@ -308,14 +332,16 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     auto step = [&](auto kk_tag, auto cur_tag, int stage, int next) __attribute__((always_inline)) {
         constexpr int KK = decltype(kk_tag)::value;
         constexpr int CUR = decltype(cur_tag)::value;
-        constexpr int NM = MI * NI;
+        constexpr int TERMS = ALPHA ? 2 : 1;
+        constexpr int NM = MI * NI * TERMS;
         constexpr int SET = KK & 1, NSET = SET ^ 1;
         constexpr int KN = (KK + 1) & 3;
         constexpr int BSRC = (KK == 3) ? (CUR ^ 1) : CUR;
         constexpr int P_RA = MI;
         constexpr int P_RB = (KK == 2) ? 1 : 0;
+        constexpr int P_AL = ALPHA ? 2 : 0;
         constexpr int P_D = 4 * NI;
-        constexpr int P = P_RA + P_RB + P_D;
+        constexpr int P = P_RA + P_RB + P_AL + P_D;
         const uint32_t a_addr = lds_base + ((KK == 3) ? next : stage) * STAGE_BYTES + aoff[KN];
         auto piece = [&](auto p_tag) __attribute__((always_inline)) {
             constexpr int pp = decltype(p_tag)::value;
@@ -323,18 +349,23 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
                 lds_read128<pp * 32 * 128>(afrag[NSET][pp], a_addr);
             } else if constexpr (pp < P_RA + P_RB) {
                 lds_read64_n<NI, 32 * 16>(breg[CUR ^ 1], lds_base + next * STAGE_BYTES + boff);
+            } else if constexpr (pp < P_RA + P_RB + P_AL) {
+                // terms of the step after the next, whose set the expansion before this step has used up
+                constexpr int term = pp - P_RA - P_RB;
+                const uint32_t at = term_base + static_cast<uint32_t>(KK < 2 ? c_cur : c_next) * 2u + (term ? term_low : 0u);
+                lds_read128<((KK + 2) & 3) * 16>(al[SET][term], at);
             } else {
-                constexpr int qq = pp - P_RA - P_RB;
+                constexpr int qq = pp - P_RA - P_RB - P_AL;
                 expand(std::integral_constant<int, KN>{}, std::integral_constant<int, qq / 4>{},
                        std::integral_constant<int, qq % 4>{}, breg[BSRC], bfrag[NSET]);
             }
         };
         static_for<NM>([&](auto j_tag) __attribute__((always_inline)) {
             constexpr int jj = decltype(j_tag)::value;
-            constexpr int mi = jj / NI, ni = jj % NI;
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bfrag[SET][ni]),
-                                                                  __builtin_bit_cast(bf16x8, afrag[SET][mi]),
-                                                                  acc[mi][ni], 0, 0, 0);
+            constexpr int mi = jj % (MI * NI) / NI, ni = jj % NI;      // ALPHA: all high terms, then all low ones
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8, jj < MI * NI ? bfrag[SET][ni] : blow[SET][ni]),
+                __builtin_bit_cast(bf16x8, afrag[SET][mi]), acc[mi][ni], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             static_for<P>([&](auto p_tag) __attribute__((always_inline)) {
                 constexpr int pp = decltype(p_tag)::value;
@@ -344,6 +375,7 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         });
         lds_wait<0>();
         lds_ready<MI>(afrag[NSET]);
+        if constexpr (ALPHA) lds_ready<2>(al[SET]);
         if constexpr (KK == 2) lds_ready<NI>(breg[CUR ^ 1]);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -441,15 +473,36 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     // ---- prologue: column parameters of the first tile; the load waves bring the first slab ----
     colparam_load(tile_id(0));
     acc_clear();
+    if constexpr (ALPHA) {
+        const int span = a.spt * 64;
+        for (int c = tid; c < span; c += 64 * NWC) {
+            const float v = c < g.IC ? g.alpha_in[c / g.alpha_in_rows] : 0.0f;
+            const uint16_t hi = f32_to_bf16(v);
+            terms[c] = hi;
+            terms[span + c] = f32_to_bf16(v - bf16_to_f32(hi));
+        }
+        c_next = KTS > 1 ? after(0) : 0;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // visible after the barrier
+    }
     TWN_PCOARSE(1);
     __builtin_amdgcn_s_barrier();                           // first slab landed (the load waves waited for it)
     asm volatile("" ::: "memory");
     TWN_PCOARSE(2);
     lds_read64_n<NI, 32 * 16>(breg[0], lds_base + boff);
     lds_read128_n<MI, 32 * 128>(afrag[0], lds_base + aoff[0]);
+    if constexpr (ALPHA) {
+        lds_read128<0>(al[0][0], term_base);
+        lds_read128<0>(al[0][1], term_base + term_low);
+        lds_read128<16>(al[1][0], term_base);
+        lds_read128<16>(al[1][1], term_base + term_low);
+    }
     lds_wait<0>();
     lds_ready<NI>(breg[0]);
     lds_ready<MI>(afrag[0]);
+    if constexpr (ALPHA) {
+        lds_ready<2>(al[0]);
+        lds_ready<2>(al[1]);
+    }
     static_for<4 * NI>([&](auto q_tag) __attribute__((always_inline)) {
         constexpr int qq = decltype(q_tag)::value;
         expand(std::integral_constant<int, 0>{}, std::integral_constant<int, qq / 4>{},
@@ -485,7 +538,14 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
 #endif
         const int done = stage;
         stage = next;
-        if (++kt == KTS) {
+        ++kt;
+        if constexpr (ALPHA) {
+            // the slab after a tile's last one is the first of the next tile
+            c_cur = c_next;
+            c_next = kt + 1 == KTS ? 0 : after(c_cur);
+            if (kt == KTS) c_next = KTS > 1 ? after(0) : 0;
+        }
+        if (kt == KTS) {
             kt = 0;
             TWN_PCOARSE(3 + 2 * ct);
             epilogue(done);
@@ -514,13 +574,15 @@ int pc_num_cus() {
     return cus;
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, int OCC, int KS, int NP>
+constexpr int kStreamAlphaMax = 1024;       // reduction channels of the table of terms: two workgroups per CU still fit
+
+template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, int OCC, int KS, int NP, bool ALPHA = false>
 int32_t launch_pc_kernel(const StreamPcArgs& a, hipStream_t st) {
-    constexpr int SMEM = STAGES * KS * (BM * 128 + BN * 16) + 4 * BN * 4 + 1024;
+    constexpr int SMEM = STAGES * KS * (BM * 128 + BN * 16) + 4 * BN * 4 + 1024 + (ALPHA ? kStreamAlphaMax * 4 : 0);
     constexpr int THREADS = 64 * (WM * WN * KS + NP);
     static_assert(SMEM <= 160 * 1024, "LDS budget");
     static_assert(THREADS <= 1024, "workgroup size");
-    auto k = conv_stream_pc_kernel<BM, BN, WM, WN, STAGES, GEMM, OCC, KS, NP>;
+    auto k = conv_stream_pc_kernel<BM, BN, WM, WN, STAGES, GEMM, OCC, KS, NP, ALPHA>;
     static std::once_flag once;
     static int per_cu = 0;
     std::call_once(once, [&] {
@@ -540,7 +602,7 @@ int32_t launch_pc_kernel(const StreamPcArgs& a, hipStream_t st) {
     return launch_status();
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int OCC, int KS, int NP>
+template <int BM, int BN, int WM, int WN, int STAGES, int OCC, int KS, int NP, bool ALPHA = false>
 int32_t launch_pc_tile(const GatherGemm& g, hipStream_t st) {
     const int64_t tiles_n = (g.NC + BN - 1) / BN;
     const int64_t tiles = ((g.M + BM - 1) / BM) * tiles_n;
@@ -550,7 +612,7 @@ int32_t launch_pc_tile(const GatherGemm& g, hipStream_t st) {
     a.divOW = make_fastdiv_u(static_cast<uint32_t>(g.OW));
     a.divOH = make_fastdiv_u(static_cast<uint32_t>(g.OH));
     a.divTN = make_fastdiv_u(static_cast<uint32_t>(tiles_n));
-    a.spt = g.plain_gemm ? 1 : g.IC / 64;
+    a.spt = !g.plain_gemm ? g.IC / 64 : ALPHA ? g.K / 64 : 1;
     a.divSPT = make_fastdiv_u(static_cast<uint32_t>(a.spt));
     a.divS = make_fastdiv_u(static_cast<uint32_t>(g.S));
     const int64_t in_rows = g.plain_gemm ? g.M : (g.M / (static_cast<int64_t>(g.OH) * g.OW)) * g.IH * g.IW;
@@ -560,8 +622,8 @@ int32_t launch_pc_tile(const GatherGemm& g, hipStream_t st) {
     a.tiles = static_cast<uint32_t>(tiles);
     a.tiles_n = static_cast<uint32_t>(tiles_n);
     a.KT = g.K / 64;
-    return g.plain_gemm ? launch_pc_kernel<BM, BN, WM, WN, STAGES, true, OCC, KS, NP>(a, st)
-                        : launch_pc_kernel<BM, BN, WM, WN, STAGES, false, OCC, KS, NP>(a, st);
+    return g.plain_gemm ? launch_pc_kernel<BM, BN, WM, WN, STAGES, true, OCC, KS, NP, ALPHA>(a, st)
+                        : launch_pc_kernel<BM, BN, WM, WN, STAGES, false, OCC, KS, NP, ALPHA>(a, st);
 }
 
 }  // namespace
@@ -581,5 +643,13 @@ int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int ks, int np, int
         default: return TWN_ERR_UNSUPPORTED;
     }
 }
+
+// Undivided backward-data with several alphas (alpha_in): 64x128 tiles, whose accumulators leave room for both terms of the codes.
+bool conv_stream_alpha_applicable(const GatherGemm& g) {
+    return g.IC <= kStreamAlphaMax && g.NC > 64 && env_int(Env::TILE, 0) == 0 && env_int(Env::STREAM, 1) != 0 &&
+           !env_set(Env::STREAM_PC) && !env_set(Env::STREAM_KS) && !env_set(Env::STREAM_PC_STAGES) && !env_set(Env::STREAM_OCC) &&
+           env_int(Env::BUFLOAD, 1) != 0 && conv_stream_applicable(g);
+}
+int32_t launch_conv_stream_alpha(const GatherGemm& g, hipStream_t st) { return launch_pc_tile<64, 128, 1, 4, 4, 2, 1, 4, true>(g, st); }
 
 }  // namespace twn

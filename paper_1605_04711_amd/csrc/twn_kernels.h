@@ -43,7 +43,7 @@ struct GatherGemm {
     float* partial;         // split-K workspace [splits][M][NC] float32 (float64 on the float32 path; null when splits == 1)
     int32_t splits;         // K is cut into this many ranges of whole 64-wide slabs
     // Backward-data with several alphas, inside the contraction: the code of reduction channel c counts alpha_in[c / alpha_in_rows]
-    // times, as two bf16 terms (null: 1).  Only the few-tile kernel takes it.
+    // times, as two bf16 terms (null: 1).  Only conv_small and conv_stream_alpha take it.
     const float* alpha_in;
     int32_t alpha_in_rows;
 };
@@ -106,6 +106,9 @@ int32_t launch_conv_addsub(const GatherGemm& g, hipStream_t st);
 bool conv_stream_applicable(const GatherGemm& g);
 int32_t launch_conv_stream(const GatherGemm& g, int tile, hipStream_t st);
 int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int ks, int np, int stages, hipStream_t st);
+// The same walk over problems with alpha_in.
+bool conv_stream_alpha_applicable(const GatherGemm& g);
+int32_t launch_conv_stream_alpha(const GatherGemm& g, hipStream_t st);
 
 // Problems of few output tiles: up to four of them in one launch, the K slabs of a tile shared out over the waves of
 // one workgroup; conv_small_tile (a pure function of the problems) names the tile, 0 when other kernels are better.

@@ -44,3 +44,30 @@ def test_dx_alpha(n, h, w, c, o, r, stride, pad, dil, per):
         got = to_host_f64(dx)
         assert np.linalg.norm(got - ref) <= norm * np.linalg.norm(ref)
         assert rel_err(got, ref) <= worst
+
+
+@pytest.mark.parametrize("n,h,w,c,o,r,pad,dil,per", [
+    (3, 9, 11, 72, 128, 3, 1, 1, 1),          # two slabs per tap, ragged rows and columns
+    (2, 13, 12, 136, 192, 3, 1, 2, 3),        # three slabs per tap, dilation, several filters per alpha
+    (5, 8, 8, 128, 64, 1, 0, 1, 1),           # plain product of one slab
+    (1, 20, 21, 264, 1024, 1, 0, 1, 1),       # plain product, the largest table
+    (1, 6, 7, 72, 1088, 1, 0, 1, 1),          # beyond it: terms of alpha * dY
+    (8, 66, 66, 128, 64, 3, 1, 1, 1)])        # several tiles per workgroup, one slab per tap
+def test_dx_alpha_persistent(knob, n, h, w, c, o, r, pad, dil, per):
+    """The same in the persistent kernel, which problems of more tiles run."""
+    knob("TWN_SMALL", 0)
+    rng = np.random.default_rng(n * h + o)
+    geo = (1, 1), (pad,) * 2, (dil,) * 2
+    wt = (rng.standard_normal((o, c, r, r)) * 0.05 * np.exp(rng.standard_normal((o, 1, 1, 1)))).astype(np.float32)
+    tw = api.twn_ternarize(to_dev_f32(wt), 0.7, groups=o // per, transposed=True)
+    codes, _, alpha, _ = ot.ternarize(wt, 0.7, groups=o // per)
+    x = to_dev_bf16(np.zeros((n, h, w, c), np.float32))
+    p, q = h + 2 * pad - dil * (r - 1), w + 2 * pad - dil * (r - 1)
+    dy = wl.bf16_round((rng.standard_normal((n, p, q, o)) * 1e-5).astype(np.float32))
+    ref = oc.conv2d_bwd_data(dy, codes, alpha, (n, h, w, c), *geo)
+    dx, _, _ = api.twn_conv2d_bwd_ste(x, to_dev_bf16(dy), tw, *geo, need_dw=False)
+    got = to_host_f64(dx)
+    assert np.linalg.norm(got - ref) <= 2.0e-3 * np.linalg.norm(ref)
+    assert rel_err(got, ref) <= BF16_TOL
+    again, _, _ = api.twn_conv2d_bwd_ste(x, to_dev_bf16(dy), tw, *geo, need_dw=False)
+    assert torch.equal(again, dx)
