@@ -632,45 +632,35 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
         if (env_int(Env::TILE, 0) == 0 && env_int(Env::C64, 1) != 0 && conv_c64_applicable(g))
             return launch_conv_c64_scaled(g, alpha, d->O / d->alpha_groups, st);
     }
-    if (p.two && d->variant == TWN_VAR_BF16_POSTSCALE && d->y_dtype == TWN_BF16 && d->O <= kSmallAlphaMax &&
-        conv_small_tile(gs, count) != 0) {
-        // Problems that would run in the few-tile kernel take the alphas with their codes: nothing is scaled (a longer K is cut over
-        // workgroups, with two terms of alpha * dY).  bf16 outputs only: two terms of alpha are as
-        // good as two of alpha * dY on average (2-norm error 2.0e-6 .. 3.1e-6 by how the alphas lie to powers of two, against 2.45e-6),
-        // which one rounding of dX to bf16 hides (1.655e-3 either way) and a float32 dX would show.
+    if (p.two && d->variant == TWN_VAR_BF16_POSTSCALE && d->y_dtype == TWN_BF16) {
+        // The alphas stay with the codes where a kernel that would run the two-term problem has a build for it: nothing is scaled.
+        // bf16 outputs only: two terms of alpha are as good as two of alpha * dY on average (2-norm error 2.0e-6 .. 3.1e-6 by how
+        // the alphas lie to powers of two, against 2.45e-6), which one rounding of dX to bf16 hides (1.655e-3 either way) and a
+        // float32 dX would show.
         DxPlan in;
         plan_dx(d, P, Q, &in, p.classes, true);
         const int n = in.classes ? in.cl.count : 1;
         GatherGemm* g = in.classes ? in.cl.g : &in.g;
-        const int tile = conv_small_tile(g, n);
-        if (tile != 0) {
-            for (int k = 0; k < n; ++k) {
-                g[k].X = dY;
-                g[k].Wq = in.classes ? codes + in.cl.tb.first_word[k] : packed_T;
-                g[k].alpha = alpha;
-                g[k].alpha_in = alpha;
-                g[k].alpha_in_rows = d->O / d->alpha_groups;
-                g[k].Y = dX;
-                g[k].splits = 1;
-            }
+        for (int k = 0; k < n; ++k) {
+            g[k].X = dY;
+            g[k].Wq = in.classes ? codes + in.cl.tb.first_word[k] : packed_T;
+            g[k].alpha = g[k].alpha_in = alpha;
+            g[k].alpha_in_rows = d->O / d->alpha_groups;
+            g[k].Y = dX;
+            g[k].splits = 1;
+        }
+        const bool few = conv_small_tile(gs, count) != 0;
+        const int tile = few && d->O <= kSmallAlphaMax ? conv_small_tile(g, n) : 0;
+        const bool persistent = !few && !in.classes && !p.classes && gather_gemm_splits(p.g) <= 1 && conv_stream_alpha_applicable(g[0]);
+        const bool batch = !few && in.classes && env_int(Env::DX_CLASS_BATCH, 1) != 0 && gather_gemm_dma_alpha_applicable(g, n);
+        if (tile != 0 || persistent || batch) {
             if (in.classes) {
                 rc = launch_dx_prep(class_prep(d, in.cl, packed_T, codes, dX), st);
                 if (rc != TWN_OK) return rc;
             }
-            return launch_conv_small(g, n, tile, st);
+            return tile != 0 ? launch_conv_small(g, n, tile, st)
+                             : persistent ? launch_conv_stream_alpha(g[0], st) : launch_gather_gemm_dma_batch_alpha(g, n, st);
         }
-    }
-    if (p.two && !p.classes && d->variant == TWN_VAR_BF16_POSTSCALE && d->y_dtype == TWN_BF16) {
-        // the same in the persistent kernel
-        GatherGemm g{};
-        fill_conv_bwd_data(g, d, P, Q);
-        g.X = dY;
-        g.Wq = packed_T;
-        g.alpha = g.alpha_in = alpha;
-        g.alpha_in_rows = d->O / d->alpha_groups;
-        g.Y = dX;
-        g.splits = 1;
-        if (gather_gemm_splits(p.g) <= 1 && conv_stream_alpha_applicable(g)) return launch_conv_stream_alpha(g, st);
     }
     if (p.two || p.classes) {
         DxPrep q = p.classes ? class_prep(d, p.cl, packed_T, codes, dX) : DxPrep{};

@@ -67,7 +67,9 @@ constexpr int dma_min_blocks(int nw, int smem) {
 }
 
 // The kernel proper: workgroup `b` of `nb` of problem `a` (`by`: the K range of a split-K launch).
-template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, bool SPLITK, bool BUF>
+// ALPHA: backward-data with several alphas (alpha_in of the problem; IC a multiple of 64), as in conv_stream_pc_kernel: both bf16
+// terms of alpha take the place of the 2 of the codes, from a table behind the stages.
+template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, bool SPLITK, bool BUF, bool ALPHA = false>
 __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uint32_t nb, const uint32_t b, const uint32_t by) {
     constexpr int NW = WM * WN;                    // waves per workgroup
     constexpr int NT = 64 * NW;
@@ -330,6 +332,13 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     u32x2 breg[2][NI];      // packed codes of the slab being multiplied / of the next slab
     u32x4 afrag[2][MI];     // activation fragments of step kk in set kk & 1
     u32x4 bfrag[2][NI];     // expanded codes of step kk in set kk & 1
+    u32x4 blow[2][NI];      // ALPHA: the same with the low terms
+    u32x4 al[2][2];         // ALPHA: high and low terms of step kk in set kk & 1
+    int c_cur = 0, c_next = 0;      // ALPHA: first reduction channel of the slab being multiplied / of the next
+    uint16_t* const terms = reinterpret_cast<uint16_t*>(smem + STAGES * STAGE_BYTES);      // [hi | lo] of alpha_in
+    const uint32_t term_base = lds_base + STAGES * STAGE_BYTES + static_cast<uint32_t>(lh) * 64u;
+    const uint32_t term_low = static_cast<uint32_t>(g.IC) * 2u;
+    auto after = [&](int c) __attribute__((always_inline)) { return c + 64 == g.IC ? 0 : c + 64; };
 
     // code field i of every 32-bit half lands in bits [14,15] of a bf16: 0 / +2.0 / -2.0.  The field is
     // masked first (masks held in scalar registers), then shifted: the intermediate is mostly zero bits.
@@ -345,7 +354,15 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     auto expand = [&](auto kk_tag, auto ni_tag, auto e_tag, const u32x2* br, u32x4* out) __attribute__((always_inline)) {
         constexpr int kk = decltype(kk_tag)::value, ni = decltype(ni_tag)::value, e = decltype(e_tag)::value;
         constexpr int i = (kk & 1) * 4 + e;
-        out[ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
+        if constexpr (ALPHA) {
+            typedef short s16x2 __attribute__((ext_vector_type(2)));
+            const uint32_t f = br[ni][kk >> 1] << (14 - 2 * i), sign = f & 0x80008000u;
+            const uint32_t on = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, f << 1) >> 15);
+            out[ni][e] = (al[kk & 1][0][e] & on) ^ sign;
+            blow[kk & 1][ni][e] = (al[kk & 1][1][e] & on) ^ sign;
+        } else {
+            out[ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
+        }
     };
 
     // One MFMA step.  Weights are the MFMA row operand, activations the column operand: a lane then owns
@@ -353,7 +370,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     auto step = [&](auto kk_tag, auto cur_tag, int kt, int stage, int next, int fill) __attribute__((always_inline)) {
         constexpr int KK = decltype(kk_tag)::value;
         constexpr int CUR = decltype(cur_tag)::value;
-        constexpr int NM = MI * NI;
+        constexpr int NM = MI * NI * (ALPHA ? 2 : 1);            // ALPHA: all high terms, then all low ones
         constexpr int SET = KK & 1, NSET = SET ^ 1;
         constexpr int KN = (KK + 1) & 3;                         // the step being prepared
         constexpr int BSRC = (KK == 3) ? (CUR ^ 1) : CUR;        // its codes: next slab's after the last step
@@ -361,9 +378,10 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
         constexpr int G0 = (KK == 2) ? 0 : HALF;
         constexpr int P_RA = MI;                                 // pieces: fragment reads,
         constexpr int P_RB = (KK == 2) ? 1 : 0;                  //   codes of the next slab,
+        constexpr int P_AL = ALPHA ? 2 : 0;                      //   terms of the step after the next,
         constexpr int P_D = 4 * NI;                              //   code expansion,
         constexpr int P_G = (KK == 2) ? HALF : (KK == 3) ? NLOAD + 1 - HALF : 0;   //   global loads
-        constexpr int P = P_RA + P_RB + P_D + P_G;
+        constexpr int P = P_RA + P_RB + P_AL + P_D + P_G;
         const uint32_t a_addr = lds_base + ((KK == 3) ? next : stage) * STAGE_BYTES + aoff[KN];
         auto piece = [&](auto p_tag) __attribute__((always_inline)) {
             constexpr int p = decltype(p_tag)::value;
@@ -371,25 +389,29 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
                 lds_read128<p * 32 * 128>(afrag[NSET][p], a_addr);
             } else if constexpr (p < P_RA + P_RB) {
                 lds_read64_n<NI, 32 * 16>(breg[CUR ^ 1], lds_base + next * STAGE_BYTES + boff);
-            } else if constexpr (p < P_RA + P_RB + P_D) {
-                constexpr int q = p - P_RA - P_RB;
+            } else if constexpr (p < P_RA + P_RB + P_AL) {
+                constexpr int term = p - P_RA - P_RB;
+                const uint32_t at = term_base + static_cast<uint32_t>(KK < 2 ? c_cur : c_next) * 2u + (term ? term_low : 0u);
+                lds_read128<((KK + 2) & 3) * 16>(al[SET][term], at);
+            } else if constexpr (p < P_RA + P_RB + P_AL + P_D) {
+                constexpr int q = p - P_RA - P_RB - P_AL;
                 expand(std::integral_constant<int, KN>{}, std::integral_constant<int, q / 4>{},
                        std::integral_constant<int, q % 4>{}, breg[BSRC], bfrag[NSET]);
             } else {
-                constexpr int gi = G0 + p - (P_RA + P_RB + P_D);
+                constexpr int gi = G0 + p - (P_RA + P_RB + P_AL + P_D);
                 if constexpr (gi == 0) issue_setup(kt + PD, fill);
                 issue_load(std::integral_constant<int, gi>{});
             }
         };
         static_for<NM>([&](auto j_tag) __attribute__((always_inline)) {
             constexpr int j = decltype(j_tag)::value;
-            constexpr int mi = j / NI, ni = j % NI;
+            constexpr int mi = j % (MI * NI) / NI, ni = j % NI;
             if constexpr (PINNED) {
                 AgprTile<j>::mfma(bfrag[SET][ni], afrag[SET][mi]);
             } else {
-                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bfrag[SET][ni]),
-                                                                      __builtin_bit_cast(bf16x8, afrag[SET][mi]),
-                                                                      acc[mi][ni], 0, 0, 0);
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    __builtin_bit_cast(bf16x8, j < MI * NI ? bfrag[SET][ni] : blow[SET][ni]),
+                    __builtin_bit_cast(bf16x8, afrag[SET][mi]), acc[mi][ni], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
             static_for<P>([&](auto p_tag) __attribute__((always_inline)) {
@@ -401,6 +423,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
         // everything read during this step is needed by the next one
         lds_wait<0>();
         lds_ready<MI>(afrag[NSET]);
+        if constexpr (ALPHA) lds_ready<2>(al[SET]);
         if constexpr (KK == 2) lds_ready<NI>(breg[CUR ^ 1]);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -409,15 +432,35 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
 #pragma unroll
     for (int s = 0; s < PD; ++s) issue(kt_begin + s, s);
     TWN_TRACE_POINT(1);
+    if constexpr (ALPHA) {
+        for (int c = tid; c < g.IC; c += NT) {
+            const float v = g.alpha_in[c / g.alpha_in_rows];
+            const uint16_t hi = f32_to_bf16(v);
+            terms[c] = hi;
+            terms[g.IC + c] = f32_to_bf16(v - bf16_to_f32(hi));
+        }
+        c_next = after(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // visible after the barrier
+    }
     __builtin_amdgcn_s_waitcnt(vmcnt_imm((PD - 1) * PER_STAGE));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     TWN_TRACE_POINT(2);
     lds_read64_n<NI, 32 * 16>(breg[0], lds_base + boff);
     lds_read128_n<MI, 32 * 128>(afrag[0], lds_base + aoff[0]);
+    if constexpr (ALPHA) {
+        lds_read128<0>(al[0][0], term_base);
+        lds_read128<0>(al[0][1], term_base + term_low);
+        lds_read128<16>(al[1][0], term_base);
+        lds_read128<16>(al[1][1], term_base + term_low);
+    }
     lds_wait<0>();
     lds_ready<NI>(breg[0]);
     lds_ready<MI>(afrag[0]);
+    if constexpr (ALPHA) {
+        lds_ready<2>(al[0]);
+        lds_ready<2>(al[1]);
+    }
     static_for<4 * NI>([&](auto q_tag) __attribute__((always_inline)) {
         constexpr int q = decltype(q_tag)::value;
         expand(std::integral_constant<int, 0>{}, std::integral_constant<int, q / 4>{},
@@ -440,6 +483,10 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
         step(std::integral_constant<int, 3>{}, cur_tag, kt, stage, next, fill);
         stage = next;
         fill = (fill + 1 == STAGES) ? 0 : fill + 1;
+        if constexpr (ALPHA) {
+            c_cur = c_next;
+            c_next = after(c_cur);
+        }
     };
     for (int kt = kt_begin; kt < KT; kt += 2) {
         slab(kt, std::integral_constant<int, 0>{});
@@ -493,7 +540,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
         float mul = 0.0f, add = 0.0f;
         if (ncol < g.NC) {
             const int ag = (g.rows_per_group >= g.NC) ? 0 : ncol / g.rows_per_group;
-            mul = 0.5f * g.alpha[ag] * (g.scale ? g.scale[ncol] : 1.0f);   // codes were +-2
+            mul = (ALPHA ? 1.0f : 0.5f * g.alpha[ag]) * (g.scale ? g.scale[ncol] : 1.0f);   // codes were +-2
             add = g.shift ? g.shift[ncol] : 0.0f;
         }
         colmul[i] = mul;
@@ -603,13 +650,14 @@ struct DmaBatchArgs {
     DmaArgs p[kDmaBatchMax];
     uint32_t blocks[kDmaBatchMax];
 };
-template <int BM, int BN, int WM, int WN, int STAGES, bool BUF>
-__global__ __launch_bounds__(64 * WM * WN, dma_min_blocks(WM * WN, STAGES * (BM * 128 + BN * 16)))
+constexpr int kDmaAlphaMax = 1024;          // reduction channels of the table of terms
+template <int BM, int BN, int WM, int WN, int STAGES, bool BUF, bool ALPHA = false>
+__global__ __launch_bounds__(64 * WM * WN, dma_min_blocks(WM * WN, STAGES * (BM * 128 + BN * 16) + (ALPHA ? kDmaAlphaMax * 4 : 0)))
 void gather_gemm_dma_batch_kernel(const DmaBatchArgs ba) {
     const uint32_t c = blockIdx.y;
     const uint32_t nb = ba.blocks[c];
     if (blockIdx.x >= nb) return;           // whole workgroup, before any barrier
-    gather_gemm_dma_body<BM, BN, WM, WN, STAGES, false, false, BUF>(ba.p[c], nb, blockIdx.x, 0u);
+    gather_gemm_dma_body<BM, BN, WM, WN, STAGES, false, false, BUF, ALPHA>(ba.p[c], nb, blockIdx.x, 0u);
 }
 
 template <int VEC>
@@ -741,10 +789,10 @@ extern "C" int32_t twn_debug_set_trace(void* buf) {
 }
 #endif
 
-template <int BM, int BN, int WM, int WN, int STAGES, bool BUF>
+template <int BM, int BN, int WM, int WN, int STAGES, bool BUF, bool ALPHA = false>
 static int32_t launch_dma_batch_kernel(const DmaBatchArgs& ba, unsigned width, int count, hipStream_t st) {
-    constexpr int SMEM = STAGES * (BM * 128 + BN * 16);
-    auto k = gather_gemm_dma_batch_kernel<BM, BN, WM, WN, STAGES, BUF>;
+    constexpr int SMEM = STAGES * (BM * 128 + BN * 16) + (ALPHA ? kDmaAlphaMax * 4 : 0);
+    auto k = gather_gemm_dma_batch_kernel<BM, BN, WM, WN, STAGES, BUF, ALPHA>;
     static std::once_flag once;
     static bool allowed = false;
     std::call_once(once, [&] {
@@ -756,7 +804,7 @@ static int32_t launch_dma_batch_kernel(const DmaBatchArgs& ba, unsigned width, i
     return launch_status();
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES>
+template <int BM, int BN, int WM, int WN, int STAGES, bool ALPHA = false>
 static int32_t launch_dma_batch_tile(const GatherGemm* gs, int count, hipStream_t st) {
     DmaBatchArgs ba{};
     int64_t width = 0;
@@ -771,6 +819,9 @@ static int32_t launch_dma_batch_tile(const GatherGemm* gs, int count, hipStream_
         if (blocks > width) width = blocks;
         buf = buf && ba.p[c].use_buf;
     }
+    if constexpr (ALPHA)
+        return buf ? launch_dma_batch_kernel<BM, BN, WM, WN, STAGES, true, true>(ba, static_cast<unsigned>(width), count, st)
+                   : TWN_ERR_UNSUPPORTED;
     // one build serves all problems of the launch: buffer-descriptor loads only if every problem qualifies
     return buf ? launch_dma_batch_kernel<BM, BN, WM, WN, STAGES, true>(ba, static_cast<unsigned>(width), count, st)
                : launch_dma_batch_kernel<BM, BN, WM, WN, STAGES, false>(ba, static_cast<unsigned>(width), count, st);
@@ -786,6 +837,23 @@ int32_t launch_gather_gemm_dma_batch(const GatherGemm* gs, int count, int tile, 
         case 16: return launch_dma_batch_tile<128, 64, 2, 2, 3>(gs, count, st);
         default: return TWN_ERR_UNSUPPORTED;
     }
+}
+
+// The same over problems with alpha_in, 64 or 128 columns wide.  ResNet-18 b64, one alpha per filter, the strided 3x3 layers with the
+// scaling and gathering launch (us): 56x56x64 <- 128 53.1 -> 36.8; 28x28x128 <- 256 41.8 -> 27.5; 14x14x256 <-
+// 512 52.3 -> 33.5.
+bool gather_gemm_dma_alpha_applicable(const GatherGemm* gs, int count) {
+    if (count < 1 || count > kDmaBatchMax || env_int(Env::TILE, 0) != 0) return false;
+    for (int c = 0; c < count; ++c) {
+        const GatherGemm& g = gs[c];
+        if (g.plain_gemm || g.chunk_gather || g.IC % 64 != 0 || g.IC > kDmaAlphaMax || g.NC % 8 != 0) return false;
+        if (!make_dma_args(g).use_buf || ((g.M + 63) / 64) * ((g.NC + 63) / 64) >= (1LL << 31)) return false;
+    }
+    return true;
+}
+int32_t launch_gather_gemm_dma_batch_alpha(const GatherGemm* gs, int count, hipStream_t st) {
+    return gs[0].NC <= 64 ? launch_dma_batch_tile<128, 64, 2, 2, 3, true>(gs, count, st)
+                          : launch_dma_batch_tile<64, 128, 1, 4, 3, true>(gs, count, st);
 }
 
 int32_t launch_gather_gemm_dma(const GatherGemm& g, int tile, hipStream_t st) {

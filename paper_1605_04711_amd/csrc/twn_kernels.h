@@ -43,7 +43,7 @@ struct GatherGemm {
     float* partial;         // split-K workspace [splits][M][NC] float32 (float64 on the float32 path; null when splits == 1)
     int32_t splits;         // K is cut into this many ranges of whole 64-wide slabs
     // Backward-data with several alphas, inside the contraction: the code of reduction channel c counts alpha_in[c / alpha_in_rows]
-    // times, as two bf16 terms (null: 1).  Only conv_small and conv_stream_alpha take it.
+    // times, as two bf16 terms (null: 1).  Only conv_small and the *_alpha launchers take it.
     const float* alpha_in;
     int32_t alpha_in_rows;
 };
@@ -93,6 +93,8 @@ int32_t launch_gather_gemm_dma(const GatherGemm& g, int tile, hipStream_t st);
 // (count <= 4); gather_gemm_dma_tile names the tile the dispatcher would use for a problem there (0: none).
 int32_t gather_gemm_dma_tile(const GatherGemm& g, bool instead_of_persistent = false);
 int32_t launch_gather_gemm_dma_batch(const GatherGemm* gs, int count, int tile, hipStream_t st);
+bool gather_gemm_dma_alpha_applicable(const GatherGemm* gs, int count);
+int32_t launch_gather_gemm_dma_batch_alpha(const GatherGemm* gs, int count, hipStream_t st);
 int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st);
 // K ranges of the float32 path (1 = no split); with more than one, g.partial holds [splits][M][NC] float64 sums.
 int32_t gather_gemm_fp32_splits(const GatherGemm& g);

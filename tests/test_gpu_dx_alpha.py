@@ -46,23 +46,27 @@ def test_dx_alpha(n, h, w, c, o, r, stride, pad, dil, per):
         assert rel_err(got, ref) <= worst
 
 
-@pytest.mark.parametrize("n,h,w,c,o,r,pad,dil,per", [
-    (3, 9, 11, 72, 128, 3, 1, 1, 1),          # two slabs per tap, ragged rows and columns
-    (2, 13, 12, 136, 192, 3, 1, 2, 3),        # three slabs per tap, dilation, several filters per alpha
-    (5, 8, 8, 128, 64, 1, 0, 1, 1),           # plain product of one slab
-    (1, 20, 21, 264, 1024, 1, 0, 1, 1),       # plain product, the largest table
-    (1, 6, 7, 72, 1088, 1, 0, 1, 1),          # beyond it: terms of alpha * dY
-    (8, 66, 66, 128, 64, 3, 1, 1, 1)])        # several tiles per workgroup, one slab per tap
-def test_dx_alpha_persistent(knob, n, h, w, c, o, r, pad, dil, per):
-    """The same in the persistent kernel, which problems of more tiles run."""
+@pytest.mark.parametrize("n,h,w,c,o,r,stride,pad,dil,per", [
+    (3, 9, 11, 72, 128, 3, 1, 1, 1, 1),       # two slabs per tap, ragged rows and columns
+    (2, 13, 12, 136, 192, 3, 1, 1, 2, 3),     # three slabs per tap, dilation, several filters per alpha
+    (5, 8, 8, 128, 64, 1, 1, 0, 1, 1),        # plain product of one slab
+    (1, 20, 21, 264, 1024, 1, 1, 0, 1, 1),    # plain product, the largest table
+    (1, 6, 7, 72, 1088, 1, 1, 0, 1, 1),       # beyond it: terms of alpha * dY
+    (8, 66, 66, 128, 64, 3, 1, 1, 1, 1),      # several tiles per workgroup, one slab per tap
+    (3, 55, 56, 64, 128, 3, 2, 1, 1, 1),      # residue classes, 64 columns
+    (9, 33, 31, 136, 192, 3, 2, 1, 1, 2),     # residue classes, 136 columns
+    (9, 33, 31, 72, 64, 1, 2, 0, 1, 1),       # three empty classes, one slab
+    (2, 67, 65, 24, 1088, 1, 2, 0, 1, 1)])    # beyond the table: terms of alpha * dY
+def test_dx_alpha_large_kernels(knob, n, h, w, c, o, r, stride, pad, dil, per):
+    """The same in the kernels that problems of more tiles run."""
     knob("TWN_SMALL", 0)
     rng = np.random.default_rng(n * h + o)
-    geo = (1, 1), (pad,) * 2, (dil,) * 2
+    geo = (stride,) * 2, (pad,) * 2, (dil,) * 2
     wt = (rng.standard_normal((o, c, r, r)) * 0.05 * np.exp(rng.standard_normal((o, 1, 1, 1)))).astype(np.float32)
     tw = api.twn_ternarize(to_dev_f32(wt), 0.7, groups=o // per, transposed=True)
     codes, _, alpha, _ = ot.ternarize(wt, 0.7, groups=o // per)
     x = to_dev_bf16(np.zeros((n, h, w, c), np.float32))
-    p, q = h + 2 * pad - dil * (r - 1), w + 2 * pad - dil * (r - 1)
+    p, q = (h + 2 * pad - dil * (r - 1) - 1) // stride + 1, (w + 2 * pad - dil * (r - 1) - 1) // stride + 1
     dy = wl.bf16_round((rng.standard_normal((n, p, q, o)) * 1e-5).astype(np.float32))
     ref = oc.conv2d_bwd_data(dy, codes, alpha, (n, h, w, c), *geo)
     dx, _, _ = api.twn_conv2d_bwd_ste(x, to_dev_bf16(dy), tw, *geo, need_dw=False)
