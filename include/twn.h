@@ -254,16 +254,18 @@ int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_desc* d1, co
  * dW_beta is 0 (overwrite) or 1 (accumulate).  A fully-connected layer is the
  * case H=W=R=S=1.  d->variant may be TWN_VAR_BF16_POSTSCALE or
  * TWN_VAR_BF16_ALPHA_LDS (it only affects dX); others: TWN_ERR_UNSUPPORTED.
- * Strided layers with dilation 1 and O % 64 == 0 compute dX as one stride-1
- * problem per residue class of the output pixels when the workspace of
- * twn_conv2d_bwd_ste_workspace_bytes is passed (otherwise, and for other
- * shapes, by the generic gather: same result, slower).
+ * Strided layers with dilation 1 may compute dX as one stride-1 problem per
+ * residue class of the output pixels, and layers with O % 8 != 0 both gradients
+ * over a copy of dY padded to whole multiples of 8 filters, when the workspace
+ * of twn_conv2d_bwd_ste_workspace_bytes is passed (with less, where that is
+ * still enough for the call, by the generic kernels: same result, slower).
  * With alpha_groups > 1 (one alpha per filter group, Alg. 1) alpha_o is a
- * factor inside the sum over o: dX then needs a workspace, where alpha_o*dY is
- * formed in float32 and kept as two bf16 terms (high part and remainder, about
- * 17 significant bits together); one contraction adds both terms in its float32
- * accumulators, so no rounding of the inputs is added (twice the arithmetic on
- * this path only). */
+ * factor inside the sum over o: dX then needs a workspace.  alpha_o*dY is formed
+ * in float32 and kept there as two bf16 terms (high part and remainder, about 17
+ * significant bits together), or, where dX is bf16 and the kernel of the shape
+ * has a build for it, dY stays as it is and alpha_o multiplies the codes as two
+ * such terms; one contraction adds both terms in its float32 accumulators, so no
+ * rounding of the inputs is added (twice the arithmetic on this path only). */
 size_t  twn_conv2d_bwd_ste_workspace_bytes(const twn_conv_desc* d);
 int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, const void* dY,
                            const uint32_t* packed_T, const float* alpha,

@@ -660,7 +660,7 @@ __global__ __launch_bounds__(256 * KS, 2) void weight_grad_patch_kernel(const WG
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const int o = o0 + wm * 64 + mi * 32 + (e >> 2) * 8 + lh * 4 + (e & 3);
-                    if (o >= w.O) continue;
+                    if (o >= w.o_real) continue;
                     float* dst = w.dW + static_cast<int64_t>(o) * a.J + col;
                     *dst = (w.beta != 0.0f) ? w.beta * *dst + acc[mi][ni][e] : acc[mi][ni][e];
                 }
@@ -697,7 +697,7 @@ __global__ __launch_bounds__(256 * KS, 2) void weight_grad_patch_kernel(const WG
 // blocks share many splits (128 filters, 48 columns, 128 splits: 6.6 -> 4.8 us).
 template <int VEC, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void weight_grad_reduce_kernel(const float* __restrict__ partial, int splits,
-                                                                 int O, int C, int R, int S, int pad_sp, float beta,
+                                                                 int O, int o_real, int C, int R, int S, int pad_sp, float beta,
                                                                  float* __restrict__ dW) {
     __shared__ float red[WAVES][64 * VEC];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -731,6 +731,7 @@ __global__ __launch_bounds__(64 * WAVES) void weight_grad_reduce_kernel(const fl
 #pragma unroll
     for (int wv = 1; wv < WAVES; ++wv) sum += red[wv][el];
     const int64_t o = id / Jsrc;
+    if (o >= o_real) return;             // a filter that pads dY
     const int64_t j = id - o * Jsrc;
     int64_t rs, c;
     int r, sx;
@@ -1003,7 +1004,7 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
     a.divSY = make_fastdiv(a.plan.patch ? a.plan.sy : 1);
     // filters with several taps: patches with halo, unless this is a first layer's 4-channel copy
     WgTapsPlan taps{};
-    if (w.dW && !w.pad_sp)
+    if (w.dW && !w.pad_sp && w.o_real == w.O)
         taps = plan_weight_grad_taps(WgShape{w.N, w.H, w.W, w.C, w.O, w.R, w.S, w.P, w.Q, w.sh, w.sw, w.dh, w.dw});
     const int32_t splits = taps.use ? taps.splits : a.plan.splits;
     a.slabs_per_split = static_cast<int32_t>((a.plan.slabs + splits - 1) / splits);
@@ -1047,17 +1048,17 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
             // whole rows up to 16 ranges (us of both launches, rows / scattered floats: 588 pixels, 256 -> 512 channels 3x3/2, 3
             // ranges 19.6 / 25.3; 3136, the same, 6 ranges 27.6 / 32.2; 12544, 128 -> 256, 24 ranges 27.6 / 25.3)
             if (!w.pad_sp && w.C % 64 == 0 && RS > 1 && RS <= kReduceRowsMaxTaps && splits <= env_int(Env::WG_ROWS_SPLITS, 16))
-                weight_grad_reduce_rows_kernel<<<static_cast<unsigned>(w.O * (w.C / 64)), 256, 0, st>>>(
+                weight_grad_reduce_rows_kernel<<<static_cast<unsigned>(w.o_real * (w.C / 64)), 256, 0, st>>>(
                     w.partial, splits, w.O, w.C, RS, w.beta, w.dW);
             else if (total % 4 == 0 && splits >= 64 && total < 256 * 256)
                 weight_grad_reduce_kernel<4, 16><<<static_cast<unsigned>((total + 255) / 256), 1024, 0, st>>>(
-                    w.partial, splits, w.O, C, w.R, S, w.pad_sp, w.beta, w.dW);
+                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW);
             else if (total % 4 == 0)
                 weight_grad_reduce_kernel<4, 4><<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(
-                    w.partial, splits, w.O, C, w.R, S, w.pad_sp, w.beta, w.dW);
+                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW);
             else
                 weight_grad_reduce_kernel<1, 4><<<static_cast<unsigned>((total + 63) / 64), 256, 0, st>>>(
-                    w.partial, splits, w.O, C, w.R, S, w.pad_sp, w.beta, w.dW);
+                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW);
         }
     }
     if (w.dbias) {
@@ -1070,14 +1071,14 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
     return launch_status();
 }
 
-int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
+int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t o_real, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
                                      float beta, float* dW, hipStream_t st) {
     const int64_t total = static_cast<int64_t>(O) * R * pad_sp * 4;
     const unsigned blocks = static_cast<unsigned>((total + 255) / 256);
     if (splits >= 64 && total < 256 * 256)
-        weight_grad_reduce_kernel<4, 16><<<blocks, 1024, 0, st>>>(partial, splits, O, C, R, S, pad_sp, beta, dW);
+        weight_grad_reduce_kernel<4, 16><<<blocks, 1024, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW);
     else
-        weight_grad_reduce_kernel<4, 4><<<blocks, 256, 0, st>>>(partial, splits, O, C, R, S, pad_sp, beta, dW);
+        weight_grad_reduce_kernel<4, 4><<<blocks, 256, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW);
     return launch_status();
 }
 

@@ -376,6 +376,38 @@ size_t weight_grad_bytes(const twn_conv_desc* d, int P, int Q) {
     return static_cast<size_t>((splits * d->O * J + 64LL * d->O) * sizeof(float));
 }
 
+// Filter counts that are no multiple of 8 (a classifier's ten, a detection head's 84): 16-byte chunks of dY do not exist, and both
+// gradients would run in the kernels that load element by element (bound by their loads, one 2-byte element each).  One launch
+// pads dY, codes and alphas to the next multiple of 8 in the workspace, the layer is that of so many filters, and dW leaves the
+// added ones out.  (us of dX + dW, before -> with the launch: 128 pixels 1024 -> 10 29.5 -> 14.9; 64x40x40x16 -> 10, 3x3
+// 134.6 -> 32.3; 5x20x22x512 -> 10, 7x7 268 -> 37.7; 64x38x38x512 -> 84, 3x3 2001 -> 214; 64x112x112x3 -> 10, 3x3, one alpha per
+// filter 934 -> 125; 3 pixels 1024 -> 10 19.3 -> 13.0, but dX alone there 6.5 -> 7.8 against 14.6 -> 7.6 at 128 pixels and
+// 6.9 -> 6.5 at 64: below 64 pixels only with dW.)
+struct FilterPadPlan {
+    bool use;
+    twn_conv_desc d;            // the padded layer
+    size_t dy_bytes, code_bytes, alpha_bytes;
+    size_t bytes() const { return dy_bytes + code_bytes + alpha_bytes; }
+};
+FilterPadPlan plan_filter_pad(const twn_conv_desc* d, int P, int Q) {
+    FilterPadPlan p{};
+    if (d->O % 8 == 0 || d->variant != TWN_VAR_BF16_POSTSCALE || d->x_dtype != TWN_BF16 ||
+        (d->alpha_groups != 1 && d->alpha_groups != d->O))
+        return p;
+    p.d = *d;
+    p.d.O = (d->O + 7) & ~7;
+    p.d.alpha_groups = d->alpha_groups == 1 ? 1 : p.d.O;
+    const int64_t pixels = static_cast<int64_t>(d->N) * P * Q, kt = static_cast<int64_t>(d->R) * d->S * p.d.O;
+    const int64_t dw = static_cast<int64_t>(p.d.O) * d->R * (d->S + 1) * (d->C < 8 ? 8 : d->C);
+    // well inside the limits of every kernel below, so that nothing is refused for the filters added
+    if (kt >= (1LL << 29) || pixels * p.d.O >= (1LL << 30) || dw >= (1LL << 28)) return p;
+    p.dy_bytes = round_up(static_cast<size_t>(pixels) * p.d.O * sizeof(uint16_t), 256);
+    p.code_bytes = round_up(twn_packed_bytes(d->C, kt), 256);
+    p.alpha_bytes = round_up(static_cast<size_t>(p.d.O) * sizeof(float), 256);
+    p.use = true;
+    return p;
+}
+
 }  // namespace
 
 extern "C" size_t twn_gemm_fwd_workspace_bytes(const twn_gemm_desc* d) {
@@ -574,7 +606,10 @@ extern "C" size_t twn_conv2d_bwd_ste_workspace_bytes(const twn_conv_desc* d) {
     plan_dx(d, P, Q, &p, true);
     if (p.bytes() > a) a = p.bytes();
     const size_t b = weight_grad_bytes(d, P, Q);
-    return a > b ? a : b;
+    if (b > a) a = b;
+    const FilterPadPlan pad = plan_filter_pad(d, P, Q);         // more than the least the call takes
+    const size_t c = pad.use ? pad.bytes() + twn_conv2d_bwd_ste_workspace_bytes(&pad.d) : 0;
+    return a > c ? a : c;
 }
 
 // Preparation of residue classes: their codes, one copy, and the clearing of dX where a class has no taps.
@@ -705,6 +740,59 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
     return TWN_OK;
 }
 
+// The two gradients of a checked call; dW has the first `o_real` of the filters.
+static int32_t bwd_run(const twn_conv_desc* d, int P, int Q, const void* X, const void* dY, const uint32_t* packed_T, const float* alpha,
+                       void* dX, float* dW, float* dbias, float dW_beta, void* workspace, size_t workspace_bytes, int32_t o_real,
+                       hipStream_t st) {
+    int32_t rc = TWN_OK;
+    if (dX) {
+        rc = data_gradient(d, P, Q, dY, packed_T, alpha, dX, workspace, workspace_bytes, st);
+        if (rc != TWN_OK) return rc;
+    }
+    if (dW || dbias) {
+        WeightGrad w{};
+        w.X = static_cast<const uint16_t*>(X);
+        w.dY = static_cast<const uint16_t*>(dY);
+        w.dW = dW;
+        w.dbias = dbias;
+        w.partial = static_cast<float*>(workspace);
+        w.partial_floats = static_cast<int64_t>(weight_grad_bytes(d, P, Q) / sizeof(float));
+        w.beta = dW_beta;
+        w.o_real = o_real;
+        w.N = d->N; w.H = d->H; w.W = d->W; w.C = d->C; w.O = d->O; w.R = d->R; w.S = d->S;
+        w.P = P; w.Q = Q;
+        w.sh = d->stride_h; w.sw = d->stride_w; w.ph = d->pad_h; w.pw = d->pad_w;
+        w.dh = d->dil_h; w.dw = d->dil_w;
+        w.xc = d->C;
+        SmallC sc;
+        const bool small = dW && small_c(d, &sc) && d->O % 8 == 0;
+        const FirstGradPlan f = small && aligned(X, 4) && aligned(dY, 16) ? first_grad_plan(d, P, Q) : FirstGradPlan{};
+        if (f.use) {
+            rc = launch_first_weight_grad(taps_shape(d, P, Q), d->pad_h, d->pad_w, f, w.X, w.dY, w.partial, st);
+            if (rc == TWN_OK)
+                rc = launch_first_weight_grad_sum(w.partial, f.splits, d->O, o_real, d->C, d->R, d->S, 4 * f.G, dW_beta, dW, st);
+            if (rc != TWN_OK || !dbias) return rc;
+            w.dW = nullptr;                 // the bias gradient is left
+        } else if (small) {
+            // first-layer mode: gather from the zero-bordered 4-channel copy (rebuilt here: the call is stateless)
+            uint16_t* Xp = static_cast<uint16_t*>(workspace);
+            rc = launch_pad_c4(static_cast<const uint16_t*>(X), d->N, d->H, d->W, d->C, d->pad_h, d->pad_w, sc.Hp,
+                               sc.Wp, Xp, st);
+            if (rc != TWN_OK) return rc;
+            w.X = Xp;
+            w.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + sc.x_bytes);
+            w.partial_floats -= static_cast<int64_t>(sc.x_bytes / sizeof(float));
+            w.H = sc.Hp; w.W = sc.Wp; w.C = 8; w.S = sc.Sp / 2;
+            w.ph = w.pw = 0; w.dw = 2;
+            w.xc = 4;
+            w.pad_sp = sc.Sp; w.c_real = d->C; w.s_real = d->S;
+        }
+        w.splits = plan_weight_grad(d->N, P, Q, w.C, d->O, d->R, w.S).splits;
+        rc = launch_weight_grad(w, st);
+    }
+    return rc;
+}
+
 extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, const void* dY,
                                       const uint32_t* packed_T, const float* alpha,
                                       void* dX, float* dW, float* dbias, float dW_beta,
@@ -734,50 +822,29 @@ extern "C" int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, con
         if (!workspace || workspace_bytes < need || !aligned(workspace, 256)) return TWN_ERR_WORKSPACE;
     }
     hipStream_t st = as_stream(stream);
-
-    if (dX) {
-        rc = data_gradient(d, P, Q, dY, packed_T, alpha, dX, workspace, workspace_bytes, st);
-        if (rc != TWN_OK) return rc;
-    }
-    if (dW || dbias) {
-        WeightGrad w{};
-        w.X = static_cast<const uint16_t*>(X);
-        w.dY = static_cast<const uint16_t*>(dY);
-        w.dW = dW;
-        w.dbias = dbias;
-        w.partial = static_cast<float*>(workspace);
-        w.partial_floats = static_cast<int64_t>(weight_grad_bytes(d, P, Q) / sizeof(float));
-        w.beta = dW_beta;
-        w.N = d->N; w.H = d->H; w.W = d->W; w.C = d->C; w.O = d->O; w.R = d->R; w.S = d->S;
-        w.P = P; w.Q = Q;
-        w.sh = d->stride_h; w.sw = d->stride_w; w.ph = d->pad_h; w.pw = d->pad_w;
-        w.dh = d->dil_h; w.dw = d->dil_w;
-        w.xc = d->C;
-        SmallC sc;
-        const bool small = dW && small_c(d, &sc) && d->O % 8 == 0;
-        const FirstGradPlan f = small && aligned(X, 4) && aligned(dY, 16) ? first_grad_plan(d, P, Q) : FirstGradPlan{};
-        if (f.use) {
-            rc = launch_first_weight_grad(taps_shape(d, P, Q), d->pad_h, d->pad_w, f, w.X, w.dY, w.partial, st);
-            if (rc == TWN_OK)
-                rc = launch_first_weight_grad_sum(w.partial, f.splits, d->O, d->C, d->R, d->S, 4 * f.G, dW_beta, dW, st);
-            if (rc != TWN_OK || !dbias) return rc;
-            w.dW = nullptr;                 // the bias gradient is left
-        } else if (small) {
-            // first-layer mode: gather from the zero-bordered 4-channel copy (rebuilt here: the call is stateless)
-            uint16_t* Xp = static_cast<uint16_t*>(workspace);
-            rc = launch_pad_c4(static_cast<const uint16_t*>(X), d->N, d->H, d->W, d->C, d->pad_h, d->pad_w, sc.Hp,
-                               sc.Wp, Xp, st);
-            if (rc != TWN_OK) return rc;
-            w.X = Xp;
-            w.partial = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + sc.x_bytes);
-            w.partial_floats -= static_cast<int64_t>(sc.x_bytes / sizeof(float));
-            w.H = sc.Hp; w.W = sc.Wp; w.C = 8; w.S = sc.Sp / 2;
-            w.ph = w.pw = 0; w.dw = 2;
-            w.xc = 4;
-            w.pad_sp = sc.Sp; w.c_real = d->C; w.s_real = d->S;
+    const FilterPadPlan pad = plan_filter_pad(d, P, Q);
+    if (pad.use && (dW || (dX && static_cast<int64_t>(d->N) * P * Q >= 64)) && workspace && aligned(workspace, 256) &&
+        workspace_bytes >= pad.bytes() + twn_conv2d_bwd_ste_workspace_bytes(&pad.d)) {
+        unsigned char* ws = static_cast<unsigned char*>(workspace);
+        FilterPad f{};
+        f.dY = static_cast<const uint16_t*>(dY);
+        f.pixels = static_cast<int64_t>(d->N) * P * Q;
+        f.O = d->O; f.O8 = pad.d.O; f.C = d->C; f.RS = d->R * d->S;
+        f.wpr = static_cast<int32_t>(twn_packed_words_per_row(static_cast<int64_t>(f.RS) * d->O));
+        f.wpr8 = static_cast<int32_t>(twn_packed_words_per_row(static_cast<int64_t>(f.RS) * pad.d.O));
+        f.dY8 = static_cast<uint16_t*>(workspace);
+        f.codes8 = reinterpret_cast<uint32_t*>(ws + pad.dy_bytes);
+        f.alpha8 = reinterpret_cast<float*>(ws + pad.dy_bytes + pad.code_bytes);
+        if (dX) {
+            f.packed_T = packed_T;
+            f.alpha = d->alpha_groups > 1 ? alpha : nullptr;
         }
-        w.splits = plan_weight_grad(d->N, P, Q, w.C, d->O, d->R, w.S).splits;
-        rc = launch_weight_grad(w, st);
+        rc = launch_filter_pad(f, st);
+        if (rc != TWN_OK) return rc;
+        rc = bwd_run(&pad.d, P, Q, X, f.dY8, f.codes8, f.alpha ? f.alpha8 : alpha, dX, dW, nullptr, dW_beta, ws + pad.bytes(),
+                     workspace_bytes - pad.bytes(), d->O, st);
+        if (rc != TWN_OK || !dbias) return rc;
+        return bwd_run(d, P, Q, X, dY, packed_T, alpha, nullptr, nullptr, dbias, 0.0f, workspace, workspace_bytes, d->O, st);
     }
-    return rc;
+    return bwd_run(d, P, Q, X, dY, packed_T, alpha, dX, dW, dbias, dW_beta, workspace, workspace_bytes, d->O, st);
 }

@@ -515,6 +515,49 @@ int32_t launch_dx_prep(const DxPrep& p, hipStream_t st) {
     return TWN_OK;
 }
 
+// Filter counts that are no multiple of 8: eight filters of a pixel, one word of codes or one alpha per thread.
+__global__ __launch_bounds__(256) void filter_pad_kernel(const FilterPad p, int64_t chunks, int64_t words) {
+    int64_t id = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (id < chunks) {
+        const int per = p.O8 >> 3;
+        const int64_t pix = id / per;
+        const int o = static_cast<int>(id - pix * per) * 8;
+        u32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t a = o + 2 * e < p.O ? p.dY[pix * p.O + o + 2 * e] : 0u;
+            const uint32_t b = o + 2 * e + 1 < p.O ? p.dY[pix * p.O + o + 2 * e + 1] : 0u;
+            v[e] = a | (b << 16);
+        }
+        *reinterpret_cast<u32x4*>(p.dY8 + pix * p.O8 + o) = v;
+        return;
+    }
+    id -= chunks;
+    if (id < words) {
+        const int c = static_cast<int>(id / p.wpr8), j = static_cast<int>(id % p.wpr8);
+        const uint32_t* row = p.packed_T + static_cast<int64_t>(c) * p.wpr;
+        uint32_t word = 0u;
+        for (int t = 0; t < 16; ++t) {
+            const int k8 = j * 16 + t, tap = k8 / p.O8, o = k8 - tap * p.O8;
+            if (tap >= p.RS || o >= p.O) continue;
+            const int k = tap * p.O + o, ts = k & 15;
+            word |= ((row[k >> 4] >> ((ts & 1) * 16 + (ts >> 1) * 2)) & 3u) << ((t & 1) * 16 + (t >> 1) * 2);
+        }
+        p.codes8[id] = word;
+        return;
+    }
+    id -= words;
+    if (p.alpha && id < p.O8) p.alpha8[id] = id < p.O ? p.alpha[id] : 0.0f;
+}
+
+int32_t launch_filter_pad(const FilterPad& p, hipStream_t st) {
+    const int64_t chunks = p.pixels * (p.O8 / 8), words = p.packed_T ? static_cast<int64_t>(p.C) * p.wpr8 : 0;
+    const int64_t blocks = (chunks + words + (p.alpha ? p.O8 : 0) + 255) / 256;
+    if (blocks >= (1LL << 23)) return TWN_ERR_SHAPE;            // the caller asks for less
+    filter_pad_kernel<<<static_cast<unsigned>(blocks), 256, 0, st>>>(p, chunks, words);
+    return launch_status();
+}
+
 int32_t launch_pad_c4(const uint16_t* X, int N, int H, int W, int C, int ph, int pw, int Hp, int Wp,
                       uint16_t* Xp, hipStream_t st) {
     const int64_t total = static_cast<int64_t>(N) * Hp * Wp;

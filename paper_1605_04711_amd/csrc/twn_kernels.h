@@ -86,6 +86,19 @@ struct DxPrep {
     int64_t zero16;
 };
 int32_t launch_dx_prep(const DxPrep& p, hipStream_t st);
+// Backward of a layer whose filter count is no multiple of 8, over O8 = that count rounded up: dY, the transposed codes and, with one
+// alpha per filter, the alphas with zeros in the filters that do not exist.
+struct FilterPad {
+    const uint16_t* dY;
+    const uint32_t* packed_T;       // null: no codes wanted
+    const float* alpha;             // null: one alpha for all
+    int64_t pixels;
+    int32_t O, O8, C, RS, wpr, wpr8;
+    uint16_t* dY8;
+    uint32_t* codes8;
+    float* alpha8;
+};
+int32_t launch_filter_pad(const FilterPad& p, hipStream_t st);
 int32_t launch_pad_repack_c4(const uint16_t* X, int N, int H, int W, int C, int ph, int pw, int Hp, int Wp, uint16_t* Xp,
                              const uint32_t* packed, int rows, int R, int S, int Sp, uint32_t* out, hipStream_t st);
 int32_t launch_gather_gemm_dma(const GatherGemm& g, int tile, hipStream_t st);
@@ -161,6 +174,7 @@ struct WeightGrad {
     // j' = (r*pad_sp + s)*4 + c back to [O][c_real][R][s_real], dropping the phantom tap and channels.
     int32_t pad_sp, c_real, s_real;
     int32_t xc;             // elements between consecutive pixels of X (C, or 4 in first-layer mode)
+    int32_t o_real;         // filters of dW (O, or fewer where dY is padded)
 };
 
 // How the weight gradient of one layer is cut up; a pure function of the shapes, shared by the
@@ -206,7 +220,7 @@ FirstGradPlan plan_first_weight_grad(const WgShape& w);
 int32_t launch_first_weight_grad(const WgShape& w, int32_t ph, int32_t pw, const FirstGradPlan& p, const uint16_t* X,
                                  const uint16_t* dY, float* partial, hipStream_t st);
 // dW = beta*dW + sum of partial tiles in first-layer mode.
-int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
+int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t o_real, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
                                      float beta, float* dW, hipStream_t st);
 
 }  // namespace twn
