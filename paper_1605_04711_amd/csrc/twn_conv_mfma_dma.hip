@@ -839,9 +839,8 @@ int32_t launch_gather_gemm_dma_batch(const GatherGemm* gs, int count, int tile, 
     }
 }
 
-// The same over problems with alpha_in, 64 or 128 columns wide.  ResNet-18 b64, one alpha per filter, the strided 3x3 layers with the
-// scaling and gathering launch (us): 56x56x64 <- 128 53.1 -> 36.8; 28x28x128 <- 256 41.8 -> 27.5; 14x14x256 <-
-// 512 52.3 -> 33.5.
+// The same over problems with alpha_in, 64 or 128 columns wide.  ResNet-18 b64, one alpha per filter, the strided 3x3 layers with
+// the scaling and gathering launch (us): 56x56x64 <- 128 53.1 -> 36.8; 28x28x128 <- 256 41.8 -> 27.5; 14x14x256 <- 512 52.3 -> 33.5.
 bool gather_gemm_dma_alpha_applicable(const GatherGemm* gs, int count) {
     if (count < 1 || count > kDmaBatchMax || env_int(Env::TILE, 0) != 0) return false;
     for (int c = 0; c < count; ++c) {
