@@ -916,7 +916,7 @@ static int32_t choose_splits(int64_t tiles, int64_t slabs, int ks = 1) {
     return static_cast<int32_t>((slabs + per - 1) / per);
 }
 
-WgPlan plan_weight_grad(int32_t N, int32_t P, int32_t Q, int32_t C, int32_t O, int32_t R, int32_t S) {
+static WgPlan plan_weight_grad(int32_t N, int32_t P, int32_t Q, int32_t C, int32_t O, int32_t R, int32_t S) {
     WgPlan pl{};
     const int64_t J = static_cast<int64_t>(R) * S * C;
     const int64_t pixels = static_cast<int64_t>(N) * P * Q;
@@ -971,6 +971,15 @@ WgPlan plan_weight_grad(int32_t N, int32_t P, int32_t Q, int32_t C, int32_t O, i
     return pl;
 }
 
+WgRoute route_weight_grad(const WgShape& w, bool first) {
+    WgRoute r{};
+    r.general = plan_weight_grad(w.N, w.P, w.Q, w.C, w.O, w.R, w.S);
+    // filters with several taps: patches with halo, unless this is a first layer's 4-channel copy
+    if (!first) r.taps = plan_weight_grad_taps(w);
+    r.splits = r.taps.use ? r.taps.splits : r.general.splits;
+    return r;
+}
+
 // One build of the patch kernel: the dynamic-LDS limit is raised once per build.
 template <bool BUF, bool EXACT, int KS, bool O64>
 static int32_t launch_patch(const WGArgs& a, dim3 grid, hipStream_t st) {
@@ -999,20 +1008,18 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
     a.divS = make_fastdiv(w.S);
     if (a.pixels >= (1LL << 31)) return TWN_ERR_SHAPE;
     if (static_cast<int64_t>(w.O) * a.J >= (1LL << 28)) return TWN_ERR_SHAPE;   // 32-bit byte offsets inside one partial tile set
-    a.plan = plan_weight_grad(w.N, w.P, w.Q, w.C, w.O, w.R, w.S);
+    const WgRoute route =
+        route_weight_grad(WgShape{w.N, w.H, w.W, w.C, w.O, w.R, w.S, w.P, w.Q, w.sh, w.sw, w.dh, w.dw}, w.pad_sp != 0);
+    a.plan = route.general;
     a.divSX = make_fastdiv(a.plan.patch ? a.plan.sx : 1);
     a.divSY = make_fastdiv(a.plan.patch ? a.plan.sy : 1);
-    // filters with several taps: patches with halo, unless this is a first layer's 4-channel copy
-    WgTapsPlan taps{};
-    if (w.dW && !w.pad_sp && w.o_real == w.O)
-        taps = plan_weight_grad_taps(WgShape{w.N, w.H, w.W, w.C, w.O, w.R, w.S, w.P, w.Q, w.sh, w.sw, w.dh, w.dw});
-    const int32_t splits = taps.use ? taps.splits : a.plan.splits;
+    const int32_t splits = route.splits;
     a.slabs_per_split = static_cast<int32_t>((a.plan.slabs + splits - 1) / splits);
     a.xcd_map = env_int(Env::WG_XCD, 1);
     a.dy_bytes = a.x_bytes = 0;
     a.exact = 0;
-    if (taps.use) {
-        const int32_t rc = launch_weight_grad_taps(w, taps, st);
+    if (w.dW && route.taps.use) {
+        const int32_t rc = launch_weight_grad_taps(w, route.taps, st);
         if (rc != TWN_OK) return rc;
     } else if (w.dW) {
         const dim3 grid(a.plan.tiles, splits);

@@ -50,6 +50,7 @@ struct TapsArgs {
     float* partial;
     float beta;
     int32_t H, W, C, O, S, P, Q, N, RS;
+    int32_t o_real;             // filters of dW: those behind them pad dY and are summed into nothing
     int32_t sh, sw, ph, pw, dh, dw;
     WgTapsPlan pl;
     FastDivU divSX, divSY, divRow, divImg, divS;
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void weight_grad_taps_kernel(const 
     const int64_t row = static_cast<int64_t>(a.C) * a.RS;
     float* out = (pl.splits == 1) ? a.dW : a.partial + static_cast<int64_t>(range) * a.O * row;
     const bool accumulate = pl.splits == 1 && a.beta != 0.0f;
-    if (a.RS == kTapsPer && !accumulate && a.aligned_out && o0 + 64 <= a.O && c_tile + 16 * kWC <= a.C) {
+    if (a.RS == kTapsPer && !accumulate && a.aligned_out && o0 + 64 <= a.o_real && c_tile + 16 * kWC <= a.C) {
         // whole tile, nine taps: a filter's run is contiguous and 16-byte aligned
         constexpr int Q = 36 * kWC, N = 64 * Q / (64 * kWaves);      // float4 per filter; per thread (rounded down)
         auto copy = [&](int i) __attribute__((always_inline)) {
@@ -368,19 +369,19 @@ __global__ __launch_bounds__(64 * kWaves, 2) void weight_grad_taps_kernel(const 
     for (int i = tid; i < 64 * 144 * kWC; i += 64 * kWaves) {
         const int o = i / (144 * kWC), j = i - o * (144 * kWC);
         const int c = j / kTapsPer, tap = j - c * kTapsPer;
-        if (o0 + o >= a.O || c_tile + c >= a.C || tap >= taps) continue;
+        if (o0 + o >= a.o_real || c_tile + c >= a.C || tap >= taps) continue;
         const float v = tile[o * kPitch + j] + tile[kTileF + o * kPitch + j];
         float* dst = out + (o0 + o) * row + static_cast<int64_t>(c_tile + c) * a.RS + tap0 + tap;
         *dst = accumulate ? a.beta * *dst + v : v;
     }
 }
 
-// dW = beta*dW + sum over ranges of partial[range], element by element.  PARTS threads share the ranges of four elements (every
+// dW = beta*dW + sum over ranges of the first n elements of partial[range], `pitch` elements apart, element by element.  PARTS threads share the ranges of four elements (every
 // PARTS-th each, then their sums in order): with one, a bank of 64 x 64 filters is 36 workgroups that read 224 ranges one
 // after the other (8.8 us; with eight 5.3).
 template <int PARTS>
-__global__ __launch_bounds__(256) void weight_grad_sum_kernel(const float* __restrict__ partial, int splits, int64_t n, float beta,
-                                                              float* __restrict__ dW) {
+__global__ __launch_bounds__(256) void weight_grad_sum_kernel(const float* __restrict__ partial, int splits, int64_t pitch, int64_t n,
+                                                              float beta, float* __restrict__ dW) {
     constexpr int COLS = 256 / PARTS;
     __shared__ f32x4 red[PARTS > 1 ? 256 : 1];
     const int col = threadIdx.x % COLS, part = threadIdx.x / COLS;
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(256) void weight_grad_sum_kernel(const float* __res
     f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
     if (id < n) {
 #pragma unroll 8
-        for (int sp = part; sp < splits; sp += PARTS) s += *reinterpret_cast<const f32x4*>(partial + sp * n + id);
+        for (int sp = part; sp < splits; sp += PARTS) s += *reinterpret_cast<const f32x4*>(partial + sp * pitch + id);
     }
     if constexpr (PARTS > 1) {
         red[threadIdx.x] = s;
@@ -578,7 +579,7 @@ static int32_t launch_taps(const TapsArgs& a, hipStream_t st) {
 int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipStream_t st) {
     TapsArgs a;
     a.X = w.X; a.dY = w.dY; a.dW = w.dW; a.partial = w.partial; a.beta = w.beta;
-    a.H = w.H; a.W = w.W; a.C = w.C; a.O = w.O; a.S = w.S; a.P = w.P; a.Q = w.Q; a.N = w.N; a.RS = w.R * w.S;
+    a.H = w.H; a.W = w.W; a.C = w.C; a.O = w.O; a.S = w.S; a.P = w.P; a.Q = w.Q; a.N = w.N; a.RS = w.R * w.S; a.o_real = w.o_real;
     a.sh = w.sh; a.sw = w.sw; a.ph = w.ph; a.pw = w.pw; a.dh = w.dh; a.dw = w.dw;
     a.pl = pl;
     a.divSX = make_fastdiv_u(pl.sx); a.divSY = make_fastdiv_u(pl.sy);
@@ -599,11 +600,11 @@ int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipSt
     else if (pl.nb == 4) rc = launch_taps<4, 3>(a, st);
     else return TWN_ERR_UNSUPPORTED;
     if (rc != TWN_OK || pl.splits == 1) return rc;
-    const int64_t n = static_cast<int64_t>(w.O) * w.C * a.RS;       // a multiple of 64
+    const int64_t row = static_cast<int64_t>(w.C) * a.RS, n = row * w.o_real, pitch = row * w.O;       // multiples of 8
     if (pl.splits >= 32 && n / 4 < 256 * 256)
-        weight_grad_sum_kernel<8><<<static_cast<unsigned>((n / 4 + 31) / 32), 256, 0, st>>>(w.partial, pl.splits, n, w.beta, w.dW);
+        weight_grad_sum_kernel<8><<<static_cast<unsigned>((n / 4 + 31) / 32), 256, 0, st>>>(w.partial, pl.splits, pitch, n, w.beta, w.dW);
     else
-        weight_grad_sum_kernel<1><<<static_cast<unsigned>((n / 4 + 255) / 256), 256, 0, st>>>(w.partial, pl.splits, n, w.beta, w.dW);
+        weight_grad_sum_kernel<1><<<static_cast<unsigned>((n / 4 + 255) / 256), 256, 0, st>>>(w.partial, pl.splits, pitch, n, w.beta, w.dW);
     return launch_status();
 }
 

@@ -364,24 +364,24 @@ size_t weight_grad_bytes(const twn_conv_desc* d, int P, int Q) {
     SmallC sc;
     if (small_c(d, &sc) && d->O % 8 == 0) {
         const int64_t Jp = static_cast<int64_t>(d->R) * sc.Sp * 4;
-        const int64_t splits = plan_weight_grad(d->N, P, Q, 8, d->O, d->R, sc.Sp / 2).splits;
+        const int64_t splits =
+            route_weight_grad(WgShape{d->N, sc.Hp, sc.Wp, 8, d->O, d->R, sc.Sp / 2, P, Q, d->stride_h, d->stride_w, 1, 2}, true).splits;
         const size_t general = sc.x_bytes + static_cast<size_t>((splits * d->O * Jp + 64LL * d->O) * sizeof(float));
         const FirstGradPlan f = first_grad_plan(d, P, Q);
         const size_t own = f.use ? static_cast<size_t>(f.splits) * d->O * f.J * sizeof(float) : 0;
         return general > own ? general : own;       // X may turn out not to be aligned for the three-channel kernel
     }
     const int64_t J = static_cast<int64_t>(d->R) * d->S * d->C;
-    const WgTapsPlan taps = plan_weight_grad_taps(taps_shape(d, P, Q));
-    const int64_t splits = taps.use ? taps.splits : plan_weight_grad(d->N, P, Q, d->C, d->O, d->R, d->S).splits;
+    const int64_t splits = route_weight_grad(taps_shape(d, P, Q), false).splits;
     return static_cast<size_t>((splits * d->O * J + 64LL * d->O) * sizeof(float));
 }
 
 // Filter counts that are no multiple of 8 (a classifier's ten, a detection head's 84): 16-byte chunks of dY do not exist, and both
 // gradients would run in the kernels that load element by element (bound by their loads, one 2-byte element each).  One launch
-// pads dY, codes and alphas to the next multiple of 8 in the workspace, the layer is that of so many filters, and dW leaves the
-// added ones out.  (us of dX + dW, before -> with the launch: 128 pixels 1024 -> 10 29.5 -> 14.9; 64x40x40x16 -> 10, 3x3
-// 134.6 -> 32.3; 5x20x22x512 -> 10, 7x7 268 -> 37.7; 64x38x38x512 -> 84, 3x3 2001 -> 214; 64x112x112x3 -> 10, 3x3, one alpha per
-// filter 934 -> 125; 3 pixels 1024 -> 10 19.3 -> 13.0, but dX alone there 6.5 -> 7.8 against 14.6 -> 7.6 at 128 pixels and
+// pads dY, codes and alphas to the next multiple of 8 in the workspace, the layer is that of so many filters (its kernels and
+// their ranges too), and dW leaves the added ones out.  (us of dX + dW, before -> with the launch: 128 pixels 1024 -> 10
+// 29.4 -> 14.9; 64x40x40x16 -> 10, 3x3 135 -> 33; 5x20x22x512 -> 10, 7x7 269 -> 38; 64x38x38x512 -> 84, 3x3 1999 -> 213;
+// 64x112x112x3 -> 10, 3x3, one alpha per filter 935 -> 124; 3 pixels 1024 -> 10 19.3 -> 13.0, but dX alone there 6.5 -> 7.8 against 14.6 -> 7.6 at 128 pixels and
 // 6.9 -> 6.5 at 64: below 64 pixels only with dW.)
 struct FilterPadPlan {
     bool use;
@@ -787,7 +787,6 @@ static int32_t bwd_run(const twn_conv_desc* d, int P, int Q, const void* X, cons
             w.xc = 4;
             w.pad_sp = sc.Sp; w.c_real = d->C; w.s_real = d->S;
         }
-        w.splits = plan_weight_grad(d->N, P, Q, w.C, d->O, d->R, w.S).splits;
         rc = launch_weight_grad(w, st);
     }
     return rc;

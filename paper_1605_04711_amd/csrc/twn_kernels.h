@@ -168,7 +168,6 @@ struct WeightGrad {
     float beta;
     int32_t N, H, W, C, O, R, S, P, Q;
     int32_t sh, sw, ph, pw, dh, dw;
-    int32_t splits;
     // First-layer mode (0 = off): X is the zero-bordered 4-channel copy, a "channel" chunk of 8 is two
     // adjacent taps x 4 channels (C = 8, S = pad_sp/2, dw = 2 above), and the reduction maps
     // j' = (r*pad_sp + s)*4 + c back to [O][c_real][R][s_real], dropping the phantom tap and channels.
@@ -188,7 +187,6 @@ struct WgPlan {
     int32_t tiles;          // output tiles (blockIdx.x)
     int32_t ks;             // patch kernel: groups of four waves per workgroup that share a range (1 or 2)
 };
-WgPlan plan_weight_grad(int32_t N, int32_t P, int32_t Q, int32_t C, int32_t O, int32_t R, int32_t S);
 int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st);
 
 // Weight gradient of filters with several taps over patches with halo (twn_bwd_weight_taps.hip).
@@ -207,6 +205,14 @@ struct WgTapsPlan {
     int32_t per, splits;                // patches per pixel range, ranges
 };
 WgTapsPlan plan_weight_grad_taps(const WgShape& w);
+// The kernel and the pixel ranges of a layer's weight gradient; `first`: the shape is that of the first-layer mode.  The workspace
+// query and the launch both ask this.
+struct WgRoute {
+    WgTapsPlan taps;            // taps.use: this kernel, otherwise the general one
+    WgPlan general;
+    int32_t splits;             // ranges of the kernel in use
+};
+WgRoute route_weight_grad(const WgShape& w, bool first);
 int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipStream_t st);
 
 // Weight gradient of a three-channel first layer (twn_bwd_first.hip): partial tiles [splits][O][(r*G + s/4)*16 + (s%4)*4 + c],

@@ -2,10 +2,12 @@
 ends of the ranges that the dispatch rules accept, and whether the GPU tests of a path have shapes that take it."""
 
 import random
+import re
 
 import pytest
 
 import test_gpu_conv as shapes
+import test_gpu_filter_pad as pad_shapes
 from launches import BF16, F32, conv, gemm, launches
 
 
@@ -162,3 +164,72 @@ def test_weight_gradient_and_pointer_load_tests_take_the_general_kernels():
         loads = [l["args"][buf[l["kernel"]]] for l in a["launches"] if l["kernel"] in buf]
         assert loads and set(loads) == {"false"}
         assert not {"conv_small_kernel", "weight_grad_taps_kernel"} & set(kernels(a))
+
+
+def _up(n, to):
+    return (n + to - 1) // to * to
+
+
+def _partials_end(d, found):
+    """Last byte of the workspace that the partial sums of a backward call reach, from the grids of its launches."""
+    n, c, o, r, s = (d[f] for f in "NCORS")
+    p, q = ((d[a] + 2 * d["pad_" + b] - d["dil_" + b] * (d[f] - 1) - 1) // d["stride_" + b] + 1 for a, b, f in ("HhR", "WwS"))
+    by = {l["kernel"]: l["grid"] for l in found}
+    end = offset = 0
+    if "filter_pad_kernel" in by:
+        assert o % 8 != 0
+        o = _up(o, 8)
+        offset = _up(n * p * q * o * 2, 256) + _up(4 * c * 8 * _up(r * s * o, 128) // 128, 256) + _up(4 * o, 256)
+    (kernel,) = [k for k in by if re.fullmatch("(first_)?weight_grad(_patch|_taps)?_kernel", k)]
+    x, y = by[kernel][:2]
+    if kernel == "first_weight_grad_kernel":
+        end = offset + x * o * r * _up(s, 4) * 4 * 4
+    elif kernel == "weight_grad_taps_kernel":
+        ranges, rest = divmod(x, _up(o, 64) // 64 * (_up(c, 32) // 32) * (_up(r * s, 9) // 9))
+        assert rest == 0
+        end = offset + ranges * o * c * r * s * 4 if ranges > 1 else 0
+    elif "pad_c4_kernel" in by:             # the copy of X, then the partial tiles
+        sp = _up(s, 2)
+        offset += _up(n * (d["H"] + 2 * d["pad_h"]) * (d["W"] + 2 * d["pad_w"] + sp - s) * 8, 256)
+        end = offset + y * o * r * sp * 4 * 4
+    elif kernel == "weight_grad_kernel" or y > 1:
+        end = offset + y * o * c * r * s * 4
+    if "bias_grad_final_kernel" in by:
+        where = offset if "pad_c4_kernel" in by and "filter_pad_kernel" not in by else 0
+        end = max(end, where + by["bias_grad_kernel"][1] * d["O"] * 4)
+    return end
+
+
+def test_partial_sums_of_the_weight_gradient_fit_the_workspace():
+    """The workspace query and the launch have to have the same kernel and ranges in mind, with and without padded filters."""
+    rng = random.Random(7)
+    calls = []
+    while len(calls) < 3000:
+        r, dil = rng.choice([1, 2, 3, 3, 3, 5, 7]), rng.choice([1, 1, 1, 2])
+        c = rng.choice([3, 8 * _log(rng, 1, 80), 8 * _log(rng, 1, 80), _log(rng, 1, 600)])
+        d = conv(_log(rng, 1, 64), _log(rng, 1, 120), _log(rng, 1, 120), c, rng.choice([_log(rng, 1, 600), 8 * _log(rng, 1, 80)]), r,
+                 rng.choice([1, 1, 1, 2]), dil=dil, groups=1, pad=rng.choice([0, r // 2 * dil, dil * (r - 1)]))
+        if min(d["H"], d["W"]) + 2 * d["pad_h"] > dil * (r - 1) and d["N"] * d["H"] * d["W"] < 1 << 19:
+            calls.append(dict(fn="bwd", d=d, parts="dw db"))
+    # around the limits of the kernel for several taps: 65536 pixels, 8192 filters x channels
+    calls += [dict(fn="bwd", d=conv(64, 38, 38, 512, 84, 3), parts="dw"), dict(fn="bwd", d=conv(64, 40, 40, 16, 10, 3), parts="dw"),
+              dict(fn="bwd", d=conv(36, 93, 92, 64, 250, 2), parts="dw"), dict(fn="bwd", d=conv(4, 128, 128, 24, 10, 3), parts="dw")]
+    routes, over = {}, []
+    for call, a in zip(calls, launches(calls)):
+        ks = kernels(a)
+        padded = "filter_pad_kernel" in ks
+        for k in ks:
+            routes[k, padded] = routes.get((k, padded), 0) + 1
+        end = _partials_end(call["d"], a["launches"])
+        if end > a["need"]:
+            over.append((call["d"], a["need"], end))
+    assert not over, (len(over), over[:4])
+    wanted = ["weight_grad_patch_kernel", "weight_grad_taps_kernel", "weight_grad_kernel", "first_weight_grad_kernel", "pad_c4_kernel"]
+    assert all(routes.get((k, padded), 0) >= 20 for k in wanted for padded in (False, True)), routes
+
+
+def test_padded_several_tap_tests_take_the_kernel_for_several_taps():
+    calls = [dict(fn="bwd", parts="dw", d=conv(n, h, w, c, o, r, pad=pad)) for n, h, w, c, o, r, pad in pad_shapes.TAPS_CASES]
+    answers = launches(calls)
+    assert all({"filter_pad_kernel", "weight_grad_taps_kernel"} <= set(kernels(a)) for a in answers)
+    assert [kernels(a)[-1] == "weight_grad_sum_kernel" for a in answers] == [True, True, False, False, False]

@@ -51,6 +51,41 @@ def test_filter_pad(groups, n, h, w, c, o, r, stride, pad):
     assert (np.abs(to_host_f64(dw) - 2 * ref_dw) <= 2 * bound).all()
 
 
+# n, h, w, c, o, r, pad: several taps over enough filters x channels or pixels for the kernel that reads patches with halo
+TAPS_CASES = [(9, 33, 29, 72, 115, 3, 1),       # several pixel ranges, a ragged filter block
+              (4, 130, 129, 8, 10, 3, 1),       # many ranges of few filters
+              (1, 8, 8, 512, 510, 3, 1),        # one range: dW written directly, whole tiles and one that ends inside
+              (1, 8, 8, 1024, 507, 2, 0),       # four taps
+              (2, 9, 11, 200, 45, 5, 2)]        # 25 taps: three groups
+
+
+@pytest.mark.parametrize("n,h,w,c,o,r,pad", TAPS_CASES)
+def test_filter_pad_several_taps(n, h, w, c, o, r, pad):
+    """dW and dX as in test_filter_pad; nothing behind the workspace of the query and behind dW is written."""
+    rng = np.random.default_rng(n * h + o)
+    geo = (1, 1), (pad,) * 2, (1, 1)
+    wt = (rng.standard_normal((o, c, r, r)) * 0.05).astype(np.float32)
+    tw = api.twn_ternarize(to_dev_f32(wt), 0.7, transposed=True)
+    codes, _, alpha, _ = ot.ternarize(wt, 0.7)
+    p, q = h + 2 * pad - r + 1, w + 2 * pad - r + 1
+    x = wl.bf16_round(rng.standard_normal((n, h, w, c)).astype(np.float32))
+    dy = wl.bf16_round(rng.standard_normal((n, p, q, o)).astype(np.float32))
+    ref_dw = oc.conv2d_bwd_weight(x, dy, (o, c, r, r), *geo)
+    # see test_filter_pad
+    bound = (n * p * q + 1) * 2.0 ** -24 * oc.conv2d_bwd_weight(np.abs(x), np.abs(dy), (o, c, r, r), *geo)
+    xd, dyd = to_dev_bf16(x), to_dev_bf16(dy)
+    need = api.twn_conv2d_bwd_ste_workspace_bytes(x.shape, tw, *geo)
+    ws = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+    rows = torch.full((o + 8, c, r, r), 3.0, device="cuda")
+    dx, _, _ = api.twn_conv2d_bwd_ste(xd, dyd, tw, *geo, dW=rows[:o], workspace=ws[:need])
+    assert rel_err(to_host_f64(dx), oc.conv2d_bwd_data(dy, codes, alpha, x.shape, *geo)) <= BF16_TOL
+    assert (np.abs(to_host_f64(rows[:o]) - ref_dw) <= bound).all()
+    api.twn_conv2d_bwd_ste(xd, dyd, tw, *geo, need_dx=False, dW=rows[:o], accumulate=True, workspace=ws[:need])
+    assert (np.abs(to_host_f64(rows[:o]) - 2 * ref_dw) <= 2 * bound).all()
+    assert torch.equal(rows[o:], torch.full_like(rows[o:], 3.0))
+    assert bool((ws[need:] == 0x5A).all())
+
+
 def test_filter_pad_no_room():
     """Too little workspace for the padded copies, enough for the partial sums: the layer runs unpadded."""
     rng = np.random.default_rng(5)
