@@ -255,8 +255,9 @@ int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_desc* d1, co
  * case H=W=R=S=1.  d->variant may be TWN_VAR_BF16_POSTSCALE or
  * TWN_VAR_BF16_ALPHA_LDS (it only affects dX); others: TWN_ERR_UNSUPPORTED.
  * Strided layers with dilation 1 may compute dX as one stride-1 problem per
- * residue class of the output pixels, and layers with O % 8 != 0 both gradients
- * over a copy of dY padded to whole multiples of 8 filters, when the workspace
+ * residue class of the output pixels, layers with O % 8 != 0 both gradients
+ * over a copy of dY padded to whole multiples of 8 filters, and three-channel
+ * layers dW in a kernel of their own, when the workspace
  * of twn_conv2d_bwd_ste_workspace_bytes is passed (with less, where that is
  * still enough for the call, by the generic kernels: same result, slower).
  * With alpha_groups > 1 (one alpha per filter group, Alg. 1) alpha_o is a

@@ -358,18 +358,18 @@ FirstGradPlan first_grad_plan(const twn_conv_desc* d, int P, int Q) {
         return FirstGradPlan{};
     return plan_first_weight_grad(taps_shape(d, P, Q));
 }
+size_t first_grad_bytes(const twn_conv_desc* d, const FirstGradPlan& f) {
+    return f.use ? static_cast<size_t>(f.splits) * d->O * f.J * sizeof(float) : 0;
+}
 
-// Weight-gradient workspace: [padded copy of X in first-layer mode] + split partials + bias partials.
+// The least workspace of a weight gradient: [padded copy of X in first-layer mode] + split partials + bias partials.
 size_t weight_grad_bytes(const twn_conv_desc* d, int P, int Q) {
     SmallC sc;
     if (small_c(d, &sc) && d->O % 8 == 0) {
         const int64_t Jp = static_cast<int64_t>(d->R) * sc.Sp * 4;
         const int64_t splits =
             route_weight_grad(WgShape{d->N, sc.Hp, sc.Wp, 8, d->O, d->R, sc.Sp / 2, P, Q, d->stride_h, d->stride_w, 1, 2}, true).splits;
-        const size_t general = sc.x_bytes + static_cast<size_t>((splits * d->O * Jp + 64LL * d->O) * sizeof(float));
-        const FirstGradPlan f = first_grad_plan(d, P, Q);
-        const size_t own = f.use ? static_cast<size_t>(f.splits) * d->O * f.J * sizeof(float) : 0;
-        return general > own ? general : own;       // X may turn out not to be aligned for the three-channel kernel
+        return sc.x_bytes + static_cast<size_t>((splits * d->O * Jp + 64LL * d->O) * sizeof(float));
     }
     const int64_t J = static_cast<int64_t>(d->R) * d->S * d->C;
     const int64_t splits = route_weight_grad(taps_shape(d, P, Q), false).splits;
@@ -607,7 +607,11 @@ extern "C" size_t twn_conv2d_bwd_ste_workspace_bytes(const twn_conv_desc* d) {
     if (p.bytes() > a) a = p.bytes();
     const size_t b = weight_grad_bytes(d, P, Q);
     if (b > a) a = b;
-    const FilterPadPlan pad = plan_filter_pad(d, P, Q);         // more than the least the call takes
+    // more than the least the call takes: a three-channel layer's own kernel, and the padded copies
+    SmallC sc;
+    const size_t f = small_c(d, &sc) && d->O % 8 == 0 ? first_grad_bytes(d, first_grad_plan(d, P, Q)) : 0;
+    if (f > a) a = f;
+    const FilterPadPlan pad = plan_filter_pad(d, P, Q);
     const size_t c = pad.use ? pad.bytes() + twn_conv2d_bwd_ste_workspace_bytes(&pad.d) : 0;
     return a > c ? a : c;
 }
@@ -767,7 +771,7 @@ static int32_t bwd_run(const twn_conv_desc* d, int P, int Q, const void* X, cons
         SmallC sc;
         const bool small = dW && small_c(d, &sc) && d->O % 8 == 0;
         const FirstGradPlan f = small && aligned(X, 4) && aligned(dY, 16) ? first_grad_plan(d, P, Q) : FirstGradPlan{};
-        if (f.use) {
+        if (f.use && workspace_bytes >= first_grad_bytes(d, f)) {
             rc = launch_first_weight_grad(taps_shape(d, P, Q), d->pad_h, d->pad_w, f, w.X, w.dY, w.partial, st);
             if (rc == TWN_OK)
                 rc = launch_first_weight_grad_sum(w.partial, f.splits, d->O, o_real, d->C, d->R, d->S, 4 * f.G, dW_beta, dW, st);

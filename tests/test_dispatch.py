@@ -180,9 +180,11 @@ def _partials_end(d, found):
         assert o % 8 != 0
         o = _up(o, 8)
         offset = _up(n * p * q * o * 2, 256) + _up(4 * c * 8 * _up(r * s * o, 128) // 128, 256) + _up(4 * o, 256)
-    (kernel,) = [k for k in by if re.fullmatch("(first_)?weight_grad(_patch|_taps)?_kernel", k)]
-    x, y = by[kernel][:2]
-    if kernel == "first_weight_grad_kernel":
+    (kernel,) = [k for k in by if re.fullmatch("(first_)?weight_grad(_patch|_taps)?_kernel", k)] or [None]
+    x, y = by.get(kernel, (0, 0))[:2]
+    if kernel is None:
+        pass                                # the bias gradient alone
+    elif kernel == "first_weight_grad_kernel":
         end = offset + x * o * r * _up(s, 4) * 4 * 4
     elif kernel == "weight_grad_taps_kernel":
         ranges, rest = divmod(x, _up(o, 64) // 64 * (_up(c, 32) // 32) * (_up(r * s, 9) // 9))
@@ -233,3 +235,16 @@ def test_padded_several_tap_tests_take_the_kernel_for_several_taps():
     answers = launches(calls)
     assert all({"filter_pad_kernel", "weight_grad_taps_kernel"} <= set(kernels(a)) for a in answers)
     assert [kernels(a)[-1] == "weight_grad_sum_kernel" for a in answers] == [True, True, False, False, False]
+
+
+def test_first_layers_run_with_the_workspace_of_the_general_kernel():
+    """The kernel for three-channel layers may want more than the general one, which the call then falls back to."""
+    ds = [conv(3, 3, 2, 3, 512, 3, 2), conv(15, 3, 20, 3, 88, 1), conv(40, 12, 2, 3, 136, 3), conv(22, 12, 4, 3, 384, 1)]
+    calls = [dict(fn="bwd", d=d, parts=parts) for d in ds for parts in ("dw", "dw db", "db")]
+    least = [a["need"] for a in launches([dict(c, env={"TWN_FIRST": 0}) for c in calls])]
+    full = launches(calls)
+    assert all(a["need"] > n for a, n in zip(full, least))
+    for call, n, f, a in zip(calls, least, full, launches([dict(c, ws=n) for c, n in zip(calls, least)])):
+        assert kernels(a) and _partials_end(call["d"], a["launches"]) <= n
+        if "dw" in call["parts"]:
+            assert "first_weight_grad_kernel" in kernels(f) and "weight_grad_patch_kernel" in kernels(a)
