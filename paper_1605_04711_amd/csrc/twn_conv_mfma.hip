@@ -660,8 +660,9 @@ int32_t launch_gather_gemm_mfma(const GatherGemm& g, int variant, hipStream_t st
             // it, at one workgroup per CU: they win where they leave the busiest CU no more 128x128 blocks than the smaller
             // tiles do (3x3, us, 128x128 -> larger: 32768 pixels, 256 -> 256 channels 33.9 -> 29.4; 50176, 128 -> 128
             // 19.0 -> 17.2; 720000, 128 -> 128 219 -> 211; 131072, 128 -> 128 36.9 both; 8192, 512 -> 512, 128 CUs with two
-            // blocks against 256 with one, 36.5 -> 43) and K is long enough to hide an epilogue that nothing overlaps.
-            if (tile == 15 && g.K >= 1024 && !env_set(Env::STREAM_PC) && !env_set(Env::STREAM_KS)) {
+            // blocks against 256 with one, 36.5 -> 43) and K is long enough to hide an epilogue that nothing overlaps.  256x128
+            // has the one build with four load waves and four stages: an override that asks for another keeps the 128x128 tiles.
+            if (tile == 15 && g.K >= 1024 && !env_set(Env::STREAM_PC) && !env_set(Env::STREAM_KS) && !env_set(Env::STREAM_PC_STAGES)) {
                 auto busiest = [&](int bm, int bn) { return (blocks(bm, bn) + 255) / 256 * (bm / 128) * (bn / 128); };
                 const int64_t have = busiest(128, 128);
                 if (g.NC > 128 && busiest(128, 256) <= have) tile = 17;

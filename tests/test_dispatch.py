@@ -248,3 +248,17 @@ def test_first_layers_run_with_the_workspace_of_the_general_kernel():
         assert kernels(a) and _partials_end(call["d"], a["launches"]) <= n
         if "dw" in call["parts"]:
             assert "first_weight_grad_kernel" in kernels(f) and "weight_grad_patch_kernel" in kernels(a)
+
+
+# 128 x 128 blocks: 392 and 512 (the wider tiles leave the busiest CU no more of them), 392 again with a short K
+WIDE = [conv(16, 56, 56, 128, 128, 3), conv(32, 32, 32, 256, 256, 3), conv(16, 56, 56, 512, 128, 1)]
+
+
+@pytest.mark.parametrize("name,value", [("TWN_STREAM_PC_STAGES", 3), ("TWN_STREAM_PC_STAGES", 4), ("TWN_STREAM_PC", 0), ("TWN_STREAM_PC", 2),
+                                        ("TWN_STREAM_KS", 2), ("TWN_STREAM_OCC", 1), ("TWN_STREAM", 0), ("TWN_BUFLOAD", 0)])
+def test_overrides_of_the_persistent_kernels_run_where_wide_tiles_would(name, value):
+    plain = launches([dict(fn="conv", d=d) for d in WIDE])
+    assert [kernels(a) + a["launches"][0]["args"][:2] for a in plain] == [["conv_stream_pc_kernel", m, n] for m, n in
+                                                                          (("256", "128"), ("128", "256"), ("128", "128"))]
+    for a in launches([dict(fn="conv", d=d, env={name: value}) for d in WIDE]):
+        assert len(kernels(a)) == 1
