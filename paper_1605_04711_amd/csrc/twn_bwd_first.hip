@@ -71,8 +71,7 @@ __global__ __launch_bounds__(256, 1) void first_weight_grad_kernel(const FirstGr
     };
     // this wave's part of dY: 1 KB blocks of eight pixels; 16-byte chunk c of pixel p lies at position c ^ 2 (p & 3), so that the
     // four pixels of a transposing read fall in different banks
-    auto load_dy = [&](int t, int stage) __attribute__((always_inline)) {
-        const At at = place(t);
+    auto load_dy = [&](int t, const At& at, int stage) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < kDyLoads; ++i) {
             const int px = (wave * kDyLoads + i) * 8 + (lane >> 3);
@@ -84,8 +83,7 @@ __global__ __launch_bounds__(256, 1) void first_weight_grad_kernel(const FirstGr
     };
     typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
     u32x3 xr[kXLoads];
-    auto load_x = [&](int t) __attribute__((always_inline)) {
-        const At at = place(t);
+    auto load_x = [&](int t, const At& at) __attribute__((always_inline)) {
         const int h0 = at.oh * a.sh - a.ph, x0 = at.ow * a.sw - a.pw - a.xoff;
 #pragma unroll
         for (int i = 0; i < kXLoads; ++i) {
@@ -162,13 +160,16 @@ __global__ __launch_bounds__(256, 1) void first_weight_grad_kernel(const FirstGr
     };
 
     // ---- prologue: dY of three tiles, X of two ----
-    load_x(first);
-    load_dy(first, 0);
+    At at0 = place(first);                              // at0, at1, at2: tiles t, t + 1, t + 2
+    load_x(first, at0);
+    load_dy(first, at0, 0);
+    At at1 = place(first + 1), at2 = place(first + 2);
+    __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     store_x(0);
-    load_dy(first + 1, 1);
-    load_x(first + 1);
-    load_dy(first + 2, 2);
+    load_dy(first + 1, at1, 1);
+    load_x(first + 1, at1);
+    load_dy(first + 2, at2, 2);
     for (int t = first; t < last; ++t) {
         const int k = t - first, stage = k & 3, buf = k & 1;
         // dY of this tile and its patch are complete in every wave (see below), and nobody reads the tile before any more
@@ -179,8 +180,9 @@ __global__ __launch_bounds__(256, 1) void first_weight_grad_kernel(const FirstGr
         // loads of dY issued after it stay in flight
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(kDyLoads));
         store_x(buf ^ 1);
-        load_x(t + 2);
-        load_dy(t + 3, (k + 3) & 3);
+        const At at3 = place(t + 3);
+        load_x(t + 2, at2);
+        load_dy(t + 3, at3, (k + 3) & 3);
         asm volatile("" ::: "memory");
         read_row(wave * 4, stage, buf, fa[0], fb[0]);
 #pragma unroll
@@ -189,6 +191,19 @@ __global__ __launch_bounds__(256, 1) void first_weight_grad_kernel(const FirstGr
             __builtin_amdgcn_sched_barrier(0);
             if (i < 3) read_row(wave * 4 + i + 1, stage, buf, fa[(i + 1) & 1], fb[(i + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
+            // Past the edge of the output dY is zero, but the windows of such pixels still hold X: zero as well, so that an
+            // infinity there stays out of taps whose sum does not contain it (0.2-0.3 us of a launch; a loop body of its own
+            // for such tiles doubles the accumulators' registers: 45 -> 102 us for the stem).
+            const int inside = at0.oh + wave * 4 + i < a.P ? a.Q - at0.ow : 0;        // pixels of this row
+            if (__builtin_expect(inside < kTile, 0)) {
+                const int left = inside - (g >> 1) * 8;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const uint32_t keep = left >= 2 * d + 2 ? 0xFFFFFFFFu : left == 2 * d + 1 ? 0xFFFFu : 0u;
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) fb[i & 1][n][d >> 1][d & 1] &= keep;
+                }
+            }
 #pragma unroll
             for (int n = 0; n < NT; ++n)
 #pragma unroll
@@ -197,6 +212,9 @@ __global__ __launch_bounds__(256, 1) void first_weight_grad_kernel(const FirstGr
                                                                          join(fb[i & 1][n][0], fb[i & 1][n][1]), acc[ot][n], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         }
+        at0 = at1;
+        at1 = at2;
+        at2 = at3;
     }
     // loads past the last tile still target LDS
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));

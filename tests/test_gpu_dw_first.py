@@ -42,3 +42,34 @@ def test_dw_first(n, h, w, o, r, stride, pad):
     assert torch.equal(again, dw)         # overwritten, and the same bits run to run
     api.twn_conv2d_bwd_ste(to_dev_bf16(x), to_dev_bf16(dy), tw, *geo, need_dx=False, dW=again, accumulate=True)
     assert rel_err(to_host_f64(again), 2 * ref) <= 1e-4
+
+
+@pytest.mark.parametrize("h,w,o,r,stride,pad", [
+    (19, 36, 64, 3, 1, 0),            # one output row and two columns more than whole tiles, no padding
+    (22, 26, 24, 5, 1, 1),
+    (35, 38, 72, 7, 2, 2),
+    (9, 12, 10, 3, 1, 1)])            # fewer than a tile, padded filters
+def test_values_that_are_not_finite_stay_in_their_taps(h, w, o, r, stride, pad):
+    """A value of X reaches the taps whose sum contains it and no other, also where a tile reaches past the output."""
+    rng = np.random.default_rng(h + o)
+    geo = (stride,) * 2, (pad,) * 2, (1, 1)
+    tw = api.twn_ternarize(to_dev_f32(rng.standard_normal((o, 3, r, r)).astype(np.float32)), 0.7, transposed=True)
+    p, q = (h + 2 * pad - r) // stride + 1, (w + 2 * pad - r) // stride + 1
+    x = wl.bf16_round(rng.standard_normal((2, h, w, 3)).astype(np.float32))
+    dy = wl.bf16_round(np.abs(rng.standard_normal((2, p, q, o)).astype(np.float32)) + 0.5)
+    x[0, :, w - 1, 0] = np.inf
+    x[1, h - 1, :, 1] = np.nan
+    x[0, h - 1, 0, 2] = -np.inf
+    at = np.pad(x, ((0, 0), (pad, pad + stride), (pad, pad + stride), (0, 0))).astype(np.float64)
+    ref = np.zeros((o, 3, r, r))
+    with np.errstate(invalid="ignore"):
+        for i in range(r):
+            for j in range(r):
+                win = at[:, i:i + stride * (p - 1) + 1:stride, j:j + stride * (q - 1) + 1:stride]
+                ref[:, :, i, j] = (win[..., None, :] * dy[..., None].astype(np.float64)).sum(axis=(0, 1, 2))
+    _, dw, _ = api.twn_conv2d_bwd_ste(to_dev_bf16(x), to_dev_bf16(dy), tw, *geo, need_dx=False)
+    got = to_host_f64(dw)
+    fine = np.isfinite(ref)
+    assert fine.any() and not fine.all()
+    assert np.array_equal(np.isfinite(got), fine)
+    assert rel_err(got[fine], ref[fine]) <= 1e-4
