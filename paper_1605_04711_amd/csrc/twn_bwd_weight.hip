@@ -834,7 +834,8 @@ __global__ __launch_bounds__(kBiasThreads) void bias_grad_kernel(const uint16_t*
         for (int v = 0; v < VEC; ++v) red[threadIdx.x * VEC + v] = acc[v];     // [row][channel of the group]
         __syncthreads();
         // column sums in two stages: `parts` threads per channel add runs of rows, then one adds the parts
-        const int nch = gc * VEC, parts = kBiasThreads / nch > 0 ? kBiasThreads / nch : 1;
+        const int nch = gc * VEC, most = VEC == 8 ? kBiasThreads / VEC : 32;
+        const int parts = kBiasThreads / nch < most ? kBiasThreads / nch : most;
         const int each = (rows + parts - 1) / parts;
         float s = 0.0f;
         const int c = threadIdx.x % nch, part = threadIdx.x / nch;
@@ -875,19 +876,26 @@ __global__ __launch_bounds__(1024) void bias_grad_final_kernel(const float* __re
     }
 }
 
-// `partial` holds `capacity` floats.  One launch up to 8192 pixels (a thread then adds at most sixteen values per channel),
-// two beyond: the second costs 4 us, and a block that reads more than 128 KB alone costs as much.
+// `partial` holds `capacity` floats, 64 ranges at least.  One launch up to 8192 pixels: a thread then adds at most sixteen values of
+// a channel with 16-byte loads and 32 with single ones, whose blocks have as many rows as that takes and fewer channels
+// the more pixels there are; where such narrow columns of many channels are read (each touches every line of dY), two
+// launches, as beyond (us of a call, one launch / two: 4000 pixels x 250 7.5 / 10; 8192 x 63 8.0 / 10; blocks of sixteen
+// columns there 7.8 and 13.6, in chains of 256).  Then ranges are enough that a thread adds no more than every 256th pixel,
+// however many channels there are.
 template <int VEC>
 static void launch_bias_grad(const uint16_t* dY, int64_t pixels, int O, float* partial, int64_t capacity, float* dbias,
                              hipStream_t st) {
     const int chunks = (O + VEC - 1) / VEC;
-    const bool single = pixels <= 8192;
-    const int gc = single ? (VEC == 8 ? 1 : (O < 16 ? O : 16)) : (VEC == 8 ? (chunks < 8 ? chunks : 8) : (O < 64 ? O : 64));
+    const bool single = pixels <= 8192 && (VEC == 8 || pixels <= 1024 || O * pixels * pixels <= (1LL << 32));
+    const int few = pixels <= 1024 ? 16 : static_cast<int>(16384 / pixels);      // single channels: 512 / few rows
+    const int gc = single ? (VEC == 8 ? 1 : (O < few ? O : few)) : (VEC == 8 ? (chunks < 8 ? chunks : 8) : (O < 64 ? O : 64));
     const int groups = (chunks + gc - 1) / gc;
     int64_t splits = 1;
     if (!single) {
+        const int rows = kBiasThreads / gc;
         splits = 1024 / groups;                                      // about four blocks per CU
-        const int64_t rows8 = static_cast<int64_t>(kBiasThreads / gc) * 8;
+        if (splits < 256 / rows) splits = 256 / rows;
+        const int64_t rows8 = static_cast<int64_t>(rows) * 8;
         if (splits > (pixels + rows8 - 1) / rows8) splits = (pixels + rows8 - 1) / rows8;
         if (splits > capacity / O) splits = capacity / O;
         if (splits < 1) splits = 1;

@@ -163,7 +163,7 @@ struct WeightGrad {
     const uint16_t* dY;     // bf16 NHWC [N][P][Q][O]
     float* dW;              // [O][C][R][S]
     float* dbias;           // [O] or null
-    float* partial;         // workspace: [splits][O][R*S*C] float32, then [splits][O] of dbias
+    float* partial;         // workspace: [splits][O][R*S*C] float32; after the final pass over them [splits][O] of dbias
     int64_t partial_floats; // its size
     float beta;
     int32_t N, H, W, C, O, R, S, P, Q;
