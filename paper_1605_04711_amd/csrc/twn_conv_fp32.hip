@@ -469,8 +469,10 @@ int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st) {
     a.divTN = make_fastdiv_u(static_cast<uint32_t>(p.tiles_n));
     a.walk = 0;
     const int mode = g.plain_gemm ? kF32Gemm : (g.IC % 4 == 0) ? kF32Quad : kF32Element;
-    // short K, no taps to divide: offsets in 32 bits, one wave per tile in the plan
+    // short K, no taps to divide: offsets in 32 bits, rows and paddings far below the 2^28 that marks an element beyond K, one wave
+    // per tile in the plan
     if (mode == kF32Element && g.K <= 64 && p.nw == 1 && g.splits <= 1 && a.narrow && g.divh == 1 && g.divw == 1 &&
+        g.ph < (1 << 24) && g.pw < (1 << 24) &&
         g.M / (static_cast<int64_t>(g.OH) * g.OW) * g.IH * g.IW * g.xs < (1LL << 30) &&
         static_cast<int64_t>(g.R) * abs(g.dh) < (1 << 24) && static_cast<int64_t>(g.S) * abs(g.dw) < (1 << 24) &&
         (static_cast<int64_t>(g.R) * abs(g.dh) * g.IW + static_cast<int64_t>(g.S) * abs(g.dw)) * g.xs < (1LL << 30)) {

@@ -262,3 +262,10 @@ def test_overrides_of_the_persistent_kernels_run_where_wide_tiles_would(name, va
                                                                           (("256", "128"), ("128", "256"), ("128", "128"))]
     for a in launches([dict(fn="conv", d=d, env={name: value}) for d in WIDE]):
         assert len(kernels(a)) == 1
+
+
+def test_short_float32_kernel_leaves_paddings_that_pass_its_sentinel():
+    """Elements behind K carry a row offset of -2^28, which a padding of 2^28 rows would bring back into the image."""
+    d = dict(conv(1, 4, 1, 1, 1, 3, x=F32, y=F32, pad=0), S=1)
+    answers = launches([dict(fn="conv", d=dict(d, pad_h=p)) for p in (1 << 16, 1 << 24, 1 << 28)])
+    assert [kernels(a) for a in answers] == [["gather_gemm_f64_short_kernel"], ["gather_gemm_f64_kernel"], ["gather_gemm_f64_kernel"]]
