@@ -8,6 +8,7 @@ import pytest
 
 import test_gpu_conv as shapes
 import test_gpu_filter_pad as pad_shapes
+import test_gpu_wide_tiles as wide_shapes
 from launches import BF16, F32, conv, gemm, launches
 
 
@@ -269,3 +270,14 @@ def test_short_float32_kernel_leaves_paddings_that_pass_its_sentinel():
     d = dict(conv(1, 4, 1, 1, 1, 3, x=F32, y=F32, pad=0), S=1)
     answers = launches([dict(fn="conv", d=dict(d, pad_h=p)) for p in (1 << 16, 1 << 24, 1 << 28)])
     assert [kernels(a) for a in answers] == [["gather_gemm_f64_short_kernel"], ["gather_gemm_f64_kernel"], ["gather_gemm_f64_kernel"]]
+
+
+def test_wide_tile_tests_walk_to_a_second_tile():
+    for tile, rows, cols in ((17, 128, 256), (18, 256, 128)):
+        answers = launches([dict(fn="conv", d=conv(n, h, w, c, o, 3, groups=g), env={"TWN_TILE": tile})
+                            for n, h, w, c, o, g in wide_shapes.CASES])
+        walks = []
+        for (n, h, w, c, o, g), a in zip(wide_shapes.CASES, answers):
+            assert kernels(a) == ["conv_stream_pc_kernel"] and a["launches"][0]["args"][:2] == [str(rows), str(cols)]
+            walks.append(-(-n * h * w // rows) * -(-o // cols) > a["launches"][0]["grid"][0])
+        assert walks == [False] * (len(walks) - 1) + [True]

@@ -1,5 +1,6 @@
 """The two tiles of one workgroup per CU (128 x 256 and 256 x 128), which large problems get by how they fill the chip: ragged
-row and column blocks, one and several tiles per workgroup, residual and several alphas, against the oracle."""
+row and column blocks, one tile per workgroup and (the last shape: 281 and 282 tiles on 256 CUs) a walk over two, residual and
+several alphas, against the oracle."""
 
 import numpy as np
 import pytest
@@ -13,12 +14,16 @@ from parity import BF16_TOL, rel_err, to_dev_bf16, to_dev_f32, to_host_f64
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("tile", [17, 18])
-@pytest.mark.parametrize("n,h,w,c,o,groups", [
+CASES = [
     (1, 16, 16, 128, 128, 1),          # one tile, whole
     (1, 15, 17, 128, 136, 1),          # a row short, a column block of 8
     (3, 13, 11, 192, 264, 264),        # ragged in both, one alpha per filter
-    (2, 9, 7, 128, 72, 1)])            # less than a tile
+    (2, 9, 7, 128, 72, 1),             # less than a tile
+    (2, 130, 138, 64, 136, 1)]         # more tiles than CUs
+
+
+@pytest.mark.parametrize("tile", [17, 18])
+@pytest.mark.parametrize("n,h,w,c,o,groups", CASES)
 def test_wide_tiles(knob, tile, n, h, w, c, o, groups):
     knob("TWN_TILE", tile)
     rng = np.random.default_rng(n * h + o)
