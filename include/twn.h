@@ -264,9 +264,10 @@ int32_t twn_conv2d_fwd_pair(const twn_conv_desc* d0, const twn_conv_desc* d1, co
  * factor inside the sum over o: dX then needs a workspace.  alpha_o*dY is formed
  * in float32 and kept there as two bf16 terms (high part and remainder, about 17
  * significant bits together), or, where dX is bf16 and the kernel of the shape
- * has a build for it, dY stays as it is and alpha_o multiplies the codes as two
- * such terms; one contraction adds both terms in its float32 accumulators, so no
- * rounding of the inputs is added (twice the arithmetic on this path only). */
+ * has a build for it, dY stays as it is and alpha_o multiplies the codes as three
+ * such terms (all its 24 bits); one contraction adds the terms in its float32
+ * accumulators, so no rounding of the inputs is added (two or three times the
+ * arithmetic on this path only). */
 size_t  twn_conv2d_bwd_ste_workspace_bytes(const twn_conv_desc* d);
 int32_t twn_conv2d_bwd_ste(const twn_conv_desc* d, const void* X, const void* dY,
                            const uint32_t* packed_T, const float* alpha,

@@ -101,6 +101,16 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
     return __uint_as_float(static_cast<uint32_t>(b) << 16);
 }
 
+// A float as three bf16 terms whose sum is the float: 3 x 8 significant bits, each term takes what the ones before leave.
+constexpr int kAlphaTerms = 3;
+__device__ __forceinline__ void alpha_terms(float v, uint16_t* t) {
+#pragma unroll
+    for (int k = 0; k < kAlphaTerms; ++k) {
+        t[k] = f32_to_bf16(v);
+        v -= bf16_to_f32(t[k]);
+    }
+}
+
 // Two bf16 values times two float32 factors, each product as two bf16 terms: hi = bf16(v), lo = bf16(v - hi).
 struct Bf16Terms {
     uint32_t hi, lo;

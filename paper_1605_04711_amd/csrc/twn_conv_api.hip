@@ -672,10 +672,15 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
             return launch_conv_c64_scaled(g, alpha, d->O / d->alpha_groups, st);
     }
     if (p.two && d->variant == TWN_VAR_BF16_POSTSCALE && d->y_dtype == TWN_BF16) {
-        // The alphas stay with the codes where a kernel that would run the two-term problem has a build for it: nothing is scaled.
-        // bf16 outputs only: two terms of alpha are as good as two of alpha * dY on average (2-norm error 2.0e-6 .. 3.1e-6 by how
-        // the alphas lie to powers of two, against 2.45e-6), which one rounding of dX to bf16 hides (1.655e-3 either way) and a
-        // float32 dX would show.
+        // The alphas stay with the codes where a kernel that would run the two-term problem has a build for it (bf16 outputs):
+        // nothing is scaled.  Three terms of alpha are alpha itself, so a product is exact where two of alpha * dY leave 2^-18 of it:
+        // of the bf16 values of dX 1.2e-4 .. 4.5e-4 differ from the rounded exact sum, with two terms of alpha * dY 2.5e-3 (two of alpha
+        // would give 1.8e-3 .. 3.3e-3, by how the alphas lie to powers of two).
+        // The third product costs what grows with the columns and taps, the two-term problem its preparation; above the line that
+        // one's wider tiles win.  us, two terms of alpha * dY against three of alpha: persistent kernel, 3x3, 12544 pixels, 128 ->
+        // 128 channels 17.9, 14.2; 256 -> 256 45.6, 41.9; 256 -> 512 80.6, 79.9; 512 -> 512 113, 174; 3136 pixels, 512 -> 512 45.4, 44.5; 50176, 128 ->
+        // 128 47.9, 46.2; 256 -> 256 117, 151; 1x1, 512 -> 128 45.1, 23.2; 512 -> 512 84.0, 70.9.  Residue classes, 3x3/2,
+        // 12544 pixels, 512 filters over 64 channels 67.1, 40.4; over 256 90.4, 92.1; over 512 150, 161; 25088 pixels 269, 302.
         DxPlan in;
         plan_dx(d, P, Q, &in, p.classes, true);
         const int n = in.classes ? in.cl.count : 1;
@@ -690,8 +695,11 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
         }
         const bool few = conv_small_tile(gs, count) != 0;
         const int tile = few && d->O <= kSmallAlphaMax ? conv_small_tile(g, n) : 0;
-        const bool persistent = !few && !in.classes && !p.classes && gather_gemm_splits(p.g) <= 1 && conv_stream_alpha_applicable(g[0]);
-        const bool batch = !few && in.classes && env_int(Env::DX_CLASS_BATCH, 1) != 0 && gather_gemm_dma_alpha_applicable(g, n);
+        const double third = static_cast<double>(d->N) * P * Q * d->O * (static_cast<double>(d->C) * d->R * d->S - 900.0);
+        const bool persistent = !few && !in.classes && !p.classes && third < 4.9e9 && gather_gemm_splits(p.g) <= 1 &&
+                                conv_stream_alpha_applicable(g[0]);
+        const bool batch = !few && in.classes && third < 1.8e10 && env_int(Env::DX_CLASS_BATCH, 1) != 0 &&
+                           gather_gemm_dma_alpha_applicable(g, n);
         if (tile != 0 || persistent || batch) {
             if (in.classes) {
                 rc = launch_dx_prep(class_prep(d, in.cl, packed_T, codes, dX), st);

@@ -67,8 +67,8 @@ constexpr int dma_min_blocks(int nw, int smem) {
 }
 
 // The kernel proper: workgroup `b` of `nb` of problem `a` (`by`: the K range of a split-K launch).
-// ALPHA: backward-data with several alphas (alpha_in of the problem; IC a multiple of 64), as in conv_stream_pc_kernel: both bf16
-// terms of alpha take the place of the 2 of the codes, from a table behind the stages.
+// ALPHA: backward-data with several alphas (alpha_in of the problem; IC a multiple of 64), as in conv_stream_pc_kernel: the three
+// bf16 terms of alpha take the place of the 2 of the codes, from a table behind the stages.
 template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, bool SPLITK, bool BUF, bool ALPHA = false>
 __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uint32_t nb, const uint32_t b, const uint32_t by) {
     constexpr int NW = WM * WN;                    // waves per workgroup
@@ -331,13 +331,13 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
 
     u32x2 breg[2][NI];      // packed codes of the slab being multiplied / of the next slab
     u32x4 afrag[2][MI];     // activation fragments of step kk in set kk & 1
-    u32x4 bfrag[2][NI];     // expanded codes of step kk in set kk & 1
-    u32x4 blow[2][NI];      // ALPHA: the same with the low terms
-    u32x4 al[2][2];         // ALPHA: high and low terms of step kk in set kk & 1
+    constexpr int TERMS = ALPHA ? kAlphaTerms : 1;
+    u32x4 bfrag[2][TERMS][NI];      // expanded codes of step kk in set kk & 1; ALPHA: times each term
+    u32x4 al[2][TERMS];             // ALPHA: the terms of step kk in set kk & 1
     int c_cur = 0, c_next = 0;      // ALPHA: first reduction channel of the slab being multiplied / of the next
-    uint16_t* const terms = reinterpret_cast<uint16_t*>(smem + STAGES * STAGE_BYTES);      // [hi | lo] of alpha_in
+    uint16_t* const terms = reinterpret_cast<uint16_t*>(smem + STAGES * STAGE_BYTES);      // [term][channel] of alpha_in
     const uint32_t term_base = lds_base + STAGES * STAGE_BYTES + static_cast<uint32_t>(lh) * 64u;
-    const uint32_t term_low = static_cast<uint32_t>(g.IC) * 2u;
+    const uint32_t term_step = static_cast<uint32_t>(g.IC) * 2u;
     auto after = [&](int c) __attribute__((always_inline)) { return c + 64 == g.IC ? 0 : c + 64; };
 
     // code field i of every 32-bit half lands in bits [14,15] of a bf16: 0 / +2.0 / -2.0.  The field is
@@ -351,17 +351,17 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     kmask[5] = sgpr_const<static_cast<int>(0xC000C000u >> 4)>();
     kmask[6] = sgpr_const<static_cast<int>(0xC000C000u >> 2)>();
     kmask[7] = sgpr_const<static_cast<int>(0xC000C000u)>();
-    auto expand = [&](auto kk_tag, auto ni_tag, auto e_tag, const u32x2* br, u32x4* out) __attribute__((always_inline)) {
+    auto expand = [&](auto kk_tag, auto ni_tag, auto e_tag, const u32x2* br, u32x4 (*out)[NI]) __attribute__((always_inline)) {
         constexpr int kk = decltype(kk_tag)::value, ni = decltype(ni_tag)::value, e = decltype(e_tag)::value;
         constexpr int i = (kk & 1) * 4 + e;
         if constexpr (ALPHA) {
             typedef short s16x2 __attribute__((ext_vector_type(2)));
             const uint32_t f = br[ni][kk >> 1] << (14 - 2 * i), sign = f & 0x80008000u;
             const uint32_t on = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, f << 1) >> 15);
-            out[ni][e] = (al[kk & 1][0][e] & on) ^ sign;
-            blow[kk & 1][ni][e] = (al[kk & 1][1][e] & on) ^ sign;
+#pragma unroll
+            for (int k = 0; k < TERMS; ++k) out[k][ni][e] = (al[kk & 1][k][e] & on) ^ sign;
         } else {
-            out[ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
+            out[0][ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
         }
     };
 
@@ -370,7 +370,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     auto step = [&](auto kk_tag, auto cur_tag, int kt, int stage, int next, int fill) __attribute__((always_inline)) {
         constexpr int KK = decltype(kk_tag)::value;
         constexpr int CUR = decltype(cur_tag)::value;
-        constexpr int NM = MI * NI * (ALPHA ? 2 : 1);            // ALPHA: all high terms, then all low ones
+        constexpr int NM = MI * NI * TERMS;                      // ALPHA: all products with one term, then the next
         constexpr int SET = KK & 1, NSET = SET ^ 1;
         constexpr int KN = (KK + 1) & 3;                         // the step being prepared
         constexpr int BSRC = (KK == 3) ? (CUR ^ 1) : CUR;        // its codes: next slab's after the last step
@@ -378,7 +378,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
         constexpr int G0 = (KK == 2) ? 0 : HALF;
         constexpr int P_RA = MI;                                 // pieces: fragment reads,
         constexpr int P_RB = (KK == 2) ? 1 : 0;                  //   codes of the next slab,
-        constexpr int P_AL = ALPHA ? 2 : 0;                      //   terms of the step after the next,
+        constexpr int P_AL = ALPHA ? TERMS : 0;                      //   terms of the step after the next,
         constexpr int P_D = 4 * NI;                              //   code expansion,
         constexpr int P_G = (KK == 2) ? HALF : (KK == 3) ? NLOAD + 1 - HALF : 0;   //   global loads
         constexpr int P = P_RA + P_RB + P_AL + P_D + P_G;
@@ -391,7 +391,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
                 lds_read64_n<NI, 32 * 16>(breg[CUR ^ 1], lds_base + next * STAGE_BYTES + boff);
             } else if constexpr (p < P_RA + P_RB + P_AL) {
                 constexpr int term = p - P_RA - P_RB;
-                const uint32_t at = term_base + static_cast<uint32_t>(KK < 2 ? c_cur : c_next) * 2u + (term ? term_low : 0u);
+                const uint32_t at = term_base + static_cast<uint32_t>(KK < 2 ? c_cur : c_next) * 2u + term * term_step;
                 lds_read128<((KK + 2) & 3) * 16>(al[SET][term], at);
             } else if constexpr (p < P_RA + P_RB + P_AL + P_D) {
                 constexpr int q = p - P_RA - P_RB - P_AL;
@@ -407,10 +407,10 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
             constexpr int j = decltype(j_tag)::value;
             constexpr int mi = j % (MI * NI) / NI, ni = j % NI;
             if constexpr (PINNED) {
-                AgprTile<j>::mfma(bfrag[SET][ni], afrag[SET][mi]);
+                AgprTile<j>::mfma(bfrag[SET][0][ni], afrag[SET][mi]);
             } else {
                 acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    __builtin_bit_cast(bf16x8, j < MI * NI ? bfrag[SET][ni] : blow[SET][ni]),
+                    __builtin_bit_cast(bf16x8, bfrag[SET][j / (MI * NI)][ni]),
                     __builtin_bit_cast(bf16x8, afrag[SET][mi]), acc[mi][ni], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -423,7 +423,7 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
         // everything read during this step is needed by the next one
         lds_wait<0>();
         lds_ready<MI>(afrag[NSET]);
-        if constexpr (ALPHA) lds_ready<2>(al[SET]);
+        if constexpr (ALPHA) lds_ready<TERMS>(al[SET]);
         if constexpr (KK == 2) lds_ready<NI>(breg[CUR ^ 1]);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -435,9 +435,10 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     if constexpr (ALPHA) {
         for (int c = tid; c < g.IC; c += NT) {
             const float v = g.alpha_in[c / g.alpha_in_rows];
-            const uint16_t hi = f32_to_bf16(v);
-            terms[c] = hi;
-            terms[g.IC + c] = f32_to_bf16(v - bf16_to_f32(hi));
+            uint16_t t[kAlphaTerms];
+            alpha_terms(v, t);
+#pragma unroll
+            for (int k = 0; k < kAlphaTerms; ++k) terms[k * g.IC + c] = t[k];
         }
         c_next = after(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // visible after the barrier
@@ -449,17 +450,18 @@ __device__ __forceinline__ void gather_gemm_dma_body(const DmaArgs& a, const uin
     lds_read64_n<NI, 32 * 16>(breg[0], lds_base + boff);
     lds_read128_n<MI, 32 * 128>(afrag[0], lds_base + aoff[0]);
     if constexpr (ALPHA) {
-        lds_read128<0>(al[0][0], term_base);
-        lds_read128<0>(al[0][1], term_base + term_low);
-        lds_read128<16>(al[1][0], term_base);
-        lds_read128<16>(al[1][1], term_base + term_low);
+#pragma unroll
+        for (int k = 0; k < TERMS; ++k) {
+            lds_read128<0>(al[0][k], term_base + k * term_step);
+            lds_read128<16>(al[1][k], term_base + k * term_step);
+        }
     }
     lds_wait<0>();
     lds_ready<NI>(breg[0]);
     lds_ready<MI>(afrag[0]);
     if constexpr (ALPHA) {
-        lds_ready<2>(al[0]);
-        lds_ready<2>(al[1]);
+        lds_ready<TERMS>(al[0]);
+        lds_ready<TERMS>(al[1]);
     }
     static_for<4 * NI>([&](auto q_tag) __attribute__((always_inline)) {
         constexpr int q = decltype(q_tag)::value;
@@ -652,7 +654,8 @@ struct DmaBatchArgs {
 };
 constexpr int kDmaAlphaMax = 1024;          // reduction channels of the table of terms
 template <int BM, int BN, int WM, int WN, int STAGES, bool BUF, bool ALPHA = false>
-__global__ __launch_bounds__(64 * WM * WN, dma_min_blocks(WM * WN, STAGES * (BM * 128 + BN * 16) + (ALPHA ? kDmaAlphaMax * 4 : 0)))
+__global__ __launch_bounds__(64 * WM * WN, dma_min_blocks(WM * WN, STAGES * (BM * 128 + BN * 16) +
+                                                                   (ALPHA ? kDmaAlphaMax * 2 * kAlphaTerms : 0)))
 void gather_gemm_dma_batch_kernel(const DmaBatchArgs ba) {
     const uint32_t c = blockIdx.y;
     const uint32_t nb = ba.blocks[c];
@@ -791,7 +794,7 @@ extern "C" int32_t twn_debug_set_trace(void* buf) {
 
 template <int BM, int BN, int WM, int WN, int STAGES, bool BUF, bool ALPHA = false>
 static int32_t launch_dma_batch_kernel(const DmaBatchArgs& ba, unsigned width, int count, hipStream_t st) {
-    constexpr int SMEM = STAGES * (BM * 128 + BN * 16) + (ALPHA ? kDmaAlphaMax * 4 : 0);
+    constexpr int SMEM = STAGES * (BM * 128 + BN * 16) + (ALPHA ? kDmaAlphaMax * 2 * kAlphaTerms : 0);
     auto k = gather_gemm_dma_batch_kernel<BM, BN, WM, WN, STAGES, BUF, ALPHA>;
     static std::once_flag once;
     static bool allowed = false;
@@ -840,7 +843,7 @@ int32_t launch_gather_gemm_dma_batch(const GatherGemm* gs, int count, int tile, 
 }
 
 // The same over problems with alpha_in, 64 or 128 columns wide.  ResNet-18 b64, one alpha per filter, the strided 3x3 layers with
-// the scaling and gathering launch (us): 56x56x64 <- 128 53.1 -> 36.8; 28x28x128 <- 256 41.8 -> 27.5; 14x14x256 <- 512 52.3 -> 33.5.
+// the scaling and gathering launch (us): 56x56x64 <- 128 51.5 -> 39.4; 28x28x128 <- 256 40.7 -> 31.3; 14x14x256 <- 512 51.5 -> 37.7.
 bool gather_gemm_dma_alpha_applicable(const GatherGemm* gs, int count) {
     if (count < 1 || count > kDmaBatchMax || env_int(Env::TILE, 0) != 0) return false;
     for (int c = 0; c < count; ++c) {

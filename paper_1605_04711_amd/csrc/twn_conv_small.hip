@@ -207,7 +207,7 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.0f;
 
-    // the terms of alpha_in: [hi | lo], whole slabs; requested before the first slabs, written after
+    // the terms of alpha_in: [term][channel], whole slabs; requested before the first slabs, written after
     const int span = (g.IC + 63) & ~63;
     uint16_t* const terms = reinterpret_cast<uint16_t*>(smem + NW * WAVE_BYTES);
     const uint32_t lds_terms = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
@@ -224,9 +224,10 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
     if constexpr (ALPHA) {
         for (int c = tid; c < span; c += 64 * NW) {
             const float v = c == tid ? my_alpha : (c < g.IC ? g.alpha_in[c / g.alpha_in_rows] : 0.0f);
-            const uint16_t hi = f32_to_bf16(v);
-            terms[c] = hi;
-            terms[span + c] = f32_to_bf16(v - bf16_to_f32(hi));
+            uint16_t t[kAlphaTerms];
+            alpha_terms(v, t);
+#pragma unroll
+            for (int k = 0; k < kAlphaTerms; ++k) terms[k * span + c] = t[k];
         }
         __syncthreads();
     }
@@ -250,8 +251,9 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
             }
             u32x2 w[NT];
             u32x4 x[4][MT];
-            u32x4 al[4][2];
-            constexpr int READS = MT + (ALPHA ? 2 : 0);         // of a step
+            u32x4 al[4][kAlphaTerms];
+            constexpr int TERMS = ALPHA ? kAlphaTerms : 1;
+            constexpr int READS = MT + (ALPHA ? TERMS : 0);         // of a step
             const uint32_t cbase = lds_mine + DEPTH * STAGE + ((sg >> 2) & 1) * CODES + lrow * 64 + lh * 8 + ((p ^ ((lrow >> 2) & 3)) * 16);
             lds_read64_n<NT, 32 * 64>(w, cbase);
 #pragma unroll
@@ -266,8 +268,9 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
                     } else if constexpr (MODE == kSmallChunk) {
                         c -= fdiv_u(c, a.divIC) * static_cast<uint32_t>(g.IC);
                     }
-                    lds_read128<0>(al[kk][0], lds_terms + c * 2u);
-                    lds_read128<0>(al[kk][1], lds_terms + static_cast<uint32_t>(span + static_cast<int>(c)) * 2u);
+#pragma unroll
+                    for (int k = 0; k < TERMS; ++k)
+                        lds_read128<0>(al[kk][k], lds_terms + static_cast<uint32_t>(k * span + static_cast<int>(c)) * 2u);
                 }
             }
             static_for<4>([&](auto kk_tag) __attribute__((always_inline)) {
@@ -275,11 +278,11 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
                 lds_wait<(3 - kk) * READS>();
                 if constexpr (kk == 0) lds_ready<NT>(w);
                 lds_ready<MT>(x[kk]);
-                if constexpr (ALPHA) lds_ready<2>(al[kk]);
+                if constexpr (ALPHA) lds_ready<TERMS>(al[kk]);
                 if constexpr (kk == 3) {
                     if (s + DEPTH < ns) fetch(s + DEPTH, st);   // every read of this stage has returned
                 }
-                u32x4 wf[NT], wl[NT];
+                u32x4 wf[TERMS][NT];
 #pragma unroll
                 for (int ni = 0; ni < NT; ++ni)
 #pragma unroll
@@ -290,24 +293,21 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
                             typedef short s16x2 __attribute__((ext_vector_type(2)));
                             const uint32_t f = w[ni][kk >> 1] << (14 - 2 * i), sign = f & 0x80008000u;
                             const uint32_t on = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, f << 1) >> 15);
-                            wf[ni][e] = (al[kk][0][e] & on) ^ sign;
-                            wl[ni][e] = (al[kk][1][e] & on) ^ sign;
+#pragma unroll
+                            for (int k = 0; k < TERMS; ++k) wf[k][ni][e] = (al[kk][k][e] & on) ^ sign;
                         } else {
-                            wf[ni][e] = (w[ni][kk >> 1] & (0xC000C000u >> (14 - 2 * i))) << (14 - 2 * i);
+                            wf[0][ni][e] = (w[ni][kk >> 1] & (0xC000C000u >> (14 - 2 * i))) << (14 - 2 * i);
                         }
                     }
 #pragma unroll
                 for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
-                    for (int ni = 0; ni < NT; ++ni) {
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[ni]),
-                                                                              __builtin_bit_cast(bf16x8, x[kk][mi]),
-                                                                              acc[mi][ni], 0, 0, 0);
-                        if constexpr (ALPHA)
-                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wl[ni]),
+                    for (int ni = 0; ni < NT; ++ni)
+#pragma unroll
+                        for (int k = 0; k < TERMS; ++k)
+                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[k][ni]),
                                                                                   __builtin_bit_cast(bf16x8, x[kk][mi]),
                                                                                   acc[mi][ni], 0, 0, 0);
-                    }
             });
             st = (st + 1 == DEPTH) ? 0 : st + 1;
         });
@@ -422,9 +422,9 @@ int32_t launch_small_build(const SmallArgs<NP>& a, uint32_t width, int count, hi
     // the table of terms takes the third slab's place where both do not fit
     constexpr int DEPTH = ALPHA && NT == 2 ? 2 : 3;
     constexpr int STAGES = NW * small_wave_bytes(MT, NT, DEPTH);
-    constexpr int MOST = STAGES + (ALPHA ? kSmallAlphaMax * 4 : 0);
+    constexpr int MOST = STAGES + (ALPHA ? kSmallAlphaMax * 2 * kAlphaTerms : 0);
     static_assert(MOST <= 160 * 1024, "LDS budget");
-    const int SMEM = STAGES + (ALPHA ? ((a.p[0].g.IC + 63) & ~63) * 4 : 0);
+    const int SMEM = STAGES + (ALPHA ? ((a.p[0].g.IC + 63) & ~63) * 2 * kAlphaTerms : 0);
     auto k = conv_small_kernel<MT, NT, NW, MODE, NP, DEPTH, ALPHA>;
     // more than 64 KB of dynamic LDS has to be allowed once per kernel
     static std::once_flag once;

@@ -13,12 +13,12 @@
 // finished the first half of the current slab; after the barrier the load waves refill the stage of the
 // previous slab.  Four stages, so that a load has two slab times to land.
 //
-// ALPHA: backward-data with several alphas (alpha_in of the problem).  alpha of a reduction channel, as two bf16 terms hi = bf16(alpha)
-// and lo = bf16(alpha - hi), replaces the 2 of its codes, and a fragment of dY is multiplied by both: against two terms of alpha * dY
-// side by side, half the slabs, half the fragment reads per MFMA and no launch that scales dY.  The terms lie in LDS; a step
-// reads the sixteen of the step after the next (the same for all lanes of a half).  dX with the scaling launch before (us): 64x28x28,
-// 128 -> 128 channels 3x3 54.3 -> 39.5; 64x14x14, 256 47.2 -> 35.3; 64x7x7, 512 49.5 -> 40.4; 128x16x16, 256 84.8 -> 73.7;
-// 64x40x40, 256 233 -> 216; 20x56x56, 1x1, 512 filters over 128 53.6 -> 20.4.
+// ALPHA: backward-data with several alphas (alpha_in of the problem).  alpha of a reduction channel, as three bf16 terms
+// (all of a float's 24 bits), replaces the 2 of its codes, and a fragment of dY is multiplied by each: against two terms of alpha * dY
+// side by side, half the slabs, a third of the fragment reads per MFMA and no launch that scales dY, for half as many products again.
+// The terms lie in LDS; a step reads those of the step after the next (the same for all lanes of a half).  dX with the scaling
+// launch before (us): 64x28x28, 128 -> 128 channels 3x3 47.9 -> 46.2; 64x14x14, 128 17.9 -> 14.2; 256 45.6 -> 41.9; 64x7x7, 256
+// filters over 512 25.9 -> 24.6; 1x1, 20x56x56, 512 filters over 128 53.6 -> 24.9.  Which of the two runs is decided in data_gradient.
 #include <mutex>
 
 #include "twn_kernels.h"
@@ -93,7 +93,7 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     float* colbuf = reinterpret_cast<float*>(smem + STAGES * STAGE_BYTES);          // [2][2][BN]: mul, add of even / odd tiles
     unsigned char* dummy = smem + STAGES * STAGE_BYTES + 4 * BN * 4;                // 1 KB sink of the padding loads
-    uint16_t* const terms = reinterpret_cast<uint16_t*>(dummy + 1024);              // ALPHA: [hi | lo] of alpha_in
+    uint16_t* const terms = reinterpret_cast<uint16_t*>(dummy + 1024);              // ALPHA: [term][channel] of alpha_in
     static_assert(!ALPHA || KS == 1, "the slabs of a wave are consecutive");
 
     const GatherGemm& g = a.g;
@@ -295,13 +295,13 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
 
     u32x2 breg[2][NI];      // packed codes of the slab being multiplied / of the next slab
     u32x4 afrag[2][MI];     // activation fragments of step kk in set kk & 1
-    u32x4 bfrag[2][NI];     // expanded codes of step kk in set kk & 1
-    u32x4 blow[2][NI];      // ALPHA: the same with the low terms
-    u32x4 al[2][2];         // ALPHA: high and low terms of step kk in set kk & 1
+    constexpr int TERMS = ALPHA ? kAlphaTerms : 1;
+    u32x4 bfrag[2][TERMS][NI];      // expanded codes of step kk in set kk & 1; ALPHA: times each term
+    u32x4 al[2][TERMS];             // ALPHA: the terms of step kk in set kk & 1
     int c_cur = 0, c_next = 0;      // ALPHA: first reduction channel of the slab being multiplied / of the next
     const uint32_t term_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) unsigned char*)(dummy + 1024))) + static_cast<uint32_t>(lh) * 64u;
-    const uint32_t term_low = static_cast<uint32_t>(a.spt) * 128u;      // 64 * spt channels of two bytes
+    const uint32_t term_step = static_cast<uint32_t>(a.spt) * 128u;      // 64 * spt channels of two bytes
     auto after = [&](int c) __attribute__((always_inline)) { return c + 64 == a.spt * 64 ? 0 : c + 64; };
 
     uint32_t kmask[8];
@@ -313,17 +313,17 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     kmask[5] = sgpr_const<static_cast<int>(0xC000C000u >> 4)>();
     kmask[6] = sgpr_const<static_cast<int>(0xC000C000u >> 2)>();
     kmask[7] = sgpr_const<static_cast<int>(0xC000C000u)>();
-    auto expand = [&](auto kk_tag, auto ni_tag, auto e_tag, const u32x2* br, u32x4* out) __attribute__((always_inline)) {
+    auto expand = [&](auto kk_tag, auto ni_tag, auto e_tag, const u32x2* br, u32x4 (*out)[NI]) __attribute__((always_inline)) {
         constexpr int kk = decltype(kk_tag)::value, ni = decltype(ni_tag)::value, e = decltype(e_tag)::value;
         constexpr int i = (kk & 1) * 4 + e;
         if constexpr (ALPHA) {
             typedef short s16x2 __attribute__((ext_vector_type(2)));
             const uint32_t f = br[ni][kk >> 1] << (14 - 2 * i), sign = f & 0x80008000u;
             const uint32_t on = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2, f << 1) >> 15);
-            out[ni][e] = (al[kk & 1][0][e] & on) ^ sign;
-            blow[kk & 1][ni][e] = (al[kk & 1][1][e] & on) ^ sign;
+#pragma unroll
+            for (int k = 0; k < TERMS; ++k) out[k][ni][e] = (al[kk & 1][k][e] & on) ^ sign;
         } else {
-            out[ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
+            out[0][ni][e] = (br[ni][kk >> 1] & kmask[i]) << (14 - 2 * i);
         }
     };
 
@@ -332,14 +332,13 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     auto step = [&](auto kk_tag, auto cur_tag, int stage, int next) __attribute__((always_inline)) {
         constexpr int KK = decltype(kk_tag)::value;
         constexpr int CUR = decltype(cur_tag)::value;
-        constexpr int TERMS = ALPHA ? 2 : 1;
         constexpr int NM = MI * NI * TERMS;
         constexpr int SET = KK & 1, NSET = SET ^ 1;
         constexpr int KN = (KK + 1) & 3;
         constexpr int BSRC = (KK == 3) ? (CUR ^ 1) : CUR;
         constexpr int P_RA = MI;
         constexpr int P_RB = (KK == 2) ? 1 : 0;
-        constexpr int P_AL = ALPHA ? 2 : 0;
+        constexpr int P_AL = ALPHA ? TERMS : 0;
         constexpr int P_D = 4 * NI;
         constexpr int P = P_RA + P_RB + P_AL + P_D;
         const uint32_t a_addr = lds_base + ((KK == 3) ? next : stage) * STAGE_BYTES + aoff[KN];
@@ -352,7 +351,7 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
             } else if constexpr (pp < P_RA + P_RB + P_AL) {
                 // terms of the step after the next, whose set the expansion before this step has used up
                 constexpr int term = pp - P_RA - P_RB;
-                const uint32_t at = term_base + static_cast<uint32_t>(KK < 2 ? c_cur : c_next) * 2u + (term ? term_low : 0u);
+                const uint32_t at = term_base + static_cast<uint32_t>(KK < 2 ? c_cur : c_next) * 2u + term * term_step;
                 lds_read128<((KK + 2) & 3) * 16>(al[SET][term], at);
             } else {
                 constexpr int qq = pp - P_RA - P_RB - P_AL;
@@ -362,9 +361,9 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         };
         static_for<NM>([&](auto j_tag) __attribute__((always_inline)) {
             constexpr int jj = decltype(j_tag)::value;
-            constexpr int mi = jj % (MI * NI) / NI, ni = jj % NI;      // ALPHA: all high terms, then all low ones
+            constexpr int mi = jj % (MI * NI) / NI, ni = jj % NI;      // ALPHA: all products with one term, then the next
             acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8, jj < MI * NI ? bfrag[SET][ni] : blow[SET][ni]),
+                __builtin_bit_cast(bf16x8, bfrag[SET][jj / (MI * NI)][ni]),
                 __builtin_bit_cast(bf16x8, afrag[SET][mi]), acc[mi][ni], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             static_for<P>([&](auto p_tag) __attribute__((always_inline)) {
@@ -375,7 +374,7 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         });
         lds_wait<0>();
         lds_ready<MI>(afrag[NSET]);
-        if constexpr (ALPHA) lds_ready<2>(al[SET]);
+        if constexpr (ALPHA) lds_ready<TERMS>(al[SET]);
         if constexpr (KK == 2) lds_ready<NI>(breg[CUR ^ 1]);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -477,9 +476,10 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         const int span = a.spt * 64;
         for (int c = tid; c < span; c += 64 * NWC) {
             const float v = c < g.IC ? g.alpha_in[c / g.alpha_in_rows] : 0.0f;
-            const uint16_t hi = f32_to_bf16(v);
-            terms[c] = hi;
-            terms[span + c] = f32_to_bf16(v - bf16_to_f32(hi));
+            uint16_t t[kAlphaTerms];
+            alpha_terms(v, t);
+#pragma unroll
+            for (int k = 0; k < kAlphaTerms; ++k) terms[k * span + c] = t[k];
         }
         c_next = KTS > 1 ? after(0) : 0;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // visible after the barrier
@@ -491,17 +491,18 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     lds_read64_n<NI, 32 * 16>(breg[0], lds_base + boff);
     lds_read128_n<MI, 32 * 128>(afrag[0], lds_base + aoff[0]);
     if constexpr (ALPHA) {
-        lds_read128<0>(al[0][0], term_base);
-        lds_read128<0>(al[0][1], term_base + term_low);
-        lds_read128<16>(al[1][0], term_base);
-        lds_read128<16>(al[1][1], term_base + term_low);
+#pragma unroll
+        for (int k = 0; k < TERMS; ++k) {
+            lds_read128<0>(al[0][k], term_base + k * term_step);
+            lds_read128<16>(al[1][k], term_base + k * term_step);
+        }
     }
     lds_wait<0>();
     lds_ready<NI>(breg[0]);
     lds_ready<MI>(afrag[0]);
     if constexpr (ALPHA) {
-        lds_ready<2>(al[0]);
-        lds_ready<2>(al[1]);
+        lds_ready<TERMS>(al[0]);
+        lds_ready<TERMS>(al[1]);
     }
     static_for<4 * NI>([&](auto q_tag) __attribute__((always_inline)) {
         constexpr int qq = decltype(q_tag)::value;
@@ -578,7 +579,7 @@ constexpr int kStreamAlphaMax = 1024;       // reduction channels of the table o
 
 template <int BM, int BN, int WM, int WN, int STAGES, bool GEMM, int OCC, int KS, int NP, bool ALPHA = false>
 int32_t launch_pc_kernel(const StreamPcArgs& a, hipStream_t st) {
-    constexpr int SMEM = STAGES * KS * (BM * 128 + BN * 16) + 4 * BN * 4 + 1024 + (ALPHA ? kStreamAlphaMax * 4 : 0);
+    constexpr int SMEM = STAGES * KS * (BM * 128 + BN * 16) + 4 * BN * 4 + 1024 + (ALPHA ? kStreamAlphaMax * 2 * kAlphaTerms : 0);
     constexpr int THREADS = 64 * (WM * WN * KS + NP);
     static_assert(SMEM <= 160 * 1024, "LDS budget");
     static_assert(THREADS <= 1024, "workgroup size");
@@ -644,7 +645,7 @@ int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int ks, int np, int
     }
 }
 
-// Undivided backward-data with several alphas (alpha_in): 64x128 tiles, whose accumulators leave room for both terms of the codes.
+// Undivided backward-data with several alphas (alpha_in): 64x128 tiles, whose accumulators leave room for the terms of the codes.
 bool conv_stream_alpha_applicable(const GatherGemm& g) {
     return g.IC <= kStreamAlphaMax && g.NC > 64 && env_int(Env::TILE, 0) == 0 && env_int(Env::STREAM, 1) != 0 &&
            !env_set(Env::STREAM_PC) && !env_set(Env::STREAM_KS) && !env_set(Env::STREAM_PC_STAGES) && !env_set(Env::STREAM_OCC) &&

@@ -43,7 +43,7 @@ struct GatherGemm {
     float* partial;         // split-K workspace [splits][M][NC] float32 (float64 on the float32 path; null when splits == 1)
     int32_t splits;         // K is cut into this many ranges of whole 64-wide slabs
     // Backward-data with several alphas, inside the contraction: the code of reduction channel c counts alpha_in[c / alpha_in_rows]
-    // times, as two bf16 terms (null: 1).  Only conv_small and the *_alpha launchers take it.
+    // times, as three bf16 terms (null: 1).  Only conv_small and the *_alpha launchers take it.
     const float* alpha_in;
     int32_t alpha_in_rows;
 };

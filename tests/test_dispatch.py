@@ -7,6 +7,7 @@ import re
 import pytest
 
 import test_gpu_conv as shapes
+import test_gpu_dx_alpha as alpha_shapes
 import test_gpu_filter_pad as pad_shapes
 import test_gpu_wide_tiles as wide_shapes
 from launches import BF16, F32, conv, gemm, launches
@@ -281,3 +282,24 @@ def test_wide_tile_tests_walk_to_a_second_tile():
             assert kernels(a) == ["conv_stream_pc_kernel"] and a["launches"][0]["args"][:2] == [str(rows), str(cols)]
             walks.append(-(-n * h * w // rows) * -(-o // cols) > a["launches"][0]["grid"][0])
         assert walks == [False] * (len(walks) - 1) + [True]
+
+
+def _dx_alpha(d, small=1):
+    """Whether the alphas of backward-data stay with the codes (the ALPHA builds), per call."""
+    return [[(l["kernel"], l["args"][-1]) for l in a["launches"] if l["kernel"] != "dx_prep_kernel"][0]
+            for a in launches([dict(fn="bwd", parts="dx", d=x, env={"TWN_SMALL": small}) for x in d])]
+
+
+def test_exact_alpha_tests_take_the_alphas_with_the_codes():
+    for small, wanted in ((1, [("conv_small_kernel", "true")] * 6),
+                          (0, [("conv_stream_pc_kernel", "true")] * 2 + [("gather_gemm_dma_batch_kernel", "true")] * 2)):
+        cases = [c[1:] for c in alpha_shapes.EXACT_CASES if c[0] == small]
+        assert _dx_alpha([conv(n, h, w, c, o, r, s, pad, groups=o) for n, h, w, c, o, r, s, pad in cases], small) == wanted
+
+
+def test_alphas_stay_with_the_codes_while_the_third_product_costs_less_than_scaling():
+    layers = [(conv(64, 14, 14, 256, 256, 3, groups=256), True), (conv(64, 14, 14, 512, 512, 3, groups=512), False),
+              (conv(64, 7, 7, 512, 512, 3, groups=512), False), (conv(64, 7, 7, 512, 256, 3, groups=256), True),
+              (conv(64, 40, 40, 256, 256, 3, groups=256), False), (conv(64, 40, 40, 256, 256, 1, groups=256), True),
+              (conv(64, 28, 28, 256, 512, 3, 2, groups=512), True), (conv(64, 28, 28, 512, 512, 3, 2, groups=512), False)]
+    assert [a == "true" for _, a in _dx_alpha([d for d, _ in layers])] == [inside for _, inside in layers]

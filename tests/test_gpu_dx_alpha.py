@@ -75,3 +75,34 @@ def test_dx_alpha_large_kernels(knob, n, h, w, c, o, r, stride, pad, dil, per):
     assert rel_err(got, ref) <= BF16_TOL
     again, _, _ = api.twn_conv2d_bwd_ste(x, to_dev_bf16(dy), tw, *geo, need_dw=False)
     assert torch.equal(again, dx)
+
+
+# few-tile kernel, each of its tiles, taps of whole slabs, chunks, plain product, residue classes; then (second field 0) the
+# persistent kernel over taps and as a plain product, and the batched residue classes of 64 and of more columns
+EXACT_CASES = [
+    (1, 2, 10, 10, 64, 128, 3, 1, 1), (1, 3, 21, 21, 256, 128, 3, 1, 1), (1, 5, 28, 27, 200, 128, 3, 1, 1),
+    (1, 2, 9, 11, 40, 72, 3, 1, 1), (1, 33, 1, 1, 72, 200, 1, 1, 0), (1, 2, 13, 11, 40, 72, 3, 2, 1),
+    (0, 100, 9, 11, 72, 128, 3, 1, 1), (0, 5, 8, 8, 128, 64, 1, 1, 0), (0, 3, 55, 56, 64, 128, 3, 2, 1), (0, 9, 33, 31, 136, 192, 3, 2, 1)]
+
+
+@pytest.mark.parametrize("small,n,h,w,c,o,r,stride,pad", EXACT_CASES)
+def test_dx_alpha_keeps_every_bit_of_alpha(knob, small, n, h, w, c, o, r, stride, pad):
+    """dY has one value, a power of two, in a neighbourhood, so every value of dX is one product alpha * dY: a float32.  The alphas
+    lie 1..3 * 2^-19 beside a tie of bf16; two bf16 terms of one would be the tie itself and round the other way."""
+    knob("TWN_SMALL", small)
+    rng = np.random.default_rng(n * h + o)
+    step = np.arange(o) % 3 + 1
+    v = np.where(np.arange(o) % 2, 1 + 2.0**-8 + step * 2.0**-19, 1 + 2.0**-7 + 2.0**-8 - step * 2.0**-19).astype(np.float32)
+    wt = v[:, None, None, None] * rng.choice(np.float32([-1, 1]), (o, c, r, r))
+    tw = api.twn_ternarize(to_dev_f32(wt), 0.7, groups=o, transposed=True)
+    assert np.array_equal(tw.alpha.cpu().numpy(), v)
+    geo = (stride,) * 2, (pad,) * 2, (1, 1)
+    p, q = (h + 2 * pad - r) // stride + 1, (w + 2 * pad - r) // stride + 1
+    dy = np.zeros((n, p, q, o), np.float32)
+    at = dy[:, ::r, ::r]                          # r apart: no value of dX sees two of them
+    which = rng.integers(0, o, at.shape[:3])
+    np.put_along_axis(at, which[..., None], rng.choice(np.float32([0.5, -1, 2]), at.shape[:3])[..., None], 3)
+    x = to_dev_bf16(np.zeros((n, h, w, c), np.float32))
+    dx, _, _ = api.twn_conv2d_bwd_ste(x, to_dev_bf16(dy), tw, *geo, need_dw=False)
+    exact = oc.conv2d_bwd_data(dy, np.sign(wt).astype(np.int8), v, (n, h, w, c), *geo)
+    assert np.count_nonzero(exact) and np.array_equal(to_host_f64(dx), wl.bf16_round(exact.astype(np.float32)))
