@@ -296,6 +296,9 @@ def test_exact_alpha_tests_take_the_alphas_with_the_codes():
         cases = [c[1:] for c in alpha_shapes.EXACT_CASES if c[0] == small]
         assert _dx_alpha([conv(n, h, w, c, o, r, s, pad, groups=o) for n, h, w, c, o, r, s, pad in cases], small) == wanted
 
+    large = _dx_alpha([conv(n, h, w, c, o, r, s, pad, dil, o // per) for n, h, w, c, o, r, s, pad, dil, per in alpha_shapes.LARGE_CASES], 0)
+    assert large[:4] == [("conv_stream_pc_kernel", "true")] * 4 and large[6] == ("conv_stream_pc_kernel", "true")
+
 
 def test_alphas_stay_with_the_codes_while_the_third_product_costs_less_than_scaling():
     layers = [(conv(64, 14, 14, 256, 256, 3, groups=256), True), (conv(64, 14, 14, 512, 512, 3, groups=512), False),

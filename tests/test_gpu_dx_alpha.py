@@ -46,17 +46,24 @@ def test_dx_alpha(n, h, w, c, o, r, stride, pad, dil, per):
         assert rel_err(got, ref) <= worst
 
 
-@pytest.mark.parametrize("n,h,w,c,o,r,stride,pad,dil,per", [
-    (3, 9, 11, 72, 128, 3, 1, 1, 1, 1),       # two slabs per tap, ragged rows and columns
-    (2, 13, 12, 136, 192, 3, 1, 1, 2, 3),     # three slabs per tap, dilation, several filters per alpha
+LARGE_CASES = [
+    (100, 9, 11, 72, 128, 3, 1, 1, 1, 1),     # two slabs per tap, ragged rows and columns
+    (60, 13, 12, 136, 192, 3, 1, 1, 2, 3),    # three slabs per tap, dilation, several filters per alpha
+    (170, 9, 11, 136, 128, 3, 1, 1, 1, 1),    # 528 tiles: several per workgroup
+    (9, 20, 21, 264, 1024, 1, 1, 0, 1, 1),    # plain product, the largest table
+    (3, 9, 11, 72, 128, 3, 1, 1, 1, 1),       # the same with K cut into ranges: terms of alpha * dY
+    (2, 13, 12, 136, 192, 3, 1, 1, 2, 3),
     (5, 8, 8, 128, 64, 1, 1, 0, 1, 1),        # plain product of one slab
-    (1, 20, 21, 264, 1024, 1, 1, 0, 1, 1),    # plain product, the largest table
-    (1, 6, 7, 72, 1088, 1, 1, 0, 1, 1),       # beyond it: terms of alpha * dY
-    (8, 66, 66, 128, 64, 3, 1, 1, 1, 1),      # several tiles per workgroup, one slab per tap
+    (1, 20, 21, 264, 1024, 1, 1, 0, 1, 1),
+    (1, 6, 7, 72, 1088, 1, 1, 0, 1, 1),       # beyond the table
+    (8, 66, 66, 128, 64, 3, 1, 1, 1, 1),      # 64 filters: terms formed in the contraction
     (3, 55, 56, 64, 128, 3, 2, 1, 1, 1),      # residue classes, 64 columns
     (9, 33, 31, 136, 192, 3, 2, 1, 1, 2),     # residue classes, 136 columns
     (9, 33, 31, 72, 64, 1, 2, 0, 1, 1),       # three empty classes, one slab
-    (2, 67, 65, 24, 1088, 1, 2, 0, 1, 1)])    # beyond the table: terms of alpha * dY
+    (2, 67, 65, 24, 1088, 1, 2, 0, 1, 1)]     # beyond the table: terms of alpha * dY
+
+
+@pytest.mark.parametrize("n,h,w,c,o,r,stride,pad,dil,per", LARGE_CASES)
 def test_dx_alpha_large_kernels(knob, n, h, w, c, o, r, stride, pad, dil, per):
     """The same in the kernels that problems of more tiles run."""
     knob("TWN_SMALL", 0)
