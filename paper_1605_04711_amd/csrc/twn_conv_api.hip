@@ -381,8 +381,8 @@ size_t weight_grad_bytes(const twn_conv_desc* d, int P, int Q) {
 // pads dY, codes and alphas to the next multiple of 8 in the workspace, the layer is that of so many filters (its kernels and
 // their ranges too), and dW leaves the added ones out.  (us of dX + dW, before -> with the launch: 128 pixels 1024 -> 10
 // 29.4 -> 14.9; 64x40x40x16 -> 10, 3x3 135 -> 33; 5x20x22x512 -> 10, 7x7 269 -> 38; 64x38x38x512 -> 84, 3x3 1999 -> 213;
-// 64x112x112x3 -> 10, 3x3, one alpha per filter 935 -> 124; 3 pixels 1024 -> 10 19.3 -> 13.0, but dX alone there 6.5 -> 7.8 against 14.6 -> 7.6 at 128 pixels and
-// 6.9 -> 6.5 at 64: below 64 pixels only with dW.)
+// 64x112x112x3 -> 10, 3x3, one alpha per filter 935 -> 124; 3 pixels 1024 -> 10 19.3 -> 13.0, but dX alone there 6.5 -> 7.8
+// against 14.6 -> 7.6 at 128 pixels and 6.9 -> 6.5 at 64: below 64 pixels only with dW.)
 struct FilterPadPlan {
     bool use;
     twn_conv_desc d;            // the padded layer
@@ -677,10 +677,11 @@ static int32_t data_gradient(const twn_conv_desc* d, int P, int Q, const void* d
         // of the bf16 values of dX 1.2e-4 .. 4.5e-4 differ from the rounded exact sum, with two terms of alpha * dY 2.5e-3 (two of alpha
         // would give 1.8e-3 .. 3.3e-3, by how the alphas lie to powers of two).
         // The third product costs what grows with the columns and taps, the two-term problem its preparation; above the line that
-        // one's wider tiles win.  us, two terms of alpha * dY against three of alpha: persistent kernel, 3x3, 12544 pixels, 128 ->
-        // 128 channels 17.9, 14.2; 256 -> 256 45.6, 41.9; 256 -> 512 80.6, 79.9; 512 -> 512 113, 174; 3136 pixels, 512 -> 512 45.4, 44.5; 50176, 128 ->
-        // 128 47.9, 46.2; 256 -> 256 117, 151; 1x1, 512 -> 128 45.1, 23.2; 512 -> 512 84.0, 70.9.  Residue classes, 3x3/2,
-        // 12544 pixels, 512 filters over 64 channels 67.1, 40.4; over 256 90.4, 92.1; over 512 150, 161; 25088 pixels 269, 302.
+        // one's wider tiles win.  us, two terms of alpha * dY against three of alpha: persistent kernel, 3x3, 12544 pixels, 128
+        // filters over 128 channels 17.9, 14.2; 256 over 256 45.6, 41.9; 512 over 256 80.6, 79.9; 512 over 512 113, 174; 3136
+        // pixels, 512 over 512 45.4, 44.5; 50176, 128 over 128 47.9, 46.2; 256 over 256 117, 151; 1x1, 512 over 128 45.1, 23.2;
+        // 512 over 512 84.0, 70.9.  Residue classes, 3x3/2, 12544 pixels, 512 filters over 64 channels 67.1, 40.4; over 256 90.4,
+        // 92.1; over 512 150, 161; 25088 pixels 269, 302.
         DxPlan in;
         plan_dx(d, P, Q, &in, p.classes, true);
         const int n = in.classes ? in.cl.count : 1;
