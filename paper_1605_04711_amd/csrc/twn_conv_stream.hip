@@ -608,14 +608,14 @@ int32_t launch_conv_stream(const GatherGemm& g, int tile, hipStream_t st) {
     // workgroups of four waves did (VGG-16 conv5-7: 5-8 % faster).  128x64 tiles (64 output channels) gain while a CU has one or two
     // of them and K is long (us, without -> with: 211 tiles, K = 4608 38.7 -> 31.5; 256, 12800 112 -> 73; 392, 2304 25.7 -> 24.4;
     // 586, 1152 17.8 -> 18.3; 1568, 1152 40.9 -> 44.0).
-    // TWN_STREAM_PC: 0 = never, 2 / 4 = that many load waves wherever a build exists, unset = this rule.
+    // TWN_STREAM_PC: 0 = never, 4 = wherever a build exists, unset = this rule.  K groups exist without load waves only.
     int np = env_int(Env::STREAM_PC, -1);
     if (np < 0) {
         const bool few = tile == 16 && ((g.M + 127) / 128) * ((g.NC + 63) / 64) <= 512 && g.K >= 1024;
         np = (tile == 14 || tile == 15 || tile == 17 || tile == 18 || few) ? 4 : 0;
     }
     if (np > 0) {
-        const int32_t rc = launch_conv_stream_pc(g, tile, ks == 0 ? 1 : ks, np, env_int(Env::STREAM_PC_STAGES, 4), st);
+        const int32_t rc = launch_conv_stream_pc(g, tile, np, env_int(Env::STREAM_PC_STAGES, 4), st);
         if (rc != TWN_ERR_UNSUPPORTED) return rc;
     }
     if (ks == 0) {

@@ -120,7 +120,7 @@ int32_t launch_conv_addsub(const GatherGemm& g, hipStream_t st);
 // direct-to-LDS launcher takes (12, 14, 15, 16, 17).
 bool conv_stream_applicable(const GatherGemm& g);
 int32_t launch_conv_stream(const GatherGemm& g, int tile, hipStream_t st);
-int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int ks, int np, int stages, hipStream_t st);
+int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int np, int stages, hipStream_t st);
 // The same walk over problems with alpha_in.
 bool conv_stream_alpha_applicable(const GatherGemm& g);
 int32_t launch_conv_stream_alpha(const GatherGemm& g, hipStream_t st);
