@@ -28,7 +28,7 @@ int64_t small_x_bytes(const GatherGemm& g) {
 
 struct SmallProblem {
     GatherGemm g;
-    FastDivU divIC, divS, divOW, divOH, divUV, divV, divTN;
+    FastDivU divIC, divS, divOW, divOH, divUV, divV, divTN, divRG;
     uint32_t x_bytes, w_bytes;
     uint32_t blocks, tiles_n;
 };
@@ -42,13 +42,17 @@ enum SmallMode : int {
     kSmallGemm = 0,     // rows of X are the reduction rows
     kSmallTap = 1,      // channel count a multiple of 64: a slab lies in one tap
     kSmallChunk = 2,    // channel count a multiple of 8: every 16-byte chunk finds its own tap
+    kSmallTapDiv = 3,   // the same two with taps divided by a stride (strided backward-data)
+    kSmallChunkDiv = 4,
 };
 
 // Bytes of LDS one wave uses: DEPTH slabs of activations and two groups of four slabs of codes.
 constexpr int small_wave_bytes(int mt, int nt, int depth) { return depth * mt * 4096 + 2 * nt * 2048; }
 
-template <int MT, int NT, int NW, int MODE, int NP, int DEPTH, bool ALPHA>
+template <int MT, int NT, int NW, int MODE_, int NP, int DEPTH, bool ALPHA>
 __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP> args) {
+    constexpr bool DIV = MODE_ >= kSmallTapDiv;
+    constexpr int MODE = DIV ? MODE_ - 2 : MODE_;
     constexpr int BM = 32 * MT, BN = 32 * NT;
     constexpr int QUADS = BM * BN / 4;                          // groups of four channels of one pixel
     constexpr int QPT = QUADS > 64 * NW ? QUADS / (64 * NW) : 1;
@@ -78,26 +82,45 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
 
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(g.X, a.x_bytes), rw = make_rsrc(g.Wq, a.w_bytes);
 
-    // ---- output column parameters: requested first, used last ----
-    // output group `i` of this thread: four consecutive channels of one pixel
+    // ---- what the output needs besides the sums: requested first, used last ----
+    // Output group `i` of this thread: four consecutive channels of one pixel.  Every load is unconditional, of an element that
+    // exists (columns behind the last one take its parameters, an absent scale or shift is read as the first alpha), and
+    // nothing is computed from a value here: with a branch or a product per column the compiler waited for the memory four
+    // times, one column after the other, before the first slab was requested (2 to 3 us of each launch).
     const bool vec = (g.NC % 8 == 0) && (g.ldy % 8 == 0);
-    float mul[QPT][4], add[QPT][4];
+    const bool f32_res = g.residual && vec && g.y_f32, bf16_res = g.residual && vec && !g.y_f32;
+    const float* const scale = g.scale ? g.scale : g.alpha;
+    const float* const shift = g.shift ? g.shift : g.alpha;
+    float c_alpha[QPT][4], c_scale[QPT][4], c_shift[QPT][4];
+    int64_t yoff[QPT];
     int ncol0[QPT];
+    u32x2 res16[QPT];
+    f32x4 res32[QPT];
 #pragma unroll
     for (int i = 0; i < QPT; ++i) {
         const int qd = i * 64 * NW + tid;                       // [pixel][BN / 4]
+        const uint32_t m = m0 + qd / (BN / 4);
         ncol0[i] = n0 + (qd % (BN / 4)) * 4;
-        if (qd >= QUADS || m0 + qd / (BN / 4) >= static_cast<uint32_t>(g.M)) ncol0[i] = g.NC;
+        if (qd >= QUADS || m >= static_cast<uint32_t>(g.M)) ncol0[i] = g.NC;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            mul[i][e] = add[i][e] = 0.0f;
-            if (ncol0[i] + e < g.NC) {
-                const int ag = (g.rows_per_group >= g.NC) ? 0 : (ncol0[i] + e) / g.rows_per_group;
-                // codes were +-2
-                mul[i][e] = (ALPHA ? 1.0f : 0.5f * g.alpha[ag]) * (g.scale ? g.scale[ncol0[i] + e] : 1.0f);
-                add[i][e] = g.shift ? g.shift[ncol0[i] + e] : 0.0f;
-            }
+            const int col = ncol0[i] + e < g.NC ? ncol0[i] + e : g.NC - 1;
+            c_alpha[i][e] = g.alpha[g.rows_per_group >= g.NC ? 0u : fdiv_u(static_cast<uint32_t>(col), a.divRG)];
+            c_scale[i][e] = scale[g.scale ? col : 0];
+            c_shift[i][e] = shift[g.shift ? col : 0];
         }
+        int64_t orow = m;
+        if (g.orU != 0) {
+            const uint32_t n = fdiv_u(m, a.divUV);
+            const uint32_t rem = m - n * static_cast<uint32_t>(g.orU * g.orV);
+            const uint32_t u = fdiv_u(rem, a.divV);
+            const uint32_t v = rem - u * static_cast<uint32_t>(g.orV);
+            orow = (static_cast<int64_t>(n) * g.orH + g.ora + g.orsh * static_cast<int>(u)) * g.orW + g.orb + g.orsw * static_cast<int>(v);
+        }
+        yoff[i] = orow * g.ldy + ncol0[i];
+        const int64_t ro = ncol0[i] < g.NC ? yoff[i] : 0;
+        if (bf16_res) res16[i] = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(g.residual) + ro);
+        if (f32_res) res32[i] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.residual) + ro);
     }
 
     // ---- addresses: load i of a slab covers rows 8i .. 8i+7 (eight lanes each); LDS row r keeps logical 16-byte
@@ -145,15 +168,17 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
     auto tap_offset = [&](int i, int rr, int ss, int c, bool kok) __attribute__((always_inline)) -> uint32_t {
         int th = ih0[i] + rr * g.dh, tw = iw0[i] + ss * g.dw;
         bool ok = kok;
-        if (g.divh > 1) {           // wave-uniform: strided backward-data
-            const int d = th / g.divh;
-            ok = ok & (th >= 0) & (d * g.divh == th);
-            th = d;
-        }
-        if (g.divw > 1) {
-            const int d = tw / g.divw;
-            ok = ok & (tw >= 0) & (d * g.divw == tw);
-            tw = d;
+        if constexpr (DIV) {
+            if (g.divh > 1) {       // wave-uniform: strided backward-data
+                const int d = th / g.divh;
+                ok = ok & (th >= 0) & (d * g.divh == th);
+                th = d;
+            }
+            if (g.divw > 1) {
+                const int d = tw / g.divw;
+                ok = ok & (tw >= 0) & (d * g.divw == tw);
+                tw = d;
+            }
         }
         ok = ok & (static_cast<unsigned>(th) < static_cast<unsigned>(g.IH)) & (static_cast<unsigned>(tw) < static_cast<unsigned>(g.IW));
         const uint32_t off = ((base[i] + static_cast<uint32_t>(th * g.IW + tw)) * static_cast<uint32_t>(g.xs) + c) * 2u;
@@ -332,30 +357,23 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
         if (ncol0[i] >= g.NC) continue;
         const int qd = i * 64 * NW + tid;
         const int pix = qd / (BN / 4), c4 = qd % (BN / 4);
-        const uint32_t m = m0 + pix;
-        int64_t orow = m;
-        if (g.orU != 0) {
-            const uint32_t n = fdiv_u(m, a.divUV);
-            const uint32_t rem = m - n * static_cast<uint32_t>(g.orU * g.orV);
-            const uint32_t u = fdiv_u(rem, a.divV);
-            const uint32_t v = rem - u * static_cast<uint32_t>(g.orV);
-            orow = (static_cast<int64_t>(n) * g.orH + g.ora + g.orsh * static_cast<int>(u)) * g.orW + g.orb + g.orsw * static_cast<int>(v);
-        }
-        const int64_t yoff = orow * g.ldy + ncol0[i];
         const unsigned char* src = smem + ((pix >> 5) * NT + (c4 >> 3)) * kPartTile + (c4 & 7) * kQuadRow + (pix & 31) * 16;
         f32x4 s = *reinterpret_cast<const f32x4*>(src);
 #pragma unroll
         for (int w = 1; w < NW; ++w) s += *reinterpret_cast<const f32x4*>(src + w * WAVE_BYTES);
         float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = s[e] * mul[i][e] + add[i][e];
+        for (int e = 0; e < 4; ++e) {
+            // codes were +-2
+            const float mul = (ALPHA ? 1.0f : 0.5f * c_alpha[i][e]) * (g.scale ? c_scale[i][e] : 1.0f);
+            v[e] = s[e] * mul + (g.shift ? c_shift[i][e] : 0.0f);
+        }
         if (vec && !g.y_f32) {
             if (g.residual) {
-                const u32x2 rr = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(g.residual) + yoff);
-                v[0] += __uint_as_float(rr[0] << 16);
-                v[1] += __uint_as_float(rr[0] & 0xFFFF0000u);
-                v[2] += __uint_as_float(rr[1] << 16);
-                v[3] += __uint_as_float(rr[1] & 0xFFFF0000u);
+                v[0] += __uint_as_float(res16[i][0] << 16);
+                v[1] += __uint_as_float(res16[i][0] & 0xFFFF0000u);
+                v[2] += __uint_as_float(res16[i][1] << 16);
+                v[3] += __uint_as_float(res16[i][1] & 0xFFFF0000u);
             }
             if (g.relu) {
 #pragma unroll
@@ -364,23 +382,22 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
             u32x2 pk;
             pk[0] = pack_bf16x2(v[0], v[1]);
             pk[1] = pack_bf16x2(v[2], v[3]);
-            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(g.Y) + yoff) = pk;
+            *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(g.Y) + yoff[i]) = pk;
         } else if (vec) {
             if (g.residual) {
-                const f32x4 rr = *reinterpret_cast<const f32x4*>(static_cast<const float*>(g.residual) + yoff);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += rr[e];
+                for (int e = 0; e < 4; ++e) v[e] += res32[i][e];
             }
             if (g.relu) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);
             }
-            *reinterpret_cast<f32x4*>(static_cast<float*>(g.Y) + yoff) = f32x4{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<f32x4*>(static_cast<float*>(g.Y) + yoff[i]) = f32x4{v[0], v[1], v[2], v[3]};
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (ncol0[i] + e >= g.NC) continue;
-                const int64_t off = yoff + e;
+                const int64_t off = yoff[i] + e;
                 if (g.y_f32) {
                     if (g.residual) v[e] += static_cast<const float*>(g.residual)[off];
                     if (g.relu) v[e] = fmaxf(v[e], 0.0f);
@@ -397,7 +414,8 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
 
 int small_mode(const GatherGemm& g) {
     if (g.plain_gemm) return kSmallGemm;
-    return (!g.chunk_gather && g.IC % 64 == 0) ? kSmallTap : kSmallChunk;
+    const int mode = (!g.chunk_gather && g.IC % 64 == 0) ? kSmallTap : kSmallChunk;
+    return g.divh > 1 || g.divw > 1 ? mode + 2 : mode;
 }
 
 SmallProblem make_problem(const GatherGemm& g, int bm, int bn) {
@@ -413,6 +431,7 @@ SmallProblem make_problem(const GatherGemm& g, int bm, int bn) {
     p.w_bytes = static_cast<uint32_t>(static_cast<int64_t>(g.NC) * g.wpr * 4);
     p.tiles_n = static_cast<uint32_t>((g.NC + bn - 1) / bn);
     p.divTN = make_fastdiv_u(p.tiles_n);
+    p.divRG = make_fastdiv_u(static_cast<uint32_t>(g.rows_per_group));
     p.blocks = static_cast<uint32_t>((g.M + bm - 1) / bm) * p.tiles_n;
     return p;
 }
@@ -454,7 +473,9 @@ int32_t launch_small_tile(const GatherGemm* gs, int count, hipStream_t st) {
         switch (small_mode(gs[0])) {
             case kSmallGemm: return launch_small_kernel<MT, NT, NW, kSmallGemm, 1>(a, width, 1, st);
             case kSmallTap: return launch_small_kernel<MT, NT, NW, kSmallTap, 1>(a, width, 1, st);
-            default: return launch_small_kernel<MT, NT, NW, kSmallChunk, 1>(a, width, 1, st);
+            case kSmallChunk: return launch_small_kernel<MT, NT, NW, kSmallChunk, 1>(a, width, 1, st);
+            case kSmallTapDiv: return launch_small_kernel<MT, NT, NW, kSmallTapDiv, 1>(a, width, 1, st);
+            default: return launch_small_kernel<MT, NT, NW, kSmallChunkDiv, 1>(a, width, 1, st);
         }
     }
     SmallArgs<kProblemsMax> a{};
@@ -497,6 +518,7 @@ int conv_small_tile(const GatherGemm* gs, int count) {
         const GatherGemm& g = gs[c];
         if (!g.chunk_gather && (g.IC % 8 != 0 || g.xs % 8 != 0)) return 0;
         if (g.M <= 0 || g.M >= (1LL << 31) - 128) return 0;
+        if (count > 1 && (g.divh > 1 || g.divw > 1)) return 0;      // several problems have undivided builds only
         if (!g.plain_gemm && g.M % (static_cast<int64_t>(g.OH) * g.OW) != 0) return 0;
         const int64_t xb = small_x_bytes(g), wb = static_cast<int64_t>(g.NC) * g.wpr * 4;
         if (xb <= 0 || xb >= (1LL << 31) || wb >= (1LL << 31)) return 0;
