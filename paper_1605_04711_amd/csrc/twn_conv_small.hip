@@ -2,7 +2,7 @@
 //
 // Same arithmetic as the other contraction kernels (bf16 activations, 2-bit codes expanded in registers to
 // 0 / +-2.0, alpha/2 and the block tail in the fp32 epilogue), for launches that the memory latency bounds: a
-// batch-1 layer, a classifier, the deep layers of a small batch.  Tiles of 32 pixels by 32 or 64 channels, and the
+// batch-1 layer, a classifier, the deep layers of a small batch.  Tiles of 16 or 32 pixels by 32 or 64 channels, and the
 // K slabs of a tile are shared out over the NW waves of ONE workgroup, whose partial tiles are summed through LDS
 // in a fixed order: no partial sums in memory and no second launch.  A wave stages its own slabs by direct-to-LDS
 // loads, DEPTH slabs ahead (rows of 128 contiguous bytes: a fragment load straight into registers touches a cache line
@@ -20,6 +20,7 @@ namespace {
 constexpr int kProblemsMax = 4;
 constexpr int kQuadRow = 544;               // bytes of one block of 32 pixels x 4 channels of a partial tile in LDS (padded)
 constexpr int kPartTile = 8 * kQuadRow;     // one 32x32 partial tile
+constexpr int kQuadRow16 = 272;             // ... of 16 pixels x 4 channels
 
 int64_t small_x_bytes(const GatherGemm& g) {
     const int64_t in_rows = g.plain_gemm ? g.M : (g.M / (static_cast<int64_t>(g.OH) * g.OW)) * g.IH * g.IW;
@@ -47,21 +48,22 @@ enum SmallMode : int {
 };
 
 // Bytes of LDS one wave uses: DEPTH slabs of activations and two groups of four slabs of codes.
-constexpr int small_wave_bytes(int mt, int nt, int depth) { return depth * mt * 4096 + 2 * nt * 2048; }
+constexpr int small_wave_bytes(int mt, int nt, int depth, bool h16) { return depth * mt * (h16 ? 2048 : 4096) + 2 * nt * 2048; }
 
-template <int MT, int NT, int NW, int MODE_, int NP, int DEPTH, bool ALPHA>
+template <int MT, int NT, int NW, int MODE_, int NP, int DEPTH, bool H16, bool ALPHA>
 __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP> args) {
     constexpr bool DIV = MODE_ >= kSmallTapDiv;
     constexpr int MODE = DIV ? MODE_ - 2 : MODE_;
-    constexpr int BM = 32 * MT, BN = 32 * NT;
+    constexpr int BM = H16 ? 16 : 32 * MT, BN = 32 * NT;
     constexpr int QUADS = BM * BN / 4;                          // groups of four channels of one pixel
     constexpr int QPT = QUADS > 64 * NW ? QUADS / (64 * NW) : 1;
-    constexpr int STAGE = MT * 4096;                            // one slab of activations: BM rows of 128 bytes
+    constexpr int STAGE = BM * 128;                             // one slab of activations: BM rows of 128 bytes
     constexpr int CODES = NT * 2048;                            // four slabs of codes: BN rows of 64 bytes
-    constexpr int WAVE_BYTES = small_wave_bytes(MT, NT, DEPTH);
-    constexpr int NA = 4 * MT, NB = 2 * NT;                     // loads of a slab / of a group of codes
-    static_assert(WAVE_BYTES >= MT * NT * kPartTile, "the partial tile reuses the wave's own staging memory");
-    static_assert(DEPTH >= 2 && DEPTH <= 4, "a wait spans at most one group of codes");
+    constexpr int WAVE_BYTES = small_wave_bytes(MT, NT, DEPTH, H16);
+    constexpr int NA = BM / 8, NB = 2 * NT;                     // loads of a slab / of a group of codes
+    static_assert(WAVE_BYTES >= (H16 ? NT * 8 * kQuadRow16 : MT * NT * kPartTile), "the partial tile reuses the wave's own staging memory");
+    static_assert(DEPTH >= 2 && DEPTH <= 5, "a wait spans at most one group of codes, and a group is requested when the one before the last is done");
+    static_assert(!H16 || (MT == 1 && !ALPHA), "16-row tiles");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
     const SmallProblem& a = args.p[NP == 1 ? 0 : blockIdx.y];
@@ -83,32 +85,38 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
     const __amdgpu_buffer_rsrc_t rx = make_rsrc(g.X, a.x_bytes), rw = make_rsrc(g.Wq, a.w_bytes);
 
     // ---- what the output needs besides the sums: requested first, used last ----
-    // Output group `i` of this thread: four consecutive channels of one pixel.  Every load is unconditional, of an element that
-    // exists (columns behind the last one take its parameters, an absent scale or shift is read as the first alpha), and
-    // nothing is computed from a value here: with a branch or a product per column the compiler waited for the memory four
-    // times, one column after the other, before the first slab was requested (2 to 3 us of each launch).
+    // Output group `i` of this thread: four consecutive channels of one pixel.  Every load is of an element that exists (columns
+    // behind the last one take its parameters), no branch is a lane's own, and nothing is computed from a value here: with a branch and
+    // a product per column the compiler waited for the memory four times, one column after the other, before the first slab was
+    // requested (up to 2 us of a launch: batch-1 ResNet-18, 18 launches, 119 -> 104 us).
     const bool vec = (g.NC % 8 == 0) && (g.ldy % 8 == 0);
     const bool f32_res = g.residual && vec && g.y_f32, bf16_res = g.residual && vec && !g.y_f32;
-    const float* const scale = g.scale ? g.scale : g.alpha;
-    const float* const shift = g.shift ? g.shift : g.alpha;
-    float c_alpha[QPT][4], c_scale[QPT][4], c_shift[QPT][4];
+    const bool one_alpha = g.rows_per_group >= g.NC;
+    const float alpha0 = g.alpha[0];
+    f32x4 c_alpha[QPT], c_scale[QPT], c_shift[QPT];
     int64_t yoff[QPT];
     int ncol0[QPT];
     u32x2 res16[QPT];
     f32x4 res32[QPT];
+    auto params = [&](const float* v, int col) __attribute__((always_inline)) -> f32x4 {
+        f32x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = v[col + e < g.NC ? col + e : g.NC - 1];
+        return r;
+    };
 #pragma unroll
     for (int i = 0; i < QPT; ++i) {
         const int qd = i * 64 * NW + tid;                       // [pixel][BN / 4]
         const uint32_t m = m0 + qd / (BN / 4);
         ncol0[i] = n0 + (qd % (BN / 4)) * 4;
         if (qd >= QUADS || m >= static_cast<uint32_t>(g.M)) ncol0[i] = g.NC;
+        if (!one_alpha) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int col = ncol0[i] + e < g.NC ? ncol0[i] + e : g.NC - 1;
-            c_alpha[i][e] = g.alpha[g.rows_per_group >= g.NC ? 0u : fdiv_u(static_cast<uint32_t>(col), a.divRG)];
-            c_scale[i][e] = scale[g.scale ? col : 0];
-            c_shift[i][e] = shift[g.shift ? col : 0];
+            for (int e = 0; e < 4; ++e)
+                c_alpha[i][e] = g.alpha[fdiv_u(static_cast<uint32_t>(ncol0[i] + e < g.NC ? ncol0[i] + e : g.NC - 1), a.divRG)];
         }
+        if (g.scale) c_scale[i] = params(g.scale, ncol0[i]);
+        if (g.shift) c_shift[i] = params(g.shift, ncol0[i]);
         int64_t orow = m;
         if (g.orU != 0) {
             const uint32_t n = fdiv_u(m, a.divUV);
@@ -225,6 +233,9 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
     };
 
     f32x16 acc[MT][NT];
+    f32x4 acc16[2 * NT];            // H16: blocks of 16 channels
+#pragma unroll
+    for (int cb = 0; cb < 2 * NT; ++cb) acc16[cb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
@@ -273,6 +284,39 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"(younger) : "memory");
             } else {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+            if constexpr (H16) {
+                // Lane group q = lane / 16 holds k = 16q .. 16q+15 of the slab, one word of codes per channel: eight k to each of two MFMAs.
+                const int r16 = lane & 15, q4 = lane >> 4;
+                uint32_t cw[2 * NT];
+                u32x4 x2[2];
+                const uint32_t cbase = lds_mine + DEPTH * STAGE + ((sg >> 2) & 1) * CODES + r16 * 64 + ((p ^ ((r16 >> 2) & 3)) * 16) + q4 * 4;
+                static_for<2 * NT>([&](auto c_tag) __attribute__((always_inline)) {
+                    constexpr int cb = decltype(c_tag)::value;
+                    lds_read32<cb * 1024>(cw[cb], cbase);
+                });
+                const uint32_t xbase = lds_mine + st * STAGE + r16 * 128 + (((q4 * 2) ^ ((r16 >> 1) & 7)) * 16);
+                lds_read128<0>(x2[0], xbase);
+                lds_read128<0>(x2[1], xbase ^ 16);
+                lds_wait<0>();
+                lds_ready<2 * NT>(cw);
+                lds_ready<2>(x2);
+                if (s + DEPTH < ns) fetch(s + DEPTH, st);           // every read of this stage has returned
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                    for (int cb = 0; cb < 2 * NT; ++cb) {
+                        u32x4 wf;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int i = kk * 4 + e;
+                            wf[e] = (cw[cb] & (0xC000C000u >> (14 - 2 * i))) << (14 - 2 * i);
+                        }
+                        acc16[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wf), __builtin_bit_cast(bf16x8, x2[kk]),
+                                                                            acc16[cb], 0, 0, 0);
+                    }
+                st = (st + 1 == DEPTH) ? 0 : st + 1;
+                return;
             }
             u32x2 w[NT];
             u32x4 x[4][MT];
@@ -339,6 +383,11 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
     }
 
     // ---- partial tiles -> LDS, each wave over its own staging memory: [mi][ni][q4*2 + lh][pixel] of four channels ----
+    if constexpr (H16) {
+#pragma unroll
+        for (int cb = 0; cb < 2 * NT; ++cb)
+            *reinterpret_cast<f32x4*>(mine + (cb * 4 + (lane >> 4)) * kQuadRow16 + (lane & 15) * 16) = acc16[cb];
+    } else
 #pragma unroll
     for (int mi = 0; mi < MT; ++mi)
 #pragma unroll
@@ -357,7 +406,8 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
         if (ncol0[i] >= g.NC) continue;
         const int qd = i * 64 * NW + tid;
         const int pix = qd / (BN / 4), c4 = qd % (BN / 4);
-        const unsigned char* src = smem + ((pix >> 5) * NT + (c4 >> 3)) * kPartTile + (c4 & 7) * kQuadRow + (pix & 31) * 16;
+        const unsigned char* src = H16 ? smem + c4 * kQuadRow16 + pix * 16
+                                       : smem + ((pix >> 5) * NT + (c4 >> 3)) * kPartTile + (c4 & 7) * kQuadRow + (pix & 31) * 16;
         f32x4 s = *reinterpret_cast<const f32x4*>(src);
 #pragma unroll
         for (int w = 1; w < NW; ++w) s += *reinterpret_cast<const f32x4*>(src + w * WAVE_BYTES);
@@ -365,7 +415,7 @@ __global__ __launch_bounds__(64 * NW) void conv_small_kernel(const SmallArgs<NP>
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             // codes were +-2
-            const float mul = (ALPHA ? 1.0f : 0.5f * c_alpha[i][e]) * (g.scale ? c_scale[i][e] : 1.0f);
+            const float mul = (ALPHA ? 1.0f : 0.5f * (one_alpha ? alpha0 : c_alpha[i][e])) * (g.scale ? c_scale[i][e] : 1.0f);
             v[e] = s[e] * mul + (g.shift ? c_shift[i][e] : 0.0f);
         }
         if (vec && !g.y_f32) {
@@ -436,15 +486,15 @@ SmallProblem make_problem(const GatherGemm& g, int bm, int bn) {
     return p;
 }
 
-template <int MT, int NT, int NW, int MODE, int NP, bool ALPHA>
+template <int MT, int NT, int NW, int MODE, int NP, bool ALPHA, bool H16>
 int32_t launch_small_build(const SmallArgs<NP>& a, uint32_t width, int count, hipStream_t st) {
     // the table of terms takes the third slab's place where both do not fit
-    constexpr int DEPTH = ALPHA && NT == 2 ? 2 : 3;
-    constexpr int STAGES = NW * small_wave_bytes(MT, NT, DEPTH);
+    constexpr int DEPTH = H16 ? 5 : ALPHA && NT == 2 ? 2 : 3;
+    constexpr int STAGES = NW * small_wave_bytes(MT, NT, DEPTH, H16);
     constexpr int MOST = STAGES + (ALPHA ? kSmallAlphaMax * 2 * kAlphaTerms : 0);
     static_assert(MOST <= 160 * 1024, "LDS budget");
     const int SMEM = STAGES + (ALPHA ? ((a.p[0].g.IC + 63) & ~63) * 2 * kAlphaTerms : 0);
-    auto k = conv_small_kernel<MT, NT, NW, MODE, NP, DEPTH, ALPHA>;
+    auto k = conv_small_kernel<MT, NT, NW, MODE, NP, DEPTH, H16, ALPHA>;
     // more than 64 KB of dynamic LDS has to be allowed once per kernel
     static std::once_flag once;
     static bool allowed = false;
@@ -457,44 +507,49 @@ int32_t launch_small_build(const SmallArgs<NP>& a, uint32_t width, int count, hi
     return launch_status();
 }
 
-template <int MT, int NT, int NW, int MODE, int NP>
+template <int MT, int NT, int NW, bool H16, int MODE, int NP>
 int32_t launch_small_kernel(const SmallArgs<NP>& a, uint32_t width, int count, hipStream_t st) {
-    if (!a.p[0].g.alpha_in) return launch_small_build<MT, NT, NW, MODE, NP, false>(a, width, count, st);
-    if (a.p[0].g.IC > kSmallAlphaMax) return TWN_ERR_UNSUPPORTED;
-    return launch_small_build<MT, NT, NW, MODE, NP, true>(a, width, count, st);
+    if (!a.p[0].g.alpha_in) return launch_small_build<MT, NT, NW, MODE, NP, false, H16>(a, width, count, st);
+    if constexpr (!H16) {
+        if (a.p[0].g.IC <= kSmallAlphaMax) return launch_small_build<MT, NT, NW, MODE, NP, true, false>(a, width, count, st);
+    }
+    return TWN_ERR_UNSUPPORTED;
 }
 
-template <int MT, int NT, int NW>
+template <int MT, int NT, int NW, bool H16 = false>
 int32_t launch_small_tile(const GatherGemm* gs, int count, hipStream_t st) {
     if (count == 1) {
         SmallArgs<1> a;
-        a.p[0] = make_problem(gs[0], 32 * MT, 32 * NT);
+        a.p[0] = make_problem(gs[0], H16 ? 16 : 32 * MT, 32 * NT);
         const uint32_t width = a.p[0].blocks;
         switch (small_mode(gs[0])) {
-            case kSmallGemm: return launch_small_kernel<MT, NT, NW, kSmallGemm, 1>(a, width, 1, st);
-            case kSmallTap: return launch_small_kernel<MT, NT, NW, kSmallTap, 1>(a, width, 1, st);
-            case kSmallChunk: return launch_small_kernel<MT, NT, NW, kSmallChunk, 1>(a, width, 1, st);
-            case kSmallTapDiv: return launch_small_kernel<MT, NT, NW, kSmallTapDiv, 1>(a, width, 1, st);
-            default: return launch_small_kernel<MT, NT, NW, kSmallChunkDiv, 1>(a, width, 1, st);
+            case kSmallGemm: return launch_small_kernel<MT, NT, NW, H16, kSmallGemm, 1>(a, width, 1, st);
+            case kSmallTap: return launch_small_kernel<MT, NT, NW, H16, kSmallTap, 1>(a, width, 1, st);
+            case kSmallChunk: return launch_small_kernel<MT, NT, NW, H16, kSmallChunk, 1>(a, width, 1, st);
+            case kSmallTapDiv: return launch_small_kernel<MT, NT, NW, H16, kSmallTapDiv, 1>(a, width, 1, st);
+            default: return launch_small_kernel<MT, NT, NW, H16, kSmallChunkDiv, 1>(a, width, 1, st);
         }
     }
     SmallArgs<kProblemsMax> a{};
     uint32_t width = 0;
     bool tap = true;
     for (int c = 0; c < count; ++c) {
-        a.p[c] = make_problem(gs[c], 32 * MT, 32 * NT);
+        a.p[c] = make_problem(gs[c], H16 ? 16 : 32 * MT, 32 * NT);
         if (a.p[c].blocks > width) width = a.p[c].blocks;
         tap = tap && gs[c].IC % 64 == 0 && !gs[c].chunk_gather;
     }
-    return tap ? launch_small_kernel<MT, NT, NW, kSmallTap, kProblemsMax>(a, width, count, st)
-               : launch_small_kernel<MT, NT, NW, kSmallChunk, kProblemsMax>(a, width, count, st);
+    return tap ? launch_small_kernel<MT, NT, NW, H16, kSmallTap, kProblemsMax>(a, width, count, st)
+               : launch_small_kernel<MT, NT, NW, H16, kSmallChunk, kProblemsMax>(a, width, count, st);
 }
 
 }  // namespace
 
-// Tile (32 pixels x 32 or 64 channels, number of waves: 1108, 1208, 1204) for `count` problems in one launch, 0 when the
+// Tile (16 or 32 pixels x 32 or 64 channels, number of waves: 608, 1108, 1208, 1204) for `count` problems in one launch, 0 when the
 // other kernels are better or the shapes do not fit.  Measured per dependent launch (us, against the split-K launch pair
 // and the persistent kernels that ran such problems before):
+//   * up to 256 tiles of 16 pixels by 32 channels (one alpha; MFMAs of 16x16): eight waves per tile.  The tiles of a batch-1 layer
+//     leave most CUs idle, and the ones at work are bound by what their own load path brings: half the rows are half of that,
+//     and five slabs in flight fit where three of 32 rows did (49, 512, 4608: 7.7 -> 6.8; 196, 256, 2304: 5.9 -> 5.2)
 //   * up to 256 tiles of 32x32: eight waves per tile, one tile per CU (M, N, K = 49, 512, 4608: 10.8 -> 8.1; 784, 128, 1152:
 //     11.6 -> 5.1; 1, 1000, 512: 5.1 -> 3.6).  Two such workgroups do not fit a CU: 1568, 256, 2304, 392 tiles of 32x32 or
 //     196 of 32x64, takes 8.1 with the former and 6.4 with the latter
@@ -511,8 +566,8 @@ int conv_small_tile(const GatherGemm* gs, int count) {
     if (env_int(Env::TILE, 0) != 0 || env_int(Env::STREAM, 1) == 0 || env_int(Env::BUFLOAD, 1) == 0 || env_set(Env::STREAM_KS) ||
         env_set(Env::STREAM_PC) || env_set(Env::STREAM_PC_STAGES) || env_set(Env::STREAM_OCC))
         return 0;
-    int64_t t11 = 0, t12 = 0;
-    bool persistent = true;
+    int64_t t16 = 0, t11 = 0, t12 = 0;
+    bool persistent = true, one_alpha = true;
     int kt = 0;
     for (int c = 0; c < count; ++c) {
         const GatherGemm& g = gs[c];
@@ -523,13 +578,16 @@ int conv_small_tile(const GatherGemm* gs, int count) {
         const int64_t xb = small_x_bytes(g), wb = static_cast<int64_t>(g.NC) * g.wpr * 4;
         if (xb <= 0 || xb >= (1LL << 31) || wb >= (1LL << 31)) return 0;
         const int64_t rows = (g.M + 31) / 32;
+        t16 += (g.M + 15) / 16 * ((g.NC + 31) / 32);
         t11 += rows * ((g.NC + 31) / 32);
+        one_alpha = one_alpha && !g.alpha_in;
         t12 += rows * ((g.NC + 63) / 64);
         const bool slabs = g.plain_gemm ? g.K % 64 == 0 : (g.IC % 64 == 0 && g.divh == 1 && g.divw == 1 && g.orU == 0);
         persistent = persistent && slabs && !g.y_f32 && g.NC % 8 == 0 && g.ldy % 8 == 0 && !g.chunk_gather;
         if (k_slabs(g.K) > kt) kt = k_slabs(g.K);
     }
     if (kt > 256) return 0;
+    if (t16 <= 256 && one_alpha) return 608;
     if (t11 <= 256) return 1108;
     if (t12 <= 256) return 1208;
     if (t12 <= 512 && (kt >= 16 || !persistent)) return 1204;
@@ -538,6 +596,7 @@ int conv_small_tile(const GatherGemm* gs, int count) {
 
 int32_t launch_conv_small(const GatherGemm* gs, int count, int tile, hipStream_t st) {
     switch (tile) {
+        case 608: return launch_small_tile<1, 1, 8, true>(gs, count, st);
         case 1108: return launch_small_tile<1, 1, 8>(gs, count, st);
         case 1208: return launch_small_tile<1, 2, 8>(gs, count, st);
         case 1204: return launch_small_tile<1, 2, 4>(gs, count, st);

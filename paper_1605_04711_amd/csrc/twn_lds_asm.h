@@ -19,6 +19,10 @@ __device__ __forceinline__ void lds_read128(u32x4& d, uint32_t addr) {
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFFSET));
 }
 template <int OFFSET>
+__device__ __forceinline__ void lds_read32(uint32_t& d, uint32_t addr) {
+    asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFFSET));
+}
+template <int OFFSET>
 __device__ __forceinline__ void lds_read64(u32x2& d, uint32_t addr) {
     asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFFSET));
 }

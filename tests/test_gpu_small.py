@@ -60,3 +60,23 @@ def test_convolution(n, h, w, c, o, r, stride, pad, dil):
     dy = wl.bf16_round(rng.standard_normal(ref.shape).astype(np.float32))
     dx, _, _ = api.twn_conv2d_bwd_ste(None, to_dev_bf16(dy), tw, *geo, need_dw=False, x_shape=x.shape)
     assert rel_err(to_host_f64(dx), oc.conv2d_bwd_data(dy, codes, alpha, x.shape, *geo)) <= BF16_TOL
+
+
+@pytest.mark.parametrize("n,h,w,c,o,r,stride,pad,groups", [
+    (1, 1, 1, 64, 8, 1, 1, 0, 1), (1, 4, 4, 64, 32, 1, 1, 0, 32), (1, 4, 4, 72, 33, 3, 1, 1, 1),         # one tile of 16 rows, whole and ragged
+    (1, 7, 7, 512, 512, 3, 1, 1, 1),                                    # nine slabs a wave, five in flight
+    (1, 17, 1, 8, 40, 5, 1, 2, 40), (2, 9, 5, 24, 257, 3, 2, 1, 1),     # chunks of 8 channels, odd columns
+    (16, 16, 16, 64, 32, 3, 1, 1, 1), (1, 16, 16, 64, 512, 1, 2, 0, 1)])        # 256 tiles, the most; one slab of K for eight waves
+def test_tiles_of_sixteen_pixels(n, h, w, c, o, r, stride, pad, groups):
+    rng = np.random.default_rng(h * c + o)
+    x, tw, codes, alpha = _layer(rng, (n, h, w, c), (o, c, r, r), groups)
+    geo = (stride,) * 2, (pad,) * 2, (1, 1)
+    ref = oc.conv2d_fwd(x, codes, alpha, *geo)
+    assert rel_err(to_host_f64(api.twn_conv2d_fwd(to_dev_bf16(x), tw, *geo, y_dtype=torch.float32)), ref) <= 1e-4
+    sc, sf = rng.uniform(0.5, 1.5, o).astype(np.float32), rng.standard_normal(o).astype(np.float32)
+    res = rng.standard_normal(ref.shape).astype(np.float32)
+    y = api.twn_conv2d_fwd(to_dev_bf16(x), tw, *geo, y_dtype=torch.float32, scale=to_dev_f32(sc), shift=to_dev_f32(sf),
+                           residual=to_dev_f32(res), relu=True)
+    assert rel_err(to_host_f64(y), oc.epilogue(ref, sc, sf, res, relu=True)) <= 2e-4        # a sum that cancels: twice the bound of the sum
+    y = api.twn_conv2d_fwd(to_dev_bf16(x), tw, *geo, scale=to_dev_f32(sc), residual=to_dev_bf16(wl.bf16_round(res)))
+    assert rel_err(to_host_f64(y), oc.epilogue(ref, sc, None, wl.bf16_round(res))) <= BF16_TOL
