@@ -598,12 +598,23 @@ int32_t launch_conv_stream_pc(const GatherGemm& g, int tile, int np, int stages,
     }
 }
 
-// Undivided backward-data with several alphas (alpha_in): 64x128 tiles, whose accumulators leave room for the terms of the codes.
+// Undivided backward-data with several alphas (alpha_in).
 bool conv_stream_alpha_applicable(const GatherGemm& g) {
     return g.IC <= kStreamAlphaMax && g.NC > 64 && env_int(Env::TILE, 0) == 0 && env_int(Env::STREAM, 1) != 0 &&
            !env_set(Env::STREAM_PC) && !env_set(Env::STREAM_KS) && !env_set(Env::STREAM_PC_STAGES) && !env_set(Env::STREAM_OCC) &&
            env_int(Env::BUFLOAD, 1) != 0 && conv_stream_applicable(g);
 }
-int32_t launch_conv_stream_alpha(const GatherGemm& g, hipStream_t st) { return launch_pc_tile<64, 128, 1, 4, 4, 2, 4, true>(g, st); }
+// The codes of 32 columns times three terms are 28 vector instructions a step: beside the six MFMAs of a 64-row wave tile they bound the
+// kernel, beside the twelve of a 128-row one they do not.  128x128 tiles, one workgroup per CU, win where they leave the
+// busiest CU no more rows than 64x128 tiles do and K is long enough to hide an epilogue that nothing overlaps (us, 64x128 -> 128x128:
+// 3x3, 50176 pixels, 128 filters over 128 channels 45.9 -> 42.2; 12544, 256 over 256 40.6 -> 36.6; 9216, 512 over 200 69.6 -> 58.1;
+// 18816, 128 over 128 20.4 -> 18.4; 1x1, 50176, 512 over 128 22.1 -> 21.1, but 256 over 128 13.4 -> 13.9; more rows for the busiest
+// CU: 12544, 128 over 128 14.4 -> 18.8; 7840, 256 over 256 24.7 -> 31.5).
+int32_t launch_conv_stream_alpha(const GatherGemm& g, hipStream_t st) {
+    const int64_t cols = (g.NC + 127) / 128;
+    auto busiest = [&](int bm) { return ((g.M + bm - 1) / bm * cols + 255) / 256 * bm; };
+    if (g.K >= 512 && busiest(128) <= busiest(64)) return launch_pc_tile<128, 128, 1, 4, 4, 1, 4, true>(g, st);
+    return launch_pc_tile<64, 128, 1, 4, 4, 2, 4, true>(g, st);
+}
 
 }  // namespace twn
