@@ -31,25 +31,31 @@ enum F32Mode : int {
 
 struct F32Args {
     GatherGemm g;
-    FastDivU divIC, divS, divOW, divOH, divTN;
+    FastDivU divIC, divS, divOW, divOH, divTN, divRG;
+    FastDivU divParts;      // K blocks of part p of splits * NW: from blocks_q * p + blocks_r * p / parts on
+    int32_t blocks_q, blocks_r;
     int64_t tiles;
     int32_t tiles_n;
     int32_t narrow;         // rows and tiles below 2^31: divisions by multiplication (a 64-bit one costs about a microsecond)
     int32_t walk;           // short kernel: row blocks per wave
 };
 
-// Parameters of one output column; requested before the sums they are applied to.
+// Parameters of one output column, requested before the sums they are applied to.  A column behind the last one reads that one's:
+// with a branch per lane around the loads the compiler waits for each of them before the first activations are requested.
 struct F32Column {
     float al, sc, sf;
 };
-__device__ __forceinline__ F32Column f32_column(const GatherGemm& g, int ncol) {
-    if (ncol >= g.NC) return F32Column{0.0f, 0.0f, 0.0f};
-    return F32Column{g.alpha[g.rows_per_group >= g.NC ? 0 : ncol / g.rows_per_group], g.scale ? g.scale[ncol] : 1.0f,
-                     g.shift ? g.shift[ncol] : 0.0f};
+__device__ __forceinline__ F32Column f32_column(const GatherGemm& g, const FastDivU& divRG, int ncol) {
+    const int n = min(ncol, g.NC - 1);
+    F32Column c;            // sc and sf: only what the call has
+    c.al = g.alpha[g.rows_per_group >= g.NC ? 0u : fdiv_u(static_cast<uint32_t>(n), divRG)];
+    if (g.scale) c.sc = g.scale[n];
+    if (g.shift) c.sf = g.shift[n];
+    return c;
 }
 
 __device__ __forceinline__ void f32_tail_store(const GatherGemm& g, int64_t m, int ncol, double sum, const F32Column& c) {
-    float v = (static_cast<float>(sum) * c.al) * c.sc + c.sf;
+    float v = (static_cast<float>(sum) * c.al) * (g.scale ? c.sc : 1.0f) + (g.shift ? c.sf : 0.0f);
     const int64_t off = m * g.ldy + ncol;
     if (g.y_f32) {
         if (g.residual) v += static_cast<const float*>(g.residual)[off];
@@ -76,10 +82,9 @@ __global__ __launch_bounds__(64 * NW) void gather_gemm_f64_kernel(const F32Args 
     const uint32_t* __restrict__ Wq = static_cast<const uint32_t*>(g.Wq);
 
     // the wave's range of K blocks; a ragged last block is done element by element after the others
-    const int nkb = (g.K + 15) >> 4;
-    const int64_t parts = static_cast<int64_t>(g.splits) * NW;
-    const int64_t p = static_cast<int64_t>(blockIdx.y) * NW + wave;
-    const int kb0 = static_cast<int>(nkb * p / parts), kb1 = static_cast<int>(nkb * (p + 1) / parts);
+    const uint32_t p = blockIdx.y * NW + static_cast<uint32_t>(wave);
+    auto first_block = [&](uint32_t q) { return static_cast<int>(args.blocks_q * q + fdiv_u(args.blocks_r * q, args.divParts)); };
+    const int kb0 = first_block(p), kb1 = first_block(p + 1);
     const int kfull = (MODE == kF32Element) ? kb1 : min(kb1, g.K >> 4);
 
     for (int64_t t = blockIdx.x; t < args.tiles; t += gridDim.x) {
@@ -91,7 +96,7 @@ __global__ __launch_bounds__(64 * NW) void gather_gemm_f64_kernel(const F32Args 
         constexpr int NE = (NW == 1) ? NT : (BN > 4 * NW ? BN / (4 * NW) : 1);
         F32Column col[NE];
 #pragma unroll
-        for (int i = 0; i < NE; ++i) col[i] = f32_column(g, n0 + (NW == 1 ? 16 * i + l16 : (threadIdx.x + i * 64 * NW) % BN));
+        for (int i = 0; i < NE; ++i) col[i] = f32_column(g, args.divRG, n0 + (NW == 1 ? 16 * i + l16 : (threadIdx.x + i * 64 * NW) % BN));
 
         // rows and columns beyond the problem repeat the last one; they are not stored
         const int64_t m = min(m0 + l16, g.M - 1);
@@ -311,7 +316,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void gather_gemm_f64_short_kernel
     uint32_t b[KB][4][NT];                  // high halves of the codes' doubles
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        col[j] = f32_column(g, n0 + 16 * j + l16);
+        col[j] = f32_column(g, args.divRG, n0 + 16 * j + l16);
         const uint32_t* wrow = Wq + static_cast<int64_t>(min(n0 + 16 * j + l16, g.NC - 1)) * g.wpr;
 #pragma unroll
         for (int d = 0; d < KB; ++d) {
@@ -379,7 +384,7 @@ __global__ __launch_bounds__(64 * kShortWaves) void gather_gemm_f64_short_kernel
 }
 
 // Sum of the K ranges in a fixed order (float64), then the same tail as the unsplit kernel.
-__global__ __launch_bounds__(256) void fp32_splitk_finish_kernel(const GatherGemm g) {
+__global__ __launch_bounds__(256) void fp32_splitk_finish_kernel(const GatherGemm g, const FastDivU divRG) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int64_t total = g.M * g.NC;
     if (i >= total) return;
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(256) void fp32_splitk_finish_kernel(const GatherGem
     for (int s = 0; s < g.splits; ++s) sum += part[static_cast<int64_t>(s) * total + i];
     const int64_t m = i / g.NC;
     const int ncol = static_cast<int>(i - m * g.NC);
-    f32_tail_store(g, m, ncol, sum, f32_column(g, ncol));
+    f32_tail_store(g, m, ncol, sum, f32_column(g, divRG, ncol));
 }
 
 // Tile width, waves per tile and K ranges of the float32 path: a pure function of the shapes (the workspace query and
@@ -467,6 +472,11 @@ int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st) {
     a.divOW = make_fastdiv_u(static_cast<uint32_t>(g.OW));
     a.divOH = make_fastdiv_u(static_cast<uint32_t>(g.OH));
     a.divTN = make_fastdiv_u(static_cast<uint32_t>(p.tiles_n));
+    a.divRG = make_fastdiv_u(static_cast<uint32_t>(g.rows_per_group));
+    const int32_t nkb = static_cast<int32_t>((static_cast<int64_t>(g.K) + 15) / 16), parts = (g.splits > 1 ? g.splits : 1) * p.nw;
+    a.divParts = make_fastdiv_u(static_cast<uint32_t>(parts));
+    a.blocks_q = nkb / parts;
+    a.blocks_r = nkb % parts;
     a.walk = 0;
     const int mode = g.plain_gemm ? kF32Gemm : (g.IC % 4 == 0) ? kF32Quad : kF32Element;
     // short K, no taps to divide: offsets in 32 bits, rows and paddings far below the 2^28 that marks an element beyond K, one wave
@@ -496,7 +506,7 @@ int32_t launch_gather_gemm_fp32(const GatherGemm& g, hipStream_t st) {
     }
     if (g.splits > 1) {
         const int64_t total = g.M * g.NC;
-        fp32_splitk_finish_kernel<<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(g);
+        fp32_splitk_finish_kernel<<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(g, a.divRG);
     }
     return launch_status();
 }
