@@ -2,6 +2,7 @@
 #pragma once
 
 #include "twn_common.h"
+#include "twn_mfma.h"
 
 namespace twn {
 
@@ -84,6 +85,9 @@ struct DxPrep {
     // 16-byte units of dX to clear (classes without taps)
     void* zero;
     int64_t zero16;
+    // filled by the launch: threads of each part below 2^31 and O a multiple of 8, so that divisions are multiplications
+    int32_t narrow;
+    FastDivU divChunks, divTap, divW[4], divNs[4];
 };
 int32_t launch_dx_prep(const DxPrep& p, hipStream_t st);
 // Backward of a layer whose filter count is no multiple of 8, over O8 = that count rounded up: dY, the transposed codes and, with one
