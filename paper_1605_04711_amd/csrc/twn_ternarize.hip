@@ -34,6 +34,22 @@ struct TernWorkspace {
 constexpr int kTickets = 17, kTicketStep = 16;
 constexpr int kMaxPass1 = kMaxBlocks - kTickets * kTicketStep;
 
+// This thread's elements of the ragged chunk that starts at `base`, zeros behind the last one.
+__device__ __forceinline__ void load_tail(const float* __restrict__ p, int64_t base, int64_t n, float4* v) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int64_t idx = base + static_cast<int64_t>(j * kTernThreads + threadIdx.x) * 4;
+        if (idx + 3 < n) {
+            v[j] = *reinterpret_cast<const float4*>(p + idx);
+        } else {
+            v[j].x = idx < n ? p[idx] : 0.0f;
+            v[j].y = idx + 1 < n ? p[idx + 1] : 0.0f;
+            v[j].z = idx + 2 < n ? p[idx + 2] : 0.0f;
+            v[j].w = 0.0f;
+        }
+    }
+}
+
 // Pass 1 of block `bid` out of `nblk` cooperating blocks: float64 partial sum of |W| -> partial[bid].
 __device__ __forceinline__ void abs_sum_body(const float* __restrict__ W, int64_t n, double* __restrict__ partial,
                                              int bid, int nblk) {
@@ -67,14 +83,17 @@ __device__ __forceinline__ void abs_sum_body(const float* __restrict__ W, int64_
         }
         c = nx;
     }
-    // ragged tail (at most one chunk), taken by one block after its full chunks
+    // ragged tail (at most one chunk), taken by one block after its full chunks; element by element behind bounds tests it was
+    // sixteen memory latencies.  Requested before the full chunks it would keep 16 registers more alive in all blocks.
     if (nfull * kChunk < n && static_cast<int64_t>(bid) == nfull % nblk) {
-        const int64_t base = nfull * kChunk;
-        for (int j = 0; j < 4; ++j)
-            for (int e = 0; e < 4; ++e) {
-                const int64_t idx = base + static_cast<int64_t>(j * kTernThreads + tid) * 4 + e;
-                if (idx < n) acc += static_cast<double>(fabsf(W[idx]));
-            }
+        load_tail(W, nfull * kChunk, n, cur);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            acc += static_cast<double>(fabsf(cur[j].x));
+            acc += static_cast<double>(fabsf(cur[j].y));
+            acc += static_cast<double>(fabsf(cur[j].z));
+            acc += static_cast<double>(fabsf(cur[j].w));
+        }
     }
     const double total = block_sum(acc, scratch);
     if (tid == 0) partial[bid] = total;
@@ -490,6 +509,34 @@ __global__ __launch_bounds__(kTernThreads) void band_fix_kernel(const float* __r
     deliver(ws, blockIdx.x, gridDim.x, total, ctotal, delta, delta_out, alpha_out, nnz_out, scratch, scratch_u);
 }
 
+// The 16 weights of word j of an output row: filter `row`'s codes k = rs*C + c in the normal copy, input channel `row`'s codes
+// k = rs*rows + o in the transposed one.  One division per word, then all sixteen loads are requested (bit t of the result:
+// weight t exists; the others read the tensor's first one).  With a 64-bit division and a wait per weight a
+// call was (us) 19 instead of 13 for 300 x 200 x 3 x 3, 91 instead of 59 for 3333 x 5008.
+template <bool TRANSPOSED>
+__device__ __forceinline__ uint32_t gather_word(const float* __restrict__ W, int rows, int C, int RS, int row, int j,
+                                                float (&w)[16]) {
+    const uint32_t len = static_cast<uint32_t>(TRANSPOSED ? rows : C), k0 = static_cast<uint32_t>(j) * 16u;
+    uint32_t rs = k0 / len, i = k0 - rs * len;
+    const int64_t step = TRANSPOSED ? static_cast<int64_t>(C) * RS : RS;
+    const int64_t base = static_cast<int64_t>(row) * (TRANSPOSED ? RS : step * C);
+    uint32_t real = 0;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        const bool ok = rs < static_cast<uint32_t>(RS);
+        real |= ok ? 1u << t : 0u;
+        w[t] = W[ok ? base + i * step + rs : 0];
+        const bool next = ++i == len;
+        i = next ? 0u : i;
+        rs += next ? 1u : 0u;
+    }
+    return real;
+}
+// quotient of a word's number, which is below 2^31 for all but the largest tensors
+__device__ __forceinline__ int64_t word_quotient(int64_t id, int d, bool narrow) {
+    return narrow ? static_cast<int64_t>(static_cast<uint32_t>(id) / static_cast<uint32_t>(d)) : id / d;
+}
+
 // Pass 2 for any layout: grid-stride over the output words of the normal copy (which also carry the
 // masked sum and count: every weight belongs to exactly one normal word) and of the transposed copy.
 //   normal:     row = filter o,        k   = (r*S+s)*C + c
@@ -505,43 +552,32 @@ __device__ __forceinline__ void mask_pack_gather_body(
     const float delta = delta_from_partials(ws->p1, nb1, f, n, scratch);
     const int64_t words_n = only_transposed ? 0 : static_cast<int64_t>(rows) * wpr;
     const int64_t words_t = packed_T ? static_cast<int64_t>(C) * wprT : 0;
-    const int64_t K = static_cast<int64_t>(RS) * C, KT = static_cast<int64_t>(RS) * rows;
+    const bool narrow = words_n + words_t < (1LL << 31);
     double acc = 0.0;
     uint32_t count = 0;
     for (int64_t id = static_cast<int64_t>(bid) * blockDim.x + threadIdx.x; id < words_n + words_t;
          id += static_cast<int64_t>(nblk) * blockDim.x) {
+        float w[16];
         uint32_t word = 0;
         if (id < words_n) {
-            const int o = static_cast<int>(id / wpr), j = static_cast<int>(id % wpr);
+            const int64_t o = word_quotient(id, wpr, narrow);
+            const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), w);
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
-                const int64_t k = static_cast<int64_t>(j) * 16 + t;
-                if (k < K) {
-                    const int rs = static_cast<int>(k / C);
-                    const int c = static_cast<int>(k - static_cast<int64_t>(rs) * C);
-                    const float w = W[(static_cast<int64_t>(o) * C + c) * RS + rs];
-                    const uint32_t fld = code_field(w, delta);
-                    if (fld) {
-                        acc += static_cast<double>(fabsf(w));
-                        ++count;
-                    }
-                    word |= fld << ((t & 1) * 16 + (t >> 1) * 2);
-                }
+                const uint32_t fld = (real >> t & 1u) ? code_field(w[t], delta) : 0u;
+                // adding +0.0 for the masked-out weights leaves the float64 sum unchanged
+                acc += static_cast<double>(fld ? fabsf(w[t]) : 0.0f);
+                count += fld & 1u;
+                word |= fld << ((t & 1) * 16 + (t >> 1) * 2);
             }
             packed[id] = word;
         } else {
-            const int64_t it = id - words_n;
-            const int c = static_cast<int>(it % C), j = static_cast<int>(it / C);
+            const int64_t it = id - words_n, j = word_quotient(it, C, narrow);
+            const int c = static_cast<int>(it - j * C);
+            const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), w);
 #pragma unroll
-            for (int t = 0; t < 16; ++t) {
-                const int64_t k = static_cast<int64_t>(j) * 16 + t;
-                if (k < KT) {
-                    const int rs = static_cast<int>(k / rows);
-                    const int o = static_cast<int>(k - static_cast<int64_t>(rs) * rows);
-                    word |= code_field(W[(static_cast<int64_t>(o) * C + c) * RS + rs], delta)
-                            << ((t & 1) * 16 + (t >> 1) * 2);
-                }
-            }
+            for (int t = 0; t < 16; ++t)
+                word |= ((real >> t & 1u) ? code_field(w[t], delta) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
             packed_T[static_cast<int64_t>(c) * wprT + j] = word;
         }
     }
@@ -767,22 +803,17 @@ __global__ __launch_bounds__(kTernThreads) void batch_abs_sum_kernel(const Batch
 __global__ __launch_bounds__(kTernThreads) void batch_mask_pack_kernel(const BatchTable tb, TernWorkspace* __restrict__ ws) {
     const int i = batch_find(tb, blockIdx.x, &BatchItem::first2, &BatchItem::nb2);
     const BatchItem& it = tb.item[i];
-    if (it.flat_blocks > 0) {
-        const int local = blockIdx.x - it.first2;
-        const int64_t n = static_cast<int64_t>(it.rows) * it.C;
-        if (local < it.flat_blocks)
-            mask_pack_flat_body(it.W, n, ws + i, it.nb1, tb.f, it.packed, 1, local, it.flat_blocks, it.nb2, it.delta, it.alpha,
-                                it.nnz);
-        else
-            mask_pack_gather_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
-                                  local - it.flat_blocks, it.nb2 - it.flat_blocks, it.nb2, it.delta, it.alpha, it.nnz, true,
-                                  it.flat_blocks);
-    } else if (it.tiled)
-        mask_pack_tile_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
-                            blockIdx.x - it.first2, it.delta, it.alpha, it.nnz);
+    const int local = static_cast<int>(blockIdx.x) - it.first2;
+    if (it.tiled)
+        mask_pack_tile_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT, local, it.delta,
+                            it.alpha, it.nnz);
+    else if (local < it.flat_blocks)
+        mask_pack_flat_body(it.W, static_cast<int64_t>(it.rows) * it.C, ws + i, it.nb1, tb.f, it.packed, 1, local, it.flat_blocks,
+                            it.nb2, it.delta, it.alpha, it.nnz);
     else
         mask_pack_gather_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
-                              blockIdx.x - it.first2, it.nb2, it.nb2, it.delta, it.alpha, it.nnz);
+                              local - it.flat_blocks, it.nb2 - it.flat_blocks, it.nb2, it.delta, it.alpha, it.nnz, it.flat_blocks > 0,
+                              it.flat_blocks);
 }
 
 // One block per group: both passes over the group's contiguous weights.
@@ -1050,38 +1081,40 @@ __global__ __launch_bounds__(256) void sign_pack_kernel(const float* __restrict_
 __device__ __forceinline__ void pack_gather_body(
     const float* __restrict__ W, int rows, int C, int RS, const float* __restrict__ delta,
     int rows_per_group, uint32_t* __restrict__ out, int wpr, int transposed, int64_t id) {
-    int64_t out_rows = transposed ? C : rows;
-    if (id >= out_rows * wpr) return;
-    int row, j;
-    if (transposed) {
-        row = static_cast<int>(id % C);   // input channel, fastest across threads
-        j = static_cast<int>(id / C);
-    } else {
-        row = static_cast<int>(id / wpr);
-        j = static_cast<int>(id % wpr);
-    }
-    const int64_t K = transposed ? static_cast<int64_t>(RS) * rows : static_cast<int64_t>(RS) * C;
+    const int64_t words = static_cast<int64_t>(transposed ? C : rows) * wpr;
+    if (id >= words) return;
+    const bool narrow = words < (1LL << 31);
+    float w[16];
     uint32_t word = 0;
+    if (transposed) {
+        const int64_t j = word_quotient(id, C, narrow);         // input channel, fastest across threads
+        const int c = static_cast<int>(id - j * C);
+        const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), w);
+        // group of the word's first filter, and the filter's place in it
+        const uint32_t per_group = static_cast<uint32_t>(rows_per_group), filters = static_cast<uint32_t>(rows);
+        const uint32_t o0 = static_cast<uint32_t>(j) * 16u % filters;
+        uint32_t g = o0 / per_group, r = o0 - g * per_group, left = filters - o0;
+        float d[16];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const int64_t k = static_cast<int64_t>(j) * 16 + t;
-        if (k < K) {
-            int o, c, rs;
-            if (transposed) {
-                rs = static_cast<int>(k / rows);
-                o = static_cast<int>(k - static_cast<int64_t>(rs) * rows);
-                c = row;
-            } else {
-                rs = static_cast<int>(k / C);
-                c = static_cast<int>(k - static_cast<int64_t>(rs) * C);
-                o = row;
-            }
-            const float w = W[(static_cast<int64_t>(o) * C + c) * RS + rs];
-            const uint32_t fld = code_field(w, delta[o / rows_per_group]);
-            word |= fld << ((t & 1) * 16 + (t >> 1) * 2);
+        for (int t = 0; t < 16; ++t) {
+            d[t] = delta[g];
+            const bool wrap = --left == 0u, next = ++r == per_group;
+            r = wrap || next ? 0u : r;
+            g = wrap ? 0u : g + (next ? 1u : 0u);
+            left = wrap ? filters : left;
         }
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+            word |= ((real >> t & 1u) ? code_field(w[t], d[t]) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
+        out[static_cast<int64_t>(c) * wpr + j] = word;
+        return;
     }
-    out[static_cast<int64_t>(row) * wpr + j] = word;
+    const int64_t o = word_quotient(id, wpr, narrow);
+    const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), w);
+    const float d = delta[static_cast<int>(o) / rows_per_group];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) word |= ((real >> t & 1u) ? code_field(w[t], d) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
+    out[id] = word;
 }
 
 __global__ __launch_bounds__(256) void pack_gather_kernel(
@@ -1332,16 +1365,29 @@ __global__ __launch_bounds__(kTernThreads) void sgd_update_kernel(float* __restr
     // ragged tail (at most one chunk), taken by the block abs_sum_body gives it to, in its element order
     if (nfull * kChunk < n && static_cast<int64_t>(bid) == nfull % nblk) {
         const int64_t base = nfull * kChunk;
-        for (int j = 0; j < 4; ++j)
-            for (int e = 0; e < 4; ++e) {
-                const int64_t idx = base + static_cast<int64_t>(j * kTernThreads + tid) * 4 + e;
-                if (idx < n) {
-                    float w = W[idx], v = V[idx];
-                    update(w, v, dW[idx]);
-                    W[idx] = w;
-                    V[idx] = v;
-                }
+        load_tail(W, base, n, w4);
+        load_tail(V, base, n, v4);
+        load_tail(dW, base, n, g4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t idx = base + static_cast<int64_t>(j * kTernThreads + tid) * 4;
+            if (idx < n) update(w4[j].x, v4[j].x, g4[j].x);
+            if (idx + 1 < n) update(w4[j].y, v4[j].y, g4[j].y);
+            if (idx + 2 < n) update(w4[j].z, v4[j].z, g4[j].z);
+            if (idx + 3 < n) update(w4[j].w, v4[j].w, g4[j].w);
+            if (idx + 3 < n) {
+                *reinterpret_cast<float4*>(W + idx) = w4[j];
+                *reinterpret_cast<float4*>(V + idx) = v4[j];
+            } else {
+                const float we[3] = {w4[j].x, w4[j].y, w4[j].z}, ve[3] = {v4[j].x, v4[j].y, v4[j].z};
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (idx + e < n) {
+                        W[idx + e] = we[e];
+                        V[idx + e] = ve[e];
+                    }
             }
+        }
     }
     const double total = block_sum(acc, scratch);
     if (partial && tid == 0) partial[bid] = total;
@@ -1535,10 +1581,16 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
         }
         it.nb2 = static_cast<int32_t>(nb2);
         it.first1 = first1;
-        it.first2 = first2;
         first1 += it.nb1;
-        first2 += it.nb2;
     }
+    // what gathers first: a block of it is a chain of latencies, which ends the launch late if it starts late (VGG-7 with both
+    // copies, whose classifier of 10 gathers: 36.2 us last, 33.0 first)
+    for (int tiled = 0; tiled < 2; ++tiled)
+        for (int i = 0; i < count; ++i)
+            if (tb.item[i].nb2 > 0 && tb.item[i].tiled == tiled) {
+                tb.item[i].first2 = first2;
+                first2 += tb.item[i].nb2;
+            }
     // longest filters first: a long one that starts late ends the launch late
     int64_t firstf = 0;
     for (int64_t below = kFilterMaxK + 1; filter_k > 0 && below > 0;) {
