@@ -1,0 +1,105 @@
+// One block's part of a bias gradient, for its own launch and for the blocks that a final pass over partial tiles of dW carries.
+#pragma once
+
+#include "twn_common.h"
+#include "twn_kernels.h"
+
+namespace twn {
+
+constexpr int kBiasThreads = 512;
+// LDS of a block, in floats (8 channels; single channels take an eighth of it)
+constexpr int kBiasLds = kBiasThreads * 8;
+
+// Group `group` of channels over pixels begin..end, dest[channel].  The sums are those of 512 threads, also in a block of fewer (a
+// thread then takes several of their places in turn) or more: the result does not depend on the launch that carries the block.
+template <int VEC, int THREADS>
+__device__ __forceinline__ void bias_grad_group(const BiasGrad& b, int group, int64_t begin, int64_t end, float* __restrict__ dest,
+                                                float* __restrict__ red) {
+    const int chunk0 = group * b.chunks_per_group;
+    const int left = (b.O + VEC - 1) / VEC - chunk0;
+    const int gc = left < b.chunks_per_group ? left : b.chunks_per_group;      // chunks of VEC channels in this block
+    const int rows = kBiasThreads / gc;
+    for (int t = threadIdx.x; t < kBiasThreads; t += THREADS) {
+        const int row = t / gc, ch = (chunk0 + t % gc) * VEC;
+        float acc[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.0f;
+        if (row < rows) {
+            const uint16_t* src = b.dY + ch;
+            // eight pixels requested at a time, those behind the last as the first of them and counted as zeros (one at a time
+            // they were a chain of latencies: a final pass with 3565 pixels x 72 channels in it 9 us, so 5.8)
+            for (int64_t p = begin + row; p < end; p += 8 * rows) {
+                if constexpr (VEC == 8) {
+                    u32x4 x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const u32x4*>(src + (p + u * rows < end ? p + u * rows : p) * b.O);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const bool real = p + u * rows < end;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t w = real ? x[u][i] : 0u;
+                            acc[(2 * i) % VEC] += __uint_as_float(w << 16);
+                            acc[(2 * i + 1) % VEC] += __uint_as_float(w & 0xFFFF0000u);
+                        }
+                    }
+                } else {
+                    uint16_t x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = src[(p + u * rows < end ? p + u * rows : p) * b.O];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) acc[0] += p + u * rows < end ? bf16_to_f32(x[u]) : 0.0f;
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) red[t * VEC + v] = acc[v];     // [row][channel of the group]
+    }
+    __syncthreads();
+    // column sums in two stages: `parts` threads per channel add runs of rows, then one adds the parts
+    const int nch = gc * VEC, most = VEC == 8 ? kBiasThreads / VEC : 32;
+    const int parts = kBiasThreads / nch < most ? kBiasThreads / nch : most;
+    const int each = (rows + parts - 1) / parts;
+    constexpr int TURNS = THREADS < kBiasThreads ? kBiasThreads / THREADS : 1;
+    float s[TURNS];
+#pragma unroll
+    for (int u = 0; u < TURNS; ++u) {
+        const int t = threadIdx.x + u * THREADS, c = t % nch, part = t / nch;
+        s[u] = 0.0f;
+        if (part < parts) {
+            const int last = (part + 1) * each < rows ? (part + 1) * each : rows;
+#pragma unroll 8
+            for (int r = part * each; r < last; ++r) s[u] += red[r * nch + c];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < TURNS; ++u) {
+        const int t = threadIdx.x + u * THREADS, c = t % nch, part = t / nch;
+        if (part < parts) red[part * nch + c] = s[u];
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < nch; c += THREADS) {
+        float t = 0.0f;
+#pragma unroll 16
+        for (int i = 0; i < parts; ++i) t += red[i * nch + c];
+        if (chunk0 * VEC + c < b.O) dest[chunk0 * VEC + c] = t;
+    }
+    __syncthreads();        // the next group of channels reuses the rows
+}
+
+// The first b.blocks blocks of a final pass sum dbias, all pixels of a group each: its result in the block's place among the
+// others, or -1 after a bias gradient.  Their own launch costs 4-5 us behind the final pass, which leaves most of the chip idle
+// in layers of few pixels (us of a forward and backward: 3565 pixels, 40 -> 72 channels 5x5/2 37.1 -> 34.7).
+template <int THREADS>
+__device__ __forceinline__ int final_pass_block(const BiasGrad& b, float* __restrict__ red) {
+    const int block = static_cast<int>(blockIdx.x) - b.blocks;
+    if (block >= 0) return block;
+    for (int group = blockIdx.x; group < b.groups; group += b.blocks) {
+        if (b.vec == 8) bias_grad_group<8, THREADS>(b, group, 0, b.pixels, b.dbias, red);
+        else bias_grad_group<1, THREADS>(b, group, 0, b.pixels, b.dbias, red);
+    }
+    return -1;
+}
+
+}  // namespace twn

@@ -26,6 +26,7 @@
 
 #include <mutex>
 
+#include "twn_bias_grad.h"
 #include "twn_kernels.h"
 #include "twn_mfma.h"
 
@@ -698,10 +699,14 @@ __global__ __launch_bounds__(256 * KS, 2) void weight_grad_patch_kernel(const WG
 template <int VEC, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void weight_grad_reduce_kernel(const float* __restrict__ partial, int splits,
                                                                  int O, int o_real, int C, int R, int S, int pad_sp, float beta,
-                                                                 float* __restrict__ dW) {
-    __shared__ float red[WAVES][64 * VEC];
+                                                                 float* __restrict__ dW, const BiasGrad bias) {
+    static_assert(WAVES * 64 * VEC <= kBiasLds, "a bias gradient's rows and the waves' sums share the space");
+    __shared__ float red_all[kBiasLds];
+    const int block = final_pass_block<64 * WAVES>(bias, red_all);
+    if (block < 0) return;
+    float (*red)[64 * VEC] = reinterpret_cast<float (*)[64 * VEC]>(red_all);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t id0 = (static_cast<int64_t>(blockIdx.x) * 64 + lane) * VEC;
+    const int64_t id0 = (static_cast<int64_t>(block) * 64 + lane) * VEC;
     const int64_t Jsrc = pad_sp ? static_cast<int64_t>(R) * pad_sp * 4 : static_cast<int64_t>(R) * S * C;
     const int64_t total = Jsrc * O;
     float acc[VEC];
@@ -725,29 +730,29 @@ __global__ __launch_bounds__(64 * WAVES) void weight_grad_reduce_kernel(const fl
     // one element per thread: element `el` of the block's 64*VEC (VEC = 1: the first wave only)
     const int el = threadIdx.x;
     if (el >= 64 * VEC) return;
-    const int64_t id = static_cast<int64_t>(blockIdx.x) * 64 * VEC + el;
+    const int64_t id = static_cast<int64_t>(block) * 64 * VEC + el;
     if (id >= total) return;
     float sum = red[0][el];
 #pragma unroll
     for (int wv = 1; wv < WAVES; ++wv) sum += red[wv][el];
-    const int64_t o = id / Jsrc;
-    if (o >= o_real) return;             // a filter that pads dY
-    const int64_t j = id - o * Jsrc;
-    int64_t rs, c;
-    int r, sx;
+    // fewer than 2^32 sums, as a grid has threads: divisions of 32 bits
+    const uint32_t o = static_cast<uint32_t>(id) / static_cast<uint32_t>(Jsrc);
+    if (o >= static_cast<uint32_t>(o_real)) return;             // a filter that pads dY
+    const uint32_t j = static_cast<uint32_t>(id) - o * static_cast<uint32_t>(Jsrc);
+    int rs, c, r, sx;
     if (pad_sp) {
-        c = j & 3;
-        rs = j >> 2;
-        r = static_cast<int>(rs / pad_sp);
-        sx = static_cast<int>(rs - static_cast<int64_t>(r) * pad_sp);
+        c = static_cast<int>(j & 3u);
+        rs = static_cast<int>(j >> 2);
+        r = rs / pad_sp;
+        sx = rs - r * pad_sp;
         if (c >= C || sx >= S) return;
     } else {
-        rs = j / C;                  // = r*S + s
-        c = j - rs * C;
-        r = static_cast<int>(rs / S);
-        sx = static_cast<int>(rs - static_cast<int64_t>(r) * S);
+        rs = static_cast<int>(j / static_cast<uint32_t>(C));                  // = r*S + s
+        c = static_cast<int>(j) - rs * C;
+        r = rs / S;
+        sx = rs - r * S;
     }
-    const int64_t dst = ((o * C + c) * R + r) * S + sx;   // [O][C][R][S]
+    const int64_t dst = ((static_cast<int64_t>(o) * C + c) * R + r) * S + sx;   // [O][C][R][S]
     dW[dst] = (beta != 0.0f) ? beta * dW[dst] + sum : sum;
 }
 
@@ -759,10 +764,13 @@ __global__ __launch_bounds__(64 * WAVES) void weight_grad_reduce_kernel(const fl
 constexpr int kReduceRowsMaxTaps = 25;
 __global__ __launch_bounds__(256) void weight_grad_reduce_rows_kernel(const float* __restrict__ partial, int splits,
                                                                       int O, int C, int RS, float beta,
-                                                                      float* __restrict__ dW) {
-    __shared__ float tile[64 * kReduceRowsMaxTaps];      // [channel][tap]
+                                                                      float* __restrict__ dW, const BiasGrad bias) {
+    static_assert(64 * kReduceRowsMaxTaps <= kBiasLds, "a bias gradient's rows and the transposed sums share the space");
+    __shared__ float tile[kBiasLds];                     // [channel][tap]
+    const int block = final_pass_block<256>(bias, tile);
+    if (block < 0) return;
     const int cchunks = C / 64;
-    const int o = blockIdx.x / cchunks, c0 = (blockIdx.x % cchunks) * 64;
+    const int o = block / cchunks, c0 = (block % cchunks) * 64;
     const int64_t J = static_cast<int64_t>(RS) * C;
     const int64_t total = J * O;
     // item = (tap, group of 4 channels): 16 items per tap
@@ -791,66 +799,13 @@ __global__ __launch_bounds__(256) void weight_grad_reduce_rows_kernel(const floa
 // itself, otherwise float32 partials [split][O] for bias_grad_final_kernel.
 // Time of both launches against 64 ranges of single values (us): 162792 pixels, 128 filters 187 -> 14 (3 TB/s); 25056, 64: 30 -> 10;
 // 9800, 200: 16 -> 10; 910, 200 (one launch): 9 -> 7.
-constexpr int kBiasThreads = 512;
 template <int VEC>
-__global__ __launch_bounds__(kBiasThreads) void bias_grad_kernel(const uint16_t* __restrict__ dY, int64_t pixels, int O,
-                                                                 int chunks_per_group, int groups, int64_t per,
-                                                                 float* __restrict__ out) {
+__global__ __launch_bounds__(kBiasThreads) void bias_grad_kernel(const BiasGrad b, int64_t per, float* __restrict__ out) {
     __shared__ float red[kBiasThreads * VEC];
-    for (int group = blockIdx.x; group < groups; group += gridDim.x) {
-        const int chunk0 = group * chunks_per_group;
-        const int left = (O + VEC - 1) / VEC - chunk0;
-        const int gc = left < chunks_per_group ? left : chunks_per_group;      // chunks of VEC channels in this block
-        const int rows = kBiasThreads / gc;
-        const int row = threadIdx.x / gc, ch = (chunk0 + threadIdx.x % gc) * VEC;
-        const int64_t begin = static_cast<int64_t>(blockIdx.y) * per;
-        const int64_t end = begin + per < pixels ? begin + per : pixels;
-        float acc[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] = 0.0f;
-        if (row < rows) {
-            const uint16_t* src = dY + ch;
-            auto add = [&](int64_t p) {
-                if constexpr (VEC == 8) {
-                    const uint4 t = *reinterpret_cast<const uint4*>(src + p * O);
-                    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        acc[(2 * i) % VEC] += __uint_as_float(w[i] << 16);
-                        acc[(2 * i + 1) % VEC] += __uint_as_float(w[i] & 0xFFFF0000u);
-                    }
-                } else {
-                    acc[0] += bf16_to_f32(src[p * O]);
-                }
-            };
-            int64_t p = begin + row;
-            for (; p + 7 * rows < end; p += 8 * rows) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) add(p + u * rows);
-            }
-            for (; p < end; p += rows) add(p);
-        }
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) red[threadIdx.x * VEC + v] = acc[v];     // [row][channel of the group]
-        __syncthreads();
-        // column sums in two stages: `parts` threads per channel add runs of rows, then one adds the parts
-        const int nch = gc * VEC, most = VEC == 8 ? kBiasThreads / VEC : 32;
-        const int parts = kBiasThreads / nch < most ? kBiasThreads / nch : most;
-        const int each = (rows + parts - 1) / parts;
-        float s = 0.0f;
-        const int c = threadIdx.x % nch, part = threadIdx.x / nch;
-        if (part < parts)
-            for (int r = part * each; r < (part + 1) * each && r < rows; ++r) s += red[r * nch + c];
-        __syncthreads();
-        if (part < parts) red[part * nch + c] = s;
-        __syncthreads();
-        if (part == 0) {
-            float t = 0.0f;
-            for (int i = 0; i < parts; ++i) t += red[i * nch + c];
-            if (chunk0 * VEC + c < O) out[static_cast<int64_t>(blockIdx.y) * O + chunk0 * VEC + c] = t;
-        }
-        __syncthreads();        // the next group of channels reuses the rows
-    }
+    const int64_t begin = static_cast<int64_t>(blockIdx.y) * per;
+    const int64_t end = begin + per < b.pixels ? begin + per : b.pixels;
+    for (int group = blockIdx.x; group < b.groups; group += gridDim.x)
+        bias_grad_group<VEC, kBiasThreads>(b, group, begin, end, out + static_cast<int64_t>(blockIdx.y) * b.O, red);
 }
 
 // Fixed-order sum of the partials: 64 channels per block, sixteen waves share the splits.
@@ -876,39 +831,63 @@ __global__ __launch_bounds__(1024) void bias_grad_final_kernel(const float* __re
     }
 }
 
-// `partial` holds `capacity` floats, 64 ranges at least.  One launch up to 8192 pixels: a thread then adds at most sixteen values of
+// One launch up to 8192 pixels: a thread then adds at most sixteen values of
 // a channel with 16-byte loads and 32 with single ones, whose blocks have as many rows as that takes and fewer channels
 // the more pixels there are; where such narrow columns of many channels are read (each touches every line of dY), two
 // launches, as beyond (us of a call, one launch / two: 4000 pixels x 250 7.5 / 10; 8192 x 63 8.0 / 10; blocks of sixteen
-// columns there 7.8 and 13.6, in chains of 256).  Then ranges are enough that a thread adds no more than every 256th pixel,
+// columns there 7.8 and 13.6, in chains of 256).
+static bool bias_in_one_launch(int64_t pixels, int O) {
+    return pixels <= 8192 && (O % 8 == 0 || pixels <= 1024 || O * pixels * pixels <= (1LL << 32));
+}
+
+static BiasGrad bias_groups(const WeightGrad& w, bool single) {
+    BiasGrad b{};
+    b.dY = w.dY;
+    b.dbias = w.dbias;
+    b.pixels = static_cast<int64_t>(w.N) * w.P * w.Q;
+    b.O = w.O;
+    b.vec = w.O % 8 == 0 ? 8 : 1;
+    const int chunks = (b.O + b.vec - 1) / b.vec;
+    const int few = b.pixels <= 1024 ? 16 : static_cast<int>(16384 / b.pixels);      // single channels: 512 / few rows
+    b.chunks_per_group = single ? (b.vec == 8 ? 1 : (b.O < few ? b.O : few)) : (b.vec == 8 ? (chunks < 8 ? chunks : 8) : (b.O < 64 ? b.O : 64));
+    b.groups = (chunks + b.chunks_per_group - 1) / b.chunks_per_group;
+    return b;
+}
+
+BiasGrad bias_in_final_pass(const WeightGrad& w) {
+    if (!w.dbias || !bias_in_one_launch(static_cast<int64_t>(w.N) * w.P * w.Q, w.O)) return BiasGrad{};
+    BiasGrad b = bias_groups(w, true);
+    b.blocks = b.groups < (1 << 20) ? b.groups : (1 << 20);
+    return b;
+}
+
+// `partial` holds 64 ranges at least.  Beyond one launch, ranges are enough that a thread adds no more than every 256th pixel,
 // however many channels there are.
-template <int VEC>
-static void launch_bias_grad(const uint16_t* dY, int64_t pixels, int O, float* partial, int64_t capacity, float* dbias,
-                             hipStream_t st) {
-    const int chunks = (O + VEC - 1) / VEC;
-    const bool single = pixels <= 8192 && (VEC == 8 || pixels <= 1024 || O * pixels * pixels <= (1LL << 32));
-    const int few = pixels <= 1024 ? 16 : static_cast<int>(16384 / pixels);      // single channels: 512 / few rows
-    const int gc = single ? (VEC == 8 ? 1 : (O < few ? O : few)) : (VEC == 8 ? (chunks < 8 ? chunks : 8) : (O < 64 ? O : 64));
-    const int groups = (chunks + gc - 1) / gc;
+static void launch_bias_grad(const WeightGrad& w, hipStream_t st) {
+    const int64_t pixels = static_cast<int64_t>(w.N) * w.P * w.Q;
+    const bool single = bias_in_one_launch(pixels, w.O);
+    const BiasGrad b = bias_groups(w, single);
     int64_t splits = 1;
     if (!single) {
-        const int rows = kBiasThreads / gc;
-        splits = 1024 / groups;                                      // about four blocks per CU
+        const int rows = kBiasThreads / b.chunks_per_group;
+        splits = 1024 / b.groups;                                      // about four blocks per CU
         if (splits < 256 / rows) splits = 256 / rows;
         const int64_t rows8 = static_cast<int64_t>(rows) * 8;
         if (splits > (pixels + rows8 - 1) / rows8) splits = (pixels + rows8 - 1) / rows8;
-        if (splits > capacity / O) splits = capacity / O;
+        if (splits > w.partial_floats / b.O) splits = w.partial_floats / b.O;
         if (splits < 1) splits = 1;
     }
     const int64_t per = (pixels + splits - 1) / splits;
     splits = (pixels + per - 1) / per;
-    const unsigned gx = static_cast<unsigned>(groups < (1 << 20) ? groups : (1 << 20));     // below 2^32 threads
-    bias_grad_kernel<VEC><<<dim3(gx, static_cast<unsigned>(splits)), kBiasThreads, 0, st>>>(dY, pixels, O, gc, groups, per,
-                                                                                            splits == 1 ? dbias : partial);
-    const int blocks = (O + 63) / 64;
+    const unsigned gx = static_cast<unsigned>(b.groups < (1 << 20) ? b.groups : (1 << 20));     // below 2^32 threads
+    const dim3 grid(gx, static_cast<unsigned>(splits));
+    float* out = splits == 1 ? w.dbias : w.partial;
+    if (b.vec == 8) bias_grad_kernel<8><<<grid, kBiasThreads, 0, st>>>(b, per, out);
+    else bias_grad_kernel<1><<<grid, kBiasThreads, 0, st>>>(b, per, out);
+    const int blocks = (b.O + 63) / 64;
     if (splits > 1)
         bias_grad_final_kernel<<<static_cast<unsigned>(blocks < (1 << 20) ? blocks : (1 << 20)), 1024, 0, st>>>(
-            partial, static_cast<int>(splits), O, dbias);
+            w.partial, static_cast<int>(splits), b.O, w.dbias);
 }
 
 static int32_t choose_splits(int64_t tiles, int64_t slabs, int ks = 1) {
@@ -1026,8 +1005,9 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
     a.xcd_map = env_int(Env::WG_XCD, 1);
     a.dy_bytes = a.x_bytes = 0;
     a.exact = 0;
+    bool bias_done = false;
     if (w.dW && route.taps.use) {
-        const int32_t rc = launch_weight_grad_taps(w, route.taps, st);
+        const int32_t rc = launch_weight_grad_taps(w, route.taps, &bias_done, st);
         if (rc != TWN_OK) return rc;
     } else if (w.dW) {
         const dim3 grid(a.plan.tiles, splits);
@@ -1060,40 +1040,37 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
             const int64_t total = static_cast<int64_t>(w.O) * a.J;
             const int C = w.pad_sp ? w.c_real : w.C, S = w.pad_sp ? w.s_real : w.S;
             const int RS = w.R * w.S;
+            const BiasGrad bias = bias_in_final_pass(w);
+            bias_done = bias.blocks > 0;
             // whole rows up to 16 ranges (us of both launches, rows / scattered floats: 588 pixels, 256 -> 512 channels 3x3/2, 3
             // ranges 19.6 / 25.3; 3136, the same, 6 ranges 27.6 / 32.2; 12544, 128 -> 256, 24 ranges 27.6 / 25.3)
             if (!w.pad_sp && w.C % 64 == 0 && RS > 1 && RS <= kReduceRowsMaxTaps && splits <= env_int(Env::WG_ROWS_SPLITS, 16))
-                weight_grad_reduce_rows_kernel<<<static_cast<unsigned>(w.o_real * (w.C / 64)), 256, 0, st>>>(
-                    w.partial, splits, w.O, w.C, RS, w.beta, w.dW);
+                weight_grad_reduce_rows_kernel<<<static_cast<unsigned>(w.o_real * (w.C / 64) + bias.blocks), 256, 0, st>>>(
+                    w.partial, splits, w.O, w.C, RS, w.beta, w.dW, bias);
             else if (total % 4 == 0 && splits >= 64 && total < 256 * 256)
-                weight_grad_reduce_kernel<4, 16><<<static_cast<unsigned>((total + 255) / 256), 1024, 0, st>>>(
-                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW);
+                weight_grad_reduce_kernel<4, 16><<<static_cast<unsigned>((total + 255) / 256 + bias.blocks), 1024, 0, st>>>(
+                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW, bias);
             else if (total % 4 == 0)
-                weight_grad_reduce_kernel<4, 4><<<static_cast<unsigned>((total + 255) / 256), 256, 0, st>>>(
-                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW);
+                weight_grad_reduce_kernel<4, 4><<<static_cast<unsigned>((total + 255) / 256 + bias.blocks), 256, 0, st>>>(
+                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW, bias);
             else
-                weight_grad_reduce_kernel<1, 4><<<static_cast<unsigned>((total + 63) / 64), 256, 0, st>>>(
-                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW);
+                weight_grad_reduce_kernel<1, 4><<<static_cast<unsigned>((total + 63) / 64 + bias.blocks), 256, 0, st>>>(
+                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW, bias);
         }
     }
-    if (w.dbias) {
-        // the partial tiles of dW have been read: their space serves the partial sums of dbias too
-        if (w.O % 8 == 0)
-            launch_bias_grad<8>(w.dY, a.pixels, w.O, w.partial, w.partial_floats, w.dbias, st);
-        else
-            launch_bias_grad<1>(w.dY, a.pixels, w.O, w.partial, w.partial_floats, w.dbias, st);
-    }
+    // the partial tiles of dW have been read: their space serves the partial sums of dbias too
+    if (w.dbias && !bias_done) launch_bias_grad(w, st);
     return launch_status();
 }
 
 int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t o_real, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
-                                     float beta, float* dW, hipStream_t st) {
+                                     float beta, float* dW, const BiasGrad& bias, hipStream_t st) {
     const int64_t total = static_cast<int64_t>(O) * R * pad_sp * 4;
-    const unsigned blocks = static_cast<unsigned>((total + 255) / 256);
+    const unsigned blocks = static_cast<unsigned>((total + 255) / 256 + bias.blocks);
     if (splits >= 64 && total < 256 * 256)
-        weight_grad_reduce_kernel<4, 16><<<blocks, 1024, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW);
+        weight_grad_reduce_kernel<4, 16><<<blocks, 1024, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW, bias);
     else
-        weight_grad_reduce_kernel<4, 4><<<blocks, 256, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW);
+        weight_grad_reduce_kernel<4, 4><<<blocks, 256, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW, bias);
     return launch_status();
 }
 

@@ -25,6 +25,7 @@
 // fragments four or five taps ahead, and stages private to each wave (no barrier) were all slower or equal.
 #include <mutex>
 
+#include "twn_bias_grad.h"
 #include "twn_kernels.h"
 #include "twn_lds_asm.h"
 
@@ -381,11 +382,13 @@ __global__ __launch_bounds__(64 * kWaves, 2) void weight_grad_taps_kernel(const 
 // after the other (8.8 us; with eight 5.3).
 template <int PARTS>
 __global__ __launch_bounds__(256) void weight_grad_sum_kernel(const float* __restrict__ partial, int splits, int64_t pitch, int64_t n,
-                                                              float beta, float* __restrict__ dW) {
+                                                              float beta, float* __restrict__ dW, const BiasGrad bias) {
     constexpr int COLS = 256 / PARTS;
-    __shared__ f32x4 red[PARTS > 1 ? 256 : 1];
+    __shared__ f32x4 red[kBiasLds / 4];
+    const int block = final_pass_block<256>(bias, reinterpret_cast<float*>(red));
+    if (block < 0) return;
     const int col = threadIdx.x % COLS, part = threadIdx.x / COLS;
-    const int64_t id = (static_cast<int64_t>(blockIdx.x) * COLS + col) * 4;
+    const int64_t id = (static_cast<int64_t>(block) * COLS + col) * 4;
     f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
     if (id < n) {
 #pragma unroll 8
@@ -576,7 +579,8 @@ static int32_t launch_taps(const TapsArgs& a, hipStream_t st) {
     return launch_status();
 }
 
-int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipStream_t st) {
+int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, bool* bias_done, hipStream_t st) {
+    *bias_done = false;
     TapsArgs a;
     a.X = w.X; a.dY = w.dY; a.dW = w.dW; a.partial = w.partial; a.beta = w.beta;
     a.H = w.H; a.W = w.W; a.C = w.C; a.O = w.O; a.S = w.S; a.P = w.P; a.Q = w.Q; a.N = w.N; a.RS = w.R * w.S; a.o_real = w.o_real;
@@ -601,10 +605,14 @@ int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipSt
     else return TWN_ERR_UNSUPPORTED;
     if (rc != TWN_OK || pl.splits == 1) return rc;
     const int64_t row = static_cast<int64_t>(w.C) * a.RS, n = row * w.o_real, pitch = row * w.O;       // multiples of 8
+    const BiasGrad bias = bias_in_final_pass(w);
+    *bias_done = bias.blocks > 0;
     if (pl.splits >= 32 && n / 4 < 256 * 256)
-        weight_grad_sum_kernel<8><<<static_cast<unsigned>((n / 4 + 31) / 32), 256, 0, st>>>(w.partial, pl.splits, pitch, n, w.beta, w.dW);
+        weight_grad_sum_kernel<8><<<static_cast<unsigned>((n / 4 + 31) / 32 + bias.blocks), 256, 0, st>>>(w.partial, pl.splits, pitch, n, w.beta,
+                                                                                                          w.dW, bias);
     else
-        weight_grad_sum_kernel<1><<<static_cast<unsigned>((n / 4 + 255) / 256), 256, 0, st>>>(w.partial, pl.splits, pitch, n, w.beta, w.dW);
+        weight_grad_sum_kernel<1><<<static_cast<unsigned>((n / 4 + 255) / 256 + bias.blocks), 256, 0, st>>>(w.partial, pl.splits, pitch, n,
+                                                                                                            w.beta, w.dW, bias);
     return launch_status();
 }
 

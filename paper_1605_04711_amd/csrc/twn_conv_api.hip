@@ -782,9 +782,10 @@ static int32_t bwd_run(const twn_conv_desc* d, int P, int Q, const void* X, cons
         const FirstGradPlan f = small && aligned(X, 4) && aligned(dY, 16) ? first_grad_plan(d, P, Q) : FirstGradPlan{};
         if (f.use && workspace_bytes >= first_grad_bytes(d, f)) {
             rc = launch_first_weight_grad(taps_shape(d, P, Q), d->pad_h, d->pad_w, f, w.X, w.dY, w.partial, st);
+            const BiasGrad bias = bias_in_final_pass(w);
             if (rc == TWN_OK)
-                rc = launch_first_weight_grad_sum(w.partial, f.splits, d->O, o_real, d->C, d->R, d->S, 4 * f.G, dW_beta, dW, st);
-            if (rc != TWN_OK || !dbias) return rc;
+                rc = launch_first_weight_grad_sum(w.partial, f.splits, d->O, o_real, d->C, d->R, d->S, 4 * f.G, dW_beta, dW, bias, st);
+            if (rc != TWN_OK || !dbias || bias.blocks > 0) return rc;
             w.dW = nullptr;                 // the bias gradient is left
         } else if (small) {
             // first-layer mode: gather from the zero-bordered 4-channel copy (rebuilt here: the call is stateless)

@@ -180,6 +180,18 @@ struct WeightGrad {
     int32_t o_real;         // filters of dW (O, or fewer where dY is padded)
 };
 
+// Bias gradient of a call, cut into groups of channels: `blocks` leading blocks of a final pass over dW's partial tiles, or a launch
+// of its own (blocks = 0 in the final pass).
+struct BiasGrad {
+    const uint16_t* dY;
+    float* dbias;
+    int64_t pixels;
+    int32_t O, vec;         // channels; 8 or 1 per load
+    int32_t chunks_per_group, groups, blocks;
+};
+// Empty (blocks = 0) unless one launch sums all pixels, which needs no partial sums.
+BiasGrad bias_in_final_pass(const WeightGrad& w);
+
 // How the weight gradient of one layer is cut up; a pure function of the shapes, shared by the
 // workspace query and the launch.
 struct WgPlan {
@@ -217,7 +229,8 @@ struct WgRoute {
     int32_t splits;             // ranges of the kernel in use
 };
 WgRoute route_weight_grad(const WgShape& w, bool first);
-int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, hipStream_t st);
+// *bias_done: the final pass summed dbias too.
+int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, bool* bias_done, hipStream_t st);
 
 // Weight gradient of a three-channel first layer (twn_bwd_first.hip): partial tiles [splits][O][(r*G + s/4)*16 + (s%4)*4 + c],
 // i.e. those of the first-layer mode above with pad_sp = 4 G.
@@ -229,8 +242,8 @@ struct FirstGradPlan {
 FirstGradPlan plan_first_weight_grad(const WgShape& w);
 int32_t launch_first_weight_grad(const WgShape& w, int32_t ph, int32_t pw, const FirstGradPlan& p, const uint16_t* X,
                                  const uint16_t* dY, float* partial, hipStream_t st);
-// dW = beta*dW + sum of partial tiles in first-layer mode.
+// dW = beta*dW + sum of partial tiles in first-layer mode, and dbias where `bias` is not empty.
 int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t o_real, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
-                                     float beta, float* dW, hipStream_t st);
+                                     float beta, float* dW, const BiasGrad& bias, hipStream_t st);
 
 }  // namespace twn
