@@ -98,8 +98,9 @@ __device__ __forceinline__ void bias_grad_group(const BiasGrad& b, int group, in
 // The first b.blocks blocks of a final pass sum dbias, all pixels of a group each: its result in the block's place among the
 // others, or -1 after a bias gradient.  Their own launch costs 4-5 us behind the final pass, which leaves most of the chip idle
 // in layers of few pixels (us of a forward and backward: 3565 pixels, 40 -> 72 channels 5x5/2 37.1 -> 34.7).
-template <int THREADS>
+template <int THREADS, bool BIAS>
 __device__ __forceinline__ int final_pass_block(const BiasGrad& b, float* __restrict__ red) {
+    if constexpr (!BIAS) return static_cast<int>(blockIdx.x);
     const int block = static_cast<int>(blockIdx.x) - b.blocks;
     if (block >= 0) return block;
     for (int group = blockIdx.x; group < b.groups; group += b.blocks) {
@@ -107,6 +108,13 @@ __device__ __forceinline__ int final_pass_block(const BiasGrad& b, float* __rest
         else bias_grad_group<1, THREADS>(b, group, 0, b.pixels, b.dbias, red);
     }
     return -1;
+}
+
+// One final pass of `blocks` blocks, with those of the bias gradient in front where there is one.
+template <typename... Params, typename... Args>
+void launch_final_pass(void (*plain)(Params...), void (*with_bias)(Params...), int64_t blocks, int threads, const BiasGrad& bias, hipStream_t st,
+                       Args... args) {
+    (bias.blocks > 0 ? with_bias : plain)<<<static_cast<unsigned>(blocks + bias.blocks), threads, 0, st>>>(args..., bias);
 }
 
 }  // namespace twn

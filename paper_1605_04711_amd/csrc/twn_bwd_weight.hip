@@ -696,13 +696,15 @@ __global__ __launch_bounds__(256 * KS, 2) void weight_grad_patch_kernel(const WG
 // each sum every WAVES-th split with several loads in flight, and their sums are combined in a fixed
 // order; the small output is scattered.  VEC = 4 needs the tile size O*J to be a multiple of 4.  Sixteen waves where few
 // blocks share many splits (128 filters, 48 columns, 128 splits: 6.6 -> 4.8 us).
-template <int VEC, int WAVES>
+// BIAS: the leading blocks sum dbias; passes without one keep the LDS, registers and code they need (16 KB a block
+// and the code in front cost dW alone 1.3 us: 1554 pixels, 256 -> 512 channels 3x3/2 21.8 us, so 20.3).
+template <int VEC, int WAVES, bool BIAS>
 __global__ __launch_bounds__(64 * WAVES) void weight_grad_reduce_kernel(const float* __restrict__ partial, int splits,
                                                                  int O, int o_real, int C, int R, int S, int pad_sp, float beta,
                                                                  float* __restrict__ dW, const BiasGrad bias) {
     static_assert(WAVES * 64 * VEC <= kBiasLds, "a bias gradient's rows and the waves' sums share the space");
-    __shared__ float red_all[kBiasLds];
-    const int block = final_pass_block<64 * WAVES>(bias, red_all);
+    __shared__ float red_all[BIAS ? kBiasLds : WAVES * 64 * VEC];
+    const int block = final_pass_block<64 * WAVES, BIAS>(bias, red_all);
     if (block < 0) return;
     float (*red)[64 * VEC] = reinterpret_cast<float (*)[64 * VEC]>(red_all);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -762,12 +764,13 @@ __global__ __launch_bounds__(64 * WAVES) void weight_grad_reduce_kernel(const fl
 // every split (float4 per lane, several splits in flight, summed in split order), transposes the R*S x 64
 // sums through LDS and writes dW[o][c0..c0+63][:][:] as ONE contiguous run of 64*R*S floats.
 constexpr int kReduceRowsMaxTaps = 25;
+template <bool BIAS>
 __global__ __launch_bounds__(256) void weight_grad_reduce_rows_kernel(const float* __restrict__ partial, int splits,
                                                                       int O, int C, int RS, float beta,
                                                                       float* __restrict__ dW, const BiasGrad bias) {
     static_assert(64 * kReduceRowsMaxTaps <= kBiasLds, "a bias gradient's rows and the transposed sums share the space");
-    __shared__ float tile[kBiasLds];                     // [channel][tap]
-    const int block = final_pass_block<256>(bias, tile);
+    __shared__ float tile[BIAS ? kBiasLds : 64 * kReduceRowsMaxTaps];                     // [channel][tap]
+    const int block = final_pass_block<256, BIAS>(bias, tile);
     if (block < 0) return;
     const int cchunks = C / 64;
     const int o = block / cchunks, c0 = (block % cchunks) * 64;
@@ -888,6 +891,18 @@ static void launch_bias_grad(const WeightGrad& w, hipStream_t st) {
     if (splits > 1)
         bias_grad_final_kernel<<<static_cast<unsigned>(blocks < (1 << 20) ? blocks : (1 << 20)), 1024, 0, st>>>(
             w.partial, static_cast<int>(splits), b.O, w.dbias);
+}
+
+// A final pass over four sums per thread: sixteen waves a block where there are many ranges and few sums.
+static void launch_reduce4(const float* partial, int32_t splits, int32_t O, int32_t o_real, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
+                           int64_t total, float beta, float* dW, const BiasGrad& bias, hipStream_t st) {
+    const int64_t blocks = (total + 255) / 256;
+    if (splits >= 64 && total < 256 * 256)
+        launch_final_pass(weight_grad_reduce_kernel<4, 16, false>, weight_grad_reduce_kernel<4, 16, true>, blocks, 1024, bias, st, partial, splits,
+                          O, o_real, C, R, S, pad_sp, beta, dW);
+    else
+        launch_final_pass(weight_grad_reduce_kernel<4, 4, false>, weight_grad_reduce_kernel<4, 4, true>, blocks, 256, bias, st, partial, splits,
+                          O, o_real, C, R, S, pad_sp, beta, dW);
 }
 
 static int32_t choose_splits(int64_t tiles, int64_t slabs, int ks = 1) {
@@ -1045,17 +1060,13 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
             // whole rows up to 16 ranges (us of both launches, rows / scattered floats: 588 pixels, 256 -> 512 channels 3x3/2, 3
             // ranges 19.6 / 25.3; 3136, the same, 6 ranges 27.6 / 32.2; 12544, 128 -> 256, 24 ranges 27.6 / 25.3)
             if (!w.pad_sp && w.C % 64 == 0 && RS > 1 && RS <= kReduceRowsMaxTaps && splits <= env_int(Env::WG_ROWS_SPLITS, 16))
-                weight_grad_reduce_rows_kernel<<<static_cast<unsigned>(w.o_real * (w.C / 64) + bias.blocks), 256, 0, st>>>(
-                    w.partial, splits, w.O, w.C, RS, w.beta, w.dW, bias);
-            else if (total % 4 == 0 && splits >= 64 && total < 256 * 256)
-                weight_grad_reduce_kernel<4, 16><<<static_cast<unsigned>((total + 255) / 256 + bias.blocks), 1024, 0, st>>>(
-                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW, bias);
+                launch_final_pass(weight_grad_reduce_rows_kernel<false>, weight_grad_reduce_rows_kernel<true>,
+                                  static_cast<int64_t>(w.o_real) * (w.C / 64), 256, bias, st, w.partial, splits, w.O, w.C, RS, w.beta, w.dW);
             else if (total % 4 == 0)
-                weight_grad_reduce_kernel<4, 4><<<static_cast<unsigned>((total + 255) / 256 + bias.blocks), 256, 0, st>>>(
-                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW, bias);
+                launch_reduce4(w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, total, w.beta, w.dW, bias, st);
             else
-                weight_grad_reduce_kernel<1, 4><<<static_cast<unsigned>((total + 63) / 64 + bias.blocks), 256, 0, st>>>(
-                    w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW, bias);
+                launch_final_pass(weight_grad_reduce_kernel<1, 4, false>, weight_grad_reduce_kernel<1, 4, true>, (total + 63) / 64, 256, bias, st,
+                                  w.partial, splits, w.O, w.o_real, C, w.R, S, w.pad_sp, w.beta, w.dW);
         }
     }
     // the partial tiles of dW have been read: their space serves the partial sums of dbias too
@@ -1066,11 +1077,7 @@ int32_t launch_weight_grad(const WeightGrad& w, hipStream_t st) {
 int32_t launch_first_weight_grad_sum(const float* partial, int32_t splits, int32_t O, int32_t o_real, int32_t C, int32_t R, int32_t S, int32_t pad_sp,
                                      float beta, float* dW, const BiasGrad& bias, hipStream_t st) {
     const int64_t total = static_cast<int64_t>(O) * R * pad_sp * 4;
-    const unsigned blocks = static_cast<unsigned>((total + 255) / 256 + bias.blocks);
-    if (splits >= 64 && total < 256 * 256)
-        weight_grad_reduce_kernel<4, 16><<<blocks, 1024, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW, bias);
-    else
-        weight_grad_reduce_kernel<4, 4><<<blocks, 256, 0, st>>>(partial, splits, O, o_real, C, R, S, pad_sp, beta, dW, bias);
+    launch_reduce4(partial, splits, O, o_real, C, R, S, pad_sp, total, beta, dW, bias, st);
     return launch_status();
 }
 

@@ -380,12 +380,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void weight_grad_taps_kernel(const 
 // dW = beta*dW + sum over ranges of the first n elements of partial[range], `pitch` elements apart, element by element.  PARTS threads share the ranges of four elements (every
 // PARTS-th each, then their sums in order): with one, a bank of 64 x 64 filters is 36 workgroups that read 224 ranges one
 // after the other (8.8 us; with eight 5.3).
-template <int PARTS>
+template <int PARTS, bool BIAS>
 __global__ __launch_bounds__(256) void weight_grad_sum_kernel(const float* __restrict__ partial, int splits, int64_t pitch, int64_t n,
                                                               float beta, float* __restrict__ dW, const BiasGrad bias) {
     constexpr int COLS = 256 / PARTS;
-    __shared__ f32x4 red[kBiasLds / 4];
-    const int block = final_pass_block<256>(bias, reinterpret_cast<float*>(red));
+    __shared__ f32x4 red[BIAS ? kBiasLds / 4 : PARTS > 1 ? 256 : 1];
+    const int block = final_pass_block<256, BIAS>(bias, reinterpret_cast<float*>(red));
     if (block < 0) return;
     const int col = threadIdx.x % COLS, part = threadIdx.x / COLS;
     const int64_t id = (static_cast<int64_t>(block) * COLS + col) * 4;
@@ -608,11 +608,11 @@ int32_t launch_weight_grad_taps(const WeightGrad& w, const WgTapsPlan& pl, bool*
     const BiasGrad bias = bias_in_final_pass(w);
     *bias_done = bias.blocks > 0;
     if (pl.splits >= 32 && n / 4 < 256 * 256)
-        weight_grad_sum_kernel<8><<<static_cast<unsigned>((n / 4 + 31) / 32 + bias.blocks), 256, 0, st>>>(w.partial, pl.splits, pitch, n, w.beta,
-                                                                                                          w.dW, bias);
+        launch_final_pass(weight_grad_sum_kernel<8, false>, weight_grad_sum_kernel<8, true>, (n / 4 + 31) / 32, 256, bias, st, w.partial, pl.splits,
+                          pitch, n, w.beta, w.dW);
     else
-        weight_grad_sum_kernel<1><<<static_cast<unsigned>((n / 4 + 255) / 256 + bias.blocks), 256, 0, st>>>(w.partial, pl.splits, pitch, n,
-                                                                                                            w.beta, w.dW, bias);
+        launch_final_pass(weight_grad_sum_kernel<1, false>, weight_grad_sum_kernel<1, true>, (n / 4 + 255) / 256, 256, bias, st, w.partial, pl.splits,
+                          pitch, n, w.beta, w.dW);
     return launch_status();
 }
 
