@@ -608,11 +608,13 @@ int32_t launch_conv_stream(const GatherGemm& g, int tile, hipStream_t st) {
     // workgroups of four waves did (VGG-16 conv5-7: 5-8 % faster).  128x64 tiles (64 output channels) gain while a CU has one or two
     // of them and K is long (us, without -> with: 211 tiles, K = 4608 38.7 -> 31.5; 256, 12800 112 -> 73; 392, 2304 25.7 -> 24.4;
     // 586, 1152 17.8 -> 18.3; 1568, 1152 40.9 -> 44.0).
-    // TWN_STREAM_PC: 0 = never, 4 = wherever a build exists, unset = this rule.  K groups exist without load waves only.
+    // TWN_STREAM_PC: 0 = never, 4 = wherever a build exists, unset = this rule.  K groups exist without load waves only: asked for by
+    // TWN_STREAM_KS on a tile that has them (14, 15, 16), they run unless TWN_STREAM_PC asks for load waves.
     int np = env_int(Env::STREAM_PC, -1);
     if (np < 0) {
         const bool few = tile == 16 && ((g.M + 127) / 128) * ((g.NC + 63) / 64) <= 512 && g.K >= 1024;
-        np = (tile == 14 || tile == 15 || tile == 17 || tile == 18 || few) ? 4 : 0;
+        const bool groups = ks > 1 && (tile == 14 || tile == 15 || tile == 16);
+        np = !groups && (tile == 14 || tile == 15 || tile == 17 || tile == 18 || few) ? 4 : 0;
     }
     if (np > 0) {
         const int32_t rc = launch_conv_stream_pc(g, tile, np, env_int(Env::STREAM_PC_STAGES, 4), st);

@@ -52,7 +52,7 @@ SMALL = [dict(fn="gemm", d=gemm(64, 1000, 512)), dict(fn="conv", d=conv(1, 14, 1
     ("TWN_BUFLOAD", 0, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", "gather_gemm_dma_batch_kernel", "weight_grad_patch_kernel"]),
     ("TWN_STREAM_PC", 0, ["conv_stream_kernel", "gather_gemm_dma_kernel", None, None]),
     ("TWN_STREAM_PC_STAGES", 4, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", None, None]),
-    ("TWN_STREAM_KS", 2, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", None, None]),
+    ("TWN_STREAM_KS", 2, ["conv_stream_kernel", "gather_gemm_dma_kernel", None, None]),
     ("TWN_STREAM_OCC", 1, ["conv_stream_pc_kernel", "gather_gemm_dma_kernel", None, None]),
     ("TWN_WG_KS", 1, [None, None, None, "weight_grad_patch_kernel"]),
     ("TWN_WG_BLOCKS", 256, [None, None, None, "weight_grad_patch_kernel"]),
@@ -256,14 +256,30 @@ def test_first_layers_run_with_the_workspace_of_the_general_kernel():
 WIDE = [conv(16, 56, 56, 128, 128, 3), conv(32, 32, 32, 256, 256, 3), conv(16, 56, 56, 512, 128, 1)]
 
 
-@pytest.mark.parametrize("name,value", [("TWN_STREAM_PC_STAGES", 3), ("TWN_STREAM_PC_STAGES", 4), ("TWN_STREAM_PC", 0), ("TWN_STREAM_PC", 2),
-                                        ("TWN_STREAM_KS", 2), ("TWN_STREAM_OCC", 1), ("TWN_STREAM", 0), ("TWN_BUFLOAD", 0)])
-def test_overrides_of_the_persistent_kernels_run_where_wide_tiles_would(name, value):
+# the kernel that answers each override where the three shapes would take wide tiles; K groups are its last template argument
+@pytest.mark.parametrize("name,value,kernel,groups", [
+    ("TWN_STREAM_PC_STAGES", 3, "conv_stream_kernel", "1"), ("TWN_STREAM_PC_STAGES", 4, "conv_stream_pc_kernel", None),
+    ("TWN_STREAM_PC", 0, "conv_stream_kernel", "1"), ("TWN_STREAM_PC", 4, "conv_stream_pc_kernel", None),
+    ("TWN_STREAM_KS", 1, "conv_stream_pc_kernel", None), ("TWN_STREAM_KS", 2, "conv_stream_kernel", "2"),
+    ("TWN_STREAM_OCC", 1, "conv_stream_pc_kernel", None), ("TWN_STREAM", 0, "gather_gemm_dma_kernel", None),
+    ("TWN_BUFLOAD", 0, "conv_stream_pc_kernel", None)])
+def test_overrides_of_the_persistent_kernels_run_where_wide_tiles_would(name, value, kernel, groups):
     plain = launches([dict(fn="conv", d=d) for d in WIDE])
     assert [kernels(a) + a["launches"][0]["args"][:2] for a in plain] == [["conv_stream_pc_kernel", m, n] for m, n in
                                                                           (("256", "128"), ("128", "256"), ("128", "128"))]
     for a in launches([dict(fn="conv", d=d, env={name: value}) for d in WIDE]):
-        assert len(kernels(a)) == 1
+        assert kernels(a) == [kernel]
+        assert groups is None or a["launches"][0]["args"][-1] == groups
+
+
+def test_k_groups_that_are_asked_for():
+    """TWN_STREAM_KS on every tile that has K groups, also where load waves are the rule; TWN_STREAM_PC asks for those all the same."""
+    d = conv(16, 14, 14, 512, 512, 3)
+    for tile, ks in ((14, 2), (14, 4), (15, 2), (16, 2)):
+        (a,) = launches([dict(fn="conv", d=d, env={"TWN_TILE": tile, "TWN_STREAM_KS": ks})])
+        assert kernels(a) == ["conv_stream_kernel"] and a["launches"][0]["args"][-1] == str(ks)
+        (a,) = launches([dict(fn="conv", d=d, env={"TWN_TILE": tile, "TWN_STREAM_KS": ks, "TWN_STREAM_PC": 4})])
+        assert kernels(a) == ["conv_stream_pc_kernel"]
 
 
 def test_short_float32_kernel_leaves_paddings_that_pass_its_sentinel():
