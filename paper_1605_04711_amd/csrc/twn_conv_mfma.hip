@@ -452,8 +452,9 @@ __device__ __forceinline__ void scale_body(const DxPrep& p, int64_t block) {
 }
 
 // Codes of the taps r = r0 + jr*sh, s = s0 + js*sw of class k, gathered from the transposed copy into a contiguous K range:
-// K order (jr, js, term, o).  Filter counts that are multiples of 8: half a word at a time, which lies in one tap; field by field otherwise
-// (with 64-bit divisions a word of 72 filters took sixteen of each kind: 5x45x61 pixels, 72 filters 5x5/2 over 40 channels 7.8 -> 3.8 us).
+// K order (jr, js, term, o).  Filter counts that are multiples of 16: a word lies in one tap; multiples of 8: half a word does; field by
+// field otherwise (with 64-bit divisions a word of 72 filters took sixteen of each kind: 5x45x61 pixels, 72 filters 5x5/2 over 40
+// channels 7.8 -> 3.8 us).
 __device__ __forceinline__ void class_codes_body(const DxPrep& p, int64_t block) {
     const int64_t id = block * 256 + threadIdx.x;
     const DxClassTable& tb = p.tb;
@@ -468,6 +469,7 @@ __device__ __forceinline__ void class_codes_body(const DxPrep& p, int64_t block)
         const uint32_t c = fdiv_u(static_cast<uint32_t>(local), p.divW[k]);
         const int j = static_cast<int>(static_cast<uint32_t>(local) - c * static_cast<uint32_t>(wpr));
         const uint32_t* row = p.packed_T + static_cast<int64_t>(c) * p.wprT;
+        const bool whole = p.O % 16 == 0;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int k2 = j * 16 + h * 8, tap = static_cast<int>(fdiv_u(static_cast<uint32_t>(k2), p.divTap));
@@ -476,26 +478,25 @@ __device__ __forceinline__ void class_codes_body(const DxPrep& p, int64_t block)
             if (o >= p.O) o -= p.O;
             const int tr = static_cast<int>(fdiv_u(static_cast<uint32_t>(tap), p.divNs[k])), ts = tap - tr * tb.ns[k];
             const int src = ((tb.r0[k] + tr * tb.sh) * p.S + tb.s0[k] + ts * tb.sw) * p.O + o;
+            const uint32_t codes = row[src >> 4];
+            if (whole) {
+                word = codes;
+                break;
+            }
             // eight codes are eight bits of each half-word
-            word |= ((row[src >> 4] >> (src & 8)) & 0x00FF00FFu) << (h * 8);
+            word |= ((codes >> (src & 8)) & 0x00FF00FFu) << (h * 8);
         }
         p.codes[id] = word;
         return;
     }
     const int c = static_cast<int>(local / wpr), j = static_cast<int>(local % wpr);
     const uint32_t* row = p.packed_T + static_cast<int64_t>(c) * p.wprT;
-    auto source_tap = [&](int tap) { return (tb.r0[k] + (tap / tb.ns[k]) * tb.sh) * p.S + tb.s0[k] + (tap % tb.ns[k]) * tb.sw; };
-    if (p.O % 16 == 0) {
-        const int tap = j * 16 / per_tap;
-        if (tap < taps) word = row[(source_tap(tap) * p.O + (j * 16 - tap * per_tap) % p.O) >> 4];
-    } else {
-        for (int t = 0; t < 16; ++t) {
-            const int k2 = j * 16 + t, tap = k2 / per_tap;
-            if (tap >= taps) break;
-            const int src = source_tap(tap) * p.O + (k2 - tap * per_tap) % p.O;
-            const int ts = src & 15;
-            word |= ((row[src >> 4] >> ((ts & 1) * 16 + (ts >> 1) * 2)) & 3u) << ((t & 1) * 16 + (t >> 1) * 2);
-        }
+    for (int t = 0; t < 16; ++t) {
+        const int k2 = j * 16 + t, tap = k2 / per_tap;
+        if (tap >= taps) break;
+        const int src = ((tb.r0[k] + (tap / tb.ns[k]) * tb.sh) * p.S + tb.s0[k] + (tap % tb.ns[k]) * tb.sw) * p.O + (k2 - tap * per_tap) % p.O;
+        const int ts = src & 15;
+        word |= ((row[src >> 4] >> ((ts & 1) * 16 + (ts >> 1) * 2)) & 3u) << ((t & 1) * 16 + (t >> 1) * 2);
     }
     p.codes[id] = word;
 }
