@@ -34,20 +34,22 @@ struct TernWorkspace {
 constexpr int kTickets = 17, kTicketStep = 16;
 constexpr int kMaxPass1 = kMaxBlocks - kTickets * kTicketStep;
 
-// This thread's elements of the ragged chunk that starts at `base`, zeros behind the last one.
+// This thread's whole float4s of the ragged chunk that starts at `base`, zeros behind the last one.  The at most three weights behind
+// all float4s are taken one by one by the thread that would own their float4, after its others.  Element by element in all threads,
+// and with a branch per element around every load, the code alone was up to 1.1 us of an update of few weights (16x16: 4.1, so 2.8).
 __device__ __forceinline__ void load_tail(const float* __restrict__ p, int64_t base, int64_t n, float4* v) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int64_t idx = base + static_cast<int64_t>(j * kTernThreads + threadIdx.x) * 4;
-        if (idx + 3 < n) {
-            v[j] = *reinterpret_cast<const float4*>(p + idx);
-        } else {
-            v[j].x = idx < n ? p[idx] : 0.0f;
-            v[j].y = idx + 1 < n ? p[idx + 1] : 0.0f;
-            v[j].z = idx + 2 < n ? p[idx + 2] : 0.0f;
-            v[j].w = 0.0f;
-        }
+        v[j] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (idx + 3 < n) v[j] = *reinterpret_cast<const float4*>(p + idx);
     }
+}
+__device__ __forceinline__ bool owns_last(int64_t n) { return static_cast<int>(threadIdx.x) == static_cast<int>(n / 4 % kTernThreads); }
+
+// The block that takes the ragged chunk behind `nfull` whole ones: fewer than 2^28 chunks, as tensors have fewer than 2^40 weights.
+__device__ __forceinline__ int tail_block(int64_t nfull, int nblk) {
+    return static_cast<int>(static_cast<uint32_t>(nfull) % static_cast<uint32_t>(nblk));
 }
 
 // Pass 1 of block `bid` out of `nblk` cooperating blocks: float64 partial sum of |W| -> partial[bid].
@@ -85,7 +87,7 @@ __device__ __forceinline__ void abs_sum_body(const float* __restrict__ W, int64_
     }
     // ragged tail (at most one chunk), taken by one block after its full chunks; element by element behind bounds tests it was
     // sixteen memory latencies.  Requested before the full chunks it would keep 16 registers more alive in all blocks.
-    if (nfull * kChunk < n && static_cast<int64_t>(bid) == nfull % nblk) {
+    if (nfull * kChunk < n && bid == tail_block(nfull, nblk)) {
         load_tail(W, nfull * kChunk, n, cur);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -94,6 +96,8 @@ __device__ __forceinline__ void abs_sum_body(const float* __restrict__ W, int64_
             acc += static_cast<double>(fabsf(cur[j].z));
             acc += static_cast<double>(fabsf(cur[j].w));
         }
+        if (owns_last(n))
+            for (int64_t idx = n & ~static_cast<int64_t>(3); idx < n; ++idx) acc += static_cast<double>(fabsf(W[idx]));
     }
     const double total = block_sum(acc, scratch);
     if (tid == 0) partial[bid] = total;
@@ -408,7 +412,7 @@ __global__ __launch_bounds__(kTernThreads) void band_pack_kernel(const float* __
         c = nx;
     }
     // ragged tail, taken by the block abs_sum_body gives it to
-    if (nfull * kChunk < n && static_cast<int64_t>(bid) == nfull % nblk) {
+    if (nfull * kChunk < n && bid == tail_block(nfull, nblk)) {
         const float4* src = reinterpret_cast<const float4*>(W);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -1363,7 +1367,7 @@ __global__ __launch_bounds__(kTernThreads) void sgd_update_kernel(float* __restr
         c = nx;
     }
     // ragged tail (at most one chunk), taken by the block abs_sum_body gives it to, in its element order
-    if (nfull * kChunk < n && static_cast<int64_t>(bid) == nfull % nblk) {
+    if (nfull * kChunk < n && bid == tail_block(nfull, nblk)) {
         const int64_t base = nfull * kChunk;
         load_tail(W, base, n, w4);
         load_tail(V, base, n, v4);
@@ -1371,23 +1375,22 @@ __global__ __launch_bounds__(kTernThreads) void sgd_update_kernel(float* __restr
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int64_t idx = base + static_cast<int64_t>(j * kTernThreads + tid) * 4;
-            if (idx < n) update(w4[j].x, v4[j].x, g4[j].x);
-            if (idx + 1 < n) update(w4[j].y, v4[j].y, g4[j].y);
-            if (idx + 2 < n) update(w4[j].z, v4[j].z, g4[j].z);
-            if (idx + 3 < n) update(w4[j].w, v4[j].w, g4[j].w);
             if (idx + 3 < n) {
+                update(w4[j].x, v4[j].x, g4[j].x);
+                update(w4[j].y, v4[j].y, g4[j].y);
+                update(w4[j].z, v4[j].z, g4[j].z);
+                update(w4[j].w, v4[j].w, g4[j].w);
                 *reinterpret_cast<float4*>(W + idx) = w4[j];
                 *reinterpret_cast<float4*>(V + idx) = v4[j];
-            } else {
-                const float we[3] = {w4[j].x, w4[j].y, w4[j].z}, ve[3] = {v4[j].x, v4[j].y, v4[j].z};
-#pragma unroll
-                for (int e = 0; e < 3; ++e)
-                    if (idx + e < n) {
-                        W[idx + e] = we[e];
-                        V[idx + e] = ve[e];
-                    }
             }
         }
+        if (owns_last(n))
+            for (int64_t idx = n & ~static_cast<int64_t>(3); idx < n; ++idx) {
+                float w = W[idx], v = V[idx];
+                update(w, v, dW[idx]);
+                W[idx] = w;
+                V[idx] = v;
+            }
     }
     const double total = block_sum(acc, scratch);
     if (partial && tid == 0) partial[bid] = total;
