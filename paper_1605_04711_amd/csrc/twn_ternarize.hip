@@ -517,22 +517,30 @@ __global__ __launch_bounds__(kTernThreads) void band_fix_kernel(const float* __r
 // k = rs*rows + o in the transposed one.  One division per word, then all sixteen loads are requested (bit t of the result:
 // weight t exists; the others read the tensor's first one).  With a 64-bit division and a wait per weight a
 // call was (us) 19 instead of 13 for 300 x 200 x 3 x 3, 91 instead of 59 for 3333 x 5008.
+// `paced`: one load at a time.  Weights that follow one another in a word are taps apart in memory, and a cache line is used by the words
+// of several taps, which other waves form at about the same time: that is one sixteenth of the tensor while all waves stand at the
+// same weight, and the whole tensor with sixteen loads each, which no L2 holds from about 6 MB on.  From 16 taps, i.e. half a line, and 3*2^19
+// weights on (us, all at once / paced): 1948x80x5x5 55.9 / 43.6, 1622x68x5x5 44.4 / 38.3, 4680x19x5x5 36.3 / 30.3, but 357x29x5x5
+// 10.7 / 14.1, 700x120x4x4 17.9 / 19.3, 2000x700x3x3 113 / 203.
 template <bool TRANSPOSED>
-__device__ __forceinline__ uint32_t gather_word(const float* __restrict__ W, int rows, int C, int RS, int row, int j,
+__device__ __forceinline__ uint32_t gather_word(const float* __restrict__ W, int rows, int C, int RS, int row, int j, bool paced,
                                                 float (&w)[16]) {
     const uint32_t len = static_cast<uint32_t>(TRANSPOSED ? rows : C), k0 = static_cast<uint32_t>(j) * 16u;
     uint32_t rs = k0 / len, i = k0 - rs * len;
     const int64_t step = TRANSPOSED ? static_cast<int64_t>(C) * RS : RS;
     const int64_t base = static_cast<int64_t>(row) * (TRANSPOSED ? RS : step * C);
+    int64_t at = base + i * step + rs;
     uint32_t real = 0;
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
         const bool ok = rs < static_cast<uint32_t>(RS);
         real |= ok ? 1u << t : 0u;
-        w[t] = W[ok ? base + i * step + rs : 0];
+        w[t] = W[ok ? at : 0];
+        if (t < 15 && paced) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const bool next = ++i == len;
         i = next ? 0u : i;
         rs += next ? 1u : 0u;
+        at = next ? base + rs : at + step;
     }
     return real;
 }
@@ -556,7 +564,7 @@ __device__ __forceinline__ void mask_pack_gather_body(
     const float delta = delta_from_partials(ws->p1, nb1, f, n, scratch);
     const int64_t words_n = only_transposed ? 0 : static_cast<int64_t>(rows) * wpr;
     const int64_t words_t = packed_T ? static_cast<int64_t>(C) * wprT : 0;
-    const bool narrow = words_n + words_t < (1LL << 31);
+    const bool narrow = words_n + words_t < (1LL << 31), paced = RS >= 16 && n >= (3 << 19);
     double acc = 0.0;
     uint32_t count = 0;
     for (int64_t id = static_cast<int64_t>(bid) * blockDim.x + threadIdx.x; id < words_n + words_t;
@@ -565,7 +573,7 @@ __device__ __forceinline__ void mask_pack_gather_body(
         uint32_t word = 0;
         if (id < words_n) {
             const int64_t o = word_quotient(id, wpr, narrow);
-            const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), w);
+            const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), paced, w);
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
                 const uint32_t fld = (real >> t & 1u) ? code_field(w[t], delta) : 0u;
@@ -578,7 +586,7 @@ __device__ __forceinline__ void mask_pack_gather_body(
         } else {
             const int64_t it = id - words_n, j = word_quotient(it, C, narrow);
             const int c = static_cast<int>(it - j * C);
-            const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), w);
+            const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), paced, w);
 #pragma unroll
             for (int t = 0; t < 16; ++t)
                 word |= ((real >> t & 1u) ? code_field(w[t], delta) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
@@ -1087,13 +1095,13 @@ __device__ __forceinline__ void pack_gather_body(
     int rows_per_group, uint32_t* __restrict__ out, int wpr, int transposed, int64_t id) {
     const int64_t words = static_cast<int64_t>(transposed ? C : rows) * wpr;
     if (id >= words) return;
-    const bool narrow = words < (1LL << 31);
+    const bool narrow = words < (1LL << 31), paced = false;
     float w[16];
     uint32_t word = 0;
     if (transposed) {
         const int64_t j = word_quotient(id, C, narrow);         // input channel, fastest across threads
         const int c = static_cast<int>(id - j * C);
-        const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), w);
+        const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), paced, w);
         // group of the word's first filter, and the filter's place in it
         const uint32_t per_group = static_cast<uint32_t>(rows_per_group), filters = static_cast<uint32_t>(rows);
         const uint32_t o0 = static_cast<uint32_t>(j) * 16u % filters;
@@ -1114,7 +1122,7 @@ __device__ __forceinline__ void pack_gather_body(
         return;
     }
     const int64_t o = word_quotient(id, wpr, narrow);
-    const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), w);
+    const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), paced, w);
     const float d = delta[static_cast<int>(o) / rows_per_group];
 #pragma unroll
     for (int t = 0; t < 16; ++t) word |= ((real >> t & 1u) ? code_field(w[t], d) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);

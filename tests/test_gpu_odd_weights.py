@@ -24,6 +24,12 @@ def test_words_across_taps(shape, groups):
     check_against_oracle(w, 0.7, groups=shape[0] if groups == "rows" else groups)
 
 
+@pytest.mark.parametrize("shape", [(1001, 63, 5, 5), (100300, 1, 4, 4)])
+def test_paced_words(shape):
+    """From 16 taps and 3 * 2^19 weights on the weights of a word are loaded one after the other."""
+    check_against_oracle(wl.normal(13, shape[1], shape, std=0.05), 0.7)
+
+
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 255, 1023, 1026, 4095, 4097, 8190, 12291])
 def test_last_chunk_of_update(n):
     w, v, dw = (wl.normal(13, i, (1, n), std=0.05) for i in (1, 2, 3))
