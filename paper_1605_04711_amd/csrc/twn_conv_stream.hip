@@ -23,6 +23,7 @@
 // loads of the buffer-descriptor path (plain GEMM with K % 64 == 0, or an undivided
 // convolution whose channel count is a multiple of 64; tensors below 2 GiB).  Every
 // other problem stays with gather_gemm_dma_kernel.
+#include <cstdlib>
 #include <mutex>
 
 #include "twn_kernels.h"
@@ -524,6 +525,10 @@ bool conv_stream_applicable(const GatherGemm& g) {
     } else {
         if (g.divh != 1 || g.divw != 1 || g.IC % 64 != 0 || g.xs % 8 != 0) return false;
         if (g.M % (static_cast<int64_t>(g.OH) * g.OW) != 0) return false;
+        // taps that span 2^30 rows or columns would bring the load waves' marks of 2^31 back into the image
+        if (static_cast<int64_t>(g.R - 1) * std::abs(static_cast<int64_t>(g.dh)) >= (1LL << 30) ||
+            static_cast<int64_t>(g.S - 1) * std::abs(static_cast<int64_t>(g.dw)) >= (1LL << 30))
+            return false;
     }
     if (!aligned(g.X, 16) || !aligned(g.Wq, 16) || !aligned(g.Y, 16) || (g.residual && !aligned(g.residual, 8))) return false;
     const int64_t in_rows = g.plain_gemm ? g.M : (g.M / (static_cast<int64_t>(g.OH) * g.OW)) * g.IH * g.IW;

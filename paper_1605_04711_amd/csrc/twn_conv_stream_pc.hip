@@ -15,7 +15,8 @@
 //
 // What a wave issues per slab is what bounds it.  A load wave that formed every address anew and fetched codes 16 bytes per
 // filter (64 cache lines touched by one load) took 400 cycles for three loads, against 256 of MFMA work in a slab of a 64x128
-// tile.  So the per-lane part of an address is formed once per filter tap (the channel slab travels in the scalar offset), and
+// tile.  So the per-lane part of an address is formed once per filter tap (the channel slab travels in the scalar offset), the rows of
+// a tap are tested once per row of taps, the scalar state advances by additions, and
 // codes come in chunks of CS slabs, CS*16 contiguous bytes per filter (16 or 32 lines per load, and lines of 128 bytes are fetched
 // from L2 that much less often); there are three chunk buffers, so that a chunk is requested together with the activations of its first
 // slab whatever the lengths of its neighbours at a tile's end.  In a compute wave, eight MFMAs alone take 265 cycles, with four
@@ -23,7 +24,9 @@
 // before, 317 otherwise: parts of two words alternate, and scalar work sits between MFMAs too.  All of it against the
 // kernel before (us, same bits): GEMM 8192x4096x4096 205 -> 195; 3x3 layers 180000 pixels, 256 -> 256 channels 164 -> 158;
 // 8192, 512 -> 512 36.4 -> 32.9; 12544, 256 -> 256 18.3 -> 17.5; 50176, 128 -> 128 17.8 -> 17.0; 3136, 512 -> 512 19.7 both
-// (one workgroup per CU: 480 cycles a slab, of which MFMAs are 256).
+// (one workgroup per CU).  Then, of a load wave's loop, the waits by nesting, one branch back per slab and 4 instead of 7 vector
+// instructions per load and tap (by instruction count alone: the same addresses formed behind the loads or between them were slower): 2303
+// pixels, 64 -> 512 channels 7x7 17.9 -> 15.0; 5x5 over 128 channels 16.1 -> 14.9; 3136, 512 -> 512 19.6 -> 19.0; 2303x512x3072 14.7 -> 13.9.
 //
 // DEEP (two MFMAs per step and wave): a step is 64 cycles, less than an LDS read takes.  Fragments lie in four sets and
 // are requested a step further ahead; all reads of a slab have landed when it ends.
@@ -77,10 +80,11 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     constexpr bool EPI_OWN = NWC * EPI_WAVE > STAGE_BYTES;      // output staging outside the pipeline stages
     static_assert(BM % 32 == 0 && BN % 64 == 0 && TN % 32 == 0 && TM % 32 == 0, "tile shape");
     static_assert(BM % (8 * NP) == 0 && BN % (CR * NP) == 0 && (CS == 2 || CS == 4), "whole loads for every load wave");
+    static_assert((STAGE_BYTES & (STAGE_BYTES - 1)) == 0, "the stages are walked by a mask");
     static_assert(STAGES == 4, "a chunk is requested three slabs ahead, and three buffers hold at least that much");
     static_assert(BN <= 64 * NWC, "one compute thread per column loads the column parameters");
     static_assert(MI <= 8 && NI <= 4, "fragment reads use immediate offsets");
-    static_assert(2 * (LX + LB) < 64, "vmcnt is a 6-bit counter");
+    static_assert(LB <= LX && LX + LB < 64, "waits of the load waves");
 
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     unsigned char* const codes = smem + STAGES * STAGE_BYTES;
@@ -105,7 +109,6 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
     auto tile_id = [&](uint32_t i) __attribute__((always_inline)) -> uint32_t { return start_x + j + i * gx; };
 
     const int KT = a.KT;
-    const uint32_t total = n_my * static_cast<uint32_t>(KT);
 
     if (wave >= NWC) {
         // =================================== load wave ===================================
@@ -119,7 +122,10 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         const int cq = (lane % CS) ^ ((lane / CS) / (16 / CS) % CS);
         uint32_t voff[LX];           // byte offset of the row (GEMM) / of tap (0,0) (convolution), wrapping where that lies outside
         uint32_t xcur[LX];           // ... of the present tap, kBufOutside where it lies outside the image
-        int ih0[LX], iw0[LX];
+        // row and column of tap (0,0); the column also kNowhere while the taps' row lies outside the image, and both where there is no
+        // pixel.  No tap brings kNowhere back (conv_stream_applicable).
+        uint32_t ih0[LX], iw0[LX], iw[LX];
+        constexpr uint32_t kNowhere = 0x80000000u;
         uint32_t coff[LB];
         auto tile_setup = [&](uint32_t t) __attribute__((always_inline)) {
             const uint32_t tm = fdiv_u(t, a.divTN);
@@ -141,8 +147,9 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
                     const uint32_t pix = (img * static_cast<uint32_t>(g.IH) + static_cast<uint32_t>(hh)) *
                                              static_cast<uint32_t>(g.IW) + static_cast<uint32_t>(ww);
                     voff[i] = (pix * static_cast<uint32_t>(g.xs) + static_cast<uint32_t>(kc * 8)) * 2u;
-                    ih0[i] = rv ? hh : -(1 << 28);
-                    iw0[i] = rv ? ww : -(1 << 28);
+                    ih0[i] = rv ? static_cast<uint32_t>(hh) : kNowhere;
+                    iw0[i] = static_cast<uint32_t>(ww);
+                    iw[i] = ih0[i] < static_cast<uint32_t>(g.IH) ? iw0[i] : kNowhere;
                 }
             }
 #pragma unroll
@@ -154,25 +161,25 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         };
         // the loads of this wave for stream position (tile lt, slab lk); returns how many they are
         uint32_t lt = 0;
-        int lk = 0, lc = 0, rr = 0, ss = 0;             // slab of the tile, channel slab of the tap, tap
-        int fill = 0, cb = 0;                           // stage and chunk buffer they go to
-        const int32_t strR = g.dh * g.IW * static_cast<int>(g.xs) * 2, strS = g.dw * static_cast<int>(g.xs) * 2;
+        int lk = 0, ss = 0;                             // slab of the tile, tap of its row
+        uint32_t soff = 0;                              // bytes of the tap's channels before the slab
+        uint32_t tap_h = 0, tap_w = 0, tap_off = 0;     // the tap's offset in rows, columns, bytes (wrapping, as above)
+        uint32_t fill = 0;                              // stage (bytes) and chunk buffer they go to
+        int cb = 0;
+        const uint32_t dh = static_cast<uint32_t>(g.dh), dw = static_cast<uint32_t>(g.dw);
+        const uint32_t strS = dw * static_cast<uint32_t>(g.xs) * 2u;
+        const uint32_t strR = dh * static_cast<uint32_t>(g.IW) * static_cast<uint32_t>(g.xs) * 2u - static_cast<uint32_t>(g.S) * strS;
+        const uint32_t tap_bytes = static_cast<uint32_t>(a.spt) * 128u;
         auto issue = [&]() __attribute__((always_inline)) -> int {
             if (lt >= n_my) return 0;
-            if (!GEMM && lc == 0) {
-                const int32_t delta = rr * strR + ss * strS;
-                const int dh = rr * g.dh, dw = ss * g.dw;
+            if (!GEMM && soff == 0) {
 #pragma unroll
-                for (int i = 0; i < LX; ++i) {
-                    const bool ok = (static_cast<unsigned>(ih0[i] + dh) < static_cast<unsigned>(g.IH)) &
-                                    (static_cast<unsigned>(iw0[i] + dw) < static_cast<unsigned>(g.IW));
-                    xcur[i] = ok ? voff[i] + static_cast<uint32_t>(delta) : kBufOutside;
-                }
+                for (int i = 0; i < LX; ++i)
+                    xcur[i] = iw[i] + tap_w < static_cast<uint32_t>(g.IW) ? voff[i] + tap_off : kBufOutside;
             }
 #pragma unroll
-            for (int i = 0; i < LX; ++i)
-                buf_dma16(rx, xcur[i], static_cast<uint32_t>(lc) * 128u, smem + fill * STAGE_BYTES + (p + NP * i) * 1024);
-            fill = (fill + 1 == STAGES) ? 0 : fill + 1;
+            for (int i = 0; i < LX; ++i) buf_dma16(rx, xcur[i], soff, smem + fill + (p + NP * i) * 1024);
+            fill = (fill + STAGE_BYTES) % (STAGES * STAGE_BYTES);
             int n = LX;
             if (lk % CS == 0) {
                 // slabs behind the last one are not read: at the last filter they would lie outside the tensor
@@ -184,26 +191,38 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
                 n += LB;
             }
             ++lk;
-            if (++lc == a.spt) {
-                lc = 0;
+            soff += 128u;
+            if (!GEMM && soff == tap_bytes) {
+                soff = 0;
+                tap_w += dw;
+                tap_off += strS;
                 if (++ss == g.S) {
                     ss = 0;
-                    ++rr;
+                    tap_w = 0;
+                    tap_h += dh;
+                    tap_off += strR;
+#pragma unroll
+                    for (int i = 0; i < LX; ++i) iw[i] = ih0[i] + tap_h < static_cast<uint32_t>(g.IH) ? iw0[i] : kNowhere;
                 }
             }
             if (lk == KT) {
-                lk = lc = rr = ss = 0;
+                lk = ss = 0;
+                soff = tap_h = tap_w = tap_off = 0;
                 if (++lt < n_my) tile_setup(tile_id(lt));
             }
             return n;
         };
-        // waits until at most n of this wave's loads are in flight (n: loads of at most two positions)
+        // Waits until no more of this wave's loads are in flight than n, the loads of the youngest position (LX, with codes LX + LB,
+        // none at the end) or of the youngest two (at least LX + LB).  A wave issues an instruction in four or five cycles at best
+        // and a taken branch costs several: what this loop executes per slab bounds a lone tile, so the waits are nested, the
+        // stricter ones behind the weaker.
         auto wait_loads = [&](int n) __attribute__((always_inline)) {
             asm volatile("" ::: "memory");
-            if (n == LX) __builtin_amdgcn_s_waitcnt(vmcnt_imm(LX));
-            else if (n == LX + LB) __builtin_amdgcn_s_waitcnt(vmcnt_imm(LX + LB));
-            else if (n >= 2 * LX) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LX));
-            else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(LX + LB));
+            if (n <= LX) {
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(LX));
+                if (n == 0) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            }
         };
 
         tile_setup(tile_id(0));
@@ -212,17 +231,16 @@ void conv_stream_pc_kernel(const StreamPcArgs a) {
         int last = issue();                                 // loads of the youngest position
         wait_loads(last == 0 ? second : second + last);
         __builtin_amdgcn_s_barrier();                       // first slab landed
-        int kt = 0;
-        for (uint32_t s = 0; s < total; ++s) {
-            // hand-over of slab s: the next slab has landed (the youngest position may stay in flight)
-            wait_loads(last);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            last = issue();                                 // refill the stage of slab s-1
-            if (++kt == KT) {
-                kt = 0;
-                __builtin_amdgcn_s_barrier();               // the one of the epilogue
-            }
+        for (uint32_t t = 0; t < n_my; ++t) {
+            int k = KT;
+            do {
+                // hand-over of a slab: the next slab has landed (the youngest position may stay in flight)
+                wait_loads(last);
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                last = issue();                             // refill the stage of the slab before
+            } while (--k != 0);
+            __builtin_amdgcn_s_barrier();                   // the one of the epilogue
         }
         return;
     }

@@ -272,6 +272,12 @@ def test_overrides_of_the_persistent_kernels_run_where_wide_tiles_would(name, va
         assert groups is None or a["launches"][0]["args"][-1] == groups
 
 
+def test_load_waves_leave_taps_that_span_their_marks():
+    """Their mark of a row outside the image, 2^31, stays outside while the taps span less than 2^30 rows and columns."""
+    calls = [dict(fn="conv", d=dict(conv(1, 1, 1, 64, 128, 3), pad_h=d, dil_h=d), env={"TWN_SMALL": 0, "TWN_TILE": 14}) for d in (1 << 28, 1 << 29)]
+    assert [kernels(a) for a in launches(calls)] == [["conv_stream_pc_kernel"], ["gather_gemm_dma_kernel"]]
+
+
 def test_k_groups_that_are_asked_for():
     """TWN_STREAM_KS on every tile that has K groups, also where load waves are the rule; TWN_STREAM_PC asks for those all the same."""
     d = conv(16, 14, 14, 512, 512, 3)
