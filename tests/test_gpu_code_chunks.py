@@ -6,17 +6,33 @@ import numpy as np
 import pytest
 import torch
 
+from launches import gemm, launches
 from oracle import packing as op
 from paper_1605_04711_amd import api
 from paper_1605_04711_amd import workloads as wl
 from parity import BF16_TOL, rel_err, to_dev_bf16, to_host_f64
 
-pytestmark = pytest.mark.gpu
+CASES = [(14, 64 * 700 - 9, 128), (15, 128 * 600 - 3, 104), (16, 128 * 700 - 5, 64), (17, 128 * 300 - 7, 264), (18, 256 * 300 - 11, 136),
+         (14, 50, 72), (18, 200, 72)]
+SLABS = [1, 2, 3, 4, 5, 9]
+BUILDS = {14: (64, 128, 4), 15: (128, 128, 2), 16: (128, 64, 4), 17: (128, 256, 4), 18: (256, 128, 4)}       # rows, columns, slabs a chunk
 
 
-@pytest.mark.parametrize("tile,m,n", [(14, 64 * 700 - 9, 128), (15, 128 * 600 - 3, 104), (16, 128 * 700 - 5, 64), (17, 128 * 300 - 7, 264),
-                                      (18, 256 * 300 - 11, 136), (14, 50, 72), (18, 200, 72)])
-@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 9])
+def test_cases_take_the_kernel_with_load_waves():
+    answers = launches([dict(fn="gemm", d=gemm(m, n, 64 * slabs), env={"TWN_TILE": tile, "TWN_STREAM_PC": 4})
+                        for tile, m, n in CASES for slabs in SLABS])
+    walks = set()
+    for (tile, m, n), a in zip([c for c in CASES for _ in SLABS], answers):
+        (l,) = a["launches"]
+        rows, cols, chunk = BUILDS[tile]
+        assert l["kernel"] == "conv_stream_pc_kernel" and l["args"][:2] == [str(rows), str(cols)] and l["args"][7] == str(chunk)
+        walks.add((tile, -(-m // rows) * -(-n // cols) > l["grid"][0]))
+    assert walks == {(tile, True) for tile in BUILDS} | {(14, False), (18, False)}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile,m,n", CASES)
+@pytest.mark.parametrize("slabs", SLABS)
 def test_chunks_of_codes(knob, tile, m, n, slabs):
     knob("TWN_TILE", tile)
     knob("TWN_STREAM_PC", 4)
