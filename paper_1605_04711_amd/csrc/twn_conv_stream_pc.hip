@@ -630,7 +630,8 @@ bool conv_stream_alpha_applicable(const GatherGemm& g) {
 // CU: 12544, 128 over 128 14.4 -> 18.8; 7840, 256 over 256 24.7 -> 31.5).
 int32_t launch_conv_stream_alpha(const GatherGemm& g, hipStream_t st) {
     const int64_t cols = (g.NC + 127) / 128;
-    auto busiest = [&](int bm) { return ((g.M + bm - 1) / bm * cols + 255) / 256 * bm; };
+    const int64_t cus = pc_num_cus();
+    auto busiest = [&](int bm) { return ((g.M + bm - 1) / bm * cols + cus - 1) / cus * bm; };
     if (g.K >= 512 && busiest(128) <= busiest(64)) return launch_pc_tile<128, 128, 1, 4, 4, 1, 4, true>(g, st);
     return launch_pc_tile<64, 128, 1, 4, 4, 2, 4, true>(g, st);
 }
