@@ -545,11 +545,15 @@ int32_t launch_small_tile(const GatherGemm* gs, int count, hipStream_t st) {
 }  // namespace
 
 // Tile (16 or 32 pixels x 32 or 64 channels, number of waves: 608, 1108, 1208, 1204) for `count` problems in one launch, 0 when the
-// other kernels are better or the shapes do not fit.  Measured per dependent launch (us, against the split-K launch pair
+// other kernels are better or the shapes do not fit.  The lines are multiples of the 256 CUs of the chip they were measured on and no
+// question to the device: the workspace query has to give the same answer without one.  Measured per dependent launch (us, against the split-K launch pair
 // and the persistent kernels that ran such problems before):
 //   * up to 256 tiles of 16 pixels by 32 channels (one alpha; MFMAs of 16x16): eight waves per tile.  The tiles of a batch-1 layer
 //     leave most CUs idle, and the ones at work are bound by what their own load path brings: half the rows are half of that,
-//     and five slabs in flight fit where three of 32 rows did (49, 512, 4608: 7.7 -> 6.8; 196, 256, 2304: 5.9 -> 5.2)
+//     and five slabs in flight fit where three of 32 rows did (49, 512, 4608: 7.7 -> 6.8; 196, 256, 2304: 5.9 -> 5.2).  Against tiles
+//     of 32 pixels in 504 inner products of 1 to 500 rows, 10 to 8192 columns and K of 64 to 16384: 0.97 to 1.18 times as fast, 1.07 in
+//     the mean, also where rows above the sixteenth read the codes again (1, 1000, 512: 3.56 -> 3.31; 16, 8192, 16384: 16.2 -> 14.1; 32,
+//     4096, 16384: 14.4 -> 14.1; 24, 4096, 512: 3.56 -> 3.63; 500, 256, 4096: 6.04 -> 5.80)
 //   * up to 256 tiles of 32x32: eight waves per tile, one tile per CU (M, N, K = 49, 512, 4608: 10.8 -> 8.1; 784, 128, 1152:
 //     11.6 -> 5.1; 1, 1000, 512: 5.1 -> 3.6).  Two such workgroups do not fit a CU: 1568, 256, 2304, 392 tiles of 32x32 or
 //     196 of 32x64, takes 8.1 with the former and 6.4 with the latter

@@ -1594,8 +1594,8 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
         it.first1 = first1;
         first1 += it.nb1;
     }
-    // what gathers first: a block of it is a chain of latencies, which ends the launch late if it starts late (VGG-7 with both
-    // copies, whose classifier of 10 gathers: 36.2 us last, 33.0 first)
+    // Untiled tensors first: a block that gathers is a chain of latencies, which ends the launch late if it starts late (VGG-7 with both
+    // copies, whose classifier of 10 gathers: 36.2 us last, 33.0 first).  Within one that streams, the gathering blocks follow.
     for (int tiled = 0; tiled < 2; ++tiled)
         for (int i = 0; i < count; ++i)
             if (tb.item[i].nb2 > 0 && tb.item[i].tiled == tiled) {
