@@ -514,34 +514,34 @@ __global__ __launch_bounds__(kTernThreads) void band_fix_kernel(const float* __r
 }
 
 // The 16 weights of word j of an output row: filter `row`'s codes k = rs*C + c in the normal copy, input channel `row`'s codes
-// k = rs*rows + o in the transposed one.  One division per word, then all sixteen loads are requested (bit t of the result:
-// weight t exists; the others read the tensor's first one).  With a 64-bit division and a wait per weight a
+// k = rs*rows + o in the transposed one.  One division per word, then all sixteen loads are requested (the result: how many
+// of them exist; the others read the tensor's first one).  With a 64-bit division and a wait per weight a
 // call was (us) 19 instead of 13 for 300 x 200 x 3 x 3, 91 instead of 59 for 3333 x 5008.
-// `paced`: one load at a time.  Weights that follow one another in a word are taps apart in memory, and a cache line is used by the words
+// PACED: one load at a time.  Weights that follow one another in a word are taps apart in memory, and a cache line is used by the words
 // of several taps, which other waves form at about the same time: that is one sixteenth of the tensor while all waves stand at the
-// same weight, and the whole tensor with sixteen loads each, which no L2 holds from about 6 MB on.  From 16 taps, i.e. half a line, and 3*2^19
-// weights on (us, all at once / paced): 1948x80x5x5 55.9 / 43.6, 1622x68x5x5 44.4 / 38.3, 4680x19x5x5 36.3 / 30.3, but 357x29x5x5
-// 10.7 / 14.1, 700x120x4x4 17.9 / 19.3, 2000x700x3x3 113 / 203.
-template <bool TRANSPOSED>
-__device__ __forceinline__ uint32_t gather_word(const float* __restrict__ W, int rows, int C, int RS, int row, int j, bool paced,
-                                                float (&w)[16]) {
+// same weight, and the whole tensor with sixteen loads each, which no L2 holds from about 6 MB on.
+__host__ __device__ inline bool paced_words(int64_t n, int RS) {
+    // from 16 taps, i.e. half a line, on (us, all at once / paced: 1948x80x5x5 57 / 42, 1622x68x5x5 45 / 39, 4680x19x5x5 36 / 30, 1000x60x7x7 46 /
+    // 35; some the other way, 746x189x5x5 60 / 72; below the line 357x29x5x5 10.7 / 14.1; 2000x700x3x3 113 / 203)
+    return RS >= 16 && n >= (3 << 19);
+}
+template <bool TRANSPOSED, bool PACED>
+__device__ __forceinline__ uint32_t gather_word(const float* __restrict__ W, int rows, int C, int RS, int row, int j, float (&w)[16]) {
     const uint32_t len = static_cast<uint32_t>(TRANSPOSED ? rows : C), k0 = static_cast<uint32_t>(j) * 16u;
     uint32_t rs = k0 / len, i = k0 - rs * len;
     const int64_t step = TRANSPOSED ? static_cast<int64_t>(C) * RS : RS;
     const int64_t base = static_cast<int64_t>(row) * (TRANSPOSED ? RS : step * C);
-    int64_t at = base + i * step + rs;
-    uint32_t real = 0;
+    const uint32_t k = len * static_cast<uint32_t>(RS);
+    uint32_t real = k > k0 ? k - k0 : 0u;
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
-        const bool ok = rs < static_cast<uint32_t>(RS);
-        real |= ok ? 1u << t : 0u;
-        w[t] = W[ok ? at : 0];
-        if (t < 15 && paced) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        w[t] = W[static_cast<uint32_t>(t) < real ? base + i * step + rs : 0];
+        if (PACED && t < 15) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const bool next = ++i == len;
         i = next ? 0u : i;
         rs += next ? 1u : 0u;
-        at = next ? base + rs : at + step;
     }
+    asm volatile("" : "+v"(real));      // sixteen tests, not kept as sixteen masks: eight blocks a CU instead of seven
     return real;
 }
 // quotient of a word's number, which is below 2^31 for all but the largest tensors
@@ -553,6 +553,7 @@ __device__ __forceinline__ int64_t word_quotient(int64_t id, int d, bool narrow)
 // masked sum and count: every weight belongs to exactly one normal word) and of the transposed copy.
 //   normal:     row = filter o,        k   = (r*S+s)*C + c
 //   transposed: row = input channel c, k_T = (r*S+s)*rows + o   (threads ordered with c fastest)
+template <bool PACED>
 __device__ __forceinline__ void mask_pack_gather_body(
     const float* __restrict__ W, int rows, int C, int RS, TernWorkspace* __restrict__ ws, int nb1, float f,
     uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT, int bid, int nblk, int slots,
@@ -564,7 +565,7 @@ __device__ __forceinline__ void mask_pack_gather_body(
     const float delta = delta_from_partials(ws->p1, nb1, f, n, scratch);
     const int64_t words_n = only_transposed ? 0 : static_cast<int64_t>(rows) * wpr;
     const int64_t words_t = packed_T ? static_cast<int64_t>(C) * wprT : 0;
-    const bool narrow = words_n + words_t < (1LL << 31), paced = RS >= 16 && n >= (3 << 19);
+    const bool narrow = words_n + words_t < (1LL << 31);
     double acc = 0.0;
     uint32_t count = 0;
     for (int64_t id = static_cast<int64_t>(bid) * blockDim.x + threadIdx.x; id < words_n + words_t;
@@ -573,10 +574,10 @@ __device__ __forceinline__ void mask_pack_gather_body(
         uint32_t word = 0;
         if (id < words_n) {
             const int64_t o = word_quotient(id, wpr, narrow);
-            const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), paced, w);
+            const uint32_t real = gather_word<false, PACED>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), w);
 #pragma unroll
             for (int t = 0; t < 16; ++t) {
-                const uint32_t fld = (real >> t & 1u) ? code_field(w[t], delta) : 0u;
+                const uint32_t fld = static_cast<uint32_t>(t) < real ? code_field(w[t], delta) : 0u;
                 // adding +0.0 for the masked-out weights leaves the float64 sum unchanged
                 acc += static_cast<double>(fld ? fabsf(w[t]) : 0.0f);
                 count += fld & 1u;
@@ -586,10 +587,10 @@ __device__ __forceinline__ void mask_pack_gather_body(
         } else {
             const int64_t it = id - words_n, j = word_quotient(it, C, narrow);
             const int c = static_cast<int>(it - j * C);
-            const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), paced, w);
+            const uint32_t real = gather_word<true, PACED>(W, rows, C, RS, c, static_cast<int>(j), w);
 #pragma unroll
             for (int t = 0; t < 16; ++t)
-                word |= ((real >> t & 1u) ? code_field(w[t], delta) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
+                word |= (static_cast<uint32_t>(t) < real ? code_field(w[t], delta) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
             packed_T[static_cast<int64_t>(c) * wprT + j] = word;
         }
     }
@@ -598,11 +599,12 @@ __device__ __forceinline__ void mask_pack_gather_body(
     deliver(ws, slot0 + bid, slots, total, ctotal, delta, delta_out, alpha_out, nnz_out, scratch, scratch_u);
 }
 
+template <bool PACED>
 __global__ __launch_bounds__(kTernThreads) void mask_pack_gather_kernel(
     const float* __restrict__ W, int rows, int C, int RS, TernWorkspace* __restrict__ ws, int nb1, float f,
     uint32_t* __restrict__ packed, int wpr, uint32_t* __restrict__ packed_T, int wprT, float* __restrict__ delta_out,
     float* __restrict__ alpha_out, uint64_t* __restrict__ nnz_out) {
-    mask_pack_gather_body(W, rows, C, RS, ws, nb1, f, packed, wpr, packed_T, wprT, blockIdx.x, gridDim.x, gridDim.x, delta_out,
+    mask_pack_gather_body<PACED>(W, rows, C, RS, ws, nb1, f, packed, wpr, packed_T, wprT, blockIdx.x, gridDim.x, gridDim.x, delta_out,
                           alpha_out, nnz_out);
 }
 
@@ -812,6 +814,7 @@ __global__ __launch_bounds__(kTernThreads) void batch_abs_sum_kernel(const Batch
     abs_sum_body(it.W, static_cast<int64_t>(it.rows) * it.C * it.RS, ws[i].p1, blockIdx.x - it.first1, it.nb1);
 }
 
+template <bool PACED>
 __global__ __launch_bounds__(kTernThreads) void batch_mask_pack_kernel(const BatchTable tb, TernWorkspace* __restrict__ ws) {
     const int i = batch_find(tb, blockIdx.x, &BatchItem::first2, &BatchItem::nb2);
     const BatchItem& it = tb.item[i];
@@ -823,7 +826,7 @@ __global__ __launch_bounds__(kTernThreads) void batch_mask_pack_kernel(const Bat
         mask_pack_flat_body(it.W, static_cast<int64_t>(it.rows) * it.C, ws + i, it.nb1, tb.f, it.packed, 1, local, it.flat_blocks,
                             it.nb2, it.delta, it.alpha, it.nnz);
     else
-        mask_pack_gather_body(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
+        mask_pack_gather_body<PACED>(it.W, it.rows, it.C, it.RS, ws + i, it.nb1, tb.f, it.packed, it.wpr, it.packed_T, it.wprT,
                               local - it.flat_blocks, it.nb2 - it.flat_blocks, it.nb2, it.delta, it.alpha, it.nnz, it.flat_blocks > 0,
                               it.flat_blocks);
 }
@@ -1095,13 +1098,13 @@ __device__ __forceinline__ void pack_gather_body(
     int rows_per_group, uint32_t* __restrict__ out, int wpr, int transposed, int64_t id) {
     const int64_t words = static_cast<int64_t>(transposed ? C : rows) * wpr;
     if (id >= words) return;
-    const bool narrow = words < (1LL << 31), paced = false;
+    const bool narrow = words < (1LL << 31);
     float w[16];
     uint32_t word = 0;
     if (transposed) {
         const int64_t j = word_quotient(id, C, narrow);         // input channel, fastest across threads
         const int c = static_cast<int>(id - j * C);
-        const uint32_t real = gather_word<true>(W, rows, C, RS, c, static_cast<int>(j), paced, w);
+        const uint32_t real = gather_word<true, false>(W, rows, C, RS, c, static_cast<int>(j), w);
         // group of the word's first filter, and the filter's place in it
         const uint32_t per_group = static_cast<uint32_t>(rows_per_group), filters = static_cast<uint32_t>(rows);
         const uint32_t o0 = static_cast<uint32_t>(j) * 16u % filters;
@@ -1117,15 +1120,15 @@ __device__ __forceinline__ void pack_gather_body(
         }
 #pragma unroll
         for (int t = 0; t < 16; ++t)
-            word |= ((real >> t & 1u) ? code_field(w[t], d[t]) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
+            word |= (static_cast<uint32_t>(t) < real ? code_field(w[t], d[t]) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
         out[static_cast<int64_t>(c) * wpr + j] = word;
         return;
     }
     const int64_t o = word_quotient(id, wpr, narrow);
-    const uint32_t real = gather_word<false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), paced, w);
+    const uint32_t real = gather_word<false, false>(W, rows, C, RS, static_cast<int>(o), static_cast<int>(id - o * wpr), w);
     const float d = delta[static_cast<int>(o) / rows_per_group];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) word |= ((real >> t & 1u) ? code_field(w[t], d) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
+    for (int t = 0; t < 16; ++t) word |= (static_cast<uint32_t>(t) < real ? code_field(w[t], d) : 0u) << ((t & 1) * 16 + (t >> 1) * 2);
     out[id] = word;
 }
 
@@ -1281,7 +1284,8 @@ static int32_t ternarize_impl(const float* W, const twn_weight_desc* wd, int32_t
                 mask_pack_tile_kernel<<<static_cast<unsigned>(nb2), kTernThreads, 0, st>>>(
                     W, wd->rows, wd->C, static_cast<int>(RS), ws, nb, delta_factor, packed, wpr, packed_T, wprT, delta, alpha, nnz);
             } else
-                mask_pack_gather_kernel<<<static_cast<unsigned>(nb2), kTernThreads, 0, st>>>(
+                (paced_words(n, static_cast<int>(RS)) ? mask_pack_gather_kernel<true> : mask_pack_gather_kernel<false>)<<<
+                    static_cast<unsigned>(nb2), kTernThreads, 0, st>>>(
                     W, wd->rows, wd->C, static_cast<int>(RS), ws, nb, delta_factor, packed, wpr, packed_T, wprT, delta, alpha, nnz);
         }
     } else if (groups == wd->rows && filter_ok(wd->rows, K, static_cast<int>(RS), packed_T != nullptr)) {
@@ -1594,11 +1598,14 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
         it.first1 = first1;
         first1 += it.nb1;
     }
-    // Untiled tensors first: a block that gathers is a chain of latencies, which ends the launch late if it starts late (VGG-7 with both
-    // copies, whose classifier of 10 gathers: 36.2 us last, 33.0 first).  Within one that streams, the gathering blocks follow.
-    for (int tiled = 0; tiled < 2; ++tiled)
+    // A block that takes long ends the launch late if it starts late: tiles of filters larger than 3x3 first, then untiled tensors, whose
+    // gathering blocks are chains of latencies (within one that streams they follow), then tiles by the weights they hold.  us with both
+    // copies, as listed / untiled tensors first / so: VGG-7, whose classifier of 10 gathers, 36.8 / 34.0 / 32.1; VGG-16 46.2 / 46.2 / 43.7;
+    // 192x64x3x3, 1024x64x5x5, 64x64x5x5 and four others 21.3 / 23.5 / 21.7.
+    auto order = [](const BatchItem& it) { return !it.tiled ? 1 : it.RS > 9 ? 0 : tile_ct(it.C, it.RS) * it.RS > 64 * 9 ? 2 : 3; };
+    for (int turn = 0; turn < 4; ++turn)
         for (int i = 0; i < count; ++i)
-            if (tb.item[i].nb2 > 0 && tb.item[i].tiled == tiled) {
+            if (tb.item[i].nb2 > 0 && order(tb.item[i]) == turn) {
                 tb.item[i].first2 = first2;
                 first2 += tb.item[i].nb2;
             }
@@ -1622,7 +1629,13 @@ extern "C" int32_t twn_ternarize_batch(const twn_ternarize_item* items, int32_t 
     TernWorkspace* ws = static_cast<TernWorkspace*>(workspace);
     if (first1 > 0) {
         batch_abs_sum_kernel<<<first1, kTernThreads, 0, st>>>(tb, ws);
-        batch_mask_pack_kernel<<<first2, kTernThreads, 0, st>>>(tb, ws);
+        // paced words: also for the smaller tensors of such a call
+        bool paced = false;
+        for (int i = 0; i < count; ++i) {
+            const BatchItem& it = tb.item[i];
+            paced = paced || (it.nb2 > 0 && !it.tiled && paced_words(static_cast<int64_t>(it.rows) * it.C * it.RS, it.RS));
+        }
+        (paced ? batch_mask_pack_kernel<true> : batch_mask_pack_kernel<false>)<<<first2, kTernThreads, 0, st>>>(tb, ws);
     }
     if (firstf > 0) {
         if (!filter_lds_allowed()) return TWN_ERR_HIP;
