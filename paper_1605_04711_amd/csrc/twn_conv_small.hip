@@ -553,7 +553,9 @@ int32_t launch_small_tile(const GatherGemm* gs, int count, hipStream_t st) {
 //     and five slabs in flight fit where three of 32 rows did (49, 512, 4608: 7.7 -> 6.8; 196, 256, 2304: 5.9 -> 5.2).  Against tiles
 //     of 32 pixels in 504 inner products of 1 to 500 rows, 10 to 8192 columns and K of 64 to 16384: 0.97 to 1.18 times as fast, 1.07 in
 //     the mean, also where rows above the sixteenth read the codes again (1, 1000, 512: 3.56 -> 3.31; 16, 8192, 16384: 16.2 -> 14.1; 32,
-//     4096, 16384: 14.4 -> 14.1; 24, 4096, 512: 3.56 -> 3.63; 500, 256, 4096: 6.04 -> 5.80)
+//     4096, 16384: 14.4 -> 14.1; 24, 4096, 512: 3.56 -> 3.63; 500, 256, 4096: 6.04 -> 5.80).  Several problems in one launch count as the
+//     largest each: residue classes of 195 tiles in a grid of 300 took a second round (13x11x9 <- 512, 96 channels 2x2/2: 8.9, with tiles of 32
+//     pixels 7.2)
 //   * up to 256 tiles of 32x32: eight waves per tile, one tile per CU (M, N, K = 49, 512, 4608: 10.8 -> 8.1; 784, 128, 1152:
 //     11.6 -> 5.1; 1, 1000, 512: 5.1 -> 3.6).  Two such workgroups do not fit a CU: 1568, 256, 2304, 392 tiles of 32x32 or
 //     196 of 32x64, takes 8.1 with the former and 6.4 with the latter
@@ -582,7 +584,8 @@ int conv_small_tile(const GatherGemm* gs, int count) {
         const int64_t xb = small_x_bytes(g), wb = static_cast<int64_t>(g.NC) * g.wpr * 4;
         if (xb <= 0 || xb >= (1LL << 31) || wb >= (1LL << 31)) return 0;
         const int64_t rows = (g.M + 31) / 32;
-        t16 += (g.M + 15) / 16 * ((g.NC + 31) / 32);
+        const int64_t tiles16 = (g.M + 15) / 16 * ((g.NC + 31) / 32);
+        if (tiles16 > t16) t16 = tiles16;
         t11 += rows * ((g.NC + 31) / 32);
         one_alpha = one_alpha && !g.alpha_in;
         t12 += rows * ((g.NC + 63) / 64);
@@ -591,7 +594,7 @@ int conv_small_tile(const GatherGemm* gs, int count) {
         if (k_slabs(g.K) > kt) kt = k_slabs(g.K);
     }
     if (kt > 256) return 0;
-    if (t16 <= 256 && one_alpha) return 608;
+    if (t16 * count <= 256 && one_alpha) return 608;        // each problem has as many workgroups as the largest
     if (t11 <= 256) return 1108;
     if (t12 <= 256) return 1208;
     if (t12 <= 512 && (kt >= 16 || !persistent)) return 1204;

@@ -68,6 +68,17 @@ def test_overrides_of_other_kernels_reach_small_problems(name, value, wanted):
             assert all(l["args"][at[l["kernel"]]] == "false" for l in a["launches"] if l["kernel"] in at)
 
 
+def test_tiles_of_sixteen_pixels_fit_one_round():
+    """The workgroups of a launch, empty ones of smaller problems among them, are at most 256: a CU holds one."""
+    rng = random.Random(5)
+    calls = [dict(fn="bwd", parts="dx", d=conv(13, 11, 9, 96, 512, 2, 2, 1))]
+    calls += [dict(fn="bwd", parts="dx", d=conv(rng.randint(1, 16), rng.randint(3, 16), rng.randint(3, 16), 8 * rng.randint(1, 32),
+                                                8 * rng.randint(1, 64), rng.choice([2, 3, 5]), 2)) for _ in range(300)]
+    small = [l for a in launches(calls) for l in a["launches"] if l["kernel"] == "conv_small_kernel" and l["args"][6] == "true"]
+    assert len(small) >= 50 and any(l["grid"][1] > 1 for l in small)
+    assert all(l["grid"][0] * l["grid"][1] <= 256 for l in small)
+
+
 def test_pair_override_never_one_launch():
     for a in launches([dict(fn="pair", d=first, d1=second, env={"TWN_FWD_PAIR": 0}) for first, second in HEADS]):
         assert len(kernels(a)) == 2
