@@ -14,7 +14,10 @@ constexpr int kBiasLds = kBiasThreads * 8;
 
 // Group `group` of channels over pixels begin..end, dest[channel].  The sums are those of 512 threads, also in a block of fewer (a
 // thread then takes several of their places in turn) or more: the result does not depend on the launch that carries the block.
-template <int VEC, int THREADS>
+// BATCH pixels are requested at once, those behind the last as the batch's first and counted as zeros: a loop over the rest behind one
+// over whole batches costs the fetch of code that is only skipped, and lanes with and without a whole batch take turns.  One request of
+// a wave is a cache line per lane, so a batch must not be much more than a thread's pixels: bias_groups.
+template <int VEC, int THREADS, int BATCH>
 __device__ __forceinline__ void bias_grad_group(const BiasGrad& b, int group, int64_t begin, int64_t end, float* __restrict__ dest,
                                                 float* __restrict__ red) {
     const int chunk0 = group * b.chunks_per_group;
@@ -28,9 +31,6 @@ __device__ __forceinline__ void bias_grad_group(const BiasGrad& b, int group, in
         for (int v = 0; v < VEC; ++v) acc[v] = 0.0f;
         if (row < rows) {
             const uint16_t* src = b.dY + ch;
-            // Whole eights of pixels are requested at once, the others one after the other: where a thread has one or two pixels,
-            // eight requests touch a cache line per lane each, and code that is only skipped costs its fetch (a call for dbias
-            // alone, 880 pixels x 64 channels, us: 3.5; eight requests always 4.9; four, those that exist 3.8).
             using Values = std::conditional_t<VEC == 8, u32x4, uint32_t>;
             auto load = [&](const uint16_t* at) -> Values {
                 if constexpr (VEC == 8) return *reinterpret_cast<const u32x4*>(at);
@@ -47,35 +47,15 @@ __device__ __forceinline__ void bias_grad_group(const BiasGrad& b, int group, in
                     acc[0] += __uint_as_float(x << 16);
                 }
             };
-            int64_t p = begin + row;
-            const uint16_t* at = src + p * b.O;         // one address, moved on: eight would take a quarter of the registers
-            const int64_t step = static_cast<int64_t>(rows) * b.O;
-            for (; p + 7 * rows < end; p += 8 * rows) {
-                Values x[8];
+            for (int64_t p = begin + row; p < end; p += BATCH * rows) {
+                Values x[BATCH];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    x[u] = load(at);
-                    at += step;
-                    asm volatile("" : "+v"(at));
+                for (int u = 0; u < BATCH; ++u) x[u] = load(src + (p + u * rows < end ? p + u * rows : p) * b.O);
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u) {
+                    if (p + u * rows >= end) x[u] = Values{};
+                    add(x[u]);
                 }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) add(x[u]);
-            }
-            if (p + 3 * rows < end) {
-                Values x[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    x[u] = load(at);
-                    at += step;
-                    asm volatile("" : "+v"(at));
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) add(x[u]);
-                p += 4 * rows;
-            }
-            for (; p < end; p += rows) {
-                add(load(at));
-                at += step;
             }
         }
 #pragma unroll
@@ -125,8 +105,9 @@ __device__ __forceinline__ int final_pass_block(const BiasGrad& b, float* __rest
     const int block = static_cast<int>(blockIdx.x) - b.blocks;
     if (block >= 0) return block;
     for (int group = blockIdx.x; group < b.groups; group += b.blocks) {
-        if (b.vec == 8) bias_grad_group<8, THREADS>(b, group, 0, b.pixels, b.dbias, red);
-        else bias_grad_group<1, THREADS>(b, group, 0, b.pixels, b.dbias, red);
+        if (b.vec == 8 && b.batch == 1) bias_grad_group<8, THREADS, 1>(b, group, 0, b.pixels, b.dbias, red);
+        else if (b.vec == 8) bias_grad_group<8, THREADS, 4>(b, group, 0, b.pixels, b.dbias, red);
+        else bias_grad_group<1, THREADS, 8>(b, group, 0, b.pixels, b.dbias, red);
     }
     return -1;
 }

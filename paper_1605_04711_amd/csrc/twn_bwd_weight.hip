@@ -802,13 +802,13 @@ __global__ __launch_bounds__(256) void weight_grad_reduce_rows_kernel(const floa
 // itself, otherwise float32 partials [split][O] for bias_grad_final_kernel.
 // Time of both launches against 64 ranges of single values (us): 162792 pixels, 128 filters 187 -> 14 (3 TB/s); 25056, 64: 30 -> 10;
 // 9800, 200: 16 -> 10; 910, 200 (one launch): 9 -> 7.
-template <int VEC>
+template <int VEC, int BATCH>
 __global__ __launch_bounds__(kBiasThreads) void bias_grad_kernel(const BiasGrad b, int64_t per, float* __restrict__ out) {
     __shared__ float red[kBiasThreads * VEC];
     const int64_t begin = static_cast<int64_t>(blockIdx.y) * per;
     const int64_t end = begin + per < b.pixels ? begin + per : b.pixels;
     for (int group = blockIdx.x; group < b.groups; group += gridDim.x)
-        bias_grad_group<VEC, kBiasThreads>(b, group, begin, end, out + static_cast<int64_t>(blockIdx.y) * b.O, red);
+        bias_grad_group<VEC, kBiasThreads, BATCH>(b, group, begin, end, out + static_cast<int64_t>(blockIdx.y) * b.O, red);
 }
 
 // Fixed-order sum of the partials: 64 channels per block, sixteen waves share the splits.
@@ -854,6 +854,11 @@ static BiasGrad bias_groups(const WeightGrad& w, bool single) {
     const int few = b.pixels <= 1024 ? 16 : static_cast<int>(16384 / b.pixels);      // single channels: 512 / few rows
     b.chunks_per_group = single ? (b.vec == 8 ? 1 : (b.O < few ? b.O : few)) : (b.vec == 8 ? (chunks < 8 ? chunks : 8) : (b.O < 64 ? b.O : 64));
     b.groups = (chunks + b.chunks_per_group - 1) / b.chunks_per_group;
+    // Pixels requested at once, us of a call for dbias alone, by eights / by fours / one by one: 630 pixels of 128 channels (1.2 a thread)
+    // 5.2 / - / 3.7; 1680, 128 (3.3) 5.2 / 4.3 / 4.2; 5382, 64 (10.5) 6.9 / 6.0 / -.  Single channels lie side by side, where eight are
+    // no more lines than four: 546, 250 4.0 / 4.4 / -; 1350, 250 4.7 / 5.5 / -.  Several ranges: eights, 52360, 128 7.5 (11.0 by whole
+    // eights and one by one).
+    b.batch = !single ? 8 : b.pixels <= 3 * (kBiasThreads / b.chunks_per_group) ? 1 : b.vec == 8 ? 4 : 8;
     return b;
 }
 
@@ -885,8 +890,10 @@ static void launch_bias_grad(const WeightGrad& w, hipStream_t st) {
     const unsigned gx = static_cast<unsigned>(b.groups < (1 << 20) ? b.groups : (1 << 20));     // below 2^32 threads
     const dim3 grid(gx, static_cast<unsigned>(splits));
     float* out = splits == 1 ? w.dbias : w.partial;
-    if (b.vec == 8) bias_grad_kernel<8><<<grid, kBiasThreads, 0, st>>>(b, per, out);
-    else bias_grad_kernel<1><<<grid, kBiasThreads, 0, st>>>(b, per, out);
+    auto k = b.batch == 1   ? (b.vec == 8 ? bias_grad_kernel<8, 1> : bias_grad_kernel<1, 1>)
+             : b.batch == 4 ? bias_grad_kernel<8, 4>
+                            : (b.vec == 8 ? bias_grad_kernel<8, 8> : bias_grad_kernel<1, 8>);
+    k<<<grid, kBiasThreads, 0, st>>>(b, per, out);
     const int blocks = (b.O + 63) / 64;
     if (splits > 1)
         bias_grad_final_kernel<<<static_cast<unsigned>(blocks < (1 << 20) ? blocks : (1 << 20)), 1024, 0, st>>>(

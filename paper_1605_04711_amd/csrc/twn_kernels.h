@@ -188,6 +188,7 @@ struct BiasGrad {
     int64_t pixels;
     int32_t O, vec;         // channels; 8 or 1 per load
     int32_t chunks_per_group, groups, blocks;
+    int32_t batch;          // pixels a thread requests at a time
 };
 // Empty (blocks = 0) unless one launch sums all pixels, which needs no partial sums.
 BiasGrad bias_in_final_pass(const WeightGrad& w);
