@@ -855,10 +855,10 @@ static BiasGrad bias_groups(const WeightGrad& w, bool single) {
     b.chunks_per_group = single ? (b.vec == 8 ? 1 : (b.O < few ? b.O : few)) : (b.vec == 8 ? (chunks < 8 ? chunks : 8) : (b.O < 64 ? b.O : 64));
     b.groups = (chunks + b.chunks_per_group - 1) / b.chunks_per_group;
     // Pixels requested at once, us of a call for dbias alone, by eights / by fours / one by one: 630 pixels of 128 channels (1.2 a thread)
-    // 5.2 / - / 3.7; 1680, 128 (3.3) 5.2 / 4.3 / 4.2; 5382, 64 (10.5) 6.9 / 6.0 / -.  Single channels lie side by side, where eight are
+    // 5.2 / - / 3.7; 1680, 128 (3.3) 5.2 / 4.3 / 4.2; 3025, 64 (5.9) 5.2 / 5.2 / 4.7; 5382, 64 (10.5) 6.9 / 6.0 / -.  Single channels lie side by side, where eight are
     // no more lines than four: 546, 250 4.0 / 4.4 / -; 1350, 250 4.7 / 5.5 / -.  Several ranges: eights, 52360, 128 7.5 (11.0 by whole
     // eights and one by one).
-    b.batch = !single ? 8 : b.pixels <= 3 * (kBiasThreads / b.chunks_per_group) ? 1 : b.vec == 8 ? 4 : 8;
+    b.batch = !single ? 8 : b.pixels <= (b.vec == 8 ? 7 : 3) * (kBiasThreads / b.chunks_per_group) ? 1 : b.vec == 8 ? 4 : 8;
     return b;
 }
 
