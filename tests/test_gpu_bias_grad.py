@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
     (2, 64, 64, 72), (2, 64, 64, 10),     # 8192 pixels: the last of one launch
     (3, 59, 47, 72), (3, 59, 47, 10),     # 8319: two launches, ragged ranges
     (1, 91, 91, 520), (1, 91, 91, 77),    # ragged last channel group
-    (40, 33, 37, 8), (40, 33, 37, 1)])    # many ranges of few channels
+    (40, 33, 37, 8), (40, 33, 37, 1),     # many ranges of few channels
+    (1, 1, 3584, 72), (1, 1, 3585, 72), (1, 1, 5121, 72), (1, 1, 6143, 72),     # 512 pixels at once: seven; fours and a remainder
+    (1, 1, 96, 33), (1, 1, 97, 33), (1, 1, 513, 33)])                           # 32 at once: three; eights and a remainder
 @pytest.mark.parametrize("need_dw", [True, False])
 def test_dbias(n, h, w, o, need_dw):
     rng = np.random.default_rng(n * h * w + o)
